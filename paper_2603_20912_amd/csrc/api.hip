@@ -12,14 +12,6 @@
 #include "pack_cubes.h"
 #include "ppl_internal.h"
 
-// Resident upper-triangle builds write the GEMM's natural layout and pack whole V+- rows,
-// mirror entries included, in one pass (0: G blocks, packing of the upper triangle, then a
-// separate mirror pass, as streaming steps still do).
-#ifndef PPL_PACK_CUBES
-#define PPL_PACK_CUBES 1
-#endif
-constexpr bool kPackCubes = PPL_PACK_CUBES;
-
 namespace ppl {
 
 static thread_local char g_err[1024] = "";
@@ -317,7 +309,7 @@ static uint64_t assign_layout(ppl_plan_t p, int64_t gcap, bool resident, int64_t
   }
   p->tiles = L.take((uint64_t)p->tiles_host.size() * 4);
   p->cols = p->sym_build ? L.take((uint64_t)npairs_plus(v) * 4) : Region{};
-  p->cube_off = (p->sym_build && resident && kPackCubes) ? L.take((uint64_t)(v + 1) * 8) : Region{};
+  p->cube_off = (p->sym_build && resident) ? L.take((uint64_t)(v + 1) * 8) : Region{};
   p->r2p = p->r2m = p->ut = Region{};
   if (p->sym_build && !resident) {
     // the K range of a step starts at its first pair rounded down to 64, so it spans at
@@ -404,24 +396,6 @@ static double build_flops(ppl_plan_t p, int a0, int a1) {
   return 2.0 * p->naux * f;
 }
 
-static int mirror_vpm(ppl_plan_t p, OperandSet& s) {
-  if (!p->sym_build || kPackCubes) return PPL_OK;   // the cube packing writes the mirror entries itself
-  ProfScope ps(p, PPL_PROF_BUILD_PACK, 0.0);
-  const int w = elem_bytes(s.prec);
-  const int np = planes(s.prec);
-  // plane k of a region starts k plane sizes after its hi plane (the lo planes of BF16x6
-  // follow the hi plane directly; the lo plane of BF16x3 lies elsewhere)
-  for (int k = 0; k < np; ++k) {
-    char* vp = k == 0 ? at<char>(p, s.vp) : at<char>(p, s.vp_lo) + (uint64_t)(k - 1) * s.vp.bytes;
-    PPL_TRY(mirror_lower(p->stream, w, vp, p->Pp, p->ldp));
-    if (p->Pm > 0) {
-      char* vm = k == 0 ? at<char>(p, s.vm) : at<char>(p, s.vm_lo) + (uint64_t)(k - 1) * s.vm.bytes;
-      PPL_TRY(mirror_lower(p->stream, w, vm, p->Pm, p->ldm));
-    }
-  }
-  return PPL_OK;
-}
-
 static int build_one(ppl_plan_t p, OperandSet& s, const double* L, int bi, bool staged) {
   const Batch& b = p->batches[bi];
   hipStream_t st = p->stream;
@@ -448,8 +422,8 @@ static int build_one(ppl_plan_t p, OperandSet& s, const double* L, int bi, bool 
         (uint64_t)(r0m + (b.q1 - b.q0)) * p->ldm * w > s.vm.bytes)
       return fail(PPL_E_STATE, "build step %d exceeds the V+- rows of the plan", bi);
   }
-  if (p->sym_build && p->resident && kPackCubes) {
-    // natural GEMM layout, then whole rows and their mirror entries in one packing pass
+  if (p->sym_build && p->resident) {
+    // natural GEMM layout, then one packing pass: upper triangles (FP64, FP32) or whole rows
     {
       ProfScope ps(p, PPL_PROF_BUILD_GEMM, build_flops(p, b.a0, b.a1));
       PPL_TRY(gemm_build_natural(st, s.prec, tile, p->v, b.a0, b.a1, p->ldx, at<void>(p, s.xt),
@@ -458,6 +432,9 @@ static int build_one(ppl_plan_t p, OperandSet& s, const double* L, int bi, bool 
     }
     ProfScope ps(p, PPL_PROF_BUILD_PACK, 0.0);
     const int64_t W = p->v - b.a0;
+    if (s.tri)
+      return pack_vpm_tri(st, s.prec, p->v, b.a0, b.a1, at<void>(p, p->g), W * (W + 1) / 2,
+                          at<int64_t>(p, p->cube_off), at<void>(p, s.vp), p->ldp, at<void>(p, s.vm), p->ldm);
     return pack_vpm_cubes(st, s.prec, p->v, b.a0, b.a1, at<void>(p, p->g), W * (W + 1) / 2,
                           at<int64_t>(p, p->cube_off), at<void>(p, s.vp), s.vp_lo.bytes ? at<void>(p, s.vp_lo) : nullptr,
                           p->ldp, at<void>(p, s.vm), s.vm_lo.bytes ? at<void>(p, s.vm_lo) : nullptr, p->ldm);
@@ -494,7 +471,6 @@ static int build_one(ppl_plan_t p, OperandSet& s, const double* L, int bi, bool 
 
 static int build_all(ppl_plan_t p, OperandSet& s, const double* L) {
   for (int bi = 0; bi < (int)p->batches.size(); ++bi) PPL_TRY(build_one(p, s, L, bi, bi > 0));
-  PPL_TRY(mirror_vpm(p, s));
   s.built = true;
   return PPL_OK;
 }
@@ -581,13 +557,13 @@ static int contract_packed(ppl_plan_t p, OperandSet& s) {
       ProfScope ps(p, PPL_PROF_CONTRACT_PLUS, fp * p->Pp);
       PPL_TRY(gemm_contract(st, s.prec, tile, p->Np, p->Pp, p->ldp, sp, sp_lo, p->ldp,
                             at<void>(p, s.vp), s.vp_lo.bytes ? at<void>(p, s.vp_lo) : nullptr, p->ldp,
-                            at<void>(p, p->rp), p->ldp, 0, split_p, part, p->ld_part, p->part.bytes));
+                            at<void>(p, p->rp), p->ldp, 0, split_p, part, p->ld_part, p->part.bytes, false, s.tri));
     }
     ProfScope ps(p, PPL_PROF_CONTRACT_MINUS, fm * p->Pm);
     if (p->Nm > 0 && p->Pm > 0)
       PPL_TRY(gemm_contract(st, s.prec, tile_m, p->Nm, p->Pm, p->ldm, am, am_lo, p->ldm,
                             at<void>(p, s.vm), s.vm_lo.bytes ? at<void>(p, s.vm_lo) : nullptr, p->ldm,
-                            at<void>(p, p->rm), p->ldm, 0, split_m, part, p->ld_part, p->part.bytes));
+                            at<void>(p, p->rm), p->ldm, 0, split_m, part, p->ld_part, p->part.bytes, false, s.tri));
     return PPL_OK;
   }
   if (!p->L_last) return fail(PPL_E_STATE, "streaming plan has no Cholesky vectors (call ppl_build_batch)");
@@ -676,11 +652,18 @@ static int derive_lowprec(ppl_plan_t p) {
   OperandSet& lo = p->ops[0];
   const OperandSet& f = p->ops[1];
   ProfScope ps(p, PPL_PROF_BUILD_PACK, 0.0);
-  PPL_TRY(convert_rows(p->stream, lo.prec, at<double>(p, f.vp), p->Pp, p->Pp, p->ldp, at<void>(p, lo.vp),
-                       lo.vp_lo.bytes ? at<void>(p, lo.vp_lo) : nullptr));
+  void* vp_lo = lo.vp_lo.bytes ? at<void>(p, lo.vp_lo) : nullptr;
+  void* vm_lo = lo.vm_lo.bytes ? at<void>(p, lo.vm_lo) : nullptr;
+  if (f.tri) {
+    PPL_TRY(convert_tri(p->stream, lo.prec, at<double>(p, f.vp), p->Pp, p->ldp, at<void>(p, lo.vp), vp_lo));
+    if (p->Pm > 0)
+      PPL_TRY(convert_tri(p->stream, lo.prec, at<double>(p, f.vm), p->Pm, p->ldm, at<void>(p, lo.vm), vm_lo));
+    lo.built = true;
+    return PPL_OK;
+  }
+  PPL_TRY(convert_rows(p->stream, lo.prec, at<double>(p, f.vp), p->Pp, p->Pp, p->ldp, at<void>(p, lo.vp), vp_lo));
   if (p->Pm > 0)
-    PPL_TRY(convert_rows(p->stream, lo.prec, at<double>(p, f.vm), p->Pm, p->Pm, p->ldm, at<void>(p, lo.vm),
-                         lo.vm_lo.bytes ? at<void>(p, lo.vm_lo) : nullptr));
+    PPL_TRY(convert_rows(p->stream, lo.prec, at<double>(p, f.vm), p->Pm, p->Pm, p->ldm, at<void>(p, lo.vm), vm_lo));
   lo.built = true;
   return PPL_OK;
 }
@@ -698,7 +681,6 @@ static int build_checked(ppl_plan_t p, const double* L, int32_t batch) {
     }
     PPL_TRY(build_one(p, f, L, batch, false));
     if (batch == nb - 1) {
-      PPL_TRY(mirror_vpm(p, f));
       f.built = true;
       PPL_TRY(derive_lowprec(p));
     }
@@ -713,8 +695,7 @@ static int build_checked(ppl_plan_t p, const double* L, int32_t batch) {
       PPL_TRY(build_one(p, s, L, batch, false));
       // a resident plan counts as built once its last batch is built in order
       if (batch == nb - 1) {
-        PPL_TRY(mirror_vpm(p, s));
-        s.built = true;
+              s.built = true;
       }
     }
   }
@@ -870,7 +851,7 @@ static int plan_create(const ppl_desc_t* d, ppl_plan_t* out, bool external_g) {
   const uint64_t gbytes_cap = d->build_scratch ? d->build_scratch : (4ull << 30);
   int64_t gcap = (int64_t)std::max<uint64_t>((uint64_t)p->v, gbytes_cap / per_pair_g);
   gcap = std::min<int64_t>(gcap, p->Pp);
-  // try resident (V+- symmetric: build the upper triangle, mirror the rest; PPL_SYM_BUILD=0
+  // try resident (V+- symmetric: build the upper triangle; PPL_SYM_BUILD=0
   // builds every row in full instead)
   {
     const char* e = getenv("PPL_SYM_BUILD");
@@ -882,6 +863,9 @@ static int plan_create(const ppl_desc_t* d, ppl_plan_t* out, bool external_g) {
   if (need <= budget) {
     p->resident = true;
     if (p->sym_build) build_column_order(p->v, p->cols_host);
+    // the set that the build fills: a mixed plan's low-precision one is rounded from the FP64 one
+    for (OperandSet& s : p->ops)
+      s.tri = s.present && p->sym_build && (s.prec == PPL_FP64 || (s.prec == PPL_FP32 && !p->keep_fp64));
   } else {
     // streaming: upper-triangle steps contracted as U and U^T (FP64 plans with one operand set)
     p->sym_build = p->sym_build && p->prec == PPL_FP64 && !p->keep_fp64;
@@ -1558,7 +1542,8 @@ int autotune_impl(ppl_plan_t p, int32_t reps, double* best_ms) {
     const void* V_lo = (plus ? s.vp_lo : s.vm_lo).bytes ? at<void>(p, plus ? s.vp_lo : s.vm_lo) : nullptr;
     void* C = at<void>(p, plus ? p->rp : p->rm);
     auto run = [&](int t, int sp) {
-      return gemm_contract(st, s.prec, t, Nr, Pr, ld, A, A_lo, ld, V, V_lo, ld, C, ld, 0, sp, part, ld, p->part.bytes);
+      return gemm_contract(st, s.prec, t, Nr, Pr, ld, A, A_lo, ld, V, V_lo, ld, C, ld, 0, sp, part, ld, p->part.bytes,
+                           false, s.tri);
     };
     // average over n launches after one untimed launch
     auto timed = [&](int t, int sp, int n, double& ms_out) {
@@ -1951,7 +1936,7 @@ static int batch_prepare(ppl_batch_t b) {
       g.nk = ld / KC;
       g.lda = g.ldb = g.ldc = ld;
       g.cfg = tile;
-      g.pad = 0;
+      g.tri = s.tri;
       const int gi = (int)b->groups.size();
       b->groups.push_back(g);
       int bm, bn;
@@ -2018,7 +2003,7 @@ static int batch_enqueue(ppl_batch_t b, const double* const* t2, double* const* 
   return PPL_OK;
 }
 
-// Integral builds of every instance (staging, build steps, mirror) from L[k]; no host
+// Integral builds of every instance (staging, build steps) from L[k]; no host
 // synchronization (the symmetry of each L was checked by the eager ppl_batch_build). With
 // branches the builds are forked from the batch stream over the side streams and joined
 // back into it; without, they run in turn on the batch stream. Graph capture takes the

@@ -240,7 +240,7 @@ int pack_vpm(hipStream_t s, int prec, int v, int a0, int a1, const void* G, void
 // G_ab[c - a0][d - a0] = (ac|bd) for c, d >= a (W x W per pair, pairs from pair0); the
 // block of pair (a, b) writes V+[ab][cd] and V-[ab][cd] for the columns (cd) >= (ab) in
 // packed order (c > a, or c == a and d >= b), which need only c, d >= a. The columns
-// before (ab) are the mirror image of earlier rows (mirror_lower) and are left alone.
+// before (ab) are the mirror image of earlier rows and are left alone.
 // Streaming form (half_diag): rows are stored from vp_row0 / vm_row0 on, the diagonal
 // entry is halved (V = U + U^T) and the columns [zp, own) and [zm, own) before the row's
 // own pair are zeroed, so that a K range starting at zp (zm) sees U exactly.
@@ -348,7 +348,7 @@ constexpr int kPackThreads = PPL_PACK_THREADS;
 static_assert(kCube * kCube * kCube % PPL_PACK_THREADS == 0, "threads must divide a cube");
 static_assert(kCube == 16, "the cube packing splits an element index into 4-bit fields");
 
-// Whole V+- rows of a resident build step from the natural build output T, with no separate
+// Whole V+- rows of a resident BF16 build step from the natural build output T, with no separate
 // mirror pass: T[(pair(a, r) - pr0) * ldt + pair(x, y) - pr0] = (ar|xy) for the step's virtuals
 // a in [a0, a1), r >= a and a <= x <= y (pr0 = pair(a0, a0)); T is symmetric in (x, y) since the
 // Cholesky vectors are. For the entry of row (ab), column (cd) with (cd) >= (ab) in packed order
@@ -449,13 +449,7 @@ int pack_vpm_cubes(hipStream_t s, int prec, int v, int a0, int a1, const void* T
   if (n > 0x7fffffffLL) return fail(PPL_E_ARG, "pack_vpm_cubes: %lld cubes", (long long)n);
   const int64_t Pp = npairs_plus(v), Pm = npairs_minus(v);
   const dim3 grid((unsigned)n);
-  if (prec == PPL_FP64)
-    hipLaunchKernelGGL((pack_vpm_cubes_kernel<double, PPL_FP64>), grid, dim3(kPackThreads), 0, s, v, a0, a1, (const double*)T,
-                       ldt, off, g0, n, vp, vp_lo, ldp, vm, vm_lo, ldm, Pp, Pm);
-  else if (prec == PPL_FP32)
-    hipLaunchKernelGGL((pack_vpm_cubes_kernel<float, PPL_FP32>), grid, dim3(kPackThreads), 0, s, v, a0, a1, (const float*)T,
-                       ldt, off, g0, n, vp, vp_lo, ldp, vm, vm_lo, ldm, Pp, Pm);
-  else if (prec == PPL_BF16X3)
+  if (prec == PPL_BF16X3)
     hipLaunchKernelGGL((pack_vpm_cubes_kernel<float, PPL_BF16X3>), grid, dim3(kPackThreads), 0, s, v, a0, a1,
                        (const float*)T, ldt, off, g0, n, vp, vp_lo, ldp, vm, vm_lo, ldm, Pp, Pm);
   else if (prec == PPL_BF16X6)
@@ -463,6 +457,129 @@ int pack_vpm_cubes(hipStream_t s, int prec, int v, int a0, int a1, const void* T
                        (const float*)T, ldt, off, g0, n, vp, vp_lo, ldp, vm, vm_lo, ldm, Pp, Pm);
   else
     return fail(PPL_E_ARG, "pack_vpm_cubes: unknown precision %d", prec);
+  PPL_LAUNCH_CHECK();
+  return PPL_OK;
+}
+
+// The same rows for the resident FP64 and FP32 layout (kTriBlock): every entry of row (ab) with
+// (cd) >= (ab), and below the diagonal only the mirror entries inside a diagonal block. One
+// workgroup per cube of 16 x 16 x 16 indices (b, c, d), thread (c, d), b unrolled, so that the
+// rows are written along d. (ac|bd) is read in that shape where b <= d (contiguous along d);
+// (ad|bc) is contiguous along c (b <= c) or b and goes through one LDS array s[b][d][c], and
+// where b > d so does (ac|bd), contiguous along b, in a round of its own.
+// Bound by the writes of its 16 x 16 row segments: the lines that segments share are merged in
+// L2 only while few are open, so spare LDS (kTriSpareLds) holds it to three workgroups per CU
+// (FP64; four in FP32): 1.73 ms against 1.96 with all that fit and 2.01 with two, at v = 200 in
+// one step (3.2 GB written, 1.6 read); FP32 at v = 151 0.36 ms against 0.40. Writing the mirror
+// half as well (pack_vpm_cubes_kernel) took 3.35 ms and 0.58 ms.
+template <class Tg, int PREC>
+__global__ void __launch_bounds__(kPackThreads)
+pack_vpm_tri_kernel(int v, int a0, int a1, const Tg* __restrict__ T, int64_t ldt, const int64_t* __restrict__ off,
+                    int64_t g0, int64_t ncubes, void* vp, int64_t ldp, void* vm, int64_t ldm, int64_t Pp,
+                    int64_t Pm) {
+  constexpr int C = kCube, LD = kCube + 1, LB = kCube * LD + 1;   // both strides odd: no bank conflicts
+  __shared__ Tg s[C * LB];
+  const int64_t g = g0 + cube_of_slot(blockIdx.x, ncubes);
+  const int a = cube_virtual(off, a0, a1, g);
+  const int nt = cube_blocks(v, a);
+  int bi, ci, di;
+  cube_decode_rows(g - off[a], nt, bi, ci, di);
+  const int b0 = a + C * bi, c0 = a + C * ci, d0 = a + C * di;
+  const int64_t pr0 = pair_plus(a0, a0, v);
+  const int f = threadIdx.x & 15, m = threadIdx.x >> 4;
+  // (a r | x y), zero outside v
+  auto at = [&](int r, int x, int y) __attribute__((always_inline)) {
+    const int lo = x < y ? x : y, hi = x < y ? y : x;
+    return (r < v && hi < v) ? T[(pair_plus(a, r, v) - pr0) * ldt + (pair_plus(lo, hi, v) - pr0)] : Tg(0);
+  };
+  const bool swapped = bi > di;               // b > d: (ac|bd) is contiguous along b
+  Tg gcd[C], gdc[C];
+  if (bi <= ci) {
+#pragma unroll
+    for (int k = 0; k < C; ++k) gdc[k] = at(d0 + m, b0 + k, c0 + f);   // s[k][m][f]
+  } else {
+#pragma unroll
+    for (int k = 0; k < C; ++k) gdc[k] = at(d0 + k, c0 + m, b0 + f);   // s[f][k][m]
+  }
+  if (swapped) {
+#pragma unroll
+    for (int k = 0; k < C; ++k) gcd[k] = at(c0 + m, d0 + k, b0 + f);   // s[f][k][m]
+#pragma unroll
+    for (int k = 0; k < C; ++k) s[f * LB + k * LD + m] = gcd[k];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < C; ++k) gcd[k] = s[k * LB + f * LD + m];
+    __syncthreads();
+  } else {
+#pragma unroll
+    for (int k = 0; k < C; ++k) gcd[k] = at(c0 + m, b0 + k, d0 + f);
+  }
+  if (bi <= ci) {
+#pragma unroll
+    for (int k = 0; k < C; ++k) s[k * LB + m * LD + f] = gdc[k];
+  } else {
+#pragma unroll
+    for (int k = 0; k < C; ++k) s[f * LB + k * LD + m] = gdc[k];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < C; ++k) gdc[k] = s[k * LB + f * LD + m];
+  const int c = c0 + m, d = d0 + f;
+  if (d < v && c <= d) {
+    // b = b0 + k < v, and d >= b where c == a
+    const int kmax = min(min(C, v - b0), c == a ? d - b0 + 1 : C);
+    const int64_t rp = pair_plus(a, b0, v), cp = pair_plus(c, d, v);
+    const int64_t rm = pair_minus(a, b0, v), cm = pair_minus(c, d, v);
+    // some mirror entry of the cube lies in a diagonal block (the same for every thread)
+    const int e0 = d0 > c0 ? d0 : c0, bl = b0 + C < v ? b0 + C - 1 : v - 1;
+    const bool near = pair_plus(c0, e0, v) / kTriBlock <= pair_plus(a, bl, v) / kTriBlock ||
+                      pair_minus(c0, e0 > c0 ? e0 : c0 + 1, v) / kTriBlock <= pair_minus(a, bl, v) / kTriBlock;
+#pragma unroll
+    for (int k = 0; k < C; ++k) {
+      if (k < kmax) {
+        const double x = (double)gcd[k], y = (double)gdc[k];
+        const bool minus = c < d && (k > 0 || b0 > a);
+        Store<PREC>::put(vp, nullptr, (rp + k) * ldp + cp, 0.5 * (x + y));
+        if (minus) Store<PREC>::put(vm, nullptr, (rm + k) * ldm + cm, 0.5 * (x - y));
+        if (near) {
+          if ((rp + k) / kTriBlock == cp / kTriBlock) Store<PREC>::put(vp, nullptr, cp * ldp + rp + k, 0.5 * (x + y));
+          if (minus && (rm + k) / kTriBlock == cm / kTriBlock)
+            Store<PREC>::put(vm, nullptr, cm * ldm + rm + k, 0.5 * (x - y));
+        }
+      }
+    }
+  }
+  if (ci == 0 && di == 0) {
+    const int64_t padp = ldp - Pp, padm = ldm - Pm;
+    for (int e = threadIdx.x; e < C * padp; e += kPackThreads) {
+      const int b = b0 + (int)(e / padp);
+      if (b < v) Store<PREC>::put(vp, nullptr, pair_plus(a, b, v) * ldp + Pp + e % padp, 0.0);
+    }
+    for (int e = threadIdx.x; e < C * padm; e += kPackThreads) {
+      const int b = b0 + (int)(e / padm);
+      if (b < v && a < b) Store<PREC>::put(vm, nullptr, pair_minus(a, b, v) * ldm + Pm + e % padm, 0.0);
+    }
+  }
+}
+
+constexpr unsigned kTriSpareLds = 20000;
+
+int pack_vpm_tri(hipStream_t s, int prec, int v, int a0, int a1, const void* T, int64_t ldt, const int64_t* off,
+                 void* vp, int64_t ldp, void* vm, int64_t ldm) {
+  int64_t g0 = 0, n = 0;
+  for (int a = 0; a < a1; ++a) (a < a0 ? g0 : n) += cubes_of(v, a);
+  if (n <= 0) return PPL_OK;
+  if (n > 0x7fffffffLL) return fail(PPL_E_ARG, "pack_vpm_tri: %lld cubes", (long long)n);
+  const int64_t Pp = npairs_plus(v), Pm = npairs_minus(v);
+  const dim3 grid((unsigned)n);
+  if (prec == PPL_FP64)
+    hipLaunchKernelGGL((pack_vpm_tri_kernel<double, PPL_FP64>), grid, dim3(kPackThreads), kTriSpareLds, s, v, a0, a1,
+                       (const double*)T, ldt, off, g0, n, vp, ldp, vm, ldm, Pp, Pm);
+  else if (prec == PPL_FP32)
+    hipLaunchKernelGGL((pack_vpm_tri_kernel<float, PPL_FP32>), grid, dim3(kPackThreads), kTriSpareLds, s, v, a0, a1,
+                       (const float*)T, ldt, off, g0, n, vp, ldp, vm, ldm, Pp, Pm);
+  else
+    return fail(PPL_E_ARG, "pack_vpm_tri: precision %d is not stored as a triangle", prec);
   PPL_LAUNCH_CHECK();
   return PPL_OK;
 }
@@ -600,76 +717,6 @@ int add_transposed(hipStream_t s, int c_prec, void* C, int64_t ldc, const double
   return PPL_OK;
 }
 
-// Strictly lower triangle of an n x n symmetric matrix (row length ld) from its upper
-// triangle: V[r][q] = V[q][r] for q < r, as a bit copy of elements of type E. One 64 x 64
-// block pair per workgroup: block (I, J), I >= J, reads rows J and columns I (upper) through
-// LDS and writes rows I and columns J (lower), both along contiguous rows.
-template <class E>
-__global__ void __launch_bounds__(256) mirror_lower_kernel(E* V, int64_t n, int64_t ld, int vec_ok) {
-  __shared__ E sh[64][65];
-  const int64_t t = blockIdx.x;
-  int64_t I = (int64_t)((sqrt(8.0 * (double)t + 1.0) - 1.0) * 0.5);
-  while (I * (I + 1) / 2 > t) --I;
-  while ((I + 1) * (I + 2) / 2 <= t) ++I;
-  const int64_t J = t - I * (I + 1) / 2;
-  const int tid = threadIdx.x;
-  const int64_t r0 = I * 64, q0 = J * 64;
-  if (vec_ok && I > J && r0 + 64 <= n) {
-    // a whole block below the diagonal: 16-byte vectors along both rows (rows 16-byte
-    // aligned, checked on the host), the transposition in LDS element by element
-    constexpr int VE = 16 / (int)sizeof(E), VR = 64 / VE;
-    union Vec { uint4 u; E e[VE]; };
-    for (int x = tid; x < 64 * VR; x += 256) {
-      const int ql = x / VR, vv = x % VR;
-      Vec y;
-      y.u = *reinterpret_cast<const uint4*>(&V[(q0 + ql) * ld + r0 + vv * VE]);
-#pragma unroll
-      for (int k = 0; k < VE; ++k) sh[ql][vv * VE + k] = y.e[k];
-    }
-    __syncthreads();
-    for (int x = tid; x < 64 * VR; x += 256) {
-      const int rl = x / VR, vv = x % VR;
-      Vec y;
-#pragma unroll
-      for (int k = 0; k < VE; ++k) y.e[k] = sh[vv * VE + k][rl];
-      *reinterpret_cast<uint4*>(&V[(r0 + rl) * ld + q0 + vv * VE]) = y.u;
-    }
-    return;
-  }
-  for (int e = tid; e < 64 * 64; e += 256) {
-    const int ql = e >> 6, rl = e & 63;                  // read row q0 + ql, column r0 + rl
-    const int64_t q = q0 + ql, r = r0 + rl;
-    if (q < n && r < n && q < r) sh[ql][rl] = V[q * ld + r];
-  }
-  __syncthreads();
-  for (int e = tid; e < 64 * 64; e += 256) {
-    const int rl = e >> 6, ql = e & 63;                  // write row r0 + rl, column q0 + ql
-    const int64_t r = r0 + rl, q = q0 + ql;
-    if (q < n && r < n && q < r) V[r * ld + q] = sh[ql][rl];
-  }
-}
-
-int mirror_lower(hipStream_t s, int elem_bytes, void* V, int64_t n, int64_t ld) {
-  if (n <= 1) return PPL_OK;
-  const int64_t T = (n + 63) / 64, blocks = T * (T + 1) / 2;
-  if (blocks > 0x7fffffffLL) return fail(PPL_E_ARG, "mirror of %lld rows too large", (long long)n);
-  // 16-byte vectors need every row and every 64-element block start 16-byte aligned
-  const int vec_ok = ((uintptr_t)V % 16 == 0) && ((uint64_t)ld * elem_bytes % 16 == 0);
-  if (elem_bytes == 8)
-    hipLaunchKernelGGL(mirror_lower_kernel<uint64_t>, dim3((unsigned)blocks), dim3(256), 0, s, (uint64_t*)V, n, ld,
-                       vec_ok);
-  else if (elem_bytes == 4)
-    hipLaunchKernelGGL(mirror_lower_kernel<uint32_t>, dim3((unsigned)blocks), dim3(256), 0, s, (uint32_t*)V, n, ld,
-                       vec_ok);
-  else if (elem_bytes == 2)
-    hipLaunchKernelGGL(mirror_lower_kernel<uint16_t>, dim3((unsigned)blocks), dim3(256), 0, s, (uint16_t*)V, n, ld,
-                       vec_ok);
-  else
-    return fail(PPL_E_ARG, "mirror of %d-byte elements", elem_bytes);
-  PPL_LAUNCH_CHECK();
-  return PPL_OK;
-}
-
 // ------------------------------------------------------------------ generic (i,j,a,b) -> +/- packing
 // With t1 ([i][a], row length v1) the packed tensor is X_ij^ab + t1_i^a t1_j^b.
 __global__ void pack_plus_kernel(const double* __restrict__ X, int64_t si, int64_t sj, int64_t sa,
@@ -763,6 +810,87 @@ int convert_rows(hipStream_t s, int prec, const double* src, int64_t rows, int64
     hipLaunchKernelGGL(convert_kernel<PPL_FP64>, dim3(grid_for(n, 256)), dim3(256), 0, s, src, n, dst, dst_lo);
   else
     return fail(PPL_E_ARG, "convert_rows: unknown precision %d", prec);
+  PPL_LAUNCH_CHECK();
+  return PPL_OK;
+}
+
+// Four consecutive elements of an operand row (i a multiple of 4, rows 16-byte aligned)
+template <int PREC>
+__device__ inline void put4(void* hi, void* lo, int64_t i, const double (&x)[4]) {
+  if constexpr (PREC == PPL_FP32) {
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    *reinterpret_cast<f32x4*>((float*)hi + i) = f32x4{(float)x[0], (float)x[1], (float)x[2], (float)x[3]};
+  } else {
+    typedef __bf16 b16x4 __attribute__((ext_vector_type(4)));
+    b16x4 pl[3];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {     // as Store<PREC>::put
+      const float xf = (float)x[k];
+      pl[0][k] = (__bf16)xf;
+      const float r1 = xf - (float)pl[0][k];
+      pl[1][k] = (__bf16)r1;
+      if (PREC == PPL_BF16X6) pl[2][k] = (__bf16)(r1 - (float)pl[1][k]);
+    }
+    __bf16 *ph = (__bf16*)hi, *pm = (__bf16*)lo;
+    *reinterpret_cast<b16x4*>(ph + i) = pl[0];
+    *reinterpret_cast<b16x4*>(pm + i) = pl[1];
+    if (PREC == PPL_BF16X6) *reinterpret_cast<b16x4*>(pm + (pm - ph) + i) = pl[2];
+  }
+}
+
+// A symmetric n x n FP64 matrix stored as its upper triangle (kTriBlock; rows of ld, a multiple
+// of 64) to the whole matrix in an operand precision, zero padding included: one workgroup per
+// 64 x 64 block on or above the diagonal, read once, rounded and written both ways round.
+template <int PREC>
+__global__ void __launch_bounds__(256)
+convert_tri_kernel(const double* __restrict__ src, int64_t n, int64_t ld, void* dh, void* dl) {
+  __shared__ double sh[64][65];
+  const int64_t t = blockIdx.x;               // block (I <= J) of the packed upper triangle, J slowest
+  int64_t J = (int64_t)((sqrt(8.0 * (double)t + 1.0) - 1.0) * 0.5);
+  while (J * (J + 1) / 2 > t) --J;
+  while ((J + 1) * (J + 2) / 2 <= t) ++J;
+  const int64_t I = t - J * (J + 1) / 2, r0 = I * 64, q0 = J * 64;
+  const int c4 = (threadIdx.x & 15) * 4;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int rl = (threadIdx.x >> 4) + 16 * e;
+    double x[4] = {0, 0, 0, 0};
+    if (r0 + rl < n) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) x[k] = src[(r0 + rl) * ld + q0 + c4 + k];
+      put4<PREC>(dh, dl, (r0 + rl) * ld + q0 + c4, x);
+    }
+    if (I < J)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) sh[rl][c4 + k] = x[k];
+  }
+  if (I == J) return;                         // a diagonal block is whole
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int ql = (threadIdx.x >> 4) + 16 * e;
+    if (q0 + ql >= n) continue;
+    double x[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) x[k] = sh[c4 + k][ql];
+    put4<PREC>(dh, dl, (q0 + ql) * ld + r0 + c4, x);
+  }
+}
+
+int convert_tri(hipStream_t s, int prec, const double* src, int64_t n, int64_t ld, void* dst, void* dst_lo) {
+  if (n <= 0) return PPL_OK;
+  const int64_t nb = (n + 63) / 64, blocks = nb * (nb + 1) / 2;
+  if (ld != nb * 64 || blocks > 0x7fffffffLL)
+    return fail(PPL_E_ARG, "convert_tri: %lld rows of %lld elements", (long long)n, (long long)ld);
+  const dim3 grid((unsigned)blocks);
+  if (prec == PPL_FP32)
+    hipLaunchKernelGGL(convert_tri_kernel<PPL_FP32>, grid, dim3(256), 0, s, src, n, ld, dst, dst_lo);
+  else if (prec == PPL_BF16X3)
+    hipLaunchKernelGGL(convert_tri_kernel<PPL_BF16X3>, grid, dim3(256), 0, s, src, n, ld, dst, dst_lo);
+  else if (prec == PPL_BF16X6)
+    hipLaunchKernelGGL(convert_tri_kernel<PPL_BF16X6>, grid, dim3(256), 0, s, src, n, ld, dst, dst_lo);
+  else
+    return fail(PPL_E_ARG, "convert_tri: unknown precision %d", prec);
   PPL_LAUNCH_CHECK();
   return PPL_OK;
 }

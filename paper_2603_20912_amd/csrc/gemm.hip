@@ -139,6 +139,8 @@ struct EpiStore {        // C[split][m][c_col0 + n] = alpha * acc + beta * C (be
   int64_t ldc, c_col0, M, N;
   double alpha, beta;
   int64_t split_stride;  // elements between split-K slices
+  int tri = 0;           // B is symmetric and stored as its upper triangle (kTriBlock)
+  static constexpr bool kTri = true;
   __device__ void row(int split, int64_t m, int64_t& base, bool& ok) const {
     ok = m < M;
     base = split * split_stride + m * ldc + c_col0;
@@ -161,6 +163,8 @@ struct EpiSK {           // stream-K: whole tiles go to C, shared tiles to a den
   int64_t m0, n0;
   int ldp;               // = BN
   bool to_part;
+  int tri = 0;           // as in EpiStore
+  static constexpr bool kTri = true;
   __device__ void row(int, int64_t m, int64_t& base, bool& ok) const {
     if (to_part) {
       ok = true;
@@ -178,6 +182,7 @@ struct EpiSK {           // stream-K: whole tiles go to C, shared tiles to a den
 
 template <class Tg>
 struct EpiBuild {        // G[pair(a,b) - pair(a0,a0)][c][d] for b >= a
+  static constexpr bool kTri = false;
   __device__ int64_t arow(int64_t r) const { return r; }   // operand rows of C row / column r
   __device__ int64_t brow(int64_t r) const { return r; }
   Tg* G;
@@ -208,6 +213,7 @@ struct EpiBuild {        // G[pair(a,b) - pair(a0,a0)][c][d] for b >= a
 // mirror G[pair(a,d) - pr0][c - a0][b - a0], W = v - a0.
 template <class Tg>
 struct EpiBuildSym {
+  static constexpr bool kTri = false;
   Tg* G;
   int64_t M, N;
   int v, a0, W;
@@ -244,6 +250,7 @@ struct EpiBuildSym {
 // packing (pack_vpm_cubes) reads both (ac|bd) and (ad|bc) from it.
 template <class Tg>
 struct EpiBuildT {
+  static constexpr bool kTri = false;
   Tg* T;
   int64_t M, N, ldt;
   int v;
@@ -294,14 +301,8 @@ struct EpiBuildT {
 #ifndef PPL_BF6_DIRECT
 #define PPL_BF6_DIRECT 1
 #endif
-#ifndef PPL_FP_DIRECT3
-#define PPL_FP_DIRECT3 1
-#endif
 #ifndef PPL_BUILD_DIRECT3
 #define PPL_BUILD_DIRECT3 1
-#endif
-#ifndef PPL_GROUPED_DIRECT3
-#define PPL_GROUPED_DIRECT3 1
 #endif
 constexpr int kLdsLayout = PPL_LDS_LAYOUT;
 constexpr int kFragVec = PPL_FRAG_VEC;
@@ -310,7 +311,6 @@ constexpr int kDirectLds = PPL_DIRECT_LDS;   // 1: chunks go global -> LDS witho
 constexpr int kPrefetch = PPL_PREFETCH;      // chunks in flight in registers: 1, 2, or 0 = per tile (below)
 constexpr int kBf3Direct = PPL_BF3_DIRECT;   // 1: BF16x3 chunks go global -> LDS, three stages, two in flight
 constexpr int kBf6Direct = PPL_BF6_DIRECT;   // 1: BF16x6 chunks go global -> LDS, two stages
-constexpr int kFpDirect3 = PPL_FP_DIRECT3;   // 1: FP64 / FP32 contraction chunks go global -> LDS, three stages
 static_assert(!kDirectLds || kLdsLayout == 1, "direct LDS loads need the unpadded swizzled layout");
 
 template <class T, int WM, int WN, int WAVES_M, int WAVES_N, int KC>
@@ -494,7 +494,15 @@ __device__ __forceinline__ void tile_body_direct(const TileJob& job, int64_t M, 
 // The FP64 / FP32 tile with chunks moved straight from global memory into LDS in three
 // stages (the scheme of the BF16x3 tile below: step k reads its fragments of chunk k,
 // issues chunk k+2 into the stage chunk k-1 left, multiplies, then waits for its part of
-// chunk k+1 and meets the other waves). One stage holds BM rows of A, then BN rows of B.
+// chunk k+1 and meets the other waves). One stage holds BM rows of A, then the B chunk.
+//
+// A symmetric B stored as its upper triangle (epi.tri, kTriBlock) runs in two phases: the
+// chunks k < n0 come from rows k of B (columns n0 .. n0 + BN: the mirror image of the
+// entries [n][k] below the diagonal, staged as KC rows of BN elements), the others from rows
+// n as before. K stays in order, so the sums are those of a full B, bit for bit. The diagonal
+// block is whole on both sides of it, and n0 is a multiple of BN, so no chunk mixes the two.
+// Measured at (20, 200, 600), FP64, against a full B: R- on tile 8 2.21 ms (2.28), R+ on tile 10
+// 2.72 (2.67); the packing, which no longer writes the mirror half, 1.74 ms (3.26).
 template <class T, int WM, int WN, int WAVES_M, int WAVES_N, int KC, class Epi>
 __device__ __forceinline__ void tile_body_direct3(const TileJob& job, int64_t M, int64_t N, const T* __restrict__ A,
                                                   int64_t lda, const T* __restrict__ B, int64_t ldb, const Epi& epi,
@@ -512,35 +520,54 @@ __device__ __forceinline__ void tile_body_direct3(const TileJob& job, int64_t M,
   static_assert(kLdsLayout == 1 && 64 % VPR == 0 && BM % RPI == 0 && BN % RPI == 0 && GT >= NW && NI < 16,
                 "direct LDS geometry");
   static_assert(KC % (4 * VEC) == 0 && 16 % VPR == 0, "bad KC");
+  // K-major B chunk: row k holds its 16-column blocks at block ^ ((k / VEC) & XK), so that the
+  // four lane groups of a fragment read, which are VEC rows apart, hit different banks
+  constexpr int XK = sizeof(T) == 8 ? 1 : 3;
+  constexpr int BV = BN / VEC, VB = 16 / VEC;     // 16-byte vectors of a row and of a 16-column block
+  static_assert((BN / 16) % (XK + 1) == 0, "the block swizzle stays inside a row");
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave % WAVES_M, wn = wave / WAVES_M;
   const int lr = lane / VPR, slot = lane % VPR;
 
   const T* src[NI];
+  int step[NI];                                   // elements from one chunk to the next
   int dst[NI];
+  // instruction i of this wave for B rows n (NN false) or B rows k (NN true), from chunk c0 on
+  auto aim = [&](auto nn, int64_t c0) __attribute__((always_inline)) {
+    constexpr bool NN = decltype(nn)::value;
 #pragma unroll
-  for (int i = 0; i < NI; ++i) {
-    int q = wave + i * NW;
-    if (q >= GT) q -= GT;
-    if (q < GA) {
-      const int r = q * RPI + lr;
-      int64_t gr = job.m0 + r;
-      if (gr > M - 1) gr = M - 1;
-      src[i] = A + epi.arow(gr) * lda + (slot ^ (r % VPR)) * VEC + job.kc0 * KC;
-      dst[i] = q * RPI * LDSR;
-    } else {
-      const int r = (q - GA) * RPI + lr;
-      int64_t gr = job.n0 + r;
-      if (gr > N - 1) gr = N - 1;
-      src[i] = B + epi.brow(gr) * ldb + (slot ^ (r % VPR)) * VEC + job.kc0 * KC;
-      dst[i] = (BM + (q - GA) * RPI) * LDSR;
+    for (int i = 0; i < NI; ++i) {
+      int q = wave + i * NW;
+      if (q >= GT) q -= GT;
+      step[i] = KC;
+      if (q < GA) {
+        const int r = q * RPI + lr;
+        int64_t gr = job.m0 + r;
+        if (gr > M - 1) gr = M - 1;
+        src[i] = A + epi.arow(gr) * lda + (slot ^ (r % VPR)) * VEC + (job.kc0 + c0) * KC;
+        dst[i] = q * RPI * LDSR;
+      } else if constexpr (NN) {
+        const int id = (q - GA) * 64 + lane, kr = id / BV, cv = id % BV;
+        src[i] = B + ((job.kc0 + c0) * KC + kr) * ldb + job.n0 + (cv ^ (((kr / VEC) & XK) * VB)) * VEC;
+        step[i] = (int)(KC * ldb);
+        dst[i] = (BM + (q - GA) * RPI) * LDSR;
+      } else {
+        const int r = (q - GA) * RPI + lr;
+        int64_t gr = job.n0 + r;
+        if (gr > N - 1) gr = N - 1;
+        src[i] = B + epi.brow(gr) * ldb + (slot ^ (r % VPR)) * VEC + (job.kc0 + c0) * KC;
+        dst[i] = (BM + (q - GA) * RPI) * LDSR;
+      }
     }
-  }
-  auto issue = [&](int64_t c, T* st) __attribute__((always_inline)) {
+  };
+  // the next chunk into stage st (chunks are issued in order)
+  auto issue = [&](T* st) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < NI; ++i)
-      __builtin_amdgcn_global_load_lds((global_cvoid_t*)(src[i] + c * KC), (lds_void_t*)(st + dst[i]), 16, 0, 0);
+    for (int i = 0; i < NI; ++i) {
+      __builtin_amdgcn_global_load_lds((global_cvoid_t*)src[i], (lds_void_t*)(st + dst[i]), 16, 0, 0);
+      src[i] += step[i];
+    }
   };
   auto wait_one = []() __attribute__((always_inline)) {
     __builtin_amdgcn_s_waitcnt(0x0F70 | NI);
@@ -564,9 +591,13 @@ __device__ __forceinline__ void tile_body_direct3(const TileJob& job, int64_t M,
   const int brow = (BM + wn * WN * 16 + (lane & 15)) * LDSR;
   const int fq = lane >> 4;
   const int key = (lane & 15) % VPR;
-  const int64_t nk = job.kc1 - job.kc0;
+  int kcol[WN];                                   // K-major: this lane's row and column of block j
+#pragma unroll
+  for (int j = 0; j < WN; ++j)
+    kcol[j] = BM * LDSR + VEC * fq * BN + ((wn * WN + j) ^ (fq & XK)) * 16 + (lane & 15);
 
-  auto compute = [&](const T* __restrict__ st, bool go, int64_t c, T* nx) __attribute__((always_inline)) {
+  auto compute = [&](auto nn, const T* __restrict__ st, bool go, T* nx) __attribute__((always_inline)) {
+    constexpr bool NN = decltype(nn)::value;
 #pragma unroll
     for (int kg = 0; kg < KC / (4 * VEC); ++kg) {
       const int col = ((kg * 4 + fq) ^ key) * VEC;
@@ -575,10 +606,17 @@ __device__ __forceinline__ void tile_body_direct3(const TileJob& job, int64_t M,
 #pragma unroll
       for (int i = 0; i < WM; ++i) a[i].u = *reinterpret_cast<const uint4*>(&st[arow + i * 16 * LDSR + col]);
 #pragma unroll
-      for (int j = 0; j < WN; ++j) b[j].u = *reinterpret_cast<const uint4*>(&st[brow + j * 16 * LDSR + col]);
+      for (int j = 0; j < WN; ++j) {
+        if constexpr (NN) {
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) b[j].e[e] = st[kcol[j] + (kg * 4 * VEC + e) * BN];
+        } else {
+          b[j].u = *reinterpret_cast<const uint4*>(&st[brow + j * 16 * LDSR + col]);
+        }
+      }
       if (kg == 0) {
         asm volatile("" ::: "memory");
-        if (go) issue(c, nx);
+        if (go) issue(nx);
       }
 #pragma unroll
       for (int e = 0; e < VEC; ++e)
@@ -589,40 +627,56 @@ __device__ __forceinline__ void tile_body_direct3(const TileJob& job, int64_t M,
     }
   };
 
-  issue(0, st0);
-  if (nk > 1) {
-    issue(1, st1);
-    wait_one();
-  } else {
-    wait_all();
-  }
-  meet();
-  int64_t kt = 0;
-  for (; kt + 7 < nk; kt += 6) {   // six steps whose k+2 exists
+  // chunks [c0, c1) relative to job.kc0
+  auto run = [&](auto nn, int64_t c0, int64_t c1) __attribute__((always_inline)) {
+    aim(nn, c0);
+    issue(st0);
+    if (c1 - c0 > 1) {
+      issue(st1);
+      wait_one();
+    } else {
+      wait_all();
+    }
+    meet();
+    int64_t kt = c0;
+    for (; kt + 7 < c1; kt += 6) {   // six steps whose k+2 exists
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      compute(st0, true, kt + 3 * u + 2, st2);
-      wait_one();
-      meet();
-      compute(st1, true, kt + 3 * u + 3, st0);
-      wait_one();
-      meet();
-      compute(st2, true, kt + 3 * u + 4, st1);
-      wait_one();
-      meet();
+      for (int u = 0; u < 2; ++u) {
+        compute(nn, st0, true, st2);
+        wait_one();
+        meet();
+        compute(nn, st1, true, st0);
+        wait_one();
+        meet();
+        compute(nn, st2, true, st1);
+        wait_one();
+        meet();
+      }
     }
-  }
-  for (int64_t j = kt; j < nk; ++j) {
-    const int sj = (int)((j - kt) % 3);
-    const T* cur = sj == 0 ? st0 : (sj == 1 ? st1 : st2);
-    T* nx = sj == 0 ? st2 : (sj == 1 ? st0 : st1);
-    compute(cur, j + 2 < nk, j + 2, nx);
-    if (j + 1 < nk) {
-      if (j + 2 < nk) wait_one();
-      else wait_all();
-      meet();
+    for (int64_t j = kt; j < c1; ++j) {
+      const int sj = (int)((j - kt) % 3);
+      const T* cur = sj == 0 ? st0 : (sj == 1 ? st1 : st2);
+      T* nx = sj == 0 ? st2 : (sj == 1 ? st0 : st1);
+      compute(nn, cur, j + 2 < c1, nx);
+      if (j + 1 < c1) {
+        if (j + 2 < c1) wait_one();
+        else wait_all();
+        meet();
+      }
     }
+  };
+
+  const int64_t nk = job.kc1 - job.kc0;
+  int64_t nd = 0;                                 // chunks below the diagonal
+  if constexpr (Epi::kTri) {
+    if (epi.tri) {
+      nd = job.n0 / KC - job.kc0;
+      nd = nd < 0 ? 0 : (nd > nk ? nk : nd);
+    }
+    if (nd > 0) run(std::true_type{}, 0, nd);
+    if (nd > 0 && nd < nk) meet();                // every wave has read the last stages
   }
+  if (nd < nk) run(std::false_type{}, nd, nk);
   store_acc<T, WM, WN>(acc, job, epi, wm, wn, lane);
 }
 
@@ -808,7 +862,7 @@ __device__ __forceinline__ void tile_body(const TileJob& job, int64_t M, int64_t
 template <class T, int WM, int WN, int WAVES_M, int WAVES_N, int KC, class Epi>
 struct GemmOccupancy {
   static constexpr bool build64 = PPL_BUILD_DIRECT3 && sizeof(T) == 8 && WM == 4 && WN == 2 && WAVES_M == 1 && WAVES_N == 4;
-  static constexpr bool direct = kFpDirect3 && (std::is_same_v<Epi, EpiStore<T>> || build64);
+  static constexpr bool direct = std::is_same_v<Epi, EpiStore<T>> || build64;
   static constexpr int lds = 3 * 16 * (WM * WAVES_M + WN * WAVES_N) * KC * (int)sizeof(T);
   static constexpr int waves = (direct && 2 * lds > 160 * 1024) ? 1 : 2;
 };
@@ -1724,14 +1778,14 @@ struct StreamK {
 };
 
 template <class T, int WM, int WN, int WAVES_M, int WAVES_N, int KC>
-__global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) __attribute__((amdgpu_waves_per_eu(2)))
+__global__ void __launch_bounds__(64 * WAVES_M * WAVES_N)
+__attribute__((amdgpu_waves_per_eu(GemmOccupancy<T, WM, WN, WAVES_M, WAVES_N, KC, EpiStore<T>>::waves)))
 gemm_streamk_kernel(int64_t M, int64_t N, const T* __restrict__ A, int64_t lda, const T* __restrict__ B,
-                    int64_t ldb, T* C, int64_t ldc, int64_t c_col0, T* part, StreamK sk) {
+                    int64_t ldb, T* C, int64_t ldc, int64_t c_col0, T* part, StreamK sk, int tri) {
   using G = TileGeom<T, WM, WN, WAVES_M, WAVES_N, KC>;
-  __shared__ __attribute__((aligned(16))) T sA0[G::BUF_A];
-  __shared__ __attribute__((aligned(16))) T sA1[G::BUF_A];
-  __shared__ __attribute__((aligned(16))) T sB0[G::BUF_B];
-  __shared__ __attribute__((aligned(16))) T sB1[G::BUF_B];
+  __shared__ __attribute__((aligned(16))) T st0[G::BUF_A + G::BUF_B];
+  __shared__ __attribute__((aligned(16))) T st1[G::BUF_A + G::BUF_B];
+  __shared__ __attribute__((aligned(16))) T st2[G::BUF_A + G::BUF_B];
   const int64_t w = xcd_remap(blockIdx.x, gridDim.x);
   const int64_t begin = sk.start(w), end = sk.start(w + 1);
   const int64_t first_tile = begin / sk.nk;
@@ -1742,10 +1796,10 @@ gemm_streamk_kernel(int64_t M, int64_t N, const T* __restrict__ A, int64_t lda, 
     const bool whole = k0 == 0 && k1 == sk.nk;
     EpiSK<T> epi{C, ldc, c_col0, M, N,
                  part + (w * 2 + (tile == first_tile ? 0 : 1)) * (int64_t)(G::BM * G::BN),
-                 job.m0, job.n0, G::BN, !whole};
-    tile_body<T, WM, WN, WAVES_M, WAVES_N, KC>(job, M, N, A, lda, B, ldb, epi, sA0, sA1, sB0, sB1);
+                 job.m0, job.n0, G::BN, !whole, tri};
+    tile_body_direct3<T, WM, WN, WAVES_M, WAVES_N, KC>(job, M, N, A, lda, B, ldb, epi, st0, st1, st2);
     it = t0 + k1;
-    __syncthreads();   // the next tile refills the LDS buffers
+    __syncthreads();   // the next tile refills the LDS stages
   }
 }
 
@@ -1940,7 +1994,7 @@ static int launch_streamk_bf6(hipStream_t s, int64_t M, int64_t N, int64_t Kpad,
 template <class T, int WM, int WN, int WAVES_M, int WAVES_N, int KC>
 static int launch_streamk(hipStream_t s, int64_t M, int64_t N, int64_t Kpad, const T* A, int64_t lda,
                           const T* B, int64_t ldb, T* C, int64_t ldc, int64_t c_col0, void* part,
-                          uint64_t part_bytes) {
+                          uint64_t part_bytes, int tri) {
   using G = TileGeom<T, WM, WN, WAVES_M, WAVES_N, KC>;
   if (Kpad % KC != 0) return fail(PPL_E_ARG, "K padding %lld not a multiple of %d", (long long)Kpad, KC);
   auto kern = gemm_streamk_kernel<T, WM, WN, WAVES_M, WAVES_N, KC>;
@@ -1950,7 +2004,7 @@ static int launch_streamk(hipStream_t s, int64_t M, int64_t N, int64_t Kpad, con
                         part_bytes, sk, n_tiles));
   if (sk.iters <= 0) return PPL_OK;
   hipLaunchKernelGGL(kern, dim3((unsigned)sk.G), dim3(G::NT), 0, s, M, N, A, lda, B, ldb, C, ldc, c_col0,
-                     (T*)part, sk);
+                     (T*)part, sk, tri);
   PPL_HIP_TRY(hipGetLastError());
   hipLaunchKernelGGL(streamk_fixup_kernel<T>, dim3((unsigned)n_tiles), dim3(256), 0, s, (const T*)part, C, ldc,
                      c_col0, M, N, G::BM, G::BN, sk);
@@ -1964,19 +2018,22 @@ static int contract_cfg(hipStream_t s, int prec, int64_t Nrows, int64_t Prows, i
                         const void* S, const void* S_lo, int64_t lds_, const void* V,
                         const void* V_lo, int64_t ldv, void* C, int64_t ldc, int64_t c_col0,
                         int splits, void* partial, int64_t partial_ld, uint64_t partial_bytes,
-                        bool accumulate) {
+                        bool accumulate, bool tri) {
   constexpr int BM = 16 * WM * WAVES_M, BN = 16 * WN * WAVES_N;
+  static_assert(kTriBlock % BN == 0, "a column tile lies in one diagonal block of a triangular operand");
   if (accumulate && splits != 1) return fail(PPL_E_ARG, "an accumulating contraction runs one K slice");
+  if (tri && (c_col0 != 0 || (prec != PPL_FP64 && prec != PPL_FP32)))
+    return fail(PPL_E_ARG, "triangular operands are whole FP64 or FP32 matrices");
   const double cbeta = accumulate ? 1.0 : 0.0;
   if (splits == 0) {   // stream-K
     if (prec == PPL_FP64)
       return launch_streamk<double, WM, WN, WAVES_M, WAVES_N, kKcF64>(
           s, Nrows, Prows, Kpad, (const double*)S, lds_, (const double*)V, ldv, (double*)C, ldc, c_col0, partial,
-          partial_bytes);
+          partial_bytes, tri);
     if (prec == PPL_FP32)
       return launch_streamk<float, WM, WN, WAVES_M, WAVES_N, kKcF32>(
           s, Nrows, Prows, Kpad, (const float*)S, lds_, (const float*)V, ldv, (float*)C, ldc, c_col0, partial,
-          partial_bytes);
+          partial_bytes, tri);
     if (prec == PPL_BF16X3)
       return launch_streamk_bf3<WM, WN, WAVES_M, WAVES_N, bf3_kc(BM, BN)>(
           s, Nrows, Prows, Kpad, (const __bf16*)S, (const __bf16*)S_lo, lds_, (const __bf16*)V,
@@ -2002,13 +2059,13 @@ static int contract_cfg(hipStream_t s, int prec, int64_t Nrows, int64_t Prows, i
   const int64_t pstride = Nrows * partial_ld;
   int rc = PPL_OK;
   if (prec == PPL_FP64) {
-    EpiStore<double> epi = direct ? EpiStore<double>{(double*)C, ldc, c_col0, Nrows, Prows, 1.0, cbeta, 0}
-                                  : EpiStore<double>{(double*)partial, partial_ld, 0, Nrows, Prows, 1.0, 0.0, pstride};
+    EpiStore<double> epi = direct ? EpiStore<double>{(double*)C, ldc, c_col0, Nrows, Prows, 1.0, cbeta, 0, tri}
+                                  : EpiStore<double>{(double*)partial, partial_ld, 0, Nrows, Prows, 1.0, 0.0, pstride, tri};
     rc = launch<double, WM, WN, WAVES_M, WAVES_N, kKcF64>(s, grid, Nrows, Prows, Kpad, (const double*)S, lds_,
                                                       (const double*)V, ldv, epi, map);
   } else if (prec == PPL_FP32) {
-    EpiStore<float> epi = direct ? EpiStore<float>{(float*)C, ldc, c_col0, Nrows, Prows, 1.0, cbeta, 0}
-                                 : EpiStore<float>{(float*)partial, partial_ld, 0, Nrows, Prows, 1.0, 0.0, pstride};
+    EpiStore<float> epi = direct ? EpiStore<float>{(float*)C, ldc, c_col0, Nrows, Prows, 1.0, cbeta, 0, tri}
+                                 : EpiStore<float>{(float*)partial, partial_ld, 0, Nrows, Prows, 1.0, 0.0, pstride, tri};
     rc = launch<float, WM, WN, WAVES_M, WAVES_N, kKcF32>(s, grid, Nrows, Prows, Kpad, (const float*)S, lds_,
                                                      (const float*)V, ldv, epi, map);
   } else if (prec == PPL_BF16X3) {
@@ -2042,12 +2099,12 @@ static int contract_cfg(hipStream_t s, int prec, int64_t Nrows, int64_t Prows, i
 int gemm_contract(hipStream_t s, int prec, int tile, int64_t Nrows, int64_t Prows, int64_t Kpad,
                   const void* S, const void* S_lo, int64_t lds_, const void* V, const void* V_lo,
                   int64_t ldv, void* C, int64_t ldc, int64_t c_col0, int splits, void* partial,
-                  int64_t partial_ld, uint64_t partial_bytes, bool accumulate) {
+                  int64_t partial_ld, uint64_t partial_bytes, bool accumulate, bool tri) {
   if (Nrows <= 0 || Prows <= 0) return PPL_OK;
 #define PPL_CFG(id, a, b, c, d)                                                                  \
   case id:                                                                                       \
     return contract_cfg<a, b, c, d>(s, prec, Nrows, Prows, Kpad, S, S_lo, lds_, V, V_lo, ldv, C,  \
-                                    ldc, c_col0, splits, partial, partial_ld, partial_bytes, accumulate);
+                                    ldc, c_col0, splits, partial, partial_ld, partial_bytes, accumulate, tri);
   switch (tile) {
     PPL_CFG(0, 7, 2, 1, 4)
     PPL_CFG(1, 4, 4, 2, 2)
@@ -2299,7 +2356,6 @@ typedef __attribute__((address_space(1))) char global_char_t;
 template <class T>
 struct GroupedLds {       // LDS of the largest allowed tile (208 x 64 rows staged, 272 in all)
   static constexpr int KC = sizeof(T) == 8 ? kKcF64 : kKcF32;
-  static constexpr int bytes = TileGeom<T, 13, 1, 1, 4, KC>::LDS_BYTES;
   static constexpr int stage = 272 * KC;   // elements of one direct-load stage of that tile
 };
 
@@ -2314,37 +2370,18 @@ __device__ __forceinline__ void grouped_tile_direct(const GroupDesc& g, int m0, 
   TileJob job{m0, n0, 0, g.nk, 0};
   const T* A = (const T*)(base + g.a_off);
   const T* B = (const T*)(base + g.b_off);
-  EpiStore<T> epi{(T*)(base + g.c_off), g.ldc, 0, g.M, g.N, 1.0, 0.0, 0};
+  EpiStore<T> epi{(T*)(base + g.c_off), g.ldc, 0, g.M, g.N, 1.0, 0.0, 0, g.tri};
   tile_body_direct3<T, WM, WN, WAVES_M, WAVES_N, KC>(job, g.M, g.N, A, g.lda, B, g.ldb, epi, st0, st1, st2);
 }
 
-template <class T, int WM, int WN, int WAVES_M, int WAVES_N, int KC>
-__device__ __noinline__ void grouped_tile(const GroupDesc& g, int m0, int n0, char* smem, global_char_t* base) {
-  using G = TileGeom<T, WM, WN, WAVES_M, WAVES_N, KC>;
-  static_assert(G::LDS_BYTES <= GroupedLds<T>::bytes, "tile does not fit the grouped LDS buffer");
-  static_assert(G::NT == 256, "grouped tiles use 256 threads");
-  TileJob job{m0, n0, 0, g.nk, 0};
-  // operands addressed from a base pointer typed as global memory: generic pointers
-  // (loaded from memory, or passed to a function that is not inlined) give flat loads,
-  // which also count against the LDS wait counter and serialize the chunk pipeline
-  const T* A = (const T*)(base + g.a_off);
-  const T* B = (const T*)(base + g.b_off);
-  EpiStore<T> epi{(T*)(base + g.c_off), g.ldc, 0, g.M, g.N, 1.0, 0.0, 0};
-  T* s = reinterpret_cast<T*>(smem);
-  tile_body<T, WM, WN, WAVES_M, WAVES_N, KC>(job, g.M, g.N, A, g.lda, B, g.ldb, epi,
-                                             s, s + G::BUF_A, s + 2 * G::BUF_A, s + 2 * G::BUF_A + G::BUF_B);
-}
-
 template <class T>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kFpDirect3 && PPL_GROUPED_DIRECT3 ? 1 : 2)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1)))
 gemm_grouped_kernel(char* base, const GroupDesc* __restrict__ groups, const int4* __restrict__ items,
                     const int* __restrict__ q_begin, int* counters) {
   constexpr int KC = GroupedLds<T>::KC;
-  constexpr bool kDirect = kFpDirect3 && PPL_GROUPED_DIRECT3;
-  __shared__ __attribute__((aligned(16))) char smem[kDirect ? 16 : GroupedLds<T>::bytes];
-  __shared__ __attribute__((aligned(16))) T st0[kDirect ? GroupedLds<T>::stage : 2];
-  __shared__ __attribute__((aligned(16))) T st1[kDirect ? GroupedLds<T>::stage : 2];
-  __shared__ __attribute__((aligned(16))) T st2[kDirect ? GroupedLds<T>::stage : 2];
+  __shared__ __attribute__((aligned(16))) T st0[GroupedLds<T>::stage];
+  __shared__ __attribute__((aligned(16))) T st1[GroupedLds<T>::stage];
+  __shared__ __attribute__((aligned(16))) T st2[GroupedLds<T>::stage];
   __shared__ int s_item;
   global_char_t* const gbase = (global_char_t*)base;
   // queue q holds items [q_begin[q], q_begin[q + 1]); a workgroup drains the queue of
@@ -2361,26 +2398,14 @@ gemm_grouped_kernel(char* base, const GroupDesc* __restrict__ groups, const int4
       if (it >= e) break;
       const int4 w = items[it];
       const GroupDesc g = groups[w.x];
-      if constexpr (kDirect) {
-        switch (g.cfg) {
-          case 0: grouped_tile_direct<T, 7, 2, 1, 4, KC>(g, w.y, w.z, st0, st1, st2, gbase); break;
-          case 1: grouped_tile_direct<T, 4, 4, 2, 2, KC>(g, w.y, w.z, st0, st1, st2, gbase); break;
-          case 2: grouped_tile_direct<T, 13, 1, 1, 4, KC>(g, w.y, w.z, st0, st1, st2, gbase); break;
-          case 5: grouped_tile_direct<T, 6, 2, 1, 4, KC>(g, w.y, w.z, st0, st1, st2, gbase); break;
-          case 6: grouped_tile_direct<T, 2, 2, 1, 4, KC>(g, w.y, w.z, st0, st1, st2, gbase); break;
-          case 7: grouped_tile_direct<T, 3, 2, 1, 4, KC>(g, w.y, w.z, st0, st1, st2, gbase); break;
-          default: grouped_tile_direct<T, 4, 2, 1, 4, KC>(g, w.y, w.z, st0, st1, st2, gbase); break;
-        }
-        continue;
-      }
       switch (g.cfg) {
-        case 0: grouped_tile<T, 7, 2, 1, 4, KC>(g, w.y, w.z, smem, gbase); break;
-        case 1: grouped_tile<T, 4, 4, 2, 2, KC>(g, w.y, w.z, smem, gbase); break;
-        case 2: grouped_tile<T, 13, 1, 1, 4, KC>(g, w.y, w.z, smem, gbase); break;
-        case 5: grouped_tile<T, 6, 2, 1, 4, KC>(g, w.y, w.z, smem, gbase); break;
-        case 6: grouped_tile<T, 2, 2, 1, 4, KC>(g, w.y, w.z, smem, gbase); break;
-        case 7: grouped_tile<T, 3, 2, 1, 4, KC>(g, w.y, w.z, smem, gbase); break;
-        default: grouped_tile<T, 4, 2, 1, 4, KC>(g, w.y, w.z, smem, gbase); break;
+        case 0: grouped_tile_direct<T, 7, 2, 1, 4, KC>(g, w.y, w.z, st0, st1, st2, gbase); break;
+        case 1: grouped_tile_direct<T, 4, 4, 2, 2, KC>(g, w.y, w.z, st0, st1, st2, gbase); break;
+        case 2: grouped_tile_direct<T, 13, 1, 1, 4, KC>(g, w.y, w.z, st0, st1, st2, gbase); break;
+        case 5: grouped_tile_direct<T, 6, 2, 1, 4, KC>(g, w.y, w.z, st0, st1, st2, gbase); break;
+        case 6: grouped_tile_direct<T, 2, 2, 1, 4, KC>(g, w.y, w.z, st0, st1, st2, gbase); break;
+        case 7: grouped_tile_direct<T, 3, 2, 1, 4, KC>(g, w.y, w.z, st0, st1, st2, gbase); break;
+        default: grouped_tile_direct<T, 4, 2, 1, 4, KC>(g, w.y, w.z, st0, st1, st2, gbase); break;
       }
     }
   }

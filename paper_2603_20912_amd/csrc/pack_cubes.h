@@ -57,6 +57,20 @@ PPL_HD inline void cube_decode(int64_t r, int nt, int& bi, int& ci, int& di) {
   di = ci + (swap ? x : y);
 }
 
+// The same cubes in the order of the rows they write: bi slowest, then the pairs (ci <= di), di
+// fastest, so that workgroups running together write neighbouring columns of the same rows.
+PPL_HD inline void cube_decode_rows(int64_t r, int nt, int& bi, int& ci, int& di) {
+  const int per = nt * (nt + 1) / 2;
+  bi = (int)(r / per);
+  int q = (int)(r % per);
+  ci = 0;
+  while (q >= nt - ci) {
+    q -= nt - ci;
+    ++ci;
+  }
+  di = ci + q;
+}
+
 // Virtual a of cube g given the prefix table off (off[a] = cubes of all virtuals below a),
 // searched in [lo, hi) with off[lo] <= g < off[hi].
 PPL_HD inline int cube_virtual(const int64_t* off, int lo, int hi, int64_t g) {

@@ -48,6 +48,12 @@ static_assert(64 % kKcF64 == 0 && 64 % kKcF32 == 0 && 64 % bf3_kc(0, 0) == 0,
 
 __host__ __device__ inline int64_t pad_ld(int64_t k) { return (k + 63) / 64 * 64; }
 
+// Resident FP64 and FP32 V+- are stored as upper triangles: entry [r][q] is valid where
+// q >= r or r / kTriBlock == q / kTriBlock (whole diagonal blocks), and the rest is never
+// read. Every column tile of a contraction (64, 128 or 256 wide, from a multiple of its
+// width) then lies in one diagonal block.
+constexpr int kTriBlock = 256;
+
 // ------------------------------------------------------------------ errors
 void set_error(const char* fmt, ...);
 int fail(int code, const char* fmt, ...);
@@ -79,6 +85,7 @@ struct OperandSet {
   Region sp, sp_lo;        // S' [N+][ldp]
   Region am, am_lo;        // A' [N-][ldm]
   bool built = false;      // resident V+- complete
+  bool tri = false;        // V+- stored as upper triangles (kTriBlock)
   // contraction tiles and K decompositions of the FP64 copy of a mixed plan (the
   // primary set uses the plan's, which the autotuner and ppl_set_contract_config set)
   int tile_p = 0, split_p = 1, tile_m = 0, split_m = 1;
@@ -137,7 +144,7 @@ struct ppl_plan_s {
   ppl::Region diis_t, diis_e;          // diis_max slots of amplitudes t' and of errors t' - t (S'/A' scaling)
   ppl::Region diis_red;                // DIIS inner-product partials and results
   ppl::Region tiles;                   // per-batch (row tile, column tile) lists of the build GEMM (int32 pairs)
-  bool sym_build = false;              // build the upper triangle of V+- (resident: then mirror it;
+  bool sym_build = false;              // build the upper triangle of V+- (resident: rows of it, see kTriBlock;
                                        // streaming: contract U and U^T of each step, V = U + U^T)
   int64_t ldq = 0, ldqm = 0;           // row lengths of the transposed streaming results (pad N+, N-)
   int64_t ldk = 0;                     // row length of a transposed row block (its K range)
@@ -185,11 +192,12 @@ int gemm_store_f64(hipStream_t s, int64_t M, int64_t N, int64_t Kpad, const doub
 // mid for BF16x6, whose lo plane lies one plane further on (mid + (mid - hi)).
 // splits > 1 splits K into that many slices written to `partial` ([splits][Nrows][partial_ld],
 // accumulator type) and summed in slice order into C. accumulate: C += the product (one
-// K slice only; PPL_E_ARG with split-K or stream-K).
+// K slice only; PPL_E_ARG with split-K or stream-K). tri (FP64, FP32): V is a symmetric
+// matrix stored as kTriBlock describes; the result is that of the full matrix, bit for bit.
 int gemm_contract(hipStream_t s, int prec, int tile, int64_t Nrows, int64_t Prows, int64_t Kpad,
                   const void* S, const void* S_lo, int64_t lds_, const void* V, const void* V_lo,
                   int64_t ldv, void* C, int64_t ldc, int64_t c_col0, int splits, void* partial,
-                  int64_t partial_ld, uint64_t partial_bytes, bool accumulate = false);
+                  int64_t partial_ld, uint64_t partial_bytes, bool accumulate = false, bool tri = false);
 // bytes of partial slots a stream-K contraction (splits == 0) with this tile needs at most
 uint64_t streamk_part_bytes(int tile, int prec, int64_t Nrows, int64_t Prows, int64_t Kpad);
 int64_t contract_jobs(int tile, int prec, int64_t Nrows, int64_t Prows, int64_t Kpad, int splits);
@@ -221,7 +229,7 @@ struct GroupDesc {       // byte offsets from the launch's base pointer (the bat
   int64_t b_off;         // V+ or V- rows [N][ldb]
   int64_t c_off;         // R+ or R- [M][ldc]
   int64_t M, N, nk, lda, ldb, ldc;
-  int cfg, pad;
+  int cfg, tri;          // tile, B stored as its upper triangle
 };
 bool grouped_tile_ok(int tile);
 int grouped_choose_tile(int prec, int64_t rows);
@@ -280,6 +288,11 @@ int pack_vpm_sym(hipStream_t s, int prec, int v, int a0, int a1, const void* G, 
 // T (row length ldt); off[a] = cubes of the virtuals below a (pack_cubes.h), v + 1 entries
 int pack_vpm_cubes(hipStream_t s, int prec, int v, int a0, int a1, const void* T, int64_t ldt, const int64_t* off,
                    void* vp, void* vp_lo, int64_t ldp, void* vm, void* vm_lo, int64_t ldm);
+// the same rows as upper triangles with whole diagonal blocks (kTriBlock; FP64 and FP32)
+int pack_vpm_tri(hipStream_t s, int prec, int v, int a0, int a1, const void* T, int64_t ldt, const int64_t* off,
+                 void* vp, int64_t ldp, void* vm, int64_t ldm);
+// a symmetric FP64 matrix stored that way to the whole matrix in an operand precision
+int convert_tri(hipStream_t s, int prec, const double* src, int64_t n, int64_t ld, void* dst, void* dst_lo);
 // C[q][p] += T[p][q] for q < nq, p < np (T FP64; C FP64 or FP32 by c_prec)
 int add_transposed(hipStream_t s, int c_prec, void* C, int64_t ldc, const double* T, int64_t ldt, int64_t nq,
                    int64_t np);
@@ -290,8 +303,6 @@ int transpose_pm(hipStream_t s, const double* X, int64_t ldx, double* Y, int64_t
 // Ut[r][k] = U[k0 + k - u0][c0 + r] for u0 <= k0 + k < u1, else 0 (r < nr, k < nk)
 int transpose_block(hipStream_t s, int elem_bytes, const void* U, int64_t ldu, int64_t u0, int64_t u1, int64_t c0,
                     int64_t k0, void* Ut, int64_t ldt, int64_t nr, int64_t nk);
-// V[r][q] = V[q][r] for q < r (bit copy of elem_bytes-wide elements)
-int mirror_lower(hipStream_t s, int elem_bytes, void* V, int64_t n, int64_t ld);
 // pair tables
 int fill_tables(hipStream_t s, int o, int v, int* tab_vp, int* tab_vm, int* tab_op, int* tab_om);
 // generic pack of an (i,j,a,b)-indexed FP64 tensor into + / - packed rows:

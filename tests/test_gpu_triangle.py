@@ -1,0 +1,106 @@
+"""Resident FP64 and FP32 plans hold V+- as upper triangles with whole 256 x 256 diagonal
+blocks. Every workspace byte is set to 0xff (NaN in every type) before the build, so a read
+of an entry that is not stored shows in the result; the results must equal, bit for bit,
+those of a plan that builds and stores every row in full (the same products summed in the
+same order), and the oracle's. Sizes put P+ and P- just below, at and past block and
+tile edges: (P+, P-) = (276, 253), (528, 496), (1035, 990)."""
+import sys
+
+import numpy as np
+import pytest
+
+import oracle as O
+import ppl_synth as S
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+def say(msg):
+    print(f"[gpu-case] {msg}", flush=True)
+    sys.stdout.flush()
+
+
+@pytest.fixture(scope="module")
+def P():
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible")
+    import paper_2603_20912_amd as P
+    return P
+
+
+def rel(a, b):
+    return float(np.linalg.norm(a - b) / max(np.linalg.norm(b), 1e-300))
+
+
+def dev(x):
+    return torch.from_numpy(np.ascontiguousarray(x)).to("cuda")
+
+
+def plan(P, monkeypatch, sym, o, v, naux, **kw):
+    monkeypatch.setenv("PPL_SYM_BUILD", sym)
+    eng = P.PPL(o, v, naux, **kw)
+    assert eng.info["resident"] == 1
+    eng.workspace.fill_(255)
+    P.ppl_bind_workspace(eng.plan, eng.workspace)
+    return eng
+
+
+SIZES = [(4, 23, 19), (3, 32, 40), (5, 45, 17)]
+
+
+@pytest.mark.parametrize("prec,bound", [("fp64", 1e-12), ("fp32", 2e-6)])
+@pytest.mark.parametrize("o,v,naux", SIZES)
+def test_triangle_equals_full_rows_in_every_configuration(P, monkeypatch, prec, bound, o, v, naux):
+    s = S.make_system(o, v, naux, 80)
+    t = S.make_amplitudes(o, v, 81)
+    ref = O.ppl(s["L"], o, t)
+    L, t = dev(s["L"]), dev(t)
+    tri = plan(P, monkeypatch, "1", o, v, naux, prec=prec, build_scratch=1 << 20)
+    full = plan(P, monkeypatch, "0", o, v, naux, prec=prec)
+    tri.build(L)
+    full.build(L)
+    for tile in range(P.ppl_tile_count()):
+        for splits in (1, 3, 8, 0):
+            say(f"triangle {prec} ({o},{v},{naux}) tile {tile} splits {splits}")
+            out = []
+            for eng in (tri, full):
+                eng.set_contract_config(tile, splits, tile, splits)
+                out.append(eng.contract(t).cpu().numpy())
+            assert np.array_equal(out[0], out[1])
+            assert rel(out[0], ref) < bound
+    tri.close()
+    full.close()
+
+
+@pytest.mark.parametrize("prec", ["fp32", "bf16x3", "bf16x6"])
+@pytest.mark.parametrize("o,v,naux", SIZES)
+def test_low_precision_copy_of_a_triangle(P, monkeypatch, prec, o, v, naux):
+    """The low-precision V+- of a mixed plan, rounded from the FP64 triangle and completed."""
+    say(f"mixed operands from a triangle {prec} ({o},{v},{naux})")
+    s = S.make_system(o, v, naux, 82)
+    t = dev(S.make_amplitudes(o, v, 83))
+    out = []
+    for sym in ("1", "0"):
+        eng = plan(P, monkeypatch, sym, o, v, naux, prec=prec, keep_fp64=True)
+        eng.build(dev(s["L"]))
+        out.append(eng.contract(t).cpu().numpy())
+        eng.close()
+    assert np.array_equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("prec,bound", [("fp64", 1e-12), ("fp32", 2e-6)])
+def test_grouped_launch_reads_triangles(P, prec, bound):
+    say(f"grouped triangles {prec}")
+    b = P.Batch(SIZES, prec=prec)
+    b.workspace.fill_(255)
+    P.ppl_batch_bind_workspace(b.h, b.workspace)
+    systems = [S.make_system(o, v, naux, 90 + k) for k, (o, v, naux) in enumerate(SIZES)]
+    ts = [S.make_amplitudes(o, v, 95 + k) for k, (o, v, _) in enumerate(SIZES)]
+    b.build([dev(s["L"]) for s in systems])
+    Rs = [torch.empty(t.shape, dtype=torch.float64, device="cuda") for t in ts]
+    b.contract([dev(t) for t in ts], Rs)
+    torch.cuda.synchronize()
+    for s, t, R in zip(systems, ts, Rs):
+        assert rel(R.cpu().numpy(), O.ppl(s["L"], s["o"], t)) < bound
+    b.close()
