@@ -1740,7 +1740,7 @@ int ppl_mlp_create(int32_t width, int64_t max_batch, void* stream, ppl_mlp_t* ou
   q->stream = (hipStream_t)stream;
   q->max_batch = max_batch;
   const uint64_t P = (uint64_t)mlp_param_count();
-  const uint64_t nwg = (uint64_t)((max_batch + mlp_train_rows() - 1) / mlp_train_rows());
+  const uint64_t nwg = (uint64_t)mlp_train_partials(max_batch);
   Layout L;
   q->prm = L.take(P * 4);
   q->m = L.take(P * 4);
@@ -1822,8 +1822,8 @@ int ppl_mlp_grad(ppl_mlp_t q, const float* X, const float* Y, int64_t n, float* 
   g_err[0] = 0;
   PPL_TRY(mlp_check(q));
   if (!X || !Y || n < 1 || n > q->max_batch) return fail(PPL_E_ARG, "bad batch (n = %lld)", (long long)n);
-  PPL_TRY(mlp_train_launch(q->stream, mat<float>(q, q->prm), X, Y, n, mat<float>(q, q->gpart),
-                           mat<float>(q, q->lpart), mat<float>(q, q->grad), mat<float>(q, q->loss)));
+  PPL_TRY(mlp_grad_launch(q->stream, mat<float>(q, q->prm), X, Y, n, mat<float>(q, q->gpart),
+                          mat<float>(q, q->lpart), mat<float>(q, q->grad), mat<float>(q, q->loss)));
   if (host_grad)
     PPL_HIP_TRY(hipMemcpyAsync(host_grad, mat<float>(q, q->grad), (size_t)mlp_param_count() * 4,
                                hipMemcpyDeviceToHost, q->stream));
@@ -1838,11 +1838,10 @@ int ppl_mlp_train_step(ppl_mlp_t q, const float* X, const float* Y, int64_t n, f
   PPL_TRY(mlp_check(q));
   if (!X || !Y || n < 1 || n > q->max_batch) return fail(PPL_E_ARG, "bad batch (n = %lld)", (long long)n);
   if (!(lr > 0.0f)) return fail(PPL_E_ARG, "lr must be > 0");
-  PPL_TRY(mlp_train_launch(q->stream, mat<float>(q, q->prm), X, Y, n, mat<float>(q, q->gpart),
-                           mat<float>(q, q->lpart), mat<float>(q, q->grad), mat<float>(q, q->loss)));
   q->step += 1;
-  PPL_TRY(mlp_adam_launch(q->stream, mat<float>(q, q->prm), mat<float>(q, q->grad), mat<float>(q, q->m),
-                          mat<float>(q, q->v), lr, q->step, 0.9f, 0.999f, 1e-8f));
+  PPL_TRY(mlp_step_launch(q->stream, mat<float>(q, q->prm), X, Y, n, mat<float>(q, q->gpart),
+                          mat<float>(q, q->lpart), mat<float>(q, q->grad), mat<float>(q, q->loss),
+                          mat<float>(q, q->m), mat<float>(q, q->v), lr, q->step, 0.9f, 0.999f, 1e-8f));
   if (host_loss) {
     PPL_HIP_TRY(hipMemcpyAsync(host_loss, mat<float>(q, q->loss), 4, hipMemcpyDeviceToHost, q->stream));
     PPL_HIP_TRY(hipStreamSynchronize(q->stream));
