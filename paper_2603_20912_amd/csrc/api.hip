@@ -1858,7 +1858,7 @@ int ppl_mlp_guess(ppl_mlp_t q, ppl_plan_t p, const double* t_mp2, const double* 
   if ((const void*)t_mp2 == (const void*)t2_out) return fail(PPL_E_ARG, "t2_out may not alias t_mp2");
   if (!(sigma > 0.0)) return fail(PPL_E_ARG, "sigma must be > 0");
   return mlp_infer_launch(p->stream, mat<float>(q, q->prm), p->o, p->v, t_mp2, e_occ, e_vir, sigma,
-                          at<int>(p, p->tab_om), at<int>(p, p->tab_vp), t2_out);
+                          at<int>(p, p->tab_om), t2_out);
 }
 
 int ppl_mlp_destroy(ppl_mlp_t q) {

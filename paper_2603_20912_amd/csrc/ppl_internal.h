@@ -391,7 +391,7 @@ int mlp_step_launch(hipStream_t s, float* prm, const float* X, const float* Y, i
 int mlp_samples_launch(hipStream_t s, int o, int v, const double* tm, const double* ts, const double* e_occ,
                        const double* e_vir, double sigma, const int64_t* idx, int64_t n, float* X, float* Y);
 int mlp_infer_launch(hipStream_t s, const float* prm, int o, int v, const double* tm, const double* e_occ,
-                     const double* e_vir, double sigma, const int* tab_om, const int* tab_vp, double* tout);
+                     const double* e_vir, double sigma, const int* tab_om, double* tout);
 int sumsq_launch(hipStream_t s, const double* x, int64_t n, double* partials, double* red_out);
 
 constexpr int kReduceBlocks = 1024;

@@ -55,3 +55,29 @@ def test_gradient_of_ragged_batches(P, n):
     mlp.close()
 
 
+@pytest.mark.parametrize("o,v", [(1, 2), (2, 15), (3, 16), (2, 17), (3, 33)])
+def test_guess_at_tile_edges(P, o, v):
+    """BF16 operands of the hidden layer: 2^-8 per operand over 128 terms (the bound of the whole
+    network's guess test); every entry written once from its own features, pair-symmetric."""
+    say(f"mlp guess ({o},{v})")
+    s = S.make_system(o, v, 3 * v, 21, "contractive")
+    p = M.init_params(128, seed=22)
+    mlp = P.MLP(max_batch=64)
+    mlp.set_params(M.flatten(p).astype(np.float32))
+    eng = P.PPL(o, v, 3 * v)
+    tm = S.make_amplitudes(o, v, 23)
+    out = torch.full((o, o, v, v), float("nan"), dtype=torch.float64, device="cuda")
+    X, sigma = M.features(tm, s["e_occ"], s["e_vir"])
+    mlp.guess(eng, dev(tm), dev(s["e_occ"]), dev(s["e_vir"]), sigma, out)
+    got = out.cpu().numpy()
+    fref, _ = M.forward(p, X)
+    i, j, a, b = np.indices((o, o, v, v))
+    fref = fref.reshape(o, o, v, v)
+    own = (i < j) | ((i == j) & (a <= b))           # the element whose features a pair takes
+    fref = np.where(own, fref, fref.transpose(1, 0, 3, 2))
+    base = np.where(own, tm, tm.transpose(1, 0, 3, 2))
+    assert np.isfinite(got).all()
+    assert np.max(np.abs((got - base) / sigma - fref)) < 2e-2 * (1.0 + np.abs(fref).max())
+    assert np.array_equal(got, got.transpose(1, 0, 3, 2))
+    eng.close()
+    mlp.close()
