@@ -615,9 +615,8 @@ static int setup_ov_integrals(ppl_plan_t p, const double* L) {
   double* vfull = at<double>(p, p->g);
   PPL_TRY(gemm_store_f64(st, ov, ov, p->ldx, at<double>(p, p->xov), p->ldx, at<double>(p, p->xov), p->ldx,
                          vfull, ov));
-  PPL_TRY(pack_pm(st, p->o, p->v, vfull, (int64_t)p->v * ov, p->v, ov, 1, 0.5, 0.5, 0.5,
-                  at<double>(p, p->vs), p->ldp, at<double>(p, p->va), p->ldm, at<int>(p, p->tab_op),
-                  at<int>(p, p->tab_om), at<int>(p, p->tab_vp), at<int>(p, p->tab_vm)));
+  PPL_TRY(pack_pm(st, PPL_FP64, p->o, p->v, vfull, (int64_t)p->v * ov, p->v, ov, 1, 0.5, 0.5, 0.5,
+                  at<double>(p, p->vs), nullptr, p->ldp, at<double>(p, p->va), nullptr, p->ldm, at<int>(p, p->tab_op)));
   return PPL_OK;
 }
 
@@ -1004,12 +1003,11 @@ static int hhl_integrals(ppl_plan_t p, const double* L) {
   char* g = at<char>(p, p->g);
   double *xoo = (double*)(g + h.xoo), *woo = (double*)(g + h.woo);
   const int64_t o = p->o, oo = o * o;
-  const int *tab_op = at<int>(p, p->tab_op), *tab_om = at<int>(p, p->tab_om);
   PPL_TRY(stage_oo(p->stream, L, p->o, p->v, p->naux, p->ldx, xoo));
   PPL_TRY(gemm_store_f64(p->stream, oo, oo, p->ldx, xoo, p->ldx, xoo, p->ldx, woo, oo));
   // X_ij^kl = Woo[(k,i)][(l,j)]
-  return pack_pm(p->stream, p->o, p->o, woo, oo, 1, o * oo, o, 0.5, 0.5, 0.5, (double*)(g + h.wp), h.ldq,
-                 (double*)(g + h.wm), h.ldqm, tab_op, tab_om, tab_op, tab_om);
+  return pack_pm(p->stream, PPL_FP64, p->o, p->o, woo, oo, 1, o * oo, o, 0.5, 0.5, 0.5, g + h.wp, nullptr, h.ldq,
+                 g + h.wm, nullptr, h.ldqm, at<int>(p, p->tab_op));
 }
 
 // The hole-hole ladder of packed amplitudes X (S' rows [N+][ldp] or A' rows [N-][ldm],
@@ -1053,6 +1051,16 @@ static int hhl_add_packed(ppl_plan_t p, const OperandSet& s) {
   return hhl_pass(p, h, false, at<double>(p, p->a64), at<void>(p, p->rm), cprec, true);
 }
 
+// S' = (2 - d_cd)(t^cd + t^dc)/2, A' = t^cd - t^dc on the i<=j / i<j rows (t + t1 t1 with singles),
+// in the precision of an operand set, or as the FP64 masters (s null)
+static int pack_amplitudes(ppl_plan_t p, const OperandSet* s, const double* t2, const double* t1 = nullptr) {
+  const int64_t o = p->o, v = p->v;
+  const Region &sp = s ? s->sp : p->s64, &am = s ? s->am : p->a64;
+  return pack_pm(p->stream, s ? s->prec : PPL_FP64, p->o, p->v, t2, o * v * v, v * v, v, 1, 1.0, 0.5, 1.0,
+                 at<void>(p, sp), s && s->sp_lo.bytes ? at<void>(p, s->sp_lo) : nullptr, p->ldp, at<void>(p, am),
+                 s && s->am_lo.bytes ? at<void>(p, s->am_lo) : nullptr, p->ldm, at<int>(p, p->tab_op), t1);
+}
+
 static int contract_impl(ppl_plan_t p, const double* t2, const double* t1, double* R, double alpha,
                          double beta) {
   g_err[0] = 0;
@@ -1060,12 +1068,7 @@ static int contract_impl(ppl_plan_t p, const double* t2, const double* t1, doubl
   if (!t2 || !R) return fail(PPL_E_ARG, "null t2 or R");
   if ((const void*)t2 == (const void*)R) return fail(PPL_E_ARG, "R may not alias t2");
   OperandSet& s = p->ops[0];
-  const int64_t o = p->o, v = p->v;
-  // S' = (2 - d_cd)(t^cd + t^dc)/2, A' = t^cd - t^dc on the i<=j / i<j rows (t + t1 t1 with singles)
-  PPL_TRY(pack_pm(p->stream, p->o, p->v, t2, o * v * v, v * v, v, 1, 1.0, 0.5, 1.0, at<double>(p, p->s64),
-                  p->ldp, at<double>(p, p->a64), p->ldm, at<int>(p, p->tab_op), at<int>(p, p->tab_om),
-                  at<int>(p, p->tab_vp), at<int>(p, p->tab_vm), t1));
-  PPL_TRY(refresh_operands(p, s));
+  PPL_TRY(pack_amplitudes(p, &s, t2, t1));
   PPL_TRY(contract_packed(p, s));
   PPL_TRY(unpack_r(p->stream, s.prec == PPL_FP64 ? PPL_FP64 : PPL_FP32, p->o, p->v, at<void>(p, p->rp),
                    p->ldp, at<void>(p, p->rm), p->ldm, R, alpha, beta));
@@ -1093,7 +1096,6 @@ int ppl_hhl(ppl_plan_t p, const double* L, const double* t2, double* R, double a
   if (h.bytes > p->g.bytes)
     return fail(PPL_E_STATE, "hole-hole scratch needs %llu B, the plan has %llu B",
                 (unsigned long long)h.bytes, (unsigned long long)p->g.bytes);
-  const int64_t o = p->o, v = p->v;
   ProfScope ps(p, PPL_PROF_OTHER, 2.0 * (double)p->Pp * p->Np * p->Np + 2.0 * (double)p->Pm * p->Nm * p->Nm);
   hipStream_t st = p->stream;
   double* s64 = at<double>(p, p->s64);
@@ -1101,8 +1103,7 @@ int ppl_hhl(ppl_plan_t p, const double* L, const double* t2, double* R, double a
   PPL_TRY(hhl_integrals(p, L));
   // S'/A' of t2 into the FP64 packed rows, the ladder chunk by chunk over the virtual
   // pairs written back over them, then unpacked
-  PPL_TRY(pack_pm(st, p->o, p->v, t2, o * v * v, v * v, v, 1, 1.0, 0.5, 1.0, s64, p->ldp, a64, p->ldm,
-                  at<int>(p, p->tab_op), at<int>(p, p->tab_om), at<int>(p, p->tab_vp), at<int>(p, p->tab_vm)));
+  PPL_TRY(pack_amplitudes(p, nullptr, t2));
   const HhlScratch hs = hhl_scratch(p, p->g.bytes);
   PPL_TRY(hhl_pass(p, hs, true, s64, nullptr, PPL_FP64, false));
   PPL_TRY(hhl_pass(p, hs, false, a64, nullptr, PPL_FP64, false));
@@ -1302,8 +1303,7 @@ int ppl_iterate(ppl_plan_t p, const double* L, const double* e_occ, const double
                      p->ldm, s64, a64, tabs[0], tabs[1], tabs[2], tabs[3], partials, red_out);
   };
   auto load_given = [&]() -> int {
-    return pack_pm(st, p->o, p->v, t2, (int64_t)p->o * p->v * p->v, (int64_t)p->v * p->v, p->v, 1, 1.0,
-                   0.5, 1.0, s64, p->ldp, a64, p->ldm, tabs[0], tabs[1], tabs[2], tabs[3]);
+    return pack_amplitudes(p, nullptr, t2);
   };
   if (o.start == PPL_START_MP2) PPL_TRY(load_mp2());
   else PPL_TRY(load_given());
@@ -1981,12 +1981,8 @@ static int batch_prepare(ppl_batch_t b) {
 static int batch_enqueue(ppl_batch_t b, const double* const* t2, double* const* R) {
   for (int k = 0; k < b->n; ++k) {
     ppl_plan_t p = b->plans[k];
-    const int64_t o = p->o, v = p->v;
     if (!t2[k] || !R[k]) return fail(PPL_E_ARG, "null t2 or R for instance %d", k);
-    PPL_TRY(pack_pm(b->stream, p->o, p->v, t2[k], o * v * v, v * v, v, 1, 1.0, 0.5, 1.0, at<double>(p, p->s64),
-                    p->ldp, at<double>(p, p->a64), p->ldm, at<int>(p, p->tab_op), at<int>(p, p->tab_om),
-                    at<int>(p, p->tab_vp), at<int>(p, p->tab_vm)));
-    PPL_TRY(refresh_operands(p, p->ops[0]));
+    PPL_TRY(pack_amplitudes(p, &p->ops[0], t2[k]));
   }
   const int n_items = (int)b->items.size();
   const int grid = n_items < 512 ? n_items : 512;

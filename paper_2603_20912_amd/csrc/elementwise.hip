@@ -13,6 +13,8 @@
 // (i<=j, a<=b) half, the rest following from the two (anti)symmetries.
 // The Fock denominator D_ij^ab = e_i + e_j - e_a - e_b is symmetric in (a,b) and
 // (i,j), so the update t <- (V + R)/D acts on each part separately.
+#include <algorithm>
+
 #include "ppl_internal.h"
 #include "pack_cubes.h"
 
@@ -718,68 +720,93 @@ int add_transposed(hipStream_t s, int c_prec, void* C, int64_t ldc, const double
 }
 
 // ------------------------------------------------------------------ generic (i,j,a,b) -> +/- packing
-// With t1 ([i][a], row length v1) the packed tensor is X_ij^ab + t1_i^a t1_j^b.
-__global__ void pack_plus_kernel(const double* __restrict__ X, int64_t si, int64_t sj, int64_t sa,
-                                 int64_t sb, double s_off, double s_diag, double* plus, int64_t Np,
-                                 int64_t Pp, int64_t ldp, const int* __restrict__ tab_op,
-                                 const int* __restrict__ tab_vp, const double* __restrict__ t1, int64_t v1) {
-  const int64_t total = Np * ldp;
-  const int64_t st = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < total; x += st) {
-    const int64_t q = x / ldp, p = x - q * ldp;
-    double val = 0.0;
-    if (p < Pp) {
-      const int ij = tab_op[q], ab = tab_vp[p];
-      const int i = pair_first(ij), j = pair_second(ij), a = pair_first(ab), b = pair_second(ab);
-      const int64_t base = i * si + j * sj;
-      double xab = X[base + a * sa + b * sb], xba = X[base + b * sa + a * sb];
-      if (t1) {
-        xab += t1[i * v1 + a] * t1[j * v1 + b];
-        xba += t1[i * v1 + b] * t1[j * v1 + a];
-      }
-      val = (a == b ? s_diag : s_off) * (xab + xba);
+// Work items are one occupied pair (i <= j) and one 32 x 32 block pair (A <= B) of virtual
+// indices: block (A, B) of X_ij is read along rows, block (B, A) too and transposed through LDS,
+// and both packed rows are written along b, so X is read once and every access is
+// coalesced for sb = 1 (48 + 39 us as two kernels with strided partners at (20, 200), 24 us). The
+// item of the last block also zeroes the rows' padding. With t1 ([i][a], row length v1) the
+// packed tensor is X_ij^ab + t1_i^a t1_j^b.
+struct PackArgs {
+  int64_t si, sj, sa, sb;
+  double s_off, s_diag, am;
+  void *plus, *plus_lo, *minus, *minus_lo;
+  int64_t ldp, ldm, v1;
+};
+
+template <int PREC>
+__global__ void __launch_bounds__(256)
+pack_tiled_kernel(int o, int v, const double* __restrict__ X, PackArgs g, const int* __restrict__ tab_op,
+                  const double* __restrict__ t1) {
+  __shared__ double tr[32][33];
+  const int nb = (v + 31) / 32;
+  const int64_t per = (int64_t)nb * (nb + 1) / 2, items = npairs_plus(o) * per;
+  const int64_t Pp = npairs_plus(v), Pm = npairs_minus(v);
+  const int f = threadIdx.x & 31, m = threadIdx.x >> 5;
+  for (int64_t it = blockIdx.x; it < items; it += gridDim.x) {
+    const int64_t pr = it / per;
+    int k = (int)(it % per), A = 0;
+    while (k >= nb - A) k -= nb - A++;          // block pair (A, B = A + k)
+    const int B = A + k, ij = tab_op[pr], i = pair_first(ij), j = pair_second(ij);
+    const bool offd = i < j;
+    const double* x = X + i * g.si + j * g.sj;
+    double ab[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int r = m + 8 * e, a = A * 32 + r, b = B * 32 + f;
+      ab[e] = (a < v && b < v) ? x[a * g.sa + b * g.sb] : 0.0;
+      if (t1 && a < v && b < v) ab[e] += t1[i * g.v1 + a] * t1[j * g.v1 + b];
     }
-    plus[x] = val;
+    if (A != B) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int r = m + 8 * e, b = B * 32 + r, a = A * 32 + f;
+        double y = (a < v && b < v) ? x[b * g.sa + a * g.sb] : 0.0;
+        if (t1 && a < v && b < v) y += t1[i * g.v1 + b] * t1[j * g.v1 + a];
+        tr[f][r] = y;
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) tr[f][m + 8 * e] = ab[e];
+    }
+    __syncthreads();
+    const int64_t qr = offd ? pair_minus(i, j, o) : 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int r = m + 8 * e, a = A * 32 + r, b = B * 32 + f;
+      if (b < v && a <= b) {
+        const double y = tr[r][f];
+        Store<PREC>::put(g.plus, g.plus_lo, pr * g.ldp + pair_plus(a, b, v), (a == b ? g.s_diag : g.s_off) * (ab[e] + y));
+        if (offd && a < b)
+          Store<PREC>::put(g.minus, g.minus_lo, qr * g.ldm + pair_minus(a, b, v), g.am * (ab[e] - y));
+      }
+    }
+    if (A == nb - 1) {                          // (A = B: the last block of the pair)
+      for (int64_t q = Pp + threadIdx.x; q < g.ldp; q += 256) Store<PREC>::put(g.plus, g.plus_lo, pr * g.ldp + q, 0.0);
+      if (offd)
+        for (int64_t q = Pm + threadIdx.x; q < g.ldm; q += 256)
+          Store<PREC>::put(g.minus, g.minus_lo, qr * g.ldm + q, 0.0);
+    }
+    __syncthreads();
   }
 }
 
-__global__ void pack_minus_kernel(const double* __restrict__ X, int64_t si, int64_t sj, int64_t sa,
-                                  int64_t sb, double am, double* minus, int64_t Nm, int64_t Pm,
-                                  int64_t ldm, const int* __restrict__ tab_om,
-                                  const int* __restrict__ tab_vm, const double* __restrict__ t1, int64_t v1) {
-  const int64_t total = Nm * ldm;
-  const int64_t st = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < total; x += st) {
-    const int64_t q = x / ldm, p = x - q * ldm;
-    double val = 0.0;
-    if (p < Pm) {
-      const int ij = tab_om[q], ab = tab_vm[p];
-      const int i = pair_first(ij), j = pair_second(ij), a = pair_first(ab), b = pair_second(ab);
-      const int64_t base = i * si + j * sj;
-      double xab = X[base + a * sa + b * sb], xba = X[base + b * sa + a * sb];
-      if (t1) {
-        xab += t1[i * v1 + a] * t1[j * v1 + b];
-        xba += t1[i * v1 + b] * t1[j * v1 + a];
-      }
-      val = am * (xab - xba);
-    }
-    minus[x] = val;
-  }
-}
-
-int pack_pm(hipStream_t s, int o, int v, const double* X, int64_t si, int64_t sj, int64_t sa,
-            int64_t sb, double sp_off, double sp_diag, double am, double* plus, int64_t ldp,
-            double* minus, int64_t ldm, const int* tab_op, const int* tab_om, const int* tab_vp,
-            const int* tab_vm, const double* t1) {
-  const int64_t Np = npairs_plus(o), Nm = npairs_minus(o), Pp = npairs_plus(v), Pm = npairs_minus(v);
-  hipLaunchKernelGGL(pack_plus_kernel, dim3(grid_for(Np * ldp, 256)), dim3(256), 0, s, X, si, sj, sa,
-                     sb, sp_off, sp_diag, plus, Np, Pp, ldp, tab_op, tab_vp, t1, (int64_t)v);
+int pack_pm(hipStream_t s, int prec, int o, int v, const double* X, int64_t si, int64_t sj, int64_t sa, int64_t sb,
+            double sp_off, double sp_diag, double am, void* plus, void* plus_lo, int64_t ldp, void* minus,
+            void* minus_lo, int64_t ldm, const int* tab_op, const double* t1) {
+  const int64_t nb = (v + 31) / 32, items = npairs_plus(o) * (nb * (nb + 1) / 2);
+  const dim3 grid((unsigned)std::min<int64_t>(items, 16384));
+  const PackArgs g{si, sj, sa, sb, sp_off, sp_diag, am, plus, plus_lo, minus, minus_lo, ldp, ldm, (int64_t)v};
+  if (prec == PPL_FP64)
+    hipLaunchKernelGGL(pack_tiled_kernel<PPL_FP64>, grid, dim3(256), 0, s, o, v, X, g, tab_op, t1);
+  else if (prec == PPL_FP32)
+    hipLaunchKernelGGL(pack_tiled_kernel<PPL_FP32>, grid, dim3(256), 0, s, o, v, X, g, tab_op, t1);
+  else if (prec == PPL_BF16X3)
+    hipLaunchKernelGGL(pack_tiled_kernel<PPL_BF16X3>, grid, dim3(256), 0, s, o, v, X, g, tab_op, t1);
+  else if (prec == PPL_BF16X6)
+    hipLaunchKernelGGL(pack_tiled_kernel<PPL_BF16X6>, grid, dim3(256), 0, s, o, v, X, g, tab_op, t1);
+  else
+    return fail(PPL_E_ARG, "pack_pm: unknown precision %d", prec);
   PPL_LAUNCH_CHECK();
-  if (Nm > 0 && Pm > 0) {
-    hipLaunchKernelGGL(pack_minus_kernel, dim3(grid_for(Nm * ldm, 256)), dim3(256), 0, s, X, si, sj,
-                       sa, sb, am, minus, Nm, Pm, ldm, tab_om, tab_vm, t1, (int64_t)v);
-    PPL_LAUNCH_CHECK();
-  }
   return PPL_OK;
 }
 

@@ -305,14 +305,14 @@ int transpose_block(hipStream_t s, int elem_bytes, const void* U, int64_t ldu, i
                     int64_t k0, void* Ut, int64_t ldt, int64_t nr, int64_t nk);
 // pair tables
 int fill_tables(hipStream_t s, int o, int v, int* tab_vp, int* tab_vm, int* tab_op, int* tab_om);
-// generic pack of an (i,j,a,b)-indexed FP64 tensor into + / - packed rows:
+// generic pack of an (i,j,a,b)-indexed FP64 tensor into + / - packed rows of precision prec
+// (plus_lo, minus_lo: the second bf16 planes), zero padding included:
 //   plus [q(i<=j)][p(a<=b)] = (a<b ? sp_off : sp_diag) * (X^ab + X^ba)
 //   minus[q(i<j)][p(a<b)]   = am * (X^ab - X^ba)
 // where, with t1 ([i][a], row length v), X_ij^ab stands for X_ij^ab + t1_i^a t1_j^b
-int pack_pm(hipStream_t s, int o, int v, const double* X, int64_t si, int64_t sj, int64_t sa,
-            int64_t sb, double sp_off, double sp_diag, double am, double* plus, int64_t ldp,
-            double* minus, int64_t ldm, const int* tab_op, const int* tab_om, const int* tab_vp,
-            const int* tab_vm, const double* t1 = nullptr);
+int pack_pm(hipStream_t s, int prec, int o, int v, const double* X, int64_t si, int64_t sj, int64_t sa, int64_t sb,
+            double sp_off, double sp_diag, double am, void* plus, void* plus_lo, int64_t ldp, void* minus,
+            void* minus_lo, int64_t ldm, const int* tab_op, const double* t1 = nullptr);
 // staging: Xoo[(k,i)][P] = L[P][k][i] (FP64)
 int stage_oo(hipStream_t s, const double* L, int o, int v, int naux, int64_t ldx, double* xoo);
 
