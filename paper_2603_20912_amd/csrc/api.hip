@@ -535,8 +535,10 @@ static int contract_stream_sym(ppl_plan_t p, OperandSet& s, int tile, int tile_m
   return PPL_OK;
 }
 
-// R+ = S' V+^T, R- = A' V-^T with the operand set s (its S'/A' must be current).
-static int contract_packed(ppl_plan_t p, OperandSet& s) {
+// R+ = S' V+^T, R- = A' V-^T with the operand set s (its S'/A' must be current). With `out`
+// (R+, R-) a resident plan leaves split-K slices unsummed where both results' slices fit the
+// partial buffer, for a consumer that sums them as it reads (out says where the results are).
+static int contract_packed(ppl_plan_t p, OperandSet& s, Slices (*out)[2] = nullptr) {
   hipStream_t st = p->stream;
   const void* sp = at<void>(p, s.sp);
   const void* sp_lo = s.sp_lo.bytes ? at<void>(p, s.sp_lo) : nullptr;
@@ -545,25 +547,52 @@ static int contract_packed(ppl_plan_t p, OperandSet& s) {
   const bool primary = &s == &p->ops[0];
   const int tile = primary ? p->tile_contract : s.tile_p, tile_m = primary ? p->tile_m : s.tile_m;
   const int split_p = primary ? p->split_p : s.split_p, split_m = primary ? p->split_m : s.split_m;
-  void* part = p->part.bytes ? at<void>(p, p->part) : nullptr;
+  char* part = p->part.bytes ? at<char>(p, p->part) : nullptr;
   if (std::max(split_p, split_m) > kMaxSplits ||
       (uint64_t)std::max(p->Np, p->Nm) * p->ld_part * kMaxSplits * 8 > p->part.bytes ||
       (uint64_t)p->Np * p->ldp * 8 > p->rp.bytes)
     return fail(PPL_E_STATE, "contraction buffers smaller than the plan requires");
+  if (out) {
+    (*out)[0] = Slices{at<void>(p, p->rp), 1, 0};
+    (*out)[1] = Slices{at<void>(p, p->rm), 1, 0};
+  }
   const double fp = 2.0 * (double)p->Np * p->Pp, fm = 2.0 * (double)p->Nm * p->Pm;
   if (p->resident) {
     if (!s.built) return fail(PPL_E_STATE, "V+- not built (call ppl_build_batch first)");
+    const uint64_t w = acc_bytes(s.prec);
+    const uint64_t part_p = align256((uint64_t)split_p * p->Np * p->ldp * w);
+    // (a stream-K R- takes the whole buffer for its partial tiles)
+    const bool keep_p = out && split_m > 0 && part_p + (uint64_t)split_m * p->Nm * p->ldm * w <= p->part.bytes;
+    char* part_m = part + (keep_p ? part_p : 0);
+    const uint64_t bytes_m = p->part.bytes - (keep_p ? part_p : 0);
+    int np = 1, nm = 1;
+    if (keep_p && tile == tile_m && !p->prof_on) {
+      const ContractSide c[2] = {
+          {p->Np, p->Pp, p->ldp, sp, at<void>(p, s.vp), at<void>(p, p->rp), part, split_p, s.tri, &np},
+          {p->Nm, p->Pm, p->ldm, am, at<void>(p, s.vm), at<void>(p, p->rm), part_m, split_m, s.tri, &nm}};
+      if (contract_pair_ok(s.prec, tile, c)) {
+        PPL_TRY(gemm_contract_pair(st, s.prec, tile, c));
+        if (np > 1) (*out)[0] = Slices{part, np, p->Np * p->ldp};
+        if (nm > 1) (*out)[1] = Slices{part_m, nm, p->Nm * p->ldm};
+        return PPL_OK;
+      }
+    }
     {
       ProfScope ps(p, PPL_PROF_CONTRACT_PLUS, fp * p->Pp);
       PPL_TRY(gemm_contract(st, s.prec, tile, p->Np, p->Pp, p->ldp, sp, sp_lo, p->ldp,
                             at<void>(p, s.vp), s.vp_lo.bytes ? at<void>(p, s.vp_lo) : nullptr, p->ldp,
-                            at<void>(p, p->rp), p->ldp, 0, split_p, part, p->ld_part, p->part.bytes, false, s.tri));
+                            at<void>(p, p->rp), p->ldp, 0, split_p, part, p->ldp, p->part.bytes, false, s.tri,
+                            keep_p ? &np : nullptr));
+      if (np > 1) (*out)[0] = Slices{part, np, p->Np * p->ldp};
     }
     ProfScope ps(p, PPL_PROF_CONTRACT_MINUS, fm * p->Pm);
-    if (p->Nm > 0 && p->Pm > 0)
+    if (p->Nm > 0 && p->Pm > 0) {
       PPL_TRY(gemm_contract(st, s.prec, tile_m, p->Nm, p->Pm, p->ldm, am, am_lo, p->ldm,
                             at<void>(p, s.vm), s.vm_lo.bytes ? at<void>(p, s.vm_lo) : nullptr, p->ldm,
-                            at<void>(p, p->rm), p->ldm, 0, split_m, part, p->ld_part, p->part.bytes, false, s.tri));
+                            at<void>(p, p->rm), p->ldm, 0, split_m, part_m, p->ldm, bytes_m, false, s.tri,
+                            out ? &nm : nullptr));
+      if (nm > 1) (*out)[1] = Slices{part_m, nm, p->Nm * p->ldm};
+    }
     return PPL_OK;
   }
   if (!p->L_last) return fail(PPL_E_STATE, "streaming plan has no Cholesky vectors (call ppl_build_batch)");
@@ -1069,9 +1098,10 @@ static int contract_impl(ppl_plan_t p, const double* t2, const double* t1, doubl
   if ((const void*)t2 == (const void*)R) return fail(PPL_E_ARG, "R may not alias t2");
   OperandSet& s = p->ops[0];
   PPL_TRY(pack_amplitudes(p, &s, t2, t1));
-  PPL_TRY(contract_packed(p, s));
-  PPL_TRY(unpack_r(p->stream, s.prec == PPL_FP64 ? PPL_FP64 : PPL_FP32, p->o, p->v, at<void>(p, p->rp),
-                   p->ldp, at<void>(p, p->rm), p->ldm, R, alpha, beta));
+  Slices r[2];
+  PPL_TRY(contract_packed(p, s, &r));
+  PPL_TRY(unpack_r(p->stream, s.prec == PPL_FP64 ? PPL_FP64 : PPL_FP32, p->o, p->v, r[0], p->ldp, r[1], p->ldm, R,
+                   alpha, beta));
   return PPL_OK;
 }
 }  // namespace ppl
@@ -1107,7 +1137,7 @@ int ppl_hhl(ppl_plan_t p, const double* L, const double* t2, double* R, double a
   const HhlScratch hs = hhl_scratch(p, p->g.bytes);
   PPL_TRY(hhl_pass(p, hs, true, s64, nullptr, PPL_FP64, false));
   PPL_TRY(hhl_pass(p, hs, false, a64, nullptr, PPL_FP64, false));
-  return unpack_r(st, PPL_FP64, p->o, p->v, s64, p->ldp, a64, p->ldm, R, alpha, beta);
+  return unpack_r(st, PPL_FP64, p->o, p->v, Slices{s64}, p->ldp, Slices{a64}, p->ldm, R, alpha, beta);
 }
 
 // J[(k,c)][(j,b)] = (kc|jb) and K[(k,c)][(j,b)] = (kj|bc) from L (scratch w laid out by r)
@@ -1992,8 +2022,8 @@ static int batch_enqueue(ppl_batch_t b, const double* const* t2, double* const* 
                        reinterpret_cast<int*>(b->ws + b->counter_r.off), grid));
   for (int k = 0; k < b->n; ++k) {
     ppl_plan_t p = b->plans[k];
-    PPL_TRY(unpack_r(b->stream, b->prec == PPL_FP64 ? PPL_FP64 : PPL_FP32, p->o, p->v, at<void>(p, p->rp),
-                     p->ldp, at<void>(p, p->rm), p->ldm, R[k], 1.0, 0.0));
+    PPL_TRY(unpack_r(b->stream, b->prec == PPL_FP64 ? PPL_FP64 : PPL_FP32, p->o, p->v, Slices{at<void>(p, p->rp)},
+                     p->ldp, Slices{at<void>(p, p->rm)}, p->ldm, R[k], 1.0, 0.0));
   }
   return PPL_OK;
 }

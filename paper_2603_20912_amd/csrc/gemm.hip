@@ -897,6 +897,34 @@ gemm_nt_kernel(int64_t M, int64_t N, int64_t Kpad, const T* __restrict__ A, int6
   }
 }
 
+// Two contractions (R+ and R-) on one tile in one launch: workgroups below grid0 (a multiple of 8,
+// so that both keep the XCD order of their maps) take the first, the others the second.
+template <class T>
+struct PairSide {
+  int64_t M, N;
+  const T *A, *B;
+  int64_t lda, ldb;
+  EpiStore<T> epi;
+  MapGrid map;
+};
+
+template <class T, int WM, int WN, int WAVES_M, int WAVES_N, int KC>
+__global__ void __launch_bounds__(64 * WAVES_M * WAVES_N)
+__attribute__((amdgpu_waves_per_eu(GemmOccupancy<T, WM, WN, WAVES_M, WAVES_N, KC, EpiStore<T>>::waves)))
+gemm_nt_pair_kernel(PairSide<T> p0, PairSide<T> p1, int64_t grid0) {
+  using G = TileGeom<T, WM, WN, WAVES_M, WAVES_N, KC>;
+  __shared__ __attribute__((aligned(16))) T st0[G::BUF_A + G::BUF_B];
+  __shared__ __attribute__((aligned(16))) T st1[G::BUF_A + G::BUF_B];
+  __shared__ __attribute__((aligned(16))) T st2[G::BUF_A + G::BUF_B];
+  const bool second = blockIdx.x >= grid0;
+  const PairSide<T> p = second ? p1 : p0;
+  const int64_t bid = second ? blockIdx.x - grid0 : blockIdx.x;
+  TileJob job;
+  if (bid >= p.map.n_mt * p.map.n_nt * p.map.splits) return;
+  p.map(bid, job);
+  tile_body_direct3<T, WM, WN, WAVES_M, WAVES_N, KC>(job, p.M, p.N, p.A, p.lda, p.B, p.ldb, p.epi, st0, st1, st2);
+}
+
 // ------------------------------------------------------------------ the kernel (BF16 x 3)
 // x = hi + lo with hi = bf16(x), lo = bf16(x - hi); x*y ~ hi*hi + hi*lo + lo*hi,
 // the two small cross products accumulated in their own FP32 register set and
@@ -2018,7 +2046,7 @@ static int contract_cfg(hipStream_t s, int prec, int64_t Nrows, int64_t Prows, i
                         const void* S, const void* S_lo, int64_t lds_, const void* V,
                         const void* V_lo, int64_t ldv, void* C, int64_t ldc, int64_t c_col0,
                         int splits, void* partial, int64_t partial_ld, uint64_t partial_bytes,
-                        bool accumulate, bool tri) {
+                        bool accumulate, bool tri, int* slices) {
   constexpr int BM = 16 * WM * WAVES_M, BN = 16 * WN * WAVES_N;
   static_assert(kTriBlock % BN == 0, "a column tile lies in one diagonal block of a triangular operand");
   if (accumulate && splits != 1) return fail(PPL_E_ARG, "an accumulating contraction runs one K slice");
@@ -2083,6 +2111,10 @@ static int contract_cfg(hipStream_t s, int prec, int64_t Nrows, int64_t Prows, i
     return fail(PPL_E_ARG, "unknown precision %d", prec);
   }
   if (rc != PPL_OK || direct) return rc;
+  if (slices) {                 // the caller sums them
+    *slices = splits;
+    return PPL_OK;
+  }
   const int64_t total = Nrows * Prows;
   int64_t g = (total + 255) / 256;
   if (g > 65536) g = 65536;
@@ -2099,12 +2131,13 @@ static int contract_cfg(hipStream_t s, int prec, int64_t Nrows, int64_t Prows, i
 int gemm_contract(hipStream_t s, int prec, int tile, int64_t Nrows, int64_t Prows, int64_t Kpad,
                   const void* S, const void* S_lo, int64_t lds_, const void* V, const void* V_lo,
                   int64_t ldv, void* C, int64_t ldc, int64_t c_col0, int splits, void* partial,
-                  int64_t partial_ld, uint64_t partial_bytes, bool accumulate, bool tri) {
+                  int64_t partial_ld, uint64_t partial_bytes, bool accumulate, bool tri, int* slices) {
+  if (slices) *slices = 1;
   if (Nrows <= 0 || Prows <= 0) return PPL_OK;
 #define PPL_CFG(id, a, b, c, d)                                                                  \
   case id:                                                                                       \
     return contract_cfg<a, b, c, d>(s, prec, Nrows, Prows, Kpad, S, S_lo, lds_, V, V_lo, ldv, C,  \
-                                    ldc, c_col0, splits, partial, partial_ld, partial_bytes, accumulate, tri);
+                                    ldc, c_col0, splits, partial, partial_ld, partial_bytes, accumulate, tri, slices);
   switch (tile) {
     PPL_CFG(0, 7, 2, 1, 4)
     PPL_CFG(1, 4, 4, 2, 2)
@@ -2121,6 +2154,57 @@ int gemm_contract(hipStream_t s, int prec, int tile, int64_t Nrows, int64_t Prow
       return fail(PPL_E_ARG, "unknown contraction tile %d", tile);
   }
 #undef PPL_CFG
+}
+
+template <class T, int WM, int WN, int WAVES_M, int WAVES_N>
+static int pair_cfg(hipStream_t s, const ContractSide (&c)[2]) {
+  constexpr int BM = 16 * WM * WAVES_M, BN = 16 * WN * WAVES_N, KC = sizeof(T) == 8 ? kKcF64 : kKcF32;
+  static_assert(kTriBlock % BN == 0, "a column tile lies in one diagonal block of a triangular operand");
+  PairSide<T> p[2];
+  int64_t grid[2];
+  for (int k = 0; k < 2; ++k) {
+    const ContractSide& q = c[k];
+    const int64_t nk = q.ld / KC;
+    int splits = q.splits > nk ? (int)nk : q.splits;
+    const int64_t kps = (nk + splits - 1) / splits;
+    splits = (int)((nk + kps - 1) / kps);               // no empty slice
+    *q.slices = splits;
+    p[k] = PairSide<T>{q.rows, q.cols, (const T*)q.S, (const T*)q.V, q.ld, q.ld,
+                       EpiStore<T>{splits > 1 ? (T*)q.partial : (T*)q.C, q.ld, 0, q.rows, q.cols, 1.0, 0.0,
+                                   q.rows * q.ld, q.tri},
+                       MapGrid{(q.rows + BM - 1) / BM, (q.cols + BN - 1) / BN, BM, BN, splits, nk, kps}};
+    grid[k] = p[k].map.n_mt * p[k].map.n_nt * splits;
+  }
+  const int64_t grid0 = (grid[0] + 7) / 8 * 8;
+  hipLaunchKernelGGL((gemm_nt_pair_kernel<T, WM, WN, WAVES_M, WAVES_N, KC>), dim3((unsigned)(grid0 + grid[1])),
+                     dim3(64 * WAVES_M * WAVES_N), 0, s, p[0], p[1], grid0);
+  PPL_HIP_TRY(hipGetLastError());
+  return PPL_OK;
+}
+
+// One launch pays where two short ones leave the device idle between and after them: both
+// contractions together at most kPairJobs workgroups (two per CU; the launch and the tail of
+// one are then a good part of its time). A contraction at (5, 20), FP64: 14.9 us in three
+// launches (packing, this one, unpacking), 24.0 us in six with two GEMMs and two slice sums.
+bool contract_pair_ok(int prec, int tile, const ContractSide (&c)[2]) {
+  if ((prec != PPL_FP64 && prec != PPL_FP32) || tile < 6 || tile > 8) return false;
+  constexpr int64_t kPairJobs = 512;
+  int64_t jobs = 0;
+  for (const ContractSide& q : c) {
+    if (q.rows <= 0 || q.cols <= 0 || q.splits < 1) return false;
+    jobs += contract_jobs(tile, prec, q.rows, q.cols, q.ld, q.splits);
+  }
+  return jobs <= kPairJobs;
+}
+
+int gemm_contract_pair(hipStream_t s, int prec, int tile, const ContractSide (&c)[2]) {
+  const bool d = prec == PPL_FP64;
+  switch (tile) {
+    case 6: return d ? pair_cfg<double, 2, 2, 1, 4>(s, c) : pair_cfg<float, 2, 2, 1, 4>(s, c);
+    case 7: return d ? pair_cfg<double, 3, 2, 1, 4>(s, c) : pair_cfg<float, 3, 2, 1, 4>(s, c);
+    case 8: return d ? pair_cfg<double, 4, 2, 1, 4>(s, c) : pair_cfg<float, 4, 2, 1, 4>(s, c);
+    default: return fail(PPL_E_ARG, "tile %d has no paired contraction", tile);
+  }
 }
 
 // Workgroups of one contraction launch for a (tile, splits) choice.

@@ -194,10 +194,22 @@ int gemm_store_f64(hipStream_t s, int64_t M, int64_t N, int64_t Kpad, const doub
 // accumulator type) and summed in slice order into C. accumulate: C += the product (one
 // K slice only; PPL_E_ARG with split-K or stream-K). tri (FP64, FP32): V is a symmetric
 // matrix stored as kTriBlock describes; the result is that of the full matrix, bit for bit.
+// slices: the K slices stay unsummed in `partial`, *slices of them (1: the result is in C).
 int gemm_contract(hipStream_t s, int prec, int tile, int64_t Nrows, int64_t Prows, int64_t Kpad,
                   const void* S, const void* S_lo, int64_t lds_, const void* V, const void* V_lo,
                   int64_t ldv, void* C, int64_t ldc, int64_t c_col0, int splits, void* partial,
-                  int64_t partial_ld, uint64_t partial_bytes, bool accumulate = false, bool tri = false);
+                  int64_t partial_ld, uint64_t partial_bytes, bool accumulate = false, bool tri = false,
+                  int* slices = nullptr);
+// R+ and R- of one operand set in one launch (tile and K decompositions as gemm_contract)
+struct ContractSide {
+  int64_t rows, cols, ld;   // occupied pairs, virtual pairs, row length of every operand
+  const void *S, *V;
+  void *C, *partial;        // partial: [splits][rows][ld]
+  int splits, tri;
+  int* slices;              // out: K slices written (1: in C, more: in partial)
+};
+bool contract_pair_ok(int prec, int tile, const ContractSide (&c)[2]);
+int gemm_contract_pair(hipStream_t s, int prec, int tile, const ContractSide (&c)[2]);
 // bytes of partial slots a stream-K contraction (splits == 0) with this tile needs at most
 uint64_t streamk_part_bytes(int tile, int prec, int64_t Nrows, int64_t Prows, int64_t Kpad);
 int64_t contract_jobs(int tile, int prec, int64_t Nrows, int64_t Prows, int64_t Kpad, int splits);
@@ -319,8 +331,14 @@ int stage_oo(hipStream_t s, const double* L, int o, int v, int naux, int64_t ldx
 // convert FP64 packed rows to an operand precision (FP32 or BF16 hi/lo), zero padding kept
 int convert_rows(hipStream_t s, int prec, const double* src, int64_t rows, int64_t cols, int64_t ld,
                  void* dst, void* dst_lo);
+// A contraction result: the sum, in slice order and in its own type, of n arrays `stride` elements apart
+struct Slices {
+  const void* p = nullptr;
+  int n = 1;
+  int64_t stride = 0;
+};
 // unpack R = beta R + alpha (R+ +- R-) into [o][o][v][v]
-int unpack_r(hipStream_t s, int acc_prec, int o, int v, const void* rp, int64_t ldp, const void* rm,
+int unpack_r(hipStream_t s, int acc_prec, int o, int v, const Slices& rp, int64_t ldp, const Slices& rm,
              int64_t ldm, double* R, double alpha, double beta);
 // packed amplitudes S'/A' (FP64) back to the full pair-symmetric t2
 int unpack_t(hipStream_t s, int o, int v, const double* sp, int64_t ldp, const double* am,
