@@ -237,8 +237,10 @@ static uint64_t assign_layout(ppl_plan_t p, int64_t gcap, bool resident, int64_t
     s.xt = L.take((uint64_t)v * v * p->ldx * w);
     s.vp = L.take((uint64_t)vrows_p * p->ldp * w);
     s.vm = L.take((uint64_t)std::max<int64_t>(vrows_m, 1) * p->ldm * w);
-    s.sp = L.take((uint64_t)p->Np * p->ldp * w);
-    s.am = L.take((uint64_t)std::max<int64_t>(p->Nm, 1) * p->ldm * w);
+    if (k == 0) {                      // the FP64 copy's operand rows are the masters (below)
+      s.sp = L.take((uint64_t)p->Np * p->ldp * w);
+      s.am = L.take((uint64_t)std::max<int64_t>(p->Nm, 1) * p->ldm * w);
+    }
     if (np == 2) {
       s.xt_lo = L.take(s.xt.bytes);
       s.vp_lo = L.take(s.vp.bytes);
@@ -284,6 +286,10 @@ static uint64_t assign_layout(ppl_plan_t p, int64_t gcap, bool resident, int64_t
   } else {
     p->s64 = p->ops[0].sp;
     p->a64 = p->ops[0].am;
+  }
+  if (p->ops[1].present) {
+    p->ops[1].sp = p->s64;
+    p->ops[1].am = p->a64;
   }
   if (p->contract_only) {
     p->bs = p->ba = p->vs = p->va = p->xov = Region{};
@@ -615,18 +621,9 @@ static int contract_packed(ppl_plan_t p, OperandSet& s, Slices (*out)[2] = nullp
   return PPL_OK;
 }
 
-// refresh the low-precision S'/A' copies of set s from the FP64 master
+// refresh the low-precision S'/A' copies of set s from the FP64 master (FP64 sets use it as it is)
 static int refresh_operands(ppl_plan_t p, OperandSet& s) {
-  if (s.prec == PPL_FP64) {
-    if (s.sp.off != p->s64.off) {   // FP64 refinement set of a mixed plan: copy the master
-      PPL_TRY(convert_rows(p->stream, PPL_FP64, at<double>(p, p->s64), p->Np, p->Pp, p->ldp,
-                           at<void>(p, s.sp), nullptr));
-      if (p->Nm > 0)
-        PPL_TRY(convert_rows(p->stream, PPL_FP64, at<double>(p, p->a64), p->Nm, p->Pm, p->ldm,
-                             at<void>(p, s.am), nullptr));
-    }
-    return PPL_OK;
-  }
+  if (s.prec == PPL_FP64) return PPL_OK;
   PPL_TRY(convert_rows(p->stream, s.prec, at<double>(p, p->s64), p->Np, p->Pp, p->ldp,
                        at<void>(p, s.sp), s.sp_lo.bytes ? at<void>(p, s.sp_lo) : nullptr));
   if (p->Nm > 0)
@@ -649,13 +646,20 @@ static int setup_ov_integrals(ppl_plan_t p, const double* L) {
   return PPL_OK;
 }
 
-static int read_red(ppl_plan_t p, double out[4]) {
-  const double* red_out = at<double>(p, p->red) + kReduceBlocks * 4;
-  PPL_HIP_TRY(hipMemcpyAsync(out, red_out, 4 * sizeof(double), hipMemcpyDeviceToHost, p->stream));
-  PPL_HIP_TRY(hipStreamSynchronize(p->stream));
-  return PPL_OK;
+// Sums that the host reads back go to mapped host memory where the plan has some (a plan that
+// iterates reads several per run: a copy and its wait took 24 us, the wait alone 11), else to
+// the workspace.
+static double* red_target(ppl_plan_t p) {
+  return p->host_red ? p->host_red : at<double>(p, p->red) + kReduceBlocks * 4;
 }
 
+static int read_red(ppl_plan_t p, double out[4]) {
+  if (!p->host_red)
+    PPL_HIP_TRY(hipMemcpyAsync(out, red_target(p), 4 * sizeof(double), hipMemcpyDeviceToHost, p->stream));
+  PPL_HIP_TRY(hipStreamSynchronize(p->stream));
+  if (p->host_red) memcpy(out, p->host_red, 4 * sizeof(double));
+  return PPL_OK;
+}
 
 // the upper-triangle build relies on symmetric Cholesky vectors (V+- symmetric): PPL_E_ARG
 // when the virtual block of L is not symmetric to a relative Frobenius asymmetry of 1e-10
@@ -664,7 +668,7 @@ static int check_symmetric(ppl_plan_t p, const double* L) {
   if (!p->sym_build) return PPL_OK;
   double* partials = at<double>(p, p->red);
   double h[4];
-  PPL_TRY(asymmetry_vv(p->stream, L, p->o, p->v, p->naux, partials, partials + kReduceBlocks * 4));
+  PPL_TRY(asymmetry_vv(p->stream, L, p->o, p->v, p->naux, partials, red_target(p)));
   PPL_TRY(read_red(p, h));
   if (!(h[0] <= 1e-20 * h[1]))
     return fail(PPL_E_ARG, "Cholesky vectors are not symmetric in their virtual block (relative asymmetry %.3g)",
@@ -1309,12 +1313,29 @@ int ppl_iterate(ppl_plan_t p, const double* L, const double* e_occ, const double
   memset(&r, 0, sizeof(r));
   hipStream_t st = p->stream;
   double* partials = at<double>(p, p->red);
-  double* red_out = partials + kReduceBlocks * 4;
+  if (!p->host_red) PPL_HIP_TRY(hipHostMalloc((void**)&p->host_red, kHostRed * sizeof(double), hipHostMallocMapped));
+  double* const red_out = p->host_red;
   double h[4];
 
-  // integrals: V = (ia|jb) packed into VS / VA, then V+- of every operand set, then the
-  // hole-hole W+- (the build scratch holds them for the sweeps of a resident plan)
+  const int* tabs[4] = {at<int>(p, p->tab_op), at<int>(p, p->tab_om), at<int>(p, p->tab_vp),
+                        at<int>(p, p->tab_vm)};
+  double* s64 = at<double>(p, p->s64);
+  double* a64 = at<double>(p, p->a64);
+  // each leaves the start's energy and non-finite count in the sums that the host reads
+  auto load_mp2 = [&]() -> int {
+    return mp2_start(st, p->o, p->v, e_occ, e_vir, at<double>(p, p->vs), at<double>(p, p->va), p->ldp,
+                     p->ldm, s64, a64, tabs[0], tabs[1], tabs[2], tabs[3], partials, red_out);
+  };
+  auto load_given = [&]() -> int {
+    PPL_TRY(pack_amplitudes(p, nullptr, t2));
+    return energy_only(st, p->o, p->v, at<double>(p, p->vs), at<double>(p, p->va), s64, a64, p->ldp, p->ldm,
+                       tabs[0], tabs[1], tabs[2], tabs[3], partials, red_out);
+  };
+  // integrals V = (ia|jb) packed into VS / VA and the start, then V+- of every operand set, then
+  // the hole-hole W+- (the build scratch holds them for the sweeps of a resident plan)
   PPL_TRY(setup_ov_integrals(p, L));
+  PPL_TRY(o.start == PPL_START_MP2 ? load_mp2() : load_given());
+  PPL_TRY(read_red(p, h));
   PPL_TRY(ppl_build_batch(p, L, -1));
   if (o.hhl) PPL_TRY(hhl_integrals(p, L));
   RingLayout rl;
@@ -1323,30 +1344,11 @@ int ppl_iterate(ppl_plan_t p, const double* L, const double* e_occ, const double
     PPL_TRY(ring_integrals(st, p->o, p->v, p->naux, L, at<char>(p, p->ring_ws), rl));
     if (rl.lp_prec != PPL_FP64) PPL_TRY(ring_integrals_lp(st, p->o, p->v, at<char>(p, p->ring_ws), rl));
   }
-
-  const int* tabs[4] = {at<int>(p, p->tab_op), at<int>(p, p->tab_om), at<int>(p, p->tab_vp),
-                        at<int>(p, p->tab_vm)};
-  double* s64 = at<double>(p, p->s64);
-  double* a64 = at<double>(p, p->a64);
-  auto load_mp2 = [&]() -> int {
-    return mp2_start(st, p->o, p->v, e_occ, e_vir, at<double>(p, p->vs), at<double>(p, p->va), p->ldp,
-                     p->ldm, s64, a64, tabs[0], tabs[1], tabs[2], tabs[3], partials, red_out);
-  };
-  auto load_given = [&]() -> int {
-    return pack_amplitudes(p, nullptr, t2);
-  };
-  if (o.start == PPL_START_MP2) PPL_TRY(load_mp2());
-  else PPL_TRY(load_given());
-  PPL_TRY(energy_only(st, p->o, p->v, at<double>(p, p->vs), at<double>(p, p->va), s64, a64, p->ldp, p->ldm,
-                      tabs[0], tabs[1], tabs[2], tabs[3], partials, red_out));
-  PPL_TRY(read_red(p, h));
   r.energy_start = h[1];
   if ((h[2] != 0.0 || !isfinite(h[1])) && o.start == PPL_START_GIVEN_CHECKED) {
     // a checked guess with NaN or Inf entries is rejected before any sweep: the
     // iteration falls back to the MP2 start, which the checked start promises
     PPL_TRY(load_mp2());
-    PPL_TRY(energy_only(st, p->o, p->v, at<double>(p, p->vs), at<double>(p, p->va), s64, a64, p->ldp, p->ldm,
-                        tabs[0], tabs[1], tabs[2], tabs[3], partials, red_out));
     PPL_TRY(read_red(p, h));
     r.energy_start = h[1];
     r.restarted_mp2 = 1;
@@ -1380,9 +1382,18 @@ int ppl_iterate(ppl_plan_t p, const double* L, const double* e_occ, const double
   double* const dE = diis_on ? at<double>(p, p->diis_e) : nullptr;
   double* const dred = diis_on ? at<double>(p, p->diis_red) : nullptr;
 
+  // the set whose operand rows hold the current amplitudes already, and rows to fill for the next
+  // low-precision sweep (an FP64 set's rows are the masters themselves)
+  const OperandSet* fresh = nullptr;
+  auto rows_of = [&](const OperandSet& s) {
+    if (s.prec == PPL_FP64) return OperandRows{};
+    return OperandRows{s.prec, at<void>(p, s.sp), s.sp_lo.bytes ? at<void>(p, s.sp_lo) : nullptr,
+                       at<void>(p, s.am), s.am_lo.bytes ? at<void>(p, s.am_lo) : nullptr};
+  };
   auto sweep_once = [&](OperandSet& s) -> int {
-    PPL_TRY(refresh_operands(p, s));
-    PPL_TRY(contract_packed(p, s));
+    if (fresh != &s) PPL_TRY(refresh_operands(p, s));
+    Slices res[2] = {Slices{at<void>(p, p->rp)}, Slices{at<void>(p, p->rm)}};
+    PPL_TRY(contract_packed(p, s, o.hhl || o.ring ? nullptr : &res));   // (both add to whole results)
     if (o.hhl) {
       ProfScope ph(p, PPL_PROF_OTHER, 2.0 * (double)p->Pp * p->Np * p->Np + 2.0 * (double)p->Pm * p->Nm * p->Nm);
       PPL_TRY(hhl_add_packed(p, s));
@@ -1402,12 +1413,22 @@ int ppl_iterate(ppl_plan_t p, const double* L, const double* e_occ, const double
                      at<void>(p, p->rp), p->ldp, at<void>(p, p->rm), p->ldm, tabs[0], tabs[1], tabs[2], tabs[3]));
     }
     ProfScope ps(p, PPL_PROF_UPDATE, 0.0);
-    double* ts = slot >= 0 ? dT + slot * p->diis_slot_n : nullptr;
-    double* es = slot >= 0 ? dE + slot * p->diis_slot_n : nullptr;
+    DiisSlot d;
+    if (slot >= 0) {
+      d.t = dT + slot * p->diis_slot_n;
+      d.e = dE + slot * p->diis_slot_n;
+      d.E = dE;
+      d.slot_n = p->diis_slot_n;
+      d.partials = dred;
+      d.others.n = (int)sub.size();
+      for (int i = 0; i < d.others.n; ++i) d.others.id[i] = sub[i];
+    }
+    // a plain sweep's amplitudes are the next input: rounded as they are written
+    const OperandRows op = slot < 0 ? rows_of(s) : OperandRows{};
     PPL_TRY(update_sweep(st, s.prec == PPL_FP64 ? PPL_FP64 : PPL_FP32, p->o, p->v, e_occ, e_vir,
-                         at<double>(p, p->vs), at<double>(p, p->va), at<void>(p, p->rp), at<void>(p, p->rm),
-                         p->ldp, p->ldm, s64, a64, tabs[0], tabs[1], tabs[2], tabs[3], partials, red_out,
-                         ts, es));
+                         at<double>(p, p->vs), at<double>(p, p->va), res[0], res[1], p->ldp, p->ldm, s64, a64,
+                         tabs[0], tabs[1], tabs[2], tabs[3], partials, red_out, op, d));
+    fresh = op.prec != PPL_FP64 ? &s : nullptr;
     return read_red(p, h);
   };
   // before a DIIS sweep: the slot it writes (the oldest vector's once the subspace is full)
@@ -1425,14 +1446,9 @@ int ppl_iterate(ppl_plan_t p, const double* L, const double* e_occ, const double
     sub.push_back(slot);
     DiisSet set{};
     set.n = (int)sub.size();
-    for (int i = 0; i < set.n; ++i) set.id[i] = sub[i];
-    PPL_TRY(diis_dots(st, p->o, p->v, p->ldp, p->ldm, tabs[0], tabs[1], tabs[2], tabs[3], dE, p->diis_slot_n,
-                      set, slot, dred, dred + kReduceBlocks * kDiisMax));
-    double dots[kDiisMax];
-    PPL_HIP_TRY(hipMemcpyAsync(dots, dred + kReduceBlocks * kDiisMax, set.n * sizeof(double),
-                               hipMemcpyDeviceToHost, st));
-    PPL_HIP_TRY(hipStreamSynchronize(st));
-    for (int i = 0; i < set.n; ++i) B[slot][sub[i]] = B[sub[i]][slot] = dots[i];
+    // the sweep left <e, e_i> of the earlier errors behind its own sums; <e, e> is the residual^2
+    for (int i = 0; i + 1 < set.n; ++i) B[slot][sub[i]] = B[sub[i]][slot] = red_out[3 + i];
+    B[slot][slot] = h[0];
     double c[kDiisMax];
     while (!diis_solve(B, sub, c)) {
       if (sub.size() == 1) {   // a zero error vector: the sweep's own amplitudes
@@ -1448,7 +1464,11 @@ int ppl_iterate(ppl_plan_t p, const double* L, const double* e_occ, const double
       set.c[i] = c[i];
     }
     slot = -1;
-    return diis_combine(st, p->o, p->v, p->ldp, p->ldm, dT, p->diis_slot_n, set, s64, a64);
+    OperandSet& next = (lp_phase || fp64_set < 0) ? p->ops[0] : p->ops[fp64_set];
+    const OperandRows op = rows_of(next);
+    PPL_TRY(diis_combine(st, p->o, p->v, p->ldp, p->ldm, dT, p->diis_slot_n, set, s64, a64, op));
+    fresh = op.prec != PPL_FP64 ? &next : nullptr;
+    return PPL_OK;
   };
   auto count_sweep = [&](const OperandSet& s, double rr) {
     if (o.history && sweeps < o.max_sweeps) o.history[sweeps] = rr;
@@ -1471,12 +1491,14 @@ int ppl_iterate(ppl_plan_t p, const double* L, const double* e_occ, const double
     PPL_TRY(convert_rows(st, PPL_FP64, s64, p->Np, p->Pp, p->ldp, at<void>(p, p->bs), nullptr));
     if (p->Nm > 0) PPL_TRY(convert_rows(st, PPL_FP64, a64, p->Nm, p->Pm, p->ldm, at<void>(p, p->ba), nullptr));
     PPL_TRY(load_mp2());
+    fresh = nullptr;
     PPL_TRY(sweep_once(s0));
     const double r_mp2 = sqrt(fabs(h[0]));
     count_sweep(s0, r_mp2);
     if (given_ok && r_given <= r_mp2) {
       PPL_TRY(convert_rows(st, PPL_FP64, at<double>(p, p->bs), p->Np, p->Pp, p->ldp, s64, nullptr));
       if (p->Nm > 0) PPL_TRY(convert_rows(st, PPL_FP64, at<double>(p, p->ba), p->Nm, p->Pm, p->ldm, a64, nullptr));
+      fresh = nullptr;
       r.residual = r_given;
       r.energy = e_given;
     } else {
@@ -1678,7 +1700,7 @@ int ppl_mp2(ppl_plan_t p, const double* L, const double* e_occ, const double* e_
   if (!L || !e_occ || !e_vir || !t2_out) return fail(PPL_E_ARG, "null device pointer");
   hipStream_t st = p->stream;
   double* partials = at<double>(p, p->red);
-  double* red_out = partials + kReduceBlocks * 4;
+  double* red_out = red_target(p);
   PPL_TRY(setup_ov_integrals(p, L));
   double* s64 = at<double>(p, p->s64);
   double* a64 = at<double>(p, p->a64);
@@ -1699,7 +1721,7 @@ int ppl_mlp_sigma(ppl_plan_t p, const double* t_mp2, double* sigma) {
   PPL_TRY(check_bound(p));
   if (!t_mp2 || !sigma) return fail(PPL_E_ARG, "null pointer");
   double* partials = at<double>(p, p->red);
-  double* red_out = partials + kReduceBlocks * 4;
+  double* red_out = red_target(p);
   const int64_t n = (int64_t)p->o * p->o * p->v * p->v;
   PPL_TRY(sumsq_launch(p->stream, t_mp2, n, partials, red_out));
   double h[4];
@@ -1722,6 +1744,7 @@ int ppl_mlp_samples(ppl_plan_t p, const double* t_mp2, const double* t_star, con
 int ppl_destroy(ppl_plan_t p) {
   if (!p) return PPL_OK;
   for (hipEvent_t e : p->prof_pool) (void)hipEventDestroy(e);
+  if (p->host_red) (void)hipHostFree(p->host_red);
   delete p;
   return PPL_OK;
 }

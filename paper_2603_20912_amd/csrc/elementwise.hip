@@ -1046,39 +1046,53 @@ int unpack_t(hipStream_t s, int o, int v, const double* sp, int64_t ldp, const d
 // ------------------------------------------------------------------ reductions
 // Fixed grid (kReduceBlocks x kReduceThreads), grid-stride loops and a fixed
 // tree order: the sums are bitwise reproducible for a given problem size.
+// Sum over the workgroup in thread 0: halves of 256 and 128 threads through LDS, the rest of
+// the same tree by lane shifts.
+__device__ inline double block_sum(double x, double* sh) {
+  const int tid = threadIdx.x;
+  sh[tid] = x;
+  __syncthreads();
+  if (tid < 128) sh[tid] += sh[tid + 128];
+  __syncthreads();
+  if (tid < 64) {
+    x = sh[tid] + sh[tid + 64];
+#pragma unroll
+    for (int w = 32; w > 0; w >>= 1) x += __shfl_down(x, w, 64);
+  }
+  return x;
+}
+static_assert(kReduceThreads == 256, "block_sum adds four waves");
+
+// one sum per value of this workgroup: partials[k][workgroup]
 template <int NV>
 __device__ inline void block_reduce_store(double (&vals)[NV], double* partials) {
   __shared__ double sh[NV][kReduceThreads];
-  const int tid = threadIdx.x;
 #pragma unroll
-  for (int k = 0; k < NV; ++k) sh[k][tid] = vals[k];
-  __syncthreads();
-  for (int w = kReduceThreads / 2; w > 0; w >>= 1) {
-    if (tid < w)
-#pragma unroll
-      for (int k = 0; k < NV; ++k) sh[k][tid] += sh[k][tid + w];
-    __syncthreads();
+  for (int k = 0; k < NV; ++k) {
+    const double x = block_sum(vals[k], sh[k]);
+    if (threadIdx.x == 0) partials[k * kReduceBlocks + blockIdx.x] = x;
   }
-  if (tid == 0)
-#pragma unroll
-    for (int k = 0; k < NV; ++k) partials[blockIdx.x * 4 + k] = sh[k][0];
 }
 
-__global__ void final_reduce_kernel(const double* __restrict__ partials, int nblocks, double* out) {
-  __shared__ double sh[4][kReduceThreads];
-  const int tid = threadIdx.x;
-  double acc[4] = {0, 0, 0, 0};
-  for (int b = tid; b < nblocks; b += kReduceThreads)
-    for (int k = 0; k < 4; ++k) acc[k] += partials[b * 4 + k];
-  for (int k = 0; k < 4; ++k) sh[k][tid] = acc[k];
-  __syncthreads();
-  for (int w = kReduceThreads / 2; w > 0; w >>= 1) {
-    if (tid < w)
-      for (int k = 0; k < 4; ++k) sh[k][tid] += sh[k][tid + w];
-    __syncthreads();
-  }
-  if (tid == 0)
-    for (int k = 0; k < 4; ++k) out[k] = sh[k][0];
+// out[k] = sum of partials[k][.], one workgroup per value k; values from n0 on come from a second
+// partial buffer. out may be mapped host memory.
+__global__ void __launch_bounds__(kReduceThreads)
+final_reduce_kernel(const double* __restrict__ partials, int n0, const double* __restrict__ partials1, double* out) {
+  __shared__ double sh[kReduceThreads];
+  const int k = blockIdx.x;
+  const double* p = k < n0 ? partials + k * kReduceBlocks : partials1 + (k - n0) * kReduceBlocks;
+  double acc = 0.0;
+#pragma unroll
+  for (int b = 0; b < kReduceBlocks; b += kReduceThreads) acc += p[b + threadIdx.x];
+  const double x = block_sum(acc, sh);
+  if (threadIdx.x == 0) out[k] = x;
+}
+
+static int final_reduce(hipStream_t s, const double* partials, int n0, const double* partials1, int n1, double* out) {
+  hipLaunchKernelGGL(final_reduce_kernel, dim3((unsigned)(n0 + n1)), dim3(kReduceThreads), 0, s, partials, n0,
+                     partials1, out);
+  PPL_LAUNCH_CHECK();
+  return PPL_OK;
 }
 
 struct PairGeom {
@@ -1105,18 +1119,34 @@ __device__ inline double denom(const double* e_occ, const double* e_vir, int ij,
 }
 
 // mode 0: MP2 start   S' = (2-d_ab) VS / D, A' = 2 VA / D, energy of the result
-// mode 1: Jacobi update from R+- (type Tr); residual^2, energy, non-finite count
+// mode 1: Jacobi update from R+- (type Tr, K slices summed here); residual^2, energy, non-finite count
 // mode 2: energy of the current S'/A' only
-// SAVE (mode 1 only): also write the new amplitudes and the error (new - old), both
-// in the packed S'/A' scaling, to one DIIS slot each (plus part, then minus part at
-// offset Np * ldp); padding columns of the slots are not written.
-template <int MODE, class Tr, bool SAVE = false>
+// ND >= 0 (mode 1): a DIIS sweep. Also writes the new amplitudes and the error e (new - old), both
+// in the packed S'/A' scaling, to one slot each (plus part, then minus part at offset Np * ldp;
+// padding columns of the slots are not written), and forms the inner products of e with up to ND
+// earlier errors over the full o x o x v x v tensors: a "+" entry of S' scaling carries weight
+// (2 - d_ij) / (2 - d_ab) (its full-tensor multiplicity over the square of its packing factor), a
+// "-" entry of A' scaling weight 1 (four entries, each half of A'). <e, e> is the residual^2.
+// PREC != PPL_FP64 (mode 1): also the new amplitudes as the operands of the next sweep's GEMMs.
+struct SweepArgs {
+  const double *e_occ, *e_vir, *vs, *va;
+  double *sp, *am, *partials;
+  void *op, *op_lo, *om, *om_lo;       // operand rows S', A'
+  double *tslot, *eslot;
+  const double* E;                     // error slots
+  int64_t slot_n;
+  DiisSet set;                         // the earlier errors
+  double* dots;                        // partials of their inner products
+};
+
+template <int MODE, class Tr, int PREC = PPL_FP64, int ND = -1>
 __global__ void __launch_bounds__(kReduceThreads)
-sweep_kernel(PairGeom g, const double* __restrict__ e_occ, const double* __restrict__ e_vir,
-             const double* __restrict__ vs, const double* __restrict__ va, const Tr* __restrict__ rp,
-             const Tr* __restrict__ rm, double* sp, double* am, double* partials,
-             double* __restrict__ tslot = nullptr, double* __restrict__ eslot = nullptr) {
-  double r2 = 0.0, en = 0.0, bad = 0.0;
+sweep_kernel(PairGeom g, SweepArgs w, SliceSum<Tr> rp, SliceSum<Tr> rm) {
+  constexpr bool SAVE = ND >= 0;
+  constexpr int NS = ND > 0 ? ND : 1;
+  double r2 = 0.0, en = 0.0, bad = 0.0, dot[NS];
+#pragma unroll
+  for (int i = 0; i < NS; ++i) dot[i] = 0.0;
   const int64_t st = (int64_t)gridDim.x * blockDim.x;
   const int64_t tid0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   // "+" part: weights (2 - d_ij)(2 - d_ab) turn packed sums into full-tensor sums
@@ -1128,28 +1158,33 @@ sweep_kernel(PairGeom g, const double* __restrict__ e_occ, const double* __restr
     if (p >= g.Pp) continue;
     const int ij = g.tab_op[q], ab = g.tab_vp[p];
     const bool dij = pair_first(ij) == pair_second(ij), dab = pair_first(ab) == pair_second(ab);
-    const double w = (dij ? 1.0 : 2.0) * (dab ? 1.0 : 2.0);
+    const double wf = (dij ? 1.0 : 2.0) * (dab ? 1.0 : 2.0);
     const double wab = dab ? 1.0 : 2.0;             // S' = wab * s
-    const double vsx = vs[x];
+    const double vsx = w.vs[x];
     double snew;
     if (MODE == 0) {
-      snew = vsx / denom(e_occ, e_vir, ij, ab);
-      sp[x] = wab * snew;
+      snew = vsx / denom(w.e_occ, w.e_vir, ij, ab);
+      w.sp[x] = wab * snew;
     } else if (MODE == 1) {
-      snew = (vsx + (double)rp[x]) / denom(e_occ, e_vir, ij, ab);
-      const double sold = sp[x] / wab;
+      snew = (vsx + (double)rp[x]) / denom(w.e_occ, w.e_vir, ij, ab);
+      const double sold = w.sp[x] / wab;
       const double ds = snew - sold;
-      r2 += w * ds * ds;
-      sp[x] = wab * snew;
-      if (SAVE) {
-        tslot[x] = wab * snew;
-        eslot[x] = wab * ds;
+      r2 += wf * ds * ds;
+      w.sp[x] = wab * snew;
+      if constexpr (PREC != PPL_FP64) Store<PREC>::put(w.op, w.op_lo, x, wab * snew);
+      if constexpr (SAVE) {
+        w.tslot[x] = wab * snew;
+        w.eslot[x] = wab * ds;
+        const double a = (dij ? 1.0 : 2.0) / wab * (wab * ds);
+#pragma unroll
+        for (int i = 0; i < ND; ++i)
+          if (i < w.set.n) dot[i] += a * w.E[w.set.id[i] * w.slot_n + x];
       }
     } else {
-      snew = sp[x] / wab;
+      snew = w.sp[x] / wab;
     }
     if (!isfinite(snew)) bad += 1.0;
-    en += w * vsx * snew;
+    en += wf * vsx * snew;
   }
   // "-" part: every packed (i<j, a<b) entry stands for 4 full-tensor entries
   for (int64_t x = tid0; x < totm; x += st) {
@@ -1157,41 +1192,34 @@ sweep_kernel(PairGeom g, const double* __restrict__ e_occ, const double* __restr
     row_col(x, g.ldm, narrow, q, p);
     if (p >= g.Pm) continue;
     const int ij = g.tab_om[q], ab = g.tab_vm[p];
-    const double vax = va[x];
+    const double vax = w.va[x];
     double anew;
     if (MODE == 0) {
-      anew = vax / denom(e_occ, e_vir, ij, ab);
-      am[x] = 2.0 * anew;
+      anew = vax / denom(w.e_occ, w.e_vir, ij, ab);
+      w.am[x] = 2.0 * anew;
     } else if (MODE == 1) {
-      anew = (vax + (double)rm[x]) / denom(e_occ, e_vir, ij, ab);
-      const double da = anew - 0.5 * am[x];
+      anew = (vax + (double)rm[x]) / denom(w.e_occ, w.e_vir, ij, ab);
+      const double da = anew - 0.5 * w.am[x];
       r2 += 4.0 * da * da;
-      am[x] = 2.0 * anew;
-      if (SAVE) {
-        tslot[totp + x] = 2.0 * anew;
-        eslot[totp + x] = 2.0 * da;
+      w.am[x] = 2.0 * anew;
+      if constexpr (PREC != PPL_FP64) Store<PREC>::put(w.om, w.om_lo, x, 2.0 * anew);
+      if constexpr (SAVE) {
+        w.tslot[totp + x] = 2.0 * anew;
+        w.eslot[totp + x] = 2.0 * da;
+        const double a = 2.0 * da;
+#pragma unroll
+        for (int i = 0; i < ND; ++i)
+          if (i < w.set.n) dot[i] += a * w.E[w.set.id[i] * w.slot_n + totp + x];
       }
     } else {
-      anew = 0.5 * am[x];
+      anew = 0.5 * w.am[x];
     }
     if (!isfinite(anew)) bad += 1.0;
     en += 12.0 * vax * anew;                        // E = sum V^S s + 3 sum V^A a (full tensor)
   }
   double vals[3] = {r2, en, bad};
-  block_reduce_store<3>(vals, partials);
-}
-
-template <int MODE, class Tr>
-static int sweep_launch(hipStream_t s, const PairGeom& g, const double* e_occ, const double* e_vir,
-                        const double* vs, const double* va, const void* rp, const void* rm,
-                        double* sp, double* am, double* partials, double* red_out) {
-  hipLaunchKernelGGL((sweep_kernel<MODE, Tr>), dim3(kReduceBlocks), dim3(kReduceThreads), 0, s, g,
-                     e_occ, e_vir, vs, va, (const Tr*)rp, (const Tr*)rm, sp, am, partials);
-  PPL_LAUNCH_CHECK();
-  hipLaunchKernelGGL(final_reduce_kernel, dim3(1), dim3(kReduceThreads), 0, s, partials,
-                     kReduceBlocks, red_out);
-  PPL_LAUNCH_CHECK();
-  return PPL_OK;
+  block_reduce_store<3>(vals, w.partials);
+  if constexpr (ND > 0) block_reduce_store<NS>(dot, w.dots);
 }
 
 static PairGeom geom(int o, int v, int64_t ldp, int64_t ldm, const int* tab_op, const int* tab_om,
@@ -1200,124 +1228,63 @@ static PairGeom geom(int o, int v, int64_t ldp, int64_t ldm, const int* tab_op, 
                   tab_op, tab_om, tab_vp, tab_vm};
 }
 
-int mp2_start(hipStream_t s, int o, int v, const double* e_occ, const double* e_vir, const double* vs,
-              const double* va, int64_t ldp, int64_t ldm, double* sp, double* am, const int* tab_op,
-              const int* tab_om, const int* tab_vp, const int* tab_vm, double* partials,
-              double* red_out) {
-  PairGeom g = geom(o, v, ldp, ldm, tab_op, tab_om, tab_vp, tab_vm);
-  return sweep_launch<0, double>(s, g, e_occ, e_vir, vs, va, nullptr, nullptr, sp, am, partials, red_out);
-}
-
-int update_sweep(hipStream_t s, int acc_prec, int o, int v, const double* e_occ, const double* e_vir,
-                 const double* vs, const double* va, const void* rp, const void* rm, int64_t ldp,
-                 int64_t ldm, double* sp, double* am, const int* tab_op, const int* tab_om,
-                 const int* tab_vp, const int* tab_vm, double* partials, double* red_out,
-                 double* tslot, double* eslot) {
-  PairGeom g = geom(o, v, ldp, ldm, tab_op, tab_om, tab_vp, tab_vm);
-  if (tslot && eslot) {
-    if (acc_prec == PPL_FP64)
-      hipLaunchKernelGGL((sweep_kernel<1, double, true>), dim3(kReduceBlocks), dim3(kReduceThreads), 0, s, g,
-                         e_occ, e_vir, vs, va, (const double*)rp, (const double*)rm, sp, am, partials, tslot,
-                         eslot);
-    else
-      hipLaunchKernelGGL((sweep_kernel<1, float, true>), dim3(kReduceBlocks), dim3(kReduceThreads), 0, s, g,
-                         e_occ, e_vir, vs, va, (const float*)rp, (const float*)rm, sp, am, partials, tslot,
-                         eslot);
-    PPL_LAUNCH_CHECK();
-    hipLaunchKernelGGL(final_reduce_kernel, dim3(1), dim3(kReduceThreads), 0, s, partials, kReduceBlocks,
-                       red_out);
-    PPL_LAUNCH_CHECK();
-    return PPL_OK;
-  }
-  if (acc_prec == PPL_FP64)
-    return sweep_launch<1, double>(s, g, e_occ, e_vir, vs, va, rp, rm, sp, am, partials, red_out);
-  return sweep_launch<1, float>(s, g, e_occ, e_vir, vs, va, rp, rm, sp, am, partials, red_out);
-}
-
-// ------------------------------------------------------------------ DIIS subspace
-// Inner products <e_new, e_i> over the full o x o x v x v tensors, from the packed
-// slots: a "+" entry of S' scaling carries weight (2 - d_ij) / (2 - d_ab) (its
-// full-tensor multiplicity over the square of its packing factor), a "-" entry of A'
-// scaling weight 1 (four entries, each half of A').
-__global__ void __launch_bounds__(kReduceThreads)
-diis_dots_kernel(PairGeom g, const double* __restrict__ E, int64_t slot_n, DiisSet set, int knew,
-                 double* partials) {
-  double acc[kDiisMax];
-#pragma unroll
-  for (int i = 0; i < kDiisMax; ++i) acc[i] = 0.0;
-  const int64_t st = (int64_t)gridDim.x * blockDim.x;
-  const int64_t tid0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  const double* en = E + knew * slot_n;
-  const int64_t totp = g.Np * g.ldp, totm = g.Nm * g.ldm;
-  const bool narrow = totp < 0x7fffffffLL && totm < 0x7fffffffLL;
-  for (int64_t x = tid0; x < totp; x += st) {
-    int64_t q, p;
-    row_col(x, g.ldp, narrow, q, p);
-    if (p >= g.Pp) continue;
-    const int ij = g.tab_op[q], ab = g.tab_vp[p];
-    const double w = (pair_first(ij) == pair_second(ij) ? 1.0 : 2.0) /
-                     (pair_first(ab) == pair_second(ab) ? 1.0 : 2.0);
-    const double a = w * en[x];
-#pragma unroll
-    for (int i = 0; i < kDiisMax; ++i)
-      if (i < set.n) acc[i] += a * E[set.id[i] * slot_n + x];
-  }
-  for (int64_t x = tid0; x < totm; x += st) {
-    int64_t q, p;
-    row_col(x, g.ldm, narrow, q, p);
-    if (p >= g.Pm) continue;
-    const double a = en[totp + x];
-#pragma unroll
-    for (int i = 0; i < kDiisMax; ++i)
-      if (i < set.n) acc[i] += a * E[set.id[i] * slot_n + totp + x];
-  }
-  __shared__ double sh[kDiisMax][kReduceThreads];
-  const int tid = threadIdx.x;
-#pragma unroll
-  for (int i = 0; i < kDiisMax; ++i) sh[i][tid] = acc[i];
-  __syncthreads();
-  for (int w = kReduceThreads / 2; w > 0; w >>= 1) {
-    if (tid < w)
-#pragma unroll
-      for (int i = 0; i < kDiisMax; ++i) sh[i][tid] += sh[i][tid + w];
-    __syncthreads();
-  }
-  if (tid < kDiisMax) partials[blockIdx.x * kDiisMax + tid] = sh[tid][0];
-}
-
-__global__ void diis_final_kernel(const double* __restrict__ partials, int nblocks, double* out) {
-  __shared__ double sh[kDiisMax][kReduceThreads];
-  const int tid = threadIdx.x;
-  double acc[kDiisMax];
-  for (int i = 0; i < kDiisMax; ++i) acc[i] = 0.0;
-  for (int b = tid; b < nblocks; b += kReduceThreads)
-    for (int i = 0; i < kDiisMax; ++i) acc[i] += partials[b * kDiisMax + i];
-  for (int i = 0; i < kDiisMax; ++i) sh[i][tid] = acc[i];
-  __syncthreads();
-  for (int w = kReduceThreads / 2; w > 0; w >>= 1) {
-    if (tid < w)
-      for (int i = 0; i < kDiisMax; ++i) sh[i][tid] += sh[i][tid + w];
-    __syncthreads();
-  }
-  if (tid < kDiisMax) out[tid] = sh[tid][0];
-}
-
-int diis_dots(hipStream_t s, int o, int v, int64_t ldp, int64_t ldm, const int* tab_op, const int* tab_om,
-              const int* tab_vp, const int* tab_vm, const double* E, int64_t slot_n, const DiisSet& set,
-              int knew, double* partials, double* out) {
-  if (set.n < 1 || set.n > kDiisMax) return fail(PPL_E_ARG, "DIIS set of %d vectors", set.n);
-  PairGeom g = geom(o, v, ldp, ldm, tab_op, tab_om, tab_vp, tab_vm);
-  hipLaunchKernelGGL(diis_dots_kernel, dim3(kReduceBlocks), dim3(kReduceThreads), 0, s, g, E, slot_n, set, knew,
-                     partials);
-  PPL_LAUNCH_CHECK();
-  hipLaunchKernelGGL(diis_final_kernel, dim3(1), dim3(kReduceThreads), 0, s, partials, kReduceBlocks, out);
+template <int MODE, class Tr, int PREC = PPL_FP64, int ND = -1>
+static int sweep_launch(hipStream_t s, const PairGeom& g, const SweepArgs& w, const Slices& rp, const Slices& rm) {
+  hipLaunchKernelGGL((sweep_kernel<MODE, Tr, PREC, ND>), dim3(kReduceBlocks), dim3(kReduceThreads), 0, s, g, w,
+                     slice_sum<Tr>(rp), slice_sum<Tr>(rm));
   PPL_LAUNCH_CHECK();
   return PPL_OK;
 }
 
-// S'/A' = sum_i c_i T_i over the slots of the set; padding columns set to zero.
-__global__ void diis_combine_kernel(PairGeom g, const double* __restrict__ T, int64_t slot_n, DiisSet set,
-                                    double* sp, double* am) {
+int mp2_start(hipStream_t s, int o, int v, const double* e_occ, const double* e_vir, const double* vs,
+              const double* va, int64_t ldp, int64_t ldm, double* sp, double* am, const int* tab_op,
+              const int* tab_om, const int* tab_vp, const int* tab_vm, double* partials,
+              double* red_out) {
+  const PairGeom g = geom(o, v, ldp, ldm, tab_op, tab_om, tab_vp, tab_vm);
+  SweepArgs w{e_occ, e_vir, vs, va, sp, am, partials};
+  PPL_TRY((sweep_launch<0, double>(s, g, w, Slices{}, Slices{})));
+  return final_reduce(s, partials, 3, nullptr, 0, red_out);
+}
+
+int update_sweep(hipStream_t s, int acc_prec, int o, int v, const double* e_occ, const double* e_vir,
+                 const double* vs, const double* va, const Slices& rp, const Slices& rm, int64_t ldp, int64_t ldm,
+                 double* sp, double* am, const int* tab_op, const int* tab_om, const int* tab_vp, const int* tab_vm,
+                 double* partials, double* red_out, const OperandRows& op, const DiisSlot& d) {
+  const PairGeom g = geom(o, v, ldp, ldm, tab_op, tab_om, tab_vp, tab_vm);
+  const SweepArgs w{e_occ, e_vir, vs,       va,       sp,       am,       partials, op.sp,   op.sp_lo, op.am,
+                    op.am_lo, d.t,   d.e,   d.E,      d.slot_n, d.others, d.partials};
+  if (!d.t) {
+    if (acc_prec == PPL_FP64) PPL_TRY((sweep_launch<1, double>(s, g, w, rp, rm)));
+    else if (op.prec == PPL_FP32) PPL_TRY((sweep_launch<1, float, PPL_FP32>(s, g, w, rp, rm)));
+    else if (op.prec == PPL_BF16X3) PPL_TRY((sweep_launch<1, float, PPL_BF16X3>(s, g, w, rp, rm)));
+    else if (op.prec == PPL_BF16X6) PPL_TRY((sweep_launch<1, float, PPL_BF16X6>(s, g, w, rp, rm)));
+    else PPL_TRY((sweep_launch<1, float>(s, g, w, rp, rm)));
+    return final_reduce(s, partials, 3, nullptr, 0, red_out);
+  }
+  const int n = d.others.n;
+  if (n < 0 || n >= kDiisMax) return fail(PPL_E_ARG, "DIIS set of %d vectors", n);
+  // the smallest count of inner products that covers the subspace (their sums live in registers)
+  if (acc_prec == PPL_FP64) {
+    if (n == 0) PPL_TRY((sweep_launch<1, double, PPL_FP64, 0>(s, g, w, rp, rm)));
+    else if (n <= 3) PPL_TRY((sweep_launch<1, double, PPL_FP64, 3>(s, g, w, rp, rm)));
+    else if (n <= 7) PPL_TRY((sweep_launch<1, double, PPL_FP64, 7>(s, g, w, rp, rm)));
+    else PPL_TRY((sweep_launch<1, double, PPL_FP64, 15>(s, g, w, rp, rm)));
+  } else {
+    if (n == 0) PPL_TRY((sweep_launch<1, float, PPL_FP64, 0>(s, g, w, rp, rm)));
+    else if (n <= 3) PPL_TRY((sweep_launch<1, float, PPL_FP64, 3>(s, g, w, rp, rm)));
+    else if (n <= 7) PPL_TRY((sweep_launch<1, float, PPL_FP64, 7>(s, g, w, rp, rm)));
+    else PPL_TRY((sweep_launch<1, float, PPL_FP64, 15>(s, g, w, rp, rm)));
+  }
+  return final_reduce(s, partials, 3, d.partials, n, red_out);
+}
+
+// ------------------------------------------------------------------ DIIS subspace
+// S'/A' = sum_i c_i T_i over the slots of the set; padding columns set to zero. PREC != PPL_FP64:
+// also as the operands of the next sweep's GEMMs.
+template <int PREC>
+__global__ void __launch_bounds__(256)
+diis_combine_kernel(PairGeom g, const double* __restrict__ T, int64_t slot_n, DiisSet set, double* sp, double* am,
+                    OperandRows op) {
   const int64_t st = (int64_t)gridDim.x * blockDim.x;
   const int64_t tid0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   const int64_t totp = g.Np * g.ldp, totm = g.Nm * g.ldm;
@@ -1329,6 +1296,7 @@ __global__ void diis_combine_kernel(PairGeom g, const double* __restrict__ T, in
     if (p < g.Pp)
       for (int i = 0; i < set.n; ++i) y += set.c[i] * T[set.id[i] * slot_n + x];
     sp[x] = y;
+    if constexpr (PREC != PPL_FP64) Store<PREC>::put(op.sp, op.sp_lo, x, y);
   }
   for (int64_t x = tid0; x < totm; x += st) {
     int64_t q, p;
@@ -1337,15 +1305,23 @@ __global__ void diis_combine_kernel(PairGeom g, const double* __restrict__ T, in
     if (p < g.Pm)
       for (int i = 0; i < set.n; ++i) y += set.c[i] * T[set.id[i] * slot_n + totp + x];
     am[x] = y;
+    if constexpr (PREC != PPL_FP64) Store<PREC>::put(op.am, op.am_lo, x, y);
   }
 }
 
 int diis_combine(hipStream_t s, int o, int v, int64_t ldp, int64_t ldm, const double* T, int64_t slot_n,
-                 const DiisSet& set, double* sp, double* am) {
+                 const DiisSet& set, double* sp, double* am, const OperandRows& op) {
   if (set.n < 1 || set.n > kDiisMax) return fail(PPL_E_ARG, "DIIS set of %d vectors", set.n);
   PairGeom g = geom(o, v, ldp, ldm, nullptr, nullptr, nullptr, nullptr);
-  const int64_t total = std::max(g.Np * ldp, g.Nm * ldm);
-  hipLaunchKernelGGL(diis_combine_kernel, dim3(grid_for(total, 256)), dim3(256), 0, s, g, T, slot_n, set, sp, am);
+  const dim3 grid(grid_for(std::max(g.Np * ldp, g.Nm * ldm), 256));
+  if (op.prec == PPL_FP32)
+    hipLaunchKernelGGL(diis_combine_kernel<PPL_FP32>, grid, dim3(256), 0, s, g, T, slot_n, set, sp, am, op);
+  else if (op.prec == PPL_BF16X3)
+    hipLaunchKernelGGL(diis_combine_kernel<PPL_BF16X3>, grid, dim3(256), 0, s, g, T, slot_n, set, sp, am, op);
+  else if (op.prec == PPL_BF16X6)
+    hipLaunchKernelGGL(diis_combine_kernel<PPL_BF16X6>, grid, dim3(256), 0, s, g, T, slot_n, set, sp, am, op);
+  else
+    hipLaunchKernelGGL(diis_combine_kernel<PPL_FP64>, grid, dim3(256), 0, s, g, T, slot_n, set, sp, am, op);
   PPL_LAUNCH_CHECK();
   return PPL_OK;
 }
@@ -1354,8 +1330,9 @@ int energy_only(hipStream_t s, int o, int v, const double* vs, const double* va,
                 const double* am, int64_t ldp, int64_t ldm, const int* tab_op, const int* tab_om,
                 const int* tab_vp, const int* tab_vm, double* partials, double* red_out) {
   PairGeom g = geom(o, v, ldp, ldm, tab_op, tab_om, tab_vp, tab_vm);
-  return sweep_launch<2, double>(s, g, nullptr, nullptr, vs, va, nullptr, nullptr, (double*)sp,
-                                 (double*)am, partials, red_out);
+  SweepArgs w{nullptr, nullptr, vs, va, (double*)sp, (double*)am, partials};
+  PPL_TRY((sweep_launch<2, double>(s, g, w, Slices{}, Slices{})));
+  return final_reduce(s, partials, 3, nullptr, 0, red_out);
 }
 
 // Sums of (L^P_ac - L^P_ca)^2 and (L^P_ac)^2 + (L^P_ca)^2 over the virtual block, a < c
@@ -1403,9 +1380,7 @@ asym_kernel(const double* __restrict__ L, int n, int o, int v, int naux, double*
 int asymmetry_vv(hipStream_t s, const double* L, int o, int v, int naux, double* partials, double* red_out) {
   hipLaunchKernelGGL(asym_kernel, dim3(kReduceBlocks), dim3(kReduceThreads), 0, s, L, o + v, o, v, naux, partials);
   PPL_LAUNCH_CHECK();
-  hipLaunchKernelGGL(final_reduce_kernel, dim3(1), dim3(kReduceThreads), 0, s, partials, kReduceBlocks, red_out);
-  PPL_LAUNCH_CHECK();
-  return PPL_OK;
+  return final_reduce(s, partials, 3, nullptr, 0, red_out);
 }
 
 __global__ void __launch_bounds__(kReduceThreads)
@@ -1421,10 +1396,7 @@ nonfinite_kernel(const double* __restrict__ x, int64_t n, double* partials) {
 int count_nonfinite(hipStream_t s, const double* x, int64_t n, double* partials, double* red_out) {
   hipLaunchKernelGGL(nonfinite_kernel, dim3(kReduceBlocks), dim3(kReduceThreads), 0, s, x, n, partials);
   PPL_LAUNCH_CHECK();
-  hipLaunchKernelGGL(final_reduce_kernel, dim3(1), dim3(kReduceThreads), 0, s, partials,
-                     kReduceBlocks, red_out);
-  PPL_LAUNCH_CHECK();
-  return PPL_OK;
+  return final_reduce(s, partials, 3, nullptr, 0, red_out);
 }
 
 

@@ -158,6 +158,7 @@ struct ppl_plan_s {
   std::vector<int64_t> tiles_n;        // tiles in each batch's list, [set][batch]
   int tile_sets = 1;                   // 2 when the FP64 copy builds on a tile of its own
   const double* L_last = nullptr;
+  double* host_red = nullptr;          // mapped host memory for the iteration's sums (kHostRed doubles)
   bool setup_done = false;
   // kernel timing
   struct ProfRec {
@@ -350,28 +351,35 @@ int mp2_start(hipStream_t s, int o, int v, const double* e_occ, const double* e_
               double* red_out);
 // Jacobi update in packed space with FP64 residual^2 / energy partial sums
 // (red_out[0] = r^2, red_out[1] = E, red_out[2] = non-finite count)
-// tslot / eslot (both or neither): DIIS slots that also receive the new amplitudes and
-// the error new - old in the packed scaling (padding columns untouched)
-int update_sweep(hipStream_t s, int acc_prec, int o, int v, const double* e_occ, const double* e_vir,
-                 const double* vs, const double* va, const void* rp, const void* rm, int64_t ldp,
-                 int64_t ldm, double* sp, double* am, const int* tab_op, const int* tab_om,
-                 const int* tab_vp, const int* tab_vm, double* partials, double* red_out,
-                 double* tslot = nullptr, double* eslot = nullptr);
-// DIIS: the vectors of a subspace (slot ids) and their extrapolation coefficients
+// rp, rm: results or their K slices. op (prec != PPL_FP64): operand rows that also receive the new
+// amplitudes. d (t set): a DIIS sweep, whose new amplitudes and error new - old also go to the
+// slots t and e in the packed scaling (padding columns untouched); then red_out[3 + i] =
+// <e, E_others.id[i]> over the full tensors (<e, e> is r^2). red_out may be mapped host memory.
 constexpr int kDiisMax = 16;
 static_assert(kDiisMax == PPL_DIIS_MAX, "one DIIS capacity limit");
-struct DiisSet {
+struct DiisSet {           // slot ids of a subspace and their extrapolation coefficients
   int n;
   int id[kDiisMax];
   double c[kDiisMax];
 };
-// out[i] = <E_knew, E_id[i]> over the full tensors, i < set.n (partials: kReduceBlocks x kDiisMax)
-int diis_dots(hipStream_t s, int o, int v, int64_t ldp, int64_t ldm, const int* tab_op, const int* tab_om,
-              const int* tab_vp, const int* tab_vm, const double* E, int64_t slot_n, const DiisSet& set,
-              int knew, double* partials, double* out);
-// S'/A' = sum_i c_i T_id[i], zero padding
+struct DiisSlot {
+  double *t = nullptr, *e = nullptr;
+  const double* E = nullptr;       // error slots, slot_n doubles each
+  int64_t slot_n = 0;
+  DiisSet others{};
+  double* partials = nullptr;      // kDiisMax x kReduceBlocks
+};
+struct OperandRows {       // S' and A' rows of a low-precision operand set
+  int prec = PPL_FP64;
+  void *sp = nullptr, *sp_lo = nullptr, *am = nullptr, *am_lo = nullptr;
+};
+int update_sweep(hipStream_t s, int acc_prec, int o, int v, const double* e_occ, const double* e_vir,
+                 const double* vs, const double* va, const Slices& rp, const Slices& rm, int64_t ldp, int64_t ldm,
+                 double* sp, double* am, const int* tab_op, const int* tab_om, const int* tab_vp, const int* tab_vm,
+                 double* partials, double* red_out, const OperandRows& op, const DiisSlot& d);
+// S'/A' = sum_i c_i T_id[i], zero padding; also rounded into op (prec != PPL_FP64)
 int diis_combine(hipStream_t s, int o, int v, int64_t ldp, int64_t ldm, const double* T, int64_t slot_n,
-                 const DiisSet& set, double* sp, double* am);
+                 const DiisSet& set, double* sp, double* am, const OperandRows& op);
 // energy of the current packed amplitudes (red_out[1] = E)
 int energy_only(hipStream_t s, int o, int v, const double* vs, const double* va, const double* sp,
                 const double* am, int64_t ldp, int64_t ldm, const int* tab_op, const int* tab_om,
@@ -413,6 +421,7 @@ int mlp_infer_launch(hipStream_t s, const float* prm, int o, int v, const double
 int sumsq_launch(hipStream_t s, const double* x, int64_t n, double* partials, double* red_out);
 
 constexpr int kReduceBlocks = 1024;
+constexpr int kHostRed = 4 + kDiisMax;
 constexpr int kReduceThreads = 256;
 
 }  // namespace ppl
