@@ -429,7 +429,7 @@ static int build_one(ppl_plan_t p, OperandSet& s, const double* L, int bi, bool 
       return fail(PPL_E_STATE, "build step %d exceeds the V+- rows of the plan", bi);
   }
   if (p->sym_build && p->resident) {
-    // natural GEMM layout, then one packing pass: upper triangles (FP64, FP32) or whole rows
+    // natural GEMM layout, then upper triangles (FP64, FP32), completed to whole rows in BF16
     {
       ProfScope ps(p, PPL_PROF_BUILD_GEMM, build_flops(p, b.a0, b.a1));
       PPL_TRY(gemm_build_natural(st, s.prec, tile, p->v, b.a0, b.a1, p->ldx, at<void>(p, s.xt),
@@ -438,12 +438,13 @@ static int build_one(ppl_plan_t p, OperandSet& s, const double* L, int bi, bool 
     }
     ProfScope ps(p, PPL_PROF_BUILD_PACK, 0.0);
     const int64_t W = p->v - b.a0;
-    if (s.tri)
-      return pack_vpm_tri(st, s.prec, p->v, b.a0, b.a1, at<void>(p, p->g), W * (W + 1) / 2,
-                          at<int64_t>(p, p->cube_off), at<void>(p, s.vp), p->ldp, at<void>(p, s.vm), p->ldm);
-    return pack_vpm_cubes(st, s.prec, p->v, b.a0, b.a1, at<void>(p, p->g), W * (W + 1) / 2,
-                          at<int64_t>(p, p->cube_off), at<void>(p, s.vp), s.vp_lo.bytes ? at<void>(p, s.vp_lo) : nullptr,
-                          p->ldp, at<void>(p, s.vm), s.vm_lo.bytes ? at<void>(p, s.vm_lo) : nullptr, p->ldm);
+    void* vp_lo = s.vp_lo.bytes ? at<void>(p, s.vp_lo) : nullptr;
+    void* vm_lo = s.vm_lo.bytes ? at<void>(p, s.vm_lo) : nullptr;
+    PPL_TRY(pack_vpm_tri(st, s.prec, p->v, b.a0, b.a1, at<void>(p, p->g), W * (W + 1) / 2, at<int64_t>(p, p->cube_off),
+                         at<void>(p, s.vp), vp_lo, p->ldp, at<void>(p, s.vm), vm_lo, p->ldm));
+    if (s.tri) return PPL_OK;
+    PPL_TRY(mirror_rows(st, s.prec, at<void>(p, s.vp), vp_lo, p->Pp, p->ldp, b.p0, b.p1));
+    return mirror_rows(st, s.prec, at<void>(p, s.vm), vm_lo, p->Pm, p->ldm, b.q0, b.q1);
   }
   if (p->sym_build) {
     {

@@ -342,143 +342,31 @@ int pack_vpm_sym(hipStream_t s, int prec, int v, int a0, int a1, const void* G, 
   return PPL_OK;
 }
 
-// threads of one cube-packing workgroup (divides the 4096 elements of a cube)
-#ifndef PPL_PACK_THREADS
-#define PPL_PACK_THREADS 256
-#endif
-constexpr int kPackThreads = PPL_PACK_THREADS;
-static_assert(kCube * kCube * kCube % PPL_PACK_THREADS == 0, "threads must divide a cube");
+constexpr int kPackThreads = 256;
 static_assert(kCube == 16, "the cube packing splits an element index into 4-bit fields");
 
-// Whole V+- rows of a resident BF16 build step from the natural build output T, with no separate
-// mirror pass: T[(pair(a, r) - pr0) * ldt + pair(x, y) - pr0] = (ar|xy) for the step's virtuals
-// a in [a0, a1), r >= a and a <= x <= y (pr0 = pair(a0, a0)); T is symmetric in (x, y) since the
-// Cholesky vectors are. For the entry of row (ab), column (cd) with (cd) >= (ab) in packed order
-//   V+[ab][cd] = ((ac|bd) + (ad|bc)) / 2,   V-[ab][cd] = ((ac|bd) - (ad|bc)) / 2  (a < b, c < d),
-// and the same value goes to the mirror entry [cd][ab], so every entry of V+- is written once
-// (pack_cubes.h). One workgroup per cube of 16 x 16 x 16 indices (b, c, d): it stages
-// (ac|bd) as s1[c][b][d] and (ad|bc) as s2[d][b][c] (each read from T along its contiguous
-// index), then writes the rows (ab) along d and the mirror rows (cd) along b. The cube with
-// ci == di == 0 also zeroes the padding columns of the rows (ab).
-template <class Tg, int PREC>
-__global__ void __launch_bounds__(kPackThreads)
-pack_vpm_cubes_kernel(int v, int a0, int a1, const Tg* __restrict__ T, int64_t ldt, const int64_t* __restrict__ off,
-                      int64_t g0, int64_t ncubes, void* vp, void* vp_lo, int64_t ldp, void* vm, void* vm_lo,
-                      int64_t ldm, int64_t Pp, int64_t Pm) {
-  constexpr int C = kCube, CP = kCube + 1;
-  __shared__ Tg s1[C][CP][CP], s2[C][CP][CP];
-  const int64_t g = g0 + cube_of_slot(blockIdx.x, ncubes);
-  const int a = cube_virtual(off, a0, a1, g);
-  const int nt = cube_blocks(v, a);
-  int bi, ci, di;
-  cube_decode(g - off[a], nt, bi, ci, di);
-  const int b0 = a + C * bi, c0 = a + C * ci, d0 = a + C * di;
-  const int64_t pr0 = pair_plus(a0, a0, v);
-  const int tid = threadIdx.x;
-  // s[rl][bl][yl] = (a r | b y) for r = r0 + rl, b = b0 + bl, y = y0 + yl (zero outside v);
-  // element e = tid + kPackThreads k of the cube, read along its contiguous index. All reads of a
-  // thread are issued before its first LDS store, so their latencies overlap.
-  constexpr int K = C * C * C / kPackThreads;
-  auto slot = [&](int k, bool bfast, int& rl, int& bl, int& yl) __attribute__((always_inline)) {
-    const int e = tid + kPackThreads * k, m = (e >> 4) & 15, f = e & 15;
-    rl = e >> 8;
-    bl = bfast ? f : m;
-    yl = bfast ? m : f;
-  };
-  auto fetch = [&](Tg (&x)[K], int r0, int y0) __attribute__((always_inline)) {
-    const bool bfast = b0 > y0;              // pairs (y, b): contiguous along b
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-      int rl, bl, yl;
-      slot(k, bfast, rl, bl, yl);
-      const int r = r0 + rl, b = b0 + bl, y = y0 + yl;
-      const int lo = b < y ? b : y, hi = b < y ? y : b;
-      x[k] = (r < v && b < v && y < v) ? T[(pair_plus(a, r, v) - pr0) * ldt + (pair_plus(lo, hi, v) - pr0)] : Tg(0);
-    }
-  };
-  auto keep = [&](Tg (*s)[CP][CP], const Tg (&x)[K], int y0) __attribute__((always_inline)) {
-    const bool bfast = b0 > y0;
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-      int rl, bl, yl;
-      slot(k, bfast, rl, bl, yl);
-      s[rl][bl][yl] = x[k];
-    }
-  };
-  Tg x1[K], x2[K];
-  fetch(x1, c0, d0);
-  if (ci != di) fetch(x2, d0, c0);
-  keep(s1, x1, d0);
-  if (ci != di) keep(s2, x2, c0);
-  __syncthreads();
-  const Tg (*t2)[CP][CP] = ci != di ? s2 : s1;   // (ad|bc) = t2[d][b][c]
-  // rows (ab), along d
-  for (int e = tid; e < C * C * C; e += kPackThreads) {
-    const int bl = e >> 8, cl = (e >> 4) & 15, dl = e & 15;
-    const int b = b0 + bl, c = c0 + cl, d = d0 + dl;
-    if (b >= v || d >= v || c > d || (c == a && d < b)) continue;
-    const double gcd = (double)s1[cl][bl][dl], gdc = (double)t2[dl][bl][cl];
-    Store<PREC>::put(vp, vp_lo, pair_plus(a, b, v) * ldp + pair_plus(c, d, v), 0.5 * (gcd + gdc));
-    if (a < b && c < d) Store<PREC>::put(vm, vm_lo, pair_minus(a, b, v) * ldm + pair_minus(c, d, v), 0.5 * (gcd - gdc));
-  }
-  // mirror rows (cd), along b
-  for (int e = tid; e < C * C * C; e += kPackThreads) {
-    const int cl = e >> 8, dl = (e >> 4) & 15, bl = e & 15;
-    const int b = b0 + bl, c = c0 + cl, d = d0 + dl;
-    if (b >= v || d >= v || c > d || (c == a && d <= b)) continue;
-    const double gcd = (double)s1[cl][bl][dl], gdc = (double)t2[dl][bl][cl];
-    Store<PREC>::put(vp, vp_lo, pair_plus(c, d, v) * ldp + pair_plus(a, b, v), 0.5 * (gcd + gdc));
-    if (a < b && c < d) Store<PREC>::put(vm, vm_lo, pair_minus(c, d, v) * ldm + pair_minus(a, b, v), 0.5 * (gcd - gdc));
-  }
-  if (ci == 0 && di == 0) {
-    const int64_t padp = ldp - Pp, padm = ldm - Pm;
-    for (int e = tid; e < C * padp; e += kPackThreads) {
-      const int b = b0 + (int)(e / padp);
-      if (b < v) Store<PREC>::put(vp, vp_lo, pair_plus(a, b, v) * ldp + Pp + e % padp, 0.0);
-    }
-    for (int e = tid; e < C * padm; e += kPackThreads) {
-      const int b = b0 + (int)(e / padm);
-      if (b < v && a < b) Store<PREC>::put(vm, vm_lo, pair_minus(a, b, v) * ldm + Pm + e % padm, 0.0);
-    }
-  }
-}
-
-int pack_vpm_cubes(hipStream_t s, int prec, int v, int a0, int a1, const void* T, int64_t ldt, const int64_t* off,
-                   void* vp, void* vp_lo, int64_t ldp, void* vm, void* vm_lo, int64_t ldm) {
-  int64_t g0 = 0, n = 0;
-  for (int a = 0; a < a1; ++a) (a < a0 ? g0 : n) += cubes_of(v, a);
-  if (n <= 0) return PPL_OK;
-  if (n > 0x7fffffffLL) return fail(PPL_E_ARG, "pack_vpm_cubes: %lld cubes", (long long)n);
-  const int64_t Pp = npairs_plus(v), Pm = npairs_minus(v);
-  const dim3 grid((unsigned)n);
-  if (prec == PPL_BF16X3)
-    hipLaunchKernelGGL((pack_vpm_cubes_kernel<float, PPL_BF16X3>), grid, dim3(kPackThreads), 0, s, v, a0, a1,
-                       (const float*)T, ldt, off, g0, n, vp, vp_lo, ldp, vm, vm_lo, ldm, Pp, Pm);
-  else if (prec == PPL_BF16X6)
-    hipLaunchKernelGGL((pack_vpm_cubes_kernel<float, PPL_BF16X6>), grid, dim3(kPackThreads), 0, s, v, a0, a1,
-                       (const float*)T, ldt, off, g0, n, vp, vp_lo, ldp, vm, vm_lo, ldm, Pp, Pm);
-  else
-    return fail(PPL_E_ARG, "pack_vpm_cubes: unknown precision %d", prec);
-  PPL_LAUNCH_CHECK();
-  return PPL_OK;
-}
-
-// The same rows for the resident FP64 and FP32 layout (kTriBlock): every entry of row (ab) with
-// (cd) >= (ab), and below the diagonal only the mirror entries inside a diagonal block. One
-// workgroup per cube of 16 x 16 x 16 indices (b, c, d), thread (c, d), b unrolled, so that the
-// rows are written along d. (ac|bd) is read in that shape where b <= d (contiguous along d);
-// (ad|bc) is contiguous along c (b <= c) or b and goes through one LDS array s[b][d][c], and
-// where b > d so does (ac|bd), contiguous along b, in a round of its own.
+// Rows of V+- of a resident build step from the natural build output T: T[(pair(a, r) - pr0) *
+// ldt + pair(x, y) - pr0] = (ar|xy) for the step's virtuals a in [a0, a1), r >= a and
+// a <= x <= y (pr0 = pair(a0, a0)); T is symmetric in (x, y) since the Cholesky vectors are. For
+// row (ab) and column (cd) >= (ab) in packed order
+//   V+[ab][cd] = ((ac|bd) + (ad|bc)) / 2,   V-[ab][cd] = ((ac|bd) - (ad|bc)) / 2  (a < b, c < d).
+// Entries below the diagonal: FP64 and FP32 get those inside a diagonal block (kTriBlock) here and
+// need no others; BF16 gets them all from mirror_rows. One workgroup per cube of 16 x 16 x 16
+// indices (b, c, d), thread (c, d), b unrolled, so that the rows are written along d. (ac|bd) is
+// read in that shape where b <= d (contiguous along d); (ad|bc) is contiguous along c (b <= c) or
+// b and goes through one LDS array s[b][d][c], and where b > d so does (ac|bd), contiguous along
+// b, in a round of its own. The cubes with ci == di == 0 also zero the rows' padding.
 // Bound by the writes of its 16 x 16 row segments: the lines that segments share are merged in
 // L2 only while few are open, so spare LDS (kTriSpareLds) holds it to three workgroups per CU
-// (FP64; four in FP32): 1.73 ms against 1.96 with all that fit and 2.01 with two, at v = 200 in
-// one step (3.2 GB written, 1.6 read); FP32 at v = 151 0.36 ms against 0.40. Writing the mirror
-// half as well (pack_vpm_cubes_kernel) took 3.35 ms and 0.58 ms.
+// (FP64; four in FP32, three in BF16): 1.73 ms against 1.96 with all that fit and 2.01 with two, at
+// v = 200 in one step (3.2 GB written, 1.6 read); FP32 at v = 151 0.36 ms against 0.40; BF16x6 at
+// v = 137 0.353 against 0.435 with all and 0.391 with four. Writing every mirror entry here, along
+// b, took 3.35 ms (FP64), 0.58 ms (FP32) and 0.845 ms (BF16x6; 0.62 with mirror_rows).
 template <class Tg, int PREC>
 __global__ void __launch_bounds__(kPackThreads)
 pack_vpm_tri_kernel(int v, int a0, int a1, const Tg* __restrict__ T, int64_t ldt, const int64_t* __restrict__ off,
-                    int64_t g0, int64_t ncubes, void* vp, int64_t ldp, void* vm, int64_t ldm, int64_t Pp,
-                    int64_t Pm) {
+                    int64_t g0, int64_t ncubes, void* vp, void* vp_lo, int64_t ldp, void* vm, void* vm_lo,
+                    int64_t ldm, int64_t Pp, int64_t Pm) {
   constexpr int C = kCube, LD = kCube + 1, LB = kCube * LD + 1;   // both strides odd: no bank conflicts
   __shared__ Tg s[C * LB];
   const int64_t g = g0 + cube_of_slot(blockIdx.x, ncubes);
@@ -534,19 +422,20 @@ pack_vpm_tri_kernel(int v, int a0, int a1, const Tg* __restrict__ T, int64_t ldt
     const int64_t rm = pair_minus(a, b0, v), cm = pair_minus(c, d, v);
     // some mirror entry of the cube lies in a diagonal block (the same for every thread)
     const int e0 = d0 > c0 ? d0 : c0, bl = b0 + C < v ? b0 + C - 1 : v - 1;
-    const bool near = pair_plus(c0, e0, v) / kTriBlock <= pair_plus(a, bl, v) / kTriBlock ||
-                      pair_minus(c0, e0 > c0 ? e0 : c0 + 1, v) / kTriBlock <= pair_minus(a, bl, v) / kTriBlock;
+    const bool near = (PREC == PPL_FP64 || PREC == PPL_FP32) &&
+                      (pair_plus(c0, e0, v) / kTriBlock <= pair_plus(a, bl, v) / kTriBlock ||
+                       pair_minus(c0, e0 > c0 ? e0 : c0 + 1, v) / kTriBlock <= pair_minus(a, bl, v) / kTriBlock);
 #pragma unroll
     for (int k = 0; k < C; ++k) {
       if (k < kmax) {
         const double x = (double)gcd[k], y = (double)gdc[k];
         const bool minus = c < d && (k > 0 || b0 > a);
-        Store<PREC>::put(vp, nullptr, (rp + k) * ldp + cp, 0.5 * (x + y));
-        if (minus) Store<PREC>::put(vm, nullptr, (rm + k) * ldm + cm, 0.5 * (x - y));
+        Store<PREC>::put(vp, vp_lo, (rp + k) * ldp + cp, 0.5 * (x + y));
+        if (minus) Store<PREC>::put(vm, vm_lo, (rm + k) * ldm + cm, 0.5 * (x - y));
         if (near) {
-          if ((rp + k) / kTriBlock == cp / kTriBlock) Store<PREC>::put(vp, nullptr, cp * ldp + rp + k, 0.5 * (x + y));
+          if ((rp + k) / kTriBlock == cp / kTriBlock) Store<PREC>::put(vp, vp_lo, cp * ldp + rp + k, 0.5 * (x + y));
           if (minus && (rm + k) / kTriBlock == cm / kTriBlock)
-            Store<PREC>::put(vm, nullptr, cm * ldm + rm + k, 0.5 * (x - y));
+            Store<PREC>::put(vm, vm_lo, cm * ldm + rm + k, 0.5 * (x - y));
         }
       }
     }
@@ -555,33 +444,104 @@ pack_vpm_tri_kernel(int v, int a0, int a1, const Tg* __restrict__ T, int64_t ldt
     const int64_t padp = ldp - Pp, padm = ldm - Pm;
     for (int e = threadIdx.x; e < C * padp; e += kPackThreads) {
       const int b = b0 + (int)(e / padp);
-      if (b < v) Store<PREC>::put(vp, nullptr, pair_plus(a, b, v) * ldp + Pp + e % padp, 0.0);
+      if (b < v) Store<PREC>::put(vp, vp_lo, pair_plus(a, b, v) * ldp + Pp + e % padp, 0.0);
     }
     for (int e = threadIdx.x; e < C * padm; e += kPackThreads) {
       const int b = b0 + (int)(e / padm);
-      if (b < v && a < b) Store<PREC>::put(vm, nullptr, pair_minus(a, b, v) * ldm + Pm + e % padm, 0.0);
+      if (b < v && a < b) Store<PREC>::put(vm, vm_lo, pair_minus(a, b, v) * ldm + Pm + e % padm, 0.0);
     }
   }
 }
 
-constexpr unsigned kTriSpareLds = 20000;
+template <class Tg, int PREC>
+static int launch_vpm_tri(hipStream_t s, int v, int a0, int a1, const void* T, int64_t ldt, const int64_t* off,
+                          int64_t g0, int64_t n, void* vp, void* vp_lo, int64_t ldp, void* vm, void* vm_lo,
+                          int64_t ldm) {
+  constexpr unsigned kTriSpareLds = PREC == PPL_FP64 || PREC == PPL_FP32 ? 20000 : 36000;
+  hipLaunchKernelGGL((pack_vpm_tri_kernel<Tg, PREC>), dim3((unsigned)n), dim3(kPackThreads), kTriSpareLds, s, v, a0,
+                     a1, (const Tg*)T, ldt, off, g0, n, vp, vp_lo, ldp, vm, vm_lo, ldm, npairs_plus(v),
+                     npairs_minus(v));
+  PPL_LAUNCH_CHECK();
+  return PPL_OK;
+}
 
 int pack_vpm_tri(hipStream_t s, int prec, int v, int a0, int a1, const void* T, int64_t ldt, const int64_t* off,
-                 void* vp, int64_t ldp, void* vm, int64_t ldm) {
+                 void* vp, void* vp_lo, int64_t ldp, void* vm, void* vm_lo, int64_t ldm) {
   int64_t g0 = 0, n = 0;
   for (int a = 0; a < a1; ++a) (a < a0 ? g0 : n) += cubes_of(v, a);
   if (n <= 0) return PPL_OK;
   if (n > 0x7fffffffLL) return fail(PPL_E_ARG, "pack_vpm_tri: %lld cubes", (long long)n);
-  const int64_t Pp = npairs_plus(v), Pm = npairs_minus(v);
-  const dim3 grid((unsigned)n);
-  if (prec == PPL_FP64)
-    hipLaunchKernelGGL((pack_vpm_tri_kernel<double, PPL_FP64>), grid, dim3(kPackThreads), kTriSpareLds, s, v, a0, a1,
-                       (const double*)T, ldt, off, g0, n, vp, ldp, vm, ldm, Pp, Pm);
-  else if (prec == PPL_FP32)
-    hipLaunchKernelGGL((pack_vpm_tri_kernel<float, PPL_FP32>), grid, dim3(kPackThreads), kTriSpareLds, s, v, a0, a1,
-                       (const float*)T, ldt, off, g0, n, vp, ldp, vm, ldm, Pp, Pm);
-  else
-    return fail(PPL_E_ARG, "pack_vpm_tri: precision %d is not stored as a triangle", prec);
+  switch (prec) {
+    case PPL_FP64:
+      return launch_vpm_tri<double, PPL_FP64>(s, v, a0, a1, T, ldt, off, g0, n, vp, nullptr, ldp, vm, nullptr, ldm);
+    case PPL_FP32:
+      return launch_vpm_tri<float, PPL_FP32>(s, v, a0, a1, T, ldt, off, g0, n, vp, nullptr, ldp, vm, nullptr, ldm);
+    case PPL_BF16X3:
+      return launch_vpm_tri<float, PPL_BF16X3>(s, v, a0, a1, T, ldt, off, g0, n, vp, vp_lo, ldp, vm, vm_lo, ldm);
+    case PPL_BF16X6:
+      return launch_vpm_tri<float, PPL_BF16X6>(s, v, a0, a1, T, ldt, off, g0, n, vp, vp_lo, ldp, vm, vm_lo, ldm);
+  }
+  return fail(PPL_E_ARG, "pack_vpm_tri: unknown precision %d", prec);
+}
+
+// V[r][q] = V[q][r] for q in [q0, q1), q < r < n: the entries below the diagonal of a build step's
+// rows, for each bf16 plane (planes lie equally far apart: hi, lo and, in BF16x6, 2 lo - hi).
+// One 64 x 64 block pair (I >= J) and plane per workgroup, through LDS: rows J, columns I are read
+// and rows I, columns J written along contiguous rows, as 16-byte vectors where the block is whole
+// (rows of V are 128-byte multiples, so blocks start aligned). Bound by memory: 0.27 ms at
+// v = 137 for three planes (0.53 GB each way), 3.9 TB/s.
+__global__ void __launch_bounds__(256)
+mirror_rows_kernel(uint16_t* hi, uint16_t* lo, int64_t n, int64_t ld, int64_t q0, int64_t q1, int64_t t0) {
+  __shared__ uint16_t sh[64][65];
+  // blocks counted from the last: t = j (j + 1) / 2 + i, j = T - 1 - J, i = T - 1 - I
+  const int64_t T = (n + 63) / 64, t = t0 + blockIdx.x;
+  int64_t j = (int64_t)((sqrt(8.0 * (double)t + 1.0) - 1.0) * 0.5);
+  while (j * (j + 1) / 2 > t) --j;
+  while ((j + 1) * (j + 2) / 2 <= t) ++j;
+  const int64_t r0 = (T - 1 - (t - j * (j + 1) / 2)) * 64, c0 = (T - 1 - j) * 64;
+  uint16_t* V = hi + (int64_t)blockIdx.y * (lo - hi);
+  const int tid = threadIdx.x;
+  if (r0 > c0 && r0 + 64 <= n && c0 >= q0 && c0 + 64 <= q1) {
+    union Vec { uint4 u; uint16_t e[8]; };
+    for (int x = tid; x < 64 * 8; x += 256) {
+      const int ql = x / 8, w = x % 8;
+      Vec y;
+      y.u = *reinterpret_cast<const uint4*>(&V[(c0 + ql) * ld + r0 + w * 8]);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) sh[ql][w * 8 + k] = y.e[k];
+    }
+    __syncthreads();
+    for (int x = tid; x < 64 * 8; x += 256) {
+      const int rl = x / 8, w = x % 8;
+      Vec y;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) y.e[k] = sh[w * 8 + k][rl];
+      *reinterpret_cast<uint4*>(&V[(r0 + rl) * ld + c0 + w * 8]) = y.u;
+    }
+    return;
+  }
+  for (int e = tid; e < 64 * 64; e += 256) {
+    const int ql = e >> 6, rl = e & 63;
+    const int64_t q = c0 + ql, r = r0 + rl;
+    if (q >= q0 && q < q1 && r < n && q < r) sh[ql][rl] = V[q * ld + r];
+  }
+  __syncthreads();
+  for (int e = tid; e < 64 * 64; e += 256) {
+    const int rl = e >> 6, ql = e & 63;
+    const int64_t r = r0 + rl, q = c0 + ql;
+    if (q >= q0 && q < q1 && r < n && q < r) V[r * ld + q] = sh[ql][rl];
+  }
+}
+
+int mirror_rows(hipStream_t s, int prec, void* hi, void* lo, int64_t n, int64_t ld, int64_t q0, int64_t q1) {
+  if (q1 <= q0 || n <= 1) return PPL_OK;
+  const int64_t T = (n + 63) / 64, ja = T - 1 - (q1 - 1) / 64, jb = T - q0 / 64;
+  const int64_t t0 = ja * (ja + 1) / 2, blocks = jb * (jb + 1) / 2 - t0;
+  if (blocks > 0x7fffffffLL) return fail(PPL_E_ARG, "mirror of %lld rows too large", (long long)n);
+  if ((prec != PPL_BF16X3 && prec != PPL_BF16X6) || ld % 8 != 0 || (uintptr_t)hi % 16 != 0 || (uintptr_t)lo % 16 != 0)
+    return fail(PPL_E_ARG, "mirror_rows: not bf16 planes of 16-byte aligned rows");
+  hipLaunchKernelGGL(mirror_rows_kernel, dim3((unsigned)blocks, prec == PPL_BF16X6 ? 3 : 2), dim3(256), 0, s,
+                     (uint16_t*)hi, (uint16_t*)lo, n, ld, q0, q1, t0);
   PPL_LAUNCH_CHECK();
   return PPL_OK;
 }

@@ -247,7 +247,7 @@ struct EpiBuildSym {
 // Upper-triangle build of a resident plan in the GEMM's natural layout: rows and columns
 // as in EpiBuildSym, T[m * ldt + n] = (ac|bd) for row m = pair(a, c) - pr0 and column
 // n = pair(b, d) - pr0 (b <= d; computed for b >= a of the row tile's first virtual). The
-// packing (pack_vpm_cubes) reads both (ac|bd) and (ad|bc) from it.
+// packing (pack_vpm_tri) reads both (ac|bd) and (ad|bc) from it.
 template <class Tg>
 struct EpiBuildT {
   static constexpr bool kTri = false;

@@ -297,13 +297,13 @@ int pack_vpm(hipStream_t s, int prec, int v, int a0, int a1, const void* G, void
 int pack_vpm_sym(hipStream_t s, int prec, int v, int a0, int a1, const void* G, void* vp, void* vp_lo,
                  int64_t ldp, void* vm, void* vm_lo, int64_t ldm, const int* tab_vp, int64_t vp_row0 = 0,
                  int64_t vm_row0 = 0, int half_diag = 0, int64_t zp = 0, int64_t zm = 0);
-// whole V+- rows (and their mirror entries) of a resident build step from gemm_build_natural's
-// T (row length ldt); off[a] = cubes of the virtuals below a (pack_cubes.h), v + 1 entries
-int pack_vpm_cubes(hipStream_t s, int prec, int v, int a0, int a1, const void* T, int64_t ldt, const int64_t* off,
-                   void* vp, void* vp_lo, int64_t ldp, void* vm, void* vm_lo, int64_t ldm);
-// the same rows as upper triangles with whole diagonal blocks (kTriBlock; FP64 and FP32)
+// V+- rows of a resident build step from gemm_build_natural's T (row length ldt) as upper
+// triangles, FP64 and FP32 with whole diagonal blocks (kTriBlock); off[a] = cubes of the virtuals
+// below a (pack_cubes.h), v + 1 entries
 int pack_vpm_tri(hipStream_t s, int prec, int v, int a0, int a1, const void* T, int64_t ldt, const int64_t* off,
-                 void* vp, int64_t ldp, void* vm, int64_t ldm);
+                 void* vp, void* vp_lo, int64_t ldp, void* vm, void* vm_lo, int64_t ldm);
+// entries below the diagonal of rows [q0, q1) of a symmetric n x n bf16 matrix (every plane)
+int mirror_rows(hipStream_t s, int prec, void* hi, void* lo, int64_t n, int64_t ld, int64_t q0, int64_t q1);
 // a symmetric FP64 matrix stored that way to the whole matrix in an operand precision
 int convert_tri(hipStream_t s, int prec, const double* src, int64_t n, int64_t ld, void* dst, void* dst_lo);
 // C[q][p] += T[p][q] for q < nq, p < np (T FP64; C FP64 or FP32 by c_prec)

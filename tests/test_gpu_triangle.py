@@ -104,3 +104,27 @@ def test_grouped_launch_reads_triangles(P, prec, bound):
     for s, t, R in zip(systems, ts, Rs):
         assert rel(R.cpu().numpy(), O.ppl(s["L"], s["o"], t)) < bound
     b.close()
+
+
+@pytest.mark.parametrize("prec,bound", [("bf16x3", 4e-5), ("bf16x6", 2e-6)])
+@pytest.mark.parametrize("o,v,naux", SIZES)
+def test_bf16_rows_completed_from_triangles(P, monkeypatch, prec, bound, o, v, naux):
+    """BF16 rows are packed as upper triangles and completed step by step: every entry is
+    written (poisoned workspace) and steps give the same rows in any order."""
+    say(f"bf16 rows {prec} ({o},{v},{naux})")
+    s = S.make_system(o, v, naux, 84)
+    t = S.make_amplitudes(o, v, 85)
+    L = dev(s["L"])
+    out = []
+    for order in (None, 1, -1):
+        eng = plan(P, monkeypatch, "1", o, v, naux, prec=prec, build_scratch=1 << 20)
+        nb = int(eng.info["n_batches"])
+        if order is None:
+            eng.build(L)
+        else:
+            for k in list(range(nb))[::order] + [nb - 1]:
+                eng.build(L, k)
+        out.append(eng.contract(dev(t)).cpu().numpy())
+        eng.close()
+    assert rel(out[0], O.ppl(s["L"], o, t)) < bound
+    assert np.array_equal(out[0], out[1]) and np.array_equal(out[0], out[2])
