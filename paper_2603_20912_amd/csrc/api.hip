@@ -218,8 +218,10 @@ static uint64_t assign_layout(ppl_plan_t p, int64_t gcap, bool resident, int64_t
     if (!s.present) continue;
     const uint64_t w = elem_bytes(s.prec);
     const int np = planes(s.prec);
-    const int64_t vrows_p = resident ? p->Pp : max_batch_pairs;
-    const int64_t vrows_m = resident ? p->Pm : max_batch_pairs;
+    // (rows of an upper-triangle step: up to kStepRows - 1 zero rows before it, kStepRows behind)
+    const int64_t spare = !resident && p->sym_build ? 2 * kStepRows - 1 : 0;
+    const int64_t vrows_p = resident ? p->Pp : max_batch_pairs + spare;
+    const int64_t vrows_m = resident ? p->Pm : max_batch_pairs + spare;
     if (np == 3) {
       // BF16x6: the mid and lo planes follow their hi plane directly (three planes spaced
       // one plane apart; the kernels find lo at mid + (mid - hi))
@@ -269,6 +271,16 @@ static uint64_t assign_layout(ppl_plan_t p, int64_t gcap, bool resident, int64_t
   }
   p->rp = L.take((uint64_t)p->Np * p->ldp * 8);
   p->rm = L.take((uint64_t)std::max<int64_t>(p->Nm, 1) * p->ldm * 8);
+  // upper-triangle steps accumulate each K slice over all columns, in as many slices as the plan was
+  // given, where they take no more than the step's own V+ rows
+  p->step_slices = 1;
+  if (!resident && p->sym_build) {
+    const uint64_t slice = (uint64_t)p->Np * p->ldp * 8 + (uint64_t)p->Nm * p->ldm * 8;
+    const uint64_t room = (uint64_t)max_batch_pairs * p->ldp * 8;
+    auto want = [](int sp) { return sp > 0 ? sp : kMaxSplits; };
+    p->step_slices = (int)std::min<uint64_t>(std::max(want(p->split_p), want(p->split_m)), room / slice);
+    if (p->step_slices < 2) p->step_slices = 1;
+  }
   // split-K slices for up to kMaxSplits (autotuning may pick any count), sized for FP64,
   // or the stream-K partial slots of the largest tile, whichever is larger. A resident
   // plan's slices span all columns; a streaming plan's span the widest batch only.
@@ -279,6 +291,8 @@ static uint64_t assign_layout(ppl_plan_t p, int64_t gcap, bool resident, int64_t
     if (p->Nm > 0)
       part_bytes = std::max(part_bytes, streamk_part_bytes(t, PPL_FP64, p->Nm, resident ? p->Pm : max_batch_pairs, p->ldm));
   }
+  if (!resident && p->sym_build)
+    part_bytes = p->step_slices > 1 ? p->step_slices * 8ull * (p->Np * p->ldp + p->Nm * p->ldm) : 0;
   p->part = L.take(part_bytes);
   if (p->ops[0].prec != PPL_FP64) {   // FP64 master amplitudes
     p->s64 = L.take((uint64_t)p->Np * p->ldp * 8);
@@ -315,18 +329,7 @@ static uint64_t assign_layout(ppl_plan_t p, int64_t gcap, bool resident, int64_t
   }
   p->tiles = L.take((uint64_t)p->tiles_host.size() * 4);
   p->cols = p->sym_build ? L.take((uint64_t)npairs_plus(v) * 4) : Region{};
-  p->cube_off = (p->sym_build && resident) ? L.take((uint64_t)(v + 1) * 8) : Region{};
-  p->r2p = p->r2m = p->ut = Region{};
-  if (p->sym_build && !resident) {
-    // the K range of a step starts at its first pair rounded down to 64, so it spans at
-    // most the step's pairs plus 63
-    p->ldq = pad_ld(p->Np);
-    p->ldqm = pad_ld(std::max<int64_t>(p->Nm, 1));
-    p->ldk = pad_ld(max_batch_pairs + 63);
-    p->r2p = L.take((uint64_t)p->Pp * p->ldq * 8);
-    p->r2m = L.take((uint64_t)std::max<int64_t>(p->Pm, 1) * p->ldqm * 8);
-    p->ut = L.take((uint64_t)p->Pp * p->ldk * 8);
-  }
+  p->cube_off = p->sym_build ? L.take((uint64_t)(v + 1) * 8) : Region{};
   return L.cur;
 }
 
@@ -422,22 +425,26 @@ static int build_one(ppl_plan_t p, OperandSet& s, const double* L, int bi, bool 
     return fail(PPL_E_STATE, "build step %d needs %llu B of scratch, plan has %llu B", bi,
                 (unsigned long long)g_need, (unsigned long long)p->g.bytes);
   {
-    const int64_t r0p = p->resident ? b.p0 : 0, r0m = p->resident ? b.q0 : 0;
+    const int64_t spare = p->sym_build ? 2 * kStepRows - 1 : 0;
+    const int64_t r0p = p->resident ? b.p0 : spare, r0m = p->resident ? b.q0 : spare;
     const uint64_t w = (uint64_t)elem_bytes(s.prec);
     if ((uint64_t)(r0p + (b.p1 - b.p0)) * p->ldp * w > s.vp.bytes ||
         (uint64_t)(r0m + (b.q1 - b.q0)) * p->ldm * w > s.vm.bytes)
       return fail(PPL_E_STATE, "build step %d exceeds the V+- rows of the plan", bi);
   }
-  if (p->sym_build && p->resident) {
+  if (p->sym_build) {
     // natural GEMM layout, then upper triangles (FP64, FP32), completed to whole rows in BF16
     {
       ProfScope ps(p, PPL_PROF_BUILD_GEMM, build_flops(p, b.a0, b.a1));
-      PPL_TRY(gemm_build_natural(st, s.prec, tile, p->v, b.a0, b.a1, p->ldx, at<void>(p, s.xt),
-                                 s.xt_lo.bytes ? at<void>(p, s.xt_lo) : nullptr, p->ldx, at<void>(p, p->g), dtiles,
-                                 nvalid, at<int>(p, p->tab_vp), at<int>(p, p->cols)));
+      PPL_TRY(gemm_build_sym(st, s.prec, tile, p->v, b.a0, b.a1, p->naux, at<void>(p, s.xt),
+                             s.xt_lo.bytes ? at<void>(p, s.xt_lo) : nullptr, p->ldx, at<void>(p, p->g), dtiles, nvalid,
+                             at<int>(p, p->tab_vp), at<int>(p, p->cols)));
     }
     ProfScope ps(p, PPL_PROF_BUILD_PACK, 0.0);
     const int64_t W = p->v - b.a0;
+    if (!p->resident)
+      return pack_vpm_step(st, p->v, b, at<double>(p, p->g), W * (W + 1) / 2, at<int64_t>(p, p->cube_off),
+                           at<double>(p, s.vp), p->ldp, at<double>(p, s.vm), p->ldm);
     void* vp_lo = s.vp_lo.bytes ? at<void>(p, s.vp_lo) : nullptr;
     void* vm_lo = s.vm_lo.bytes ? at<void>(p, s.vm_lo) : nullptr;
     PPL_TRY(pack_vpm_tri(st, s.prec, p->v, b.a0, b.a1, at<void>(p, p->g), W * (W + 1) / 2, at<int64_t>(p, p->cube_off),
@@ -446,23 +453,9 @@ static int build_one(ppl_plan_t p, OperandSet& s, const double* L, int bi, bool 
     PPL_TRY(mirror_rows(st, s.prec, at<void>(p, s.vp), vp_lo, p->Pp, p->ldp, b.p0, b.p1));
     return mirror_rows(st, s.prec, at<void>(p, s.vm), vm_lo, p->Pm, p->ldm, b.q0, b.q1);
   }
-  if (p->sym_build) {
-    {
-      ProfScope ps(p, PPL_PROF_BUILD_GEMM, build_flops(p, b.a0, b.a1));
-      PPL_TRY(gemm_build_sym(st, s.prec, tile, p->v, b.a0, b.a1, p->ldx, at<void>(p, s.xt),
-                             s.xt_lo.bytes ? at<void>(p, s.xt_lo) : nullptr, p->ldx, at<void>(p, p->g), dtiles,
-                             nvalid, at<int>(p, p->tab_vp), at<int>(p, p->cols)));
-    }
-    ProfScope ps(p, PPL_PROF_BUILD_PACK, 0.0);
-    const bool str = !p->resident;
-    return pack_vpm_sym(st, s.prec, p->v, b.a0, b.a1, at<void>(p, p->g), at<void>(p, s.vp),
-                        s.vp_lo.bytes ? at<void>(p, s.vp_lo) : nullptr, p->ldp, at<void>(p, s.vm),
-                        s.vm_lo.bytes ? at<void>(p, s.vm_lo) : nullptr, p->ldm, at<int>(p, p->tab_vp),
-                        str ? b.p0 : 0, str ? b.q0 : 0, str ? 1 : 0, b.p0 / 64 * 64, b.q0 / 64 * 64);
-  }
   {
     ProfScope ps(p, PPL_PROF_BUILD_GEMM, build_flops(p, b.a0, b.a1));
-    PPL_TRY(gemm_build(st, s.prec, tile, p->v, b.a0, b.a1, p->ldx, at<void>(p, s.xt),
+    PPL_TRY(gemm_build(st, s.prec, tile, p->v, b.a0, b.a1, p->naux, at<void>(p, s.xt),
                        s.xt_lo.bytes ? at<void>(p, s.xt_lo) : nullptr, p->ldx, at<void>(p, p->g), dtiles,
                        nvalid));
   }
@@ -483,30 +476,23 @@ static int build_all(ppl_plan_t p, OperandSet& s, const double* L) {
 }
 
 // ------------------------------------------------------------------ contraction of packed operands
-// Streaming with upper-triangle steps (FP64): V = U + U^T, U the rows of a step from their
-// own pair on, diagonal halved. Per step, R[:, step] = S' U_step^T over K from the step's
-// first pair (rounded down to 64; U is zero before its own pair there), and
-// R^T[k0:, :] += U_step^T S'[:, step]^T with the step's pairs as K, through a transposed
-// copy of the step's rows. The transposed sums are added into R+- after the last step.
+// Streaming with upper-triangle steps (FP64): V = U + U^T, and each step adds the products with
+// its rows of U and U^T into R+- in one launch per sign (EpiStep). Bound by the matrix cores: at
+// (30, 300, 900) with a third of V+- in memory 58.6 ms (62 TF/s, 6 steps), 81 as two products per
+// sign, the second through a transposed copy of the step's rows into transposed sums (8 steps:
+// that copy took as much memory as a step's V+ rows, and half of the step's own columns was
+// computed on zeros). K slices accumulate apart and are summed by the consumer (out) or at the end.
 static int contract_stream_sym(ppl_plan_t p, OperandSet& s, int tile, int tile_m, int split_p, int split_m,
-                               void* part) {
+                               Slices (*out)[2]) {
   hipStream_t st = p->stream;
-  if (s.prec != PPL_FP64 || !p->r2p.bytes || !p->ut.bytes)
-    return fail(PPL_E_STATE, "streaming upper-triangle plan without its buffers");
-  double* sp = at<double>(p, s.sp);
-  double* am = at<double>(p, s.am);
-  double* vp = at<double>(p, s.vp);
-  double* vm = at<double>(p, s.vm);
-  double* rp = at<double>(p, p->rp);
-  double* rm = at<double>(p, p->rm);
-  double* r2p = at<double>(p, p->r2p);
-  double* r2m = at<double>(p, p->r2m);
-  double* ut = at<double>(p, p->ut);
-  PPL_TRY(zero_bytes(st, r2p, p->r2p.bytes));
-  if (p->Nm > 0) PPL_TRY(zero_bytes(st, r2m, p->r2m.bytes));
-  int t2p = -1, s2p = 1, t2m = -1, s2m = 1;
-  contract_choose(PPL_FP64, p->Pp, p->Np, p->ldk, 1, &t2p, &s2p);
-  if (p->Nm > 0) contract_choose(PPL_FP64, p->Pm, p->Nm, p->ldk, 1, &t2m, &s2m);
+  if (s.prec != PPL_FP64) return fail(PPL_E_STATE, "streaming upper-triangle plan in precision %d", s.prec);
+  auto slices = [&](int sp) { return sp > 0 ? std::min(sp, p->step_slices) : p->step_slices; };
+  const int np = slices(split_p), nm = slices(split_m);
+  double* part = at<double>(p, p->part);
+  StepSide plus{p->Np, p->Pp, p->ldp, at<double>(p, s.sp), at<double>(p, s.vp), np > 1 ? part : at<double>(p, p->rp),
+                p->Np * p->ldp, 0, 0, np, false};
+  StepSide minus{p->Nm, p->Pm, p->ldm, at<double>(p, s.am), at<double>(p, s.vm),
+                 nm > 1 ? part + p->step_slices * plus.stride : at<double>(p, p->rm), p->Nm * p->ldm, 0, 0, nm, false};
   // one half (U or U^T) of a step's rows [r0, r1) of an n-row block: useful flops
   auto half_flops = [](int64_t rows, int64_t n, int64_t r0, int64_t r1) {
     const double w = (double)(r1 - r0);
@@ -515,36 +501,31 @@ static int contract_stream_sym(ppl_plan_t p, OperandSet& s, int tile, int tile_m
   for (int bi = 0; bi < (int)p->batches.size(); ++bi) {
     const Batch& b = p->batches[bi];
     PPL_TRY(build_one(p, s, p->L_last, bi, bi > 0));
+    plus.p0 = b.p0, plus.p1 = b.p1, minus.p0 = b.q0, minus.p1 = b.q1;
+    plus.first = minus.first = bi == 0;
     {
       ProfScope ps(p, PPL_PROF_CONTRACT_PLUS, 2.0 * half_flops(p->Np, p->Pp, b.p0, b.p1));
-      const int64_t k0 = b.p0 / 64 * 64, w = b.p1 - b.p0, K2 = pad_ld(b.p1 - k0), nr = p->Pp - k0;
-      if (K2 > p->ldk) return fail(PPL_E_STATE, "step %d exceeds the transposed block", bi);
-      PPL_TRY(gemm_contract(st, PPL_FP64, tile, p->Np, w, p->ldp - k0, sp + k0, nullptr, p->ldp, vp + k0, nullptr,
-                            p->ldp, rp, p->ldp, b.p0, split_p, part, p->ld_part, p->part.bytes));
-      PPL_TRY(transpose_block(st, 8, vp, p->ldp, b.p0, b.p1, k0, k0, ut, p->ldk, nr, K2));
-      PPL_TRY(gemm_contract(st, PPL_FP64, t2p, nr, p->Np, K2, ut, nullptr, p->ldk, sp + k0, nullptr, p->ldp,
-                            r2p + k0 * p->ldq, p->ldq, 0, 1, nullptr, p->ldq, 0, true));
+      PPL_TRY(gemm_step(st, tile, plus));
     }
-    if (p->Nm > 0 && b.q1 > b.q0) {
-      ProfScope ps(p, PPL_PROF_CONTRACT_MINUS, 2.0 * half_flops(p->Nm, p->Pm, b.q0, b.q1));
-      const int64_t k0 = b.q0 / 64 * 64, w = b.q1 - b.q0, K2 = pad_ld(b.q1 - k0), nr = p->Pm - k0;
-      if (K2 > p->ldk) return fail(PPL_E_STATE, "step %d exceeds the transposed block", bi);
-      PPL_TRY(gemm_contract(st, PPL_FP64, tile_m, p->Nm, w, p->ldm - k0, am + k0, nullptr, p->ldm, vm + k0, nullptr,
-                            p->ldm, rm, p->ldm, b.q0, split_m, part, p->ld_part, p->part.bytes));
-      PPL_TRY(transpose_block(st, 8, vm, p->ldm, b.q0, b.q1, k0, k0, ut, p->ldk, nr, K2));
-      PPL_TRY(gemm_contract(st, PPL_FP64, t2m, nr, p->Nm, K2, ut, nullptr, p->ldk, am + k0, nullptr, p->ldm,
-                            r2m + k0 * p->ldqm, p->ldqm, 0, 1, nullptr, p->ldqm, 0, true));
-    }
+    ProfScope ps(p, PPL_PROF_CONTRACT_MINUS, 2.0 * half_flops(p->Nm, p->Pm, b.q0, b.q1));
+    PPL_TRY(gemm_step(st, tile_m, minus));
   }
   ProfScope ps(p, PPL_PROF_OTHER, 0.0);
-  PPL_TRY(add_transposed(st, PPL_FP64, rp, p->ldp, r2p, p->ldq, p->Np, p->Pp));
-  if (p->Nm > 0) PPL_TRY(add_transposed(st, PPL_FP64, rm, p->ldm, r2m, p->ldqm, p->Nm, p->Pm));
+  if (np > 1) {
+    if (out) (*out)[0] = Slices{plus.C, np, plus.stride};
+    else PPL_TRY(sum_slices(st, plus.C, np, plus.stride, p->Np, p->Pp, p->ldp, at<double>(p, p->rp)));
+  }
+  if (nm > 1 && p->Nm > 0) {
+    if (out) (*out)[1] = Slices{minus.C, nm, minus.stride};
+    else PPL_TRY(sum_slices(st, minus.C, nm, minus.stride, p->Nm, p->Pm, p->ldm, at<double>(p, p->rm)));
+  }
   return PPL_OK;
 }
 
 // R+ = S' V+^T, R- = A' V-^T with the operand set s (its S'/A' must be current). With `out`
 // (R+, R-) a resident plan leaves split-K slices unsummed where both results' slices fit the
-// partial buffer, for a consumer that sums them as it reads (out says where the results are).
+// partial buffer, and so does a streaming plan of upper-triangle steps, for a consumer that sums
+// them as it reads (out says where the results are).
 static int contract_packed(ppl_plan_t p, OperandSet& s, Slices (*out)[2] = nullptr) {
   hipStream_t st = p->stream;
   const void* sp = at<void>(p, s.sp);
@@ -555,8 +536,9 @@ static int contract_packed(ppl_plan_t p, OperandSet& s, Slices (*out)[2] = nullp
   const int tile = primary ? p->tile_contract : s.tile_p, tile_m = primary ? p->tile_m : s.tile_m;
   const int split_p = primary ? p->split_p : s.split_p, split_m = primary ? p->split_m : s.split_m;
   char* part = p->part.bytes ? at<char>(p, p->part) : nullptr;
+  const bool steps = !p->resident && p->sym_build;
   if (std::max(split_p, split_m) > kMaxSplits ||
-      (uint64_t)std::max(p->Np, p->Nm) * p->ld_part * kMaxSplits * 8 > p->part.bytes ||
+      (!steps && (uint64_t)std::max(p->Np, p->Nm) * p->ld_part * kMaxSplits * 8 > p->part.bytes) ||
       (uint64_t)p->Np * p->ldp * 8 > p->rp.bytes)
     return fail(PPL_E_STATE, "contraction buffers smaller than the plan requires");
   if (out) {
@@ -603,7 +585,7 @@ static int contract_packed(ppl_plan_t p, OperandSet& s, Slices (*out)[2] = nullp
     return PPL_OK;
   }
   if (!p->L_last) return fail(PPL_E_STATE, "streaming plan has no Cholesky vectors (call ppl_build_batch)");
-  if (p->sym_build) return contract_stream_sym(p, s, tile, tile_m, split_p, split_m, part);
+  if (steps) return contract_stream_sym(p, s, tile, tile_m, split_p, split_m, out);
   for (int bi = 0; bi < (int)p->batches.size(); ++bi) {
     const Batch& b = p->batches[bi];
     PPL_TRY(build_one(p, s, p->L_last, bi, bi > 0));
@@ -640,7 +622,7 @@ static int setup_ov_integrals(ppl_plan_t p, const double* L) {
   PPL_TRY(stage_ov(st, L, p->o, p->v, p->naux, p->ldx, at<double>(p, p->xov)));
   const int64_t ov = (int64_t)p->o * p->v;
   double* vfull = at<double>(p, p->g);
-  PPL_TRY(gemm_store_f64(st, ov, ov, p->ldx, at<double>(p, p->xov), p->ldx, at<double>(p, p->xov), p->ldx,
+  PPL_TRY(gemm_store_f64(st, ov, ov, p->naux, at<double>(p, p->xov), p->ldx, at<double>(p, p->xov), p->ldx,
                          vfull, ov));
   PPL_TRY(pack_pm(st, PPL_FP64, p->o, p->v, vfull, (int64_t)p->v * ov, p->v, ov, 1, 0.5, 0.5, 0.5,
                   at<double>(p, p->vs), nullptr, p->ldp, at<double>(p, p->va), nullptr, p->ldm, at<int>(p, p->tab_op)));
@@ -1038,7 +1020,7 @@ static int hhl_integrals(ppl_plan_t p, const double* L) {
   double *xoo = (double*)(g + h.xoo), *woo = (double*)(g + h.woo);
   const int64_t o = p->o, oo = o * o;
   PPL_TRY(stage_oo(p->stream, L, p->o, p->v, p->naux, p->ldx, xoo));
-  PPL_TRY(gemm_store_f64(p->stream, oo, oo, p->ldx, xoo, p->ldx, xoo, p->ldx, woo, oo));
+  PPL_TRY(gemm_store_f64(p->stream, oo, oo, p->naux, xoo, p->ldx, xoo, p->ldx, woo, oo));
   // X_ij^kl = Woo[(k,i)][(l,j)]
   return pack_pm(p->stream, PPL_FP64, p->o, p->o, woo, oo, 1, o * oo, o, 0.5, 0.5, 0.5, g + h.wp, nullptr, h.ldq,
                  g + h.wm, nullptr, h.ldqm, at<int>(p, p->tab_op));
@@ -1155,8 +1137,8 @@ static int ring_integrals(hipStream_t st, int o, int v, int naux, const double* 
   PPL_TRY(stage_oo(st, L, o, v, naux, r.ldx, d(r.xoo)));
   PPL_TRY(stage_vv(st, PPL_FP64, L, o, v, naux, r.ldx, d(r.xvv), nullptr));
   // J[(k,c)][(j,b)] = sum_P L^P_kc L^P_jb;  G[(k,j)][(b,c)] = sum_P L^P_kj L^P_bc -> K
-  PPL_TRY(gemm_store_f64(st, ov, ov, r.ldx, d(r.xov), r.ldx, d(r.xov), r.ldx, d(r.j), r.ldk));
-  PPL_TRY(gemm_store_f64(st, (int64_t)o * o, (int64_t)v * v, r.ldx, d(r.xoo), r.ldx, d(r.xvv), r.ldx, d(r.g),
+  PPL_TRY(gemm_store_f64(st, ov, ov, naux, d(r.xov), r.ldx, d(r.xov), r.ldx, d(r.j), r.ldk));
+  PPL_TRY(gemm_store_f64(st, (int64_t)o * o, (int64_t)v * v, naux, d(r.xoo), r.ldx, d(r.xvv), r.ldx, d(r.g),
                          r.ldg));
   return ring_exchange(st, o, v, d(r.g), r.ldg, d(r.k), r.ldk);
 }

@@ -238,120 +238,17 @@ int pack_vpm(hipStream_t s, int prec, int v, int a0, int a1, const void* G, void
   return PPL_OK;
 }
 
-// Upper triangle of V+- rows from an upper-triangle build step: G holds
-// G_ab[c - a0][d - a0] = (ac|bd) for c, d >= a (W x W per pair, pairs from pair0); the
-// block of pair (a, b) writes V+[ab][cd] and V-[ab][cd] for the columns (cd) >= (ab) in
-// packed order (c > a, or c == a and d >= b), which need only c, d >= a. The columns
-// before (ab) are the mirror image of earlier rows and are left alone.
-// Streaming form (half_diag): rows are stored from vp_row0 / vm_row0 on, the diagonal
-// entry is halved (V = U + U^T) and the columns [zp, own) and [zm, own) before the row's
-// own pair are zeroed, so that a K range starting at zp (zm) sees U exactly.
-template <class Tg, int PREC>
-__global__ void __launch_bounds__(256)
-pack_vpm_sym_kernel(int v, int a0, int64_t pair0, const Tg* __restrict__ G, const int* __restrict__ tab_vp,
-                    void* vp, void* vp_lo, int64_t ldp, void* vm, void* vm_lo, int64_t ldm, int64_t Pp,
-                    int64_t Pm, int64_t vp_row0, int64_t vm_row0, int half_diag, int64_t zp, int64_t zm) {
-  __shared__ double t1[32][33], t2[32][33];
-  const int W = v - a0;
-  const int64_t pr = pair0 + blockIdx.x;
-  const int ab = tab_vp[pr];
-  const int a = pair_first(ab), b = pair_second(ab);
-  const Tg* g = G + (int64_t)blockIdx.x * W * W;
-  const bool has_minus = a < b;
-  const int64_t qr = has_minus ? pair_minus(a, b, v) : 0;
-  const int64_t rowp = pr - vp_row0, rowm = qr - vm_row0;
-  const double dscale = half_diag ? 0.25 : 0.5;
-  const int tid = threadIdx.x;
-  const int nt = (v - a + 31) / 32;            // 32-wide tiles of c and d, starting at a
-  // the tile pairs (ci, di >= ci) in turn; the G values of the next pair are fetched into
-  // registers before the current pair is written, so that their latency overlaps it
-  double n1[4], n2[4];
-  auto fetch = [&](int ci, int di) __attribute__((always_inline)) {
-    const int cB = a + ci * 32, dB = a + di * 32;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int e = tid + 256 * k, r = e >> 5, q = e & 31;
-      const int c1 = cB + r, d1 = dB + q;
-      n1[k] = (c1 < v && d1 < v) ? (double)g[(int64_t)(c1 - a0) * W + (d1 - a0)] : 0.0;
-      const int c2 = dB + r, d2 = cB + q;     // row d, col c
-      n2[k] = (c2 < v && d2 < v) ? (double)g[(int64_t)(c2 - a0) * W + (d2 - a0)] : 0.0;
-    }
-  };
-  int ci = 0, di = 0;
-  fetch(ci, di);
-  while (ci < nt) {
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int e = tid + 256 * k, r = e >> 5, q = e & 31;
-      t1[r][q] = n1[k];
-      t2[q][r] = n2[k];
-    }
-    __syncthreads();
-    const int cB = a + ci * 32, dB = a + di * 32;
-    if (++di == nt) di = ++ci;                 // the next pair
-    if (ci < nt) fetch(ci, di);
-    for (int e = tid; e < 1024; e += 256) {
-      const int r = e >> 5, q = e & 31;
-      const int c = cB + r, d = dB + q;
-      if (c < v && d < v && c <= d && (c > a || d >= b)) {
-        const double gcd = t1[r][q], gdc = t2[r][q];
-        const bool diag = c == a && d == b;
-        Store<PREC>::put(vp, vp_lo, rowp * ldp + pair_plus(c, d, v), (diag ? dscale : 0.5) * (gcd + gdc));
-        if (has_minus && c < d)
-          Store<PREC>::put(vm, vm_lo, rowm * ldm + pair_minus(c, d, v), (diag ? dscale : 0.5) * (gcd - gdc));
-      }
-    }
-    __syncthreads();
-  }
-  for (int64_t k = Pp + tid; k < ldp; k += 256) Store<PREC>::put(vp, vp_lo, rowp * ldp + k, 0.0);
-  if (has_minus)
-    for (int64_t k = Pm + tid; k < ldm; k += 256) Store<PREC>::put(vm, vm_lo, rowm * ldm + k, 0.0);
-  if (half_diag) {
-    for (int64_t k = zp + tid; k < pr; k += 256) Store<PREC>::put(vp, vp_lo, rowp * ldp + k, 0.0);
-    if (has_minus)
-      for (int64_t k = zm + tid; k < qr; k += 256) Store<PREC>::put(vm, vm_lo, rowm * ldm + k, 0.0);
-  }
-}
-
-int pack_vpm_sym(hipStream_t s, int prec, int v, int a0, int a1, const void* G, void* vp, void* vp_lo,
-                 int64_t ldp, void* vm, void* vm_lo, int64_t ldm, const int* tab_vp, int64_t vp_row0,
-                 int64_t vm_row0, int half_diag, int64_t zp, int64_t zm) {
-  const int64_t p0 = pair_plus(a0, a0, v);
-  const int64_t p1 = (a1 >= v) ? npairs_plus(v) : pair_plus(a1, a1, v);
-  const int64_t npairs = p1 - p0;
-  if (npairs <= 0) return PPL_OK;
-  const int64_t Pp = npairs_plus(v), Pm = npairs_minus(v);
-  dim3 grid((unsigned)npairs);
-  if (prec == PPL_FP64)
-    hipLaunchKernelGGL((pack_vpm_sym_kernel<double, PPL_FP64>), grid, dim3(256), 0, s, v, a0, p0, (const double*)G,
-                       tab_vp, vp, vp_lo, ldp, vm, vm_lo, ldm, Pp, Pm, vp_row0, vm_row0, half_diag, zp, zm);
-  else if (prec == PPL_FP32)
-    hipLaunchKernelGGL((pack_vpm_sym_kernel<float, PPL_FP32>), grid, dim3(256), 0, s, v, a0, p0, (const float*)G,
-                       tab_vp, vp, vp_lo, ldp, vm, vm_lo, ldm, Pp, Pm, vp_row0, vm_row0, half_diag, zp, zm);
-  else if (prec == PPL_BF16X3)
-    hipLaunchKernelGGL((pack_vpm_sym_kernel<float, PPL_BF16X3>), grid, dim3(256), 0, s, v, a0, p0,
-                       (const float*)G, tab_vp, vp, vp_lo, ldp, vm, vm_lo, ldm, Pp, Pm, vp_row0, vm_row0, half_diag,
-                       zp, zm);
-  else if (prec == PPL_BF16X6)
-    hipLaunchKernelGGL((pack_vpm_sym_kernel<float, PPL_BF16X6>), grid, dim3(256), 0, s, v, a0, p0,
-                       (const float*)G, tab_vp, vp, vp_lo, ldp, vm, vm_lo, ldm, Pp, Pm, vp_row0, vm_row0, half_diag,
-                       zp, zm);
-  else
-    return fail(PPL_E_ARG, "pack_vpm_sym: unknown precision %d", prec);
-  PPL_LAUNCH_CHECK();
-  return PPL_OK;
-}
-
 constexpr int kPackThreads = 256;
 static_assert(kCube == 16, "the cube packing splits an element index into 4-bit fields");
 
-// Rows of V+- of a resident build step from the natural build output T: T[(pair(a, r) - pr0) *
+// Rows of V+- of an upper-triangle build step from the natural build output T: T[(pair(a, r) - pr0) *
 // ldt + pair(x, y) - pr0] = (ar|xy) for the step's virtuals a in [a0, a1), r >= a and
 // a <= x <= y (pr0 = pair(a0, a0)); T is symmetric in (x, y) since the Cholesky vectors are. For
 // row (ab) and column (cd) >= (ab) in packed order
 //   V+[ab][cd] = ((ac|bd) + (ad|bc)) / 2,   V-[ab][cd] = ((ac|bd) - (ad|bc)) / 2  (a < b, c < d).
 // Entries below the diagonal: FP64 and FP32 get those inside a diagonal block (kTriBlock) here and
-// need no others; BF16 gets them all from mirror_rows. One workgroup per cube of 16 x 16 x 16
+// need no others; BF16 gets them all from mirror_rows; a streaming step (STEP, EpiStep) has none,
+// halves its diagonal and stores its rows from global rows row0p / row0m on. One workgroup per cube of 16 x 16 x 16
 // indices (b, c, d), thread (c, d), b unrolled, so that the rows are written along d. (ac|bd) is
 // read in that shape where b <= d (contiguous along d); (ad|bc) is contiguous along c (b <= c) or
 // b and goes through one LDS array s[b][d][c], and where b > d so does (ac|bd), contiguous along
@@ -362,11 +259,11 @@ static_assert(kCube == 16, "the cube packing splits an element index into 4-bit 
 // v = 200 in one step (3.2 GB written, 1.6 read); FP32 at v = 151 0.36 ms against 0.40; BF16x6 at
 // v = 137 0.353 against 0.435 with all and 0.391 with four. Writing every mirror entry here, along
 // b, took 3.35 ms (FP64), 0.58 ms (FP32) and 0.845 ms (BF16x6; 0.62 with mirror_rows).
-template <class Tg, int PREC>
+template <class Tg, int PREC, bool STEP>
 __global__ void __launch_bounds__(kPackThreads)
 pack_vpm_tri_kernel(int v, int a0, int a1, const Tg* __restrict__ T, int64_t ldt, const int64_t* __restrict__ off,
                     int64_t g0, int64_t ncubes, void* vp, void* vp_lo, int64_t ldp, void* vm, void* vm_lo,
-                    int64_t ldm, int64_t Pp, int64_t Pm) {
+                    int64_t ldm, int64_t Pp, int64_t Pm, int64_t row0p, int64_t row0m) {
   constexpr int C = kCube, LD = kCube + 1, LB = kCube * LD + 1;   // both strides odd: no bank conflicts
   __shared__ Tg s[C * LB];
   const int64_t g = g0 + cube_of_slot(blockIdx.x, ncubes);
@@ -422,7 +319,7 @@ pack_vpm_tri_kernel(int v, int a0, int a1, const Tg* __restrict__ T, int64_t ldt
     const int64_t rm = pair_minus(a, b0, v), cm = pair_minus(c, d, v);
     // some mirror entry of the cube lies in a diagonal block (the same for every thread)
     const int e0 = d0 > c0 ? d0 : c0, bl = b0 + C < v ? b0 + C - 1 : v - 1;
-    const bool near = (PREC == PPL_FP64 || PREC == PPL_FP32) &&
+    const bool near = (PREC == PPL_FP64 || PREC == PPL_FP32) && !STEP &&
                       (pair_plus(c0, e0, v) / kTriBlock <= pair_plus(a, bl, v) / kTriBlock ||
                        pair_minus(c0, e0 > c0 ? e0 : c0 + 1, v) / kTriBlock <= pair_minus(a, bl, v) / kTriBlock);
 #pragma unroll
@@ -430,8 +327,9 @@ pack_vpm_tri_kernel(int v, int a0, int a1, const Tg* __restrict__ T, int64_t ldt
       if (k < kmax) {
         const double x = (double)gcd[k], y = (double)gdc[k];
         const bool minus = c < d && (k > 0 || b0 > a);
-        Store<PREC>::put(vp, vp_lo, (rp + k) * ldp + cp, 0.5 * (x + y));
-        if (minus) Store<PREC>::put(vm, vm_lo, (rm + k) * ldm + cm, 0.5 * (x - y));
+        const double w = STEP && cp == rp + k ? 0.25 : 0.5;   // (V+ and V- meet their diagonals together)
+        Store<PREC>::put(vp, vp_lo, (rp + k - row0p) * ldp + cp, w * (x + y));
+        if (minus) Store<PREC>::put(vm, vm_lo, (rm + k - row0m) * ldm + cm, w * (x - y));
         if (near) {
           if ((rp + k) / kTriBlock == cp / kTriBlock) Store<PREC>::put(vp, vp_lo, cp * ldp + rp + k, 0.5 * (x + y));
           if (minus && (rm + k) / kTriBlock == cm / kTriBlock)
@@ -444,44 +342,67 @@ pack_vpm_tri_kernel(int v, int a0, int a1, const Tg* __restrict__ T, int64_t ldt
     const int64_t padp = ldp - Pp, padm = ldm - Pm;
     for (int e = threadIdx.x; e < C * padp; e += kPackThreads) {
       const int b = b0 + (int)(e / padp);
-      if (b < v) Store<PREC>::put(vp, vp_lo, pair_plus(a, b, v) * ldp + Pp + e % padp, 0.0);
+      if (b < v) Store<PREC>::put(vp, vp_lo, (pair_plus(a, b, v) - row0p) * ldp + Pp + e % padp, 0.0);
     }
     for (int e = threadIdx.x; e < C * padm; e += kPackThreads) {
       const int b = b0 + (int)(e / padm);
-      if (b < v && a < b) Store<PREC>::put(vm, vm_lo, pair_minus(a, b, v) * ldm + Pm + e % padm, 0.0);
+      if (b < v && a < b) Store<PREC>::put(vm, vm_lo, (pair_minus(a, b, v) - row0m) * ldm + Pm + e % padm, 0.0);
     }
   }
 }
 
-template <class Tg, int PREC>
+template <class Tg, int PREC, bool STEP = false>
 static int launch_vpm_tri(hipStream_t s, int v, int a0, int a1, const void* T, int64_t ldt, const int64_t* off,
-                          int64_t g0, int64_t n, void* vp, void* vp_lo, int64_t ldp, void* vm, void* vm_lo,
-                          int64_t ldm) {
+                          void* vp, void* vp_lo, int64_t ldp, void* vm, void* vm_lo, int64_t ldm, int64_t row0p = 0,
+                          int64_t row0m = 0) {
+  int64_t g0 = 0, n = 0;
+  for (int a = 0; a < a1; ++a) (a < a0 ? g0 : n) += cubes_of(v, a);
+  if (n <= 0) return PPL_OK;
+  if (n > 0x7fffffffLL) return fail(PPL_E_ARG, "pack_vpm_tri: %lld cubes", (long long)n);
   constexpr unsigned kTriSpareLds = PREC == PPL_FP64 || PREC == PPL_FP32 ? 20000 : 36000;
-  hipLaunchKernelGGL((pack_vpm_tri_kernel<Tg, PREC>), dim3((unsigned)n), dim3(kPackThreads), kTriSpareLds, s, v, a0,
-                     a1, (const Tg*)T, ldt, off, g0, n, vp, vp_lo, ldp, vm, vm_lo, ldm, npairs_plus(v),
-                     npairs_minus(v));
+  hipLaunchKernelGGL((pack_vpm_tri_kernel<Tg, PREC, STEP>), dim3((unsigned)n), dim3(kPackThreads), kTriSpareLds, s, v,
+                     a0, a1, (const Tg*)T, ldt, off, g0, n, vp, vp_lo, ldp, vm, vm_lo, ldm, npairs_plus(v),
+                     npairs_minus(v), row0p, row0m);
   PPL_LAUNCH_CHECK();
   return PPL_OK;
 }
 
 int pack_vpm_tri(hipStream_t s, int prec, int v, int a0, int a1, const void* T, int64_t ldt, const int64_t* off,
                  void* vp, void* vp_lo, int64_t ldp, void* vm, void* vm_lo, int64_t ldm) {
-  int64_t g0 = 0, n = 0;
-  for (int a = 0; a < a1; ++a) (a < a0 ? g0 : n) += cubes_of(v, a);
-  if (n <= 0) return PPL_OK;
-  if (n > 0x7fffffffLL) return fail(PPL_E_ARG, "pack_vpm_tri: %lld cubes", (long long)n);
   switch (prec) {
     case PPL_FP64:
-      return launch_vpm_tri<double, PPL_FP64>(s, v, a0, a1, T, ldt, off, g0, n, vp, nullptr, ldp, vm, nullptr, ldm);
+      return launch_vpm_tri<double, PPL_FP64>(s, v, a0, a1, T, ldt, off, vp, nullptr, ldp, vm, nullptr, ldm);
     case PPL_FP32:
-      return launch_vpm_tri<float, PPL_FP32>(s, v, a0, a1, T, ldt, off, g0, n, vp, nullptr, ldp, vm, nullptr, ldm);
+      return launch_vpm_tri<float, PPL_FP32>(s, v, a0, a1, T, ldt, off, vp, nullptr, ldp, vm, nullptr, ldm);
     case PPL_BF16X3:
-      return launch_vpm_tri<float, PPL_BF16X3>(s, v, a0, a1, T, ldt, off, g0, n, vp, vp_lo, ldp, vm, vm_lo, ldm);
+      return launch_vpm_tri<float, PPL_BF16X3>(s, v, a0, a1, T, ldt, off, vp, vp_lo, ldp, vm, vm_lo, ldm);
     case PPL_BF16X6:
-      return launch_vpm_tri<float, PPL_BF16X6>(s, v, a0, a1, T, ldt, off, g0, n, vp, vp_lo, ldp, vm, vm_lo, ldm);
+      return launch_vpm_tri<float, PPL_BF16X6>(s, v, a0, a1, T, ldt, off, vp, vp_lo, ldp, vm, vm_lo, ldm);
   }
   return fail(PPL_E_ARG, "pack_vpm_tri: unknown precision %d", prec);
+}
+
+// The zeros that EpiStep reads: of rows k in [p0, p1) the columns of their kTriBlock block before
+// the own pair, of the rows [k0, p0) and from p1 on everything right of k0's block.
+__global__ void __launch_bounds__(256)
+step_zero_kernel(double* U, int64_t ld, int64_t k0, int64_t p0, int64_t p1) {
+  const int64_t k = k0 + blockIdx.x;
+  const bool own = k >= p0 && k < p1;
+  const int64_t c1 = own ? k : ld;
+  for (int64_t c = (own ? k : k0) / kTriBlock * kTriBlock + threadIdx.x; c < c1; c += 256) U[(k - k0) * ld + c] = 0.0;
+}
+
+int pack_vpm_step(hipStream_t s, int v, const Batch& b, const double* T, int64_t ldt, const int64_t* off, double* vp,
+                  int64_t ldp, double* vm, int64_t ldm) {
+  const int64_t kp = b.p0 / kStepRows * kStepRows, km = b.q0 / kStepRows * kStepRows;
+  PPL_TRY((launch_vpm_tri<double, PPL_FP64, true>(s, v, b.a0, b.a1, T, ldt, off, vp, nullptr, ldp, vm, nullptr, ldm, kp,
+                                                  km)));
+  hipLaunchKernelGGL(step_zero_kernel, dim3((unsigned)(b.p1 - kp + kStepRows)), dim3(256), 0, s, vp, ldp, kp, b.p0, b.p1);
+  if (b.q1 > b.q0)
+    hipLaunchKernelGGL(step_zero_kernel, dim3((unsigned)(b.q1 - km + kStepRows)), dim3(256), 0, s, vm, ldm, km, b.q0,
+                       b.q1);
+  PPL_LAUNCH_CHECK();
+  return PPL_OK;
 }
 
 // V[r][q] = V[q][r] for q in [q0, q1), q < r < n: the entries below the diagonal of a build step's
@@ -542,53 +463,6 @@ int mirror_rows(hipStream_t s, int prec, void* hi, void* lo, int64_t n, int64_t 
     return fail(PPL_E_ARG, "mirror_rows: not bf16 planes of 16-byte aligned rows");
   hipLaunchKernelGGL(mirror_rows_kernel, dim3((unsigned)blocks, prec == PPL_BF16X6 ? 3 : 2), dim3(256), 0, s,
                      (uint16_t*)hi, (uint16_t*)lo, n, ld, q0, q1, t0);
-  PPL_LAUNCH_CHECK();
-  return PPL_OK;
-}
-
-// Ut[r][k] = U[k0 + k - u0][c0 + r] for rows u0 <= k0 + k < u1 of the block U (row length
-// ldu, its first row is global row u0), zero for the other k; r < nr, k < nk (row length
-// ldt). A bit copy of elements of type E through 64 x 64 LDS tiles.
-template <class E>
-__global__ void __launch_bounds__(256)
-transpose_block_kernel(const E* __restrict__ U, int64_t ldu, int64_t u0, int64_t u1, int64_t c0, int64_t k0,
-                       E* __restrict__ Ut, int64_t ldt, int64_t nr, int64_t nk, int64_t tiles_k) {
-  __shared__ E sh[64][65];
-  const int64_t tr = blockIdx.x / tiles_k, tk = blockIdx.x % tiles_k;
-  const int64_t r0 = tr * 64, kb = tk * 64;
-  const int tid = threadIdx.x;
-  for (int e = tid; e < 64 * 64; e += 256) {
-    const int kl = e >> 6, rl = e & 63;                   // read U row k0 + kb + kl, column c0 + r0 + rl
-    const int64_t gk = k0 + kb + kl, r = r0 + rl;
-    E x = E(0);
-    if (gk >= u0 && gk < u1 && r < nr) x = U[(gk - u0) * ldu + c0 + r];
-    sh[kl][rl] = x;
-  }
-  __syncthreads();
-  for (int e = tid; e < 64 * 64; e += 256) {
-    const int rl = e >> 6, kl = e & 63;                   // write Ut row r0 + rl, column kb + kl
-    const int64_t r = r0 + rl, k = kb + kl;
-    if (r < nr && k < nk) Ut[r * ldt + k] = sh[kl][rl];
-  }
-}
-
-int transpose_block(hipStream_t s, int elem_bytes, const void* U, int64_t ldu, int64_t u0, int64_t u1, int64_t c0,
-                    int64_t k0, void* Ut, int64_t ldt, int64_t nr, int64_t nk) {
-  if (nr <= 0 || nk <= 0) return PPL_OK;
-  const int64_t tr = (nr + 63) / 64, tk = (nk + 63) / 64;
-  if (tr * tk > 0x7fffffffLL) return fail(PPL_E_ARG, "transpose of %lld x %lld too large", (long long)nr, (long long)nk);
-  const dim3 grid((unsigned)(tr * tk));
-  if (elem_bytes == 8)
-    hipLaunchKernelGGL(transpose_block_kernel<uint64_t>, grid, dim3(256), 0, s, (const uint64_t*)U, ldu, u0, u1, c0,
-                       k0, (uint64_t*)Ut, ldt, nr, nk, tk);
-  else if (elem_bytes == 4)
-    hipLaunchKernelGGL(transpose_block_kernel<uint32_t>, grid, dim3(256), 0, s, (const uint32_t*)U, ldu, u0, u1, c0,
-                       k0, (uint32_t*)Ut, ldt, nr, nk, tk);
-  else if (elem_bytes == 2)
-    hipLaunchKernelGGL(transpose_block_kernel<uint16_t>, grid, dim3(256), 0, s, (const uint16_t*)U, ldu, u0, u1, c0,
-                       k0, (uint16_t*)Ut, ldt, nr, nk, tk);
-  else
-    return fail(PPL_E_ARG, "transpose of %d-byte elements", elem_bytes);
   PPL_LAUNCH_CHECK();
   return PPL_OK;
 }

@@ -114,6 +114,25 @@ struct MapGrid {
   }
 };
 
+// Column tiles [nt0, n_nt) of a streaming step (EpiStep). The tiles of the step's own columns
+// run over nearly all of K, the others over the step's rows only, so the long ones (nt < nt_own)
+// start first. Order within each part as in MapGrid.
+struct MapStep {
+  int64_t n_mt, nt0, nt_own, n_nt;
+  int bm, bn, splits;
+  __device__ bool operator()(int64_t bid, TileJob& j) const {
+    const int64_t own = n_mt * (nt_own - nt0) * splits;
+    const bool second = bid >= own;
+    const int64_t n = n_mt * (second ? n_nt - nt_own : nt_own - nt0);
+    const int64_t t = xcd_remap(second ? bid - own : bid, n * splits), r = t % n;
+    j.split = (int)(t / n);
+    j.m0 = (r % n_mt) * bm;
+    j.n0 = ((second ? nt_own : nt0) + r / n_mt) * bn;
+    j.kc0 = j.kc1 = 0;   // EpiStep::phases
+    return true;
+  }
+};
+
 struct MapBuild {        // block-upper-triangle of the (a,c) x (b,d) grid: only tiles with some b >= a
   const int* tiles;      // (row tile, column tile) of each job, in launch order
   int64_t total;
@@ -140,7 +159,7 @@ struct EpiStore {        // C[split][m][c_col0 + n] = alpha * acc + beta * C (be
   double alpha, beta;
   int64_t split_stride;  // elements between split-K slices
   int tri = 0;           // B is symmetric and stored as its upper triangle (kTriBlock)
-  static constexpr bool kTri = true;
+  static constexpr bool kTri = true, kStep = false;
   __device__ void row(int split, int64_t m, int64_t& base, bool& ok) const {
     ok = m < M;
     base = split * split_stride + m * ldc + c_col0;
@@ -164,7 +183,7 @@ struct EpiSK {           // stream-K: whole tiles go to C, shared tiles to a den
   int ldp;               // = BN
   bool to_part;
   int tri = 0;           // as in EpiStore
-  static constexpr bool kTri = true;
+  static constexpr bool kTri = true, kStep = false;
   __device__ void row(int, int64_t m, int64_t& base, bool& ok) const {
     if (to_part) {
       ok = true;
@@ -180,9 +199,49 @@ struct EpiSK {           // stream-K: whole tiles go to C, shared tiles to a den
   }
 };
 
+// One step of a streaming plan, R += S' V_step: V = U + U^T, and the step holds the rows
+// k in [p0, p1) of U (entries at and right of the row's own pair, its diagonal halved) from global
+// row k0 on, zero in the rows [k0, p0) and p1 .. p1 + 15, and in the columns of a row's
+// kTriBlock block before its own pair. Column tile n0 takes the chunks of the step's rows
+// k < n0 + bn, K-major (U^T), and, where it meets the step's own columns, then the chunks from
+// its first column on along the rows n (U). Both runs are cut into `splits` equal slices,
+// slice s accumulating in C + s * stride (first: written).
+struct EpiStep {
+  static constexpr bool kTri = false, kStep = true;
+  static constexpr int KC = kKcF64;
+  double* C;
+  int64_t ldc, M, N, stride;
+  int64_t k0, p0, p1, nk;   // nk: chunks of a whole row
+  int splits;
+  bool first;
+  __device__ int64_t arow(int64_t r) const { return r; }
+  // columns outside the step take a zero row
+  __device__ int64_t brow(int64_t n) const { return n < k0 || n >= p1 ? p1 - k0 : n - k0; }
+  // chunks [c0, cd) K-major and [t0, c1) along the rows of V
+  __device__ void phases(const TileJob& j, int bn, int64_t& c0, int64_t& cd, int64_t& t0, int64_t& c1) const {
+    const int64_t ka = k0 / KC, ke = (p1 + KC - 1) / KC, ne = (j.n0 + bn) / KC;
+    const int64_t nn = (ke < ne ? ke : ne) - ka;
+    const int64_t ta = j.n0 / KC > ka ? j.n0 / KC : ka, total = nn + (j.n0 < p1 ? nk - ta : 0);
+    const int64_t s0 = total * j.split / splits, s1 = total * (j.split + 1) / splits;
+    c0 = ka + (s0 < nn ? s0 : nn);
+    cd = ka + (s1 < nn ? s1 : nn);
+    t0 = ta + (s0 > nn ? s0 - nn : 0);
+    c1 = ta + (s1 > nn ? s1 - nn : 0);
+  }
+  __device__ void row(int split, int64_t m, int64_t& base, bool& ok) const {
+    ok = m < M;
+    base = split * stride + m * ldc;
+  }
+  __device__ void put(int64_t base, bool ok, int64_t n, double x) const {
+    if (!ok || n >= N) return;
+    double* p = C + base + n;
+    *p = first ? x : *p + x;
+  }
+};
+
 template <class Tg>
 struct EpiBuild {        // G[pair(a,b) - pair(a0,a0)][c][d] for b >= a
-  static constexpr bool kTri = false;
+  static constexpr bool kTri = false, kStep = false;
   __device__ int64_t arow(int64_t r) const { return r; }   // operand rows of C row / column r
   __device__ int64_t brow(int64_t r) const { return r; }
   Tg* G;
@@ -206,51 +265,15 @@ struct EpiBuild {        // G[pair(a,b) - pair(a0,a0)][c][d] for b >= a
   }
 };
 
-// Upper-triangle build of a resident plan. Rows are the packed pairs (a, c), c >= a, of
-// the step's virtuals a in [a0, a1) (packed pairs pr0 + m); columns are the packed pairs
-// (b, d), b <= d, as operand rows b * v + d listed in `cols` (ordered by b, starting at
-// b = a0). Only (ac|bd) with b, d >= a is kept: G[pair(a,b) - pr0][c - a0][d - a0] and its
-// mirror G[pair(a,d) - pr0][c - a0][b - a0], W = v - a0.
-template <class Tg>
-struct EpiBuildSym {
-  static constexpr bool kTri = false;
-  Tg* G;
-  int64_t M, N;
-  int v, a0, W;
-  int64_t pr0;
-  const int* tab;        // packed pair -> (first << 16) | second
-  const int* cols;       // column n -> operand row b * v + d
-  __device__ int64_t arow(int64_t m) const {
-    const int ac = tab[pr0 + m];
-    return (int64_t)pair_first(ac) * v + pair_second(ac);
-  }
-  __device__ int64_t brow(int64_t n) const { return cols[n]; }
-  __device__ void row(int, int64_t m, int64_t& base, bool& ok) const {
-    ok = m < M;
-    const int ac = ok ? tab[pr0 + m] : 0;
-    base = ((int64_t)pair_first(ac) << 20) | pair_second(ac);
-  }
-  // Column n is the packed pair (b <= d); (ac|bd) = (ac|db) for symmetric Cholesky vectors,
-  // so the product fills G_ab[c][d] and G_ad[c][b].
-  __device__ void put(int64_t base, bool ok, int64_t n, Tg x) const {
-    if (!ok || n >= N) return;
-    const int a = (int)(base >> 20), c = (int)(base & ((1 << 20) - 1));
-    const int bd = cols[n];
-    const int b = bd / v, d = bd - b * v;
-    if (b < a) return;
-    const int64_t cr = c - a0;
-    G[((pair_plus(a, b, v) - pr0) * W + cr) * W + (d - a0)] = x;
-    if (d != b) G[((pair_plus(a, d, v) - pr0) * W + cr) * W + (b - a0)] = x;
-  }
-};
-
-// Upper-triangle build of a resident plan in the GEMM's natural layout: rows and columns
-// as in EpiBuildSym, T[m * ldt + n] = (ac|bd) for row m = pair(a, c) - pr0 and column
-// n = pair(b, d) - pr0 (b <= d; computed for b >= a of the row tile's first virtual). The
-// packing (pack_vpm_tri) reads both (ac|bd) and (ad|bc) from it.
+// Upper-triangle build in the GEMM's natural layout. Rows are the packed pairs (a, c), c >= a, of
+// the step's virtuals a in [a0, a1) (packed pairs pr0 + m); columns are the packed pairs (b, d),
+// b <= d, as operand rows b * v + d listed in `cols` (ordered by b, starting at b = a0).
+// T[m * ldt + n] = (ac|bd) for row m = pair(a, c) - pr0 and column n = pair(b, d) - pr0 (computed
+// for b >= a of the row tile's first virtual). The packing (pack_vpm_tri) reads both (ac|bd) and
+// (ad|bc) from it.
 template <class Tg>
 struct EpiBuildT {
-  static constexpr bool kTri = false;
+  static constexpr bool kTri = false, kStep = false;
   Tg* T;
   int64_t M, N, ldt;
   int v;
@@ -502,7 +525,8 @@ __device__ __forceinline__ void tile_body_direct(const TileJob& job, int64_t M, 
 // n as before. K stays in order, so the sums are those of a full B, bit for bit. The diagonal
 // block is whole on both sides of it, and n0 is a multiple of BN, so no chunk mixes the two.
 // Measured at (20, 200, 600), FP64, against a full B: R- on tile 8 2.21 ms (2.28), R+ on tile 10
-// 2.72 (2.67); the packing, which no longer writes the mirror half, 1.74 ms (3.26).
+// 2.72 (2.67); the packing, which no longer writes the mirror half, 1.74 ms (3.26). A streaming
+// step (EpiStep) runs the same two phases over its rows.
 template <class T, int WM, int WN, int WAVES_M, int WAVES_N, int KC, class Epi>
 __device__ __forceinline__ void tile_body_direct3(const TileJob& job, int64_t M, int64_t N, const T* __restrict__ A,
                                                   int64_t lda, const T* __restrict__ B, int64_t ldb, const Epi& epi,
@@ -545,18 +569,20 @@ __device__ __forceinline__ void tile_body_direct3(const TileJob& job, int64_t M,
         const int r = q * RPI + lr;
         int64_t gr = job.m0 + r;
         if (gr > M - 1) gr = M - 1;
-        src[i] = A + epi.arow(gr) * lda + (slot ^ (r % VPR)) * VEC + (job.kc0 + c0) * KC;
+        src[i] = A + epi.arow(gr) * lda + (slot ^ (r % VPR)) * VEC + c0 * KC;
         dst[i] = q * RPI * LDSR;
       } else if constexpr (NN) {
         const int id = (q - GA) * 64 + lane, kr = id / BV, cv = id % BV;
-        src[i] = B + ((job.kc0 + c0) * KC + kr) * ldb + job.n0 + (cv ^ (((kr / VEC) & XK) * VB)) * VEC;
+        int64_t k = c0 * KC + kr;
+        if constexpr (Epi::kStep) k -= epi.k0;
+        src[i] = B + k * ldb + job.n0 + (cv ^ (((kr / VEC) & XK) * VB)) * VEC;
         step[i] = (int)(KC * ldb);
         dst[i] = (BM + (q - GA) * RPI) * LDSR;
       } else {
         const int r = (q - GA) * RPI + lr;
         int64_t gr = job.n0 + r;
         if (gr > N - 1) gr = N - 1;
-        src[i] = B + epi.brow(gr) * ldb + (slot ^ (r % VPR)) * VEC + (job.kc0 + c0) * KC;
+        src[i] = B + epi.brow(gr) * ldb + (slot ^ (r % VPR)) * VEC + c0 * KC;
         dst[i] = (BM + (q - GA) * RPI) * LDSR;
       }
     }
@@ -627,7 +653,7 @@ __device__ __forceinline__ void tile_body_direct3(const TileJob& job, int64_t M,
     }
   };
 
-  // chunks [c0, c1) relative to job.kc0
+  // chunks [c0, c1)
   auto run = [&](auto nn, int64_t c0, int64_t c1) __attribute__((always_inline)) {
     aim(nn, c0);
     issue(st0);
@@ -666,17 +692,21 @@ __device__ __forceinline__ void tile_body_direct3(const TileJob& job, int64_t M,
     }
   };
 
-  const int64_t nk = job.kc1 - job.kc0;
-  int64_t nd = 0;                                 // chunks below the diagonal
+  int64_t c0 = job.kc0, cd = c0, t0 = c0, c1 = job.kc1;   // chunks [c0, cd) from B rows k, [t0, c1) from rows n
   if constexpr (Epi::kTri) {
     if (epi.tri) {
-      nd = job.n0 / KC - job.kc0;
-      nd = nd < 0 ? 0 : (nd > nk ? nk : nd);
+      cd = job.n0 / KC;
+      cd = cd < c0 ? c0 : (cd > c1 ? c1 : cd);
+      t0 = cd;
     }
-    if (nd > 0) run(std::true_type{}, 0, nd);
-    if (nd > 0 && nd < nk) meet();                // every wave has read the last stages
+  } else if constexpr (Epi::kStep) {
+    epi.phases(job, BN, c0, cd, t0, c1);
   }
-  if (nd < nk) run(std::false_type{}, nd, nk);
+  if constexpr (Epi::kTri || Epi::kStep) {
+    if (c0 < cd) run(std::true_type{}, c0, cd);
+    if (c0 < cd && t0 < c1) meet();               // every wave has read the last stages
+  }
+  if (t0 < c1) run(std::false_type{}, t0, c1);
   store_acc<T, WM, WN>(acc, job, epi, wm, wn, lane);
 }
 
@@ -862,7 +892,7 @@ __device__ __forceinline__ void tile_body(const TileJob& job, int64_t M, int64_t
 template <class T, int WM, int WN, int WAVES_M, int WAVES_N, int KC, class Epi>
 struct GemmOccupancy {
   static constexpr bool build64 = PPL_BUILD_DIRECT3 && sizeof(T) == 8 && WM == 4 && WN == 2 && WAVES_M == 1 && WAVES_N == 4;
-  static constexpr bool direct = std::is_same_v<Epi, EpiStore<T>> || build64;
+  static constexpr bool direct = std::is_same_v<Epi, EpiStore<T>> || Epi::kStep || build64;
   static constexpr int lds = 3 * 16 * (WM * WAVES_M + WN * WAVES_N) * KC * (int)sizeof(T);
   static constexpr int waves = (direct && 2 * lds > 160 * 1024) ? 1 : 2;
 };
@@ -1694,7 +1724,7 @@ void build_tile_table(int tile, int v, int a0, int a1, std::vector<int>& tiles, 
   }
 }
 
-// The upper-triangle build of one step (see EpiBuildSym): row tiles over the packed pairs
+// The upper-triangle build of one step (see EpiBuildT): row tiles over the packed pairs
 // (a, c >= a) of a in [a0, a1), column tiles over the packed pairs (b <= d) of b >= a0,
 // ordered by b. Columns with b >= a start at a v - a (a - 1) / 2 of that order, so a row
 // tile whose first virtual is a needs only the column tiles from there on. Launch order
@@ -2156,6 +2186,48 @@ int gemm_contract(hipStream_t s, int prec, int tile, int64_t Nrows, int64_t Prow
 #undef PPL_CFG
 }
 
+// One streaming step (EpiStep): the tile's rows of S' against the step's rows of U and U^T.
+template <int WM, int WN, int WAVES_M, int WAVES_N>
+static int step_cfg(hipStream_t s, const StepSide& c) {
+  constexpr int BM = 16 * WM * WAVES_M, BN = 16 * WN * WAVES_N;
+  static_assert(kTriBlock % BN == 0, "a column tile lies in one diagonal block");
+  const EpiStep epi{(double*)c.C, c.ld, c.rows, c.cols, c.stride, c.p0 / kStepRows * kStepRows,
+                    c.p0, c.p1, c.ld / kKcF64, c.splits, c.first};
+  const MapStep map{(c.rows + BM - 1) / BM, c.p0 / BN, (c.p1 + BN - 1) / BN, (c.cols + BN - 1) / BN, BM, BN, c.splits};
+  return launch<double, WM, WN, WAVES_M, WAVES_N, kKcF64>(s, map.n_mt * (map.n_nt - map.nt0) * c.splits, c.rows, c.cols,
+                                                      c.ld, c.S, c.ld, c.U, c.ld, epi, map);
+}
+
+int gemm_step(hipStream_t s, int tile, const StepSide& c) {
+  static_assert(kStepRows == kKcF64, "a step starts on a chunk");
+  if (c.rows <= 0 || c.p1 <= c.p0) return PPL_OK;
+  if (c.p1 > c.cols || c.ld % 64 != 0 || c.ld < c.cols || c.splits < 1 || c.splits > kMaxSplits)
+    return fail(PPL_E_ARG, "streaming step out of range");
+  switch (tile) {
+    case 0: return step_cfg<7, 2, 1, 4>(s, c);
+    case 1: return step_cfg<4, 4, 2, 2>(s, c);
+    case 2: return step_cfg<13, 1, 1, 4>(s, c);
+    case 3: return step_cfg<2, 4, 1, 4>(s, c);
+    case 4: return step_cfg<3, 4, 1, 4>(s, c);
+    case 5: return step_cfg<6, 2, 1, 4>(s, c);
+    case 6: return step_cfg<2, 2, 1, 4>(s, c);
+    case 7: return step_cfg<3, 2, 1, 4>(s, c);
+    case 8: return step_cfg<4, 2, 1, 4>(s, c);
+    case 9: return step_cfg<7, 2, 2, 4>(s, c);
+    case 10: return step_cfg<7, 1, 2, 4>(s, c);
+    default: return fail(PPL_E_ARG, "unknown contraction tile %d", tile);
+  }
+}
+
+int sum_slices(hipStream_t s, const double* part, int n, int64_t stride, int64_t rows, int64_t cols, int64_t ld,
+               double* C) {
+  const int64_t g = std::min<int64_t>((rows * cols + 255) / 256, 65536);
+  hipLaunchKernelGGL(splitk_reduce_kernel<double>, dim3((unsigned)g), dim3(256), 0, s, part, n, stride, rows, cols, ld,
+                     C, ld, (int64_t)0);
+  PPL_HIP_TRY(hipGetLastError());
+  return PPL_OK;
+}
+
 template <class T, int WM, int WN, int WAVES_M, int WAVES_N>
 static int pair_cfg(hipStream_t s, const ContractSide (&c)[2]) {
   constexpr int BM = 16 * WM * WAVES_M, BN = 16 * WN * WAVES_N, KC = sizeof(T) == 8 ? kKcF64 : kKcF32;
@@ -2277,51 +2349,47 @@ void contract_choose(int prec, int64_t Nrows, int64_t Prows, int64_t Kpad, int m
   *splits_out = bs;
 }
 
+// K of a product over naux Cholesky vectors: rows are zero from naux to their padded length.
+static int64_t build_k(int64_t naux, int, int, int) { return pad_ld(naux); }
+
 template <int WM, int WN, int WAVES_M, int WAVES_N>
-static int build_cfg(hipStream_t s, int prec, int v, int a0, int a1, int64_t Kpad, const void* Xt,
+static int build_cfg(hipStream_t s, int prec, int v, int a0, int a1, int64_t naux, const void* Xt,
                      const void* Xt_lo, int64_t ldx, void* G, const int* tile_list, int64_t n_valid_tiles) {
   constexpr int BM = 16 * WM * WAVES_M, BN = 16 * WN * WAVES_N;
   const int64_t M = (int64_t)(a1 - a0) * v, N = (int64_t)(v - a0) * v;
   MapBuild map{tile_list, n_valid_tiles, BM, BN, 0};
-  map.nk = Kpad / kc_of(prec, BM, BN);
+  const int64_t K = build_k(naux, prec, BM, BN);
+  map.nk = K / kc_of(prec, BM, BN);
   if (prec == PPL_FP64) {
     const double* X = (const double*)Xt + (int64_t)a0 * v * ldx;
     EpiBuild<double> epi{(double*)G, M, N, v, a0};
-    return launch<double, WM, WN, WAVES_M, WAVES_N, kKcF64>(s, n_valid_tiles, M, N, Kpad, X, ldx, X, ldx,
+    return launch<double, WM, WN, WAVES_M, WAVES_N, kKcF64>(s, n_valid_tiles, M, N, K, X, ldx, X, ldx,
                                                             epi, map);
   }
   if (prec == PPL_FP32) {
     const float* X = (const float*)Xt + (int64_t)a0 * v * ldx;
     EpiBuild<float> epi{(float*)G, M, N, v, a0};
-    return launch<float, WM, WN, WAVES_M, WAVES_N, kKcF32>(s, n_valid_tiles, M, N, Kpad, X, ldx, X, ldx,
+    return launch<float, WM, WN, WAVES_M, WAVES_N, kKcF32>(s, n_valid_tiles, M, N, K, X, ldx, X, ldx,
                                                            epi, map);
   }
   if (prec == PPL_BF16X3) {
     const __bf16* Xh = (const __bf16*)Xt + (int64_t)a0 * v * ldx;
     const __bf16* Xl = (const __bf16*)Xt_lo + (int64_t)a0 * v * ldx;
     EpiBuild<float> epi{(float*)G, M, N, v, a0};
-    return launch_bf3<WM, WN, WAVES_M, WAVES_N, bf3_kc(BM, BN)>(s, n_valid_tiles, M, N, Kpad, Xh, Xl, ldx, Xh,
+    return launch_bf3<WM, WN, WAVES_M, WAVES_N, bf3_kc(BM, BN)>(s, n_valid_tiles, M, N, K, Xh, Xl, ldx, Xh,
                                                         Xl, ldx, epi, map);
   }
   if (prec == PPL_BF16X6) {
     const __bf16* Xh = (const __bf16*)Xt + (int64_t)a0 * v * ldx;
     const __bf16* Xm = (const __bf16*)Xt_lo + (int64_t)a0 * v * ldx;
     EpiBuild<float> epi{(float*)G, M, N, v, a0};
-    return launch_bf6<WM, WN, WAVES_M, WAVES_N>(s, n_valid_tiles, M, N, Kpad, Xh, Xm, ldx, Xh, Xm, ldx, epi, map);
+    return launch_bf6<WM, WN, WAVES_M, WAVES_N>(s, n_valid_tiles, M, N, K, Xh, Xm, ldx, Xh, Xm, ldx, epi, map);
   }
   return fail(PPL_E_ARG, "unknown precision %d", prec);
 }
 
-// epilogue of the upper-triangle build: G blocks (EpiBuildSym) or the natural layout (EpiBuildT)
-template <class Tg, bool NAT>
-static auto build_sym_epi(void* G, int64_t M, int64_t N, int v, int a0, int W, int64_t pr0, const int* tab_vp,
-                          const int* cstep) {
-  if constexpr (NAT) return EpiBuildT<Tg>{(Tg*)G, M, N, N, v, pr0, tab_vp, cstep};
-  else return EpiBuildSym<Tg>{(Tg*)G, M, N, v, a0, W, pr0, tab_vp, cstep};
-}
-
-template <int WM, int WN, int WAVES_M, int WAVES_N, bool NAT>
-static int build_sym_cfg(hipStream_t s, int prec, int v, int a0, int a1, int64_t Kpad, const void* Xt,
+template <int WM, int WN, int WAVES_M, int WAVES_N>
+static int build_sym_cfg(hipStream_t s, int prec, int v, int a0, int a1, int64_t naux, const void* Xt,
                          const void* Xt_lo, int64_t ldx, void* G, const int* tile_list, int64_t n_valid_tiles,
                          const int* tab_vp, const int* cols) {
   constexpr int BM = 16 * WM * WAVES_M, BN = 16 * WN * WAVES_N;
@@ -2331,82 +2399,69 @@ static int build_sym_cfg(hipStream_t s, int prec, int v, int a0, int a1, int64_t
   const int64_t M = pr1 - pr0, N = (int64_t)W * (W + 1) / 2;
   const int* cstep = cols + (npairs_plus(v) - N);       // first column with b = a0
   MapBuild map{tile_list, n_valid_tiles, BM, BN, 0};
-  map.nk = Kpad / kc_of(prec, BM, BN);
+  const int64_t K = build_k(naux, prec, BM, BN);
+  map.nk = K / kc_of(prec, BM, BN);
   if (prec == PPL_FP64) {
-    auto epi = build_sym_epi<double, NAT>(G, M, N, v, a0, W, pr0, tab_vp, cstep);
-    return launch<double, WM, WN, WAVES_M, WAVES_N, kKcF64>(s, n_valid_tiles, M, N, Kpad, (const double*)Xt, ldx,
+    EpiBuildT<double> epi{(double*)G, M, N, N, v, pr0, tab_vp, cstep};
+    return launch<double, WM, WN, WAVES_M, WAVES_N, kKcF64>(s, n_valid_tiles, M, N, K, (const double*)Xt, ldx,
                                                             (const double*)Xt, ldx, epi, map);
   }
   if (prec == PPL_FP32) {
-    auto epi = build_sym_epi<float, NAT>(G, M, N, v, a0, W, pr0, tab_vp, cstep);
-    return launch<float, WM, WN, WAVES_M, WAVES_N, kKcF32>(s, n_valid_tiles, M, N, Kpad, (const float*)Xt, ldx,
+    EpiBuildT<float> epi{(float*)G, M, N, N, v, pr0, tab_vp, cstep};
+    return launch<float, WM, WN, WAVES_M, WAVES_N, kKcF32>(s, n_valid_tiles, M, N, K, (const float*)Xt, ldx,
                                                            (const float*)Xt, ldx, epi, map);
   }
   if (prec == PPL_BF16X3) {
-    auto epi = build_sym_epi<float, NAT>(G, M, N, v, a0, W, pr0, tab_vp, cstep);
-    return launch_bf3<WM, WN, WAVES_M, WAVES_N, bf3_kc(BM, BN)>(s, n_valid_tiles, M, N, Kpad, (const __bf16*)Xt,
+    EpiBuildT<float> epi{(float*)G, M, N, N, v, pr0, tab_vp, cstep};
+    return launch_bf3<WM, WN, WAVES_M, WAVES_N, bf3_kc(BM, BN)>(s, n_valid_tiles, M, N, K, (const __bf16*)Xt,
                                                                 (const __bf16*)Xt_lo, ldx, (const __bf16*)Xt,
                                                                 (const __bf16*)Xt_lo, ldx, epi, map);
   }
   if (prec == PPL_BF16X6) {
-    auto epi = build_sym_epi<float, NAT>(G, M, N, v, a0, W, pr0, tab_vp, cstep);
-    return launch_bf6<WM, WN, WAVES_M, WAVES_N>(s, n_valid_tiles, M, N, Kpad, (const __bf16*)Xt,
+    EpiBuildT<float> epi{(float*)G, M, N, N, v, pr0, tab_vp, cstep};
+    return launch_bf6<WM, WN, WAVES_M, WAVES_N>(s, n_valid_tiles, M, N, K, (const __bf16*)Xt,
                                                 (const __bf16*)Xt_lo, ldx, (const __bf16*)Xt, (const __bf16*)Xt_lo,
                                                 ldx, epi, map);
   }
   return fail(PPL_E_ARG, "unknown precision %d", prec);
 }
 
-template <bool NAT>
-static int build_sym_tile(hipStream_t s, int prec, int tile, int v, int a0, int a1, int64_t Kpad, const void* Xt,
-                          const void* Xt_lo, int64_t ldx, void* G, const int* tl, int64_t nv, const int* tab_vp,
-                          const int* cols) {
+int gemm_build_sym(hipStream_t s, int prec, int tile, int v, int a0, int a1, int64_t naux, const void* Xt,
+                   const void* Xt_lo, int64_t ldx, void* T, const int* tl, int64_t nv, const int* tab_vp,
+                   const int* cols) {
   switch (tile) {
-    case 0: return build_sym_cfg<7, 2, 1, 4, NAT>(s, prec, v, a0, a1, Kpad, Xt, Xt_lo, ldx, G, tl, nv, tab_vp, cols);
-    case 1: return build_sym_cfg<4, 4, 2, 2, NAT>(s, prec, v, a0, a1, Kpad, Xt, Xt_lo, ldx, G, tl, nv, tab_vp, cols);
-    case 5: return build_sym_cfg<6, 2, 1, 4, NAT>(s, prec, v, a0, a1, Kpad, Xt, Xt_lo, ldx, G, tl, nv, tab_vp, cols);
-    case 8: return build_sym_cfg<4, 2, 1, 4, NAT>(s, prec, v, a0, a1, Kpad, Xt, Xt_lo, ldx, G, tl, nv, tab_vp, cols);
-    case 9: return build_sym_cfg<7, 2, 2, 4, NAT>(s, prec, v, a0, a1, Kpad, Xt, Xt_lo, ldx, G, tl, nv, tab_vp, cols);
-    case 10: return build_sym_cfg<7, 1, 2, 4, NAT>(s, prec, v, a0, a1, Kpad, Xt, Xt_lo, ldx, G, tl, nv, tab_vp, cols);
+    case 0: return build_sym_cfg<7, 2, 1, 4>(s, prec, v, a0, a1, naux, Xt, Xt_lo, ldx, T, tl, nv, tab_vp, cols);
+    case 1: return build_sym_cfg<4, 4, 2, 2>(s, prec, v, a0, a1, naux, Xt, Xt_lo, ldx, T, tl, nv, tab_vp, cols);
+    case 5: return build_sym_cfg<6, 2, 1, 4>(s, prec, v, a0, a1, naux, Xt, Xt_lo, ldx, T, tl, nv, tab_vp, cols);
+    case 8: return build_sym_cfg<4, 2, 1, 4>(s, prec, v, a0, a1, naux, Xt, Xt_lo, ldx, T, tl, nv, tab_vp, cols);
+    case 9: return build_sym_cfg<7, 2, 2, 4>(s, prec, v, a0, a1, naux, Xt, Xt_lo, ldx, T, tl, nv, tab_vp, cols);
+    case 10: return build_sym_cfg<7, 1, 2, 4>(s, prec, v, a0, a1, naux, Xt, Xt_lo, ldx, T, tl, nv, tab_vp, cols);
     default: return fail(PPL_E_ARG, "tile %d is not a build tile", tile);
   }
 }
 
-int gemm_build_sym(hipStream_t s, int prec, int tile, int v, int a0, int a1, int64_t Kpad, const void* Xt,
-                   const void* Xt_lo, int64_t ldx, void* G, const int* tile_list, int64_t n_valid_tiles,
-                   const int* tab_vp, const int* cols) {
-  return build_sym_tile<false>(s, prec, tile, v, a0, a1, Kpad, Xt, Xt_lo, ldx, G, tile_list, n_valid_tiles, tab_vp,
-                               cols);
-}
-
-int gemm_build_natural(hipStream_t s, int prec, int tile, int v, int a0, int a1, int64_t Kpad, const void* Xt,
-                       const void* Xt_lo, int64_t ldx, void* T, const int* tile_list, int64_t n_valid_tiles,
-                       const int* tab_vp, const int* cols) {
-  return build_sym_tile<true>(s, prec, tile, v, a0, a1, Kpad, Xt, Xt_lo, ldx, T, tile_list, n_valid_tiles, tab_vp,
-                              cols);
-}
-
-int gemm_build(hipStream_t s, int prec, int tile, int v, int a0, int a1, int64_t Kpad,
+int gemm_build(hipStream_t s, int prec, int tile, int v, int a0, int a1, int64_t naux,
                const void* Xt, const void* Xt_lo, int64_t ldx, void* G, const int* tile_list,
                int64_t n_valid_tiles) {
   switch (tile) {
-    case 0: return build_cfg<7, 2, 1, 4>(s, prec, v, a0, a1, Kpad, Xt, Xt_lo, ldx, G, tile_list, n_valid_tiles);
-    case 1: return build_cfg<4, 4, 2, 2>(s, prec, v, a0, a1, Kpad, Xt, Xt_lo, ldx, G, tile_list, n_valid_tiles);
-    case 5: return build_cfg<6, 2, 1, 4>(s, prec, v, a0, a1, Kpad, Xt, Xt_lo, ldx, G, tile_list, n_valid_tiles);
-    case 8: return build_cfg<4, 2, 1, 4>(s, prec, v, a0, a1, Kpad, Xt, Xt_lo, ldx, G, tile_list, n_valid_tiles);
-    case 9: return build_cfg<7, 2, 2, 4>(s, prec, v, a0, a1, Kpad, Xt, Xt_lo, ldx, G, tile_list, n_valid_tiles);
-    case 10: return build_cfg<7, 1, 2, 4>(s, prec, v, a0, a1, Kpad, Xt, Xt_lo, ldx, G, tile_list, n_valid_tiles);
+    case 0: return build_cfg<7, 2, 1, 4>(s, prec, v, a0, a1, naux, Xt, Xt_lo, ldx, G, tile_list, n_valid_tiles);
+    case 1: return build_cfg<4, 4, 2, 2>(s, prec, v, a0, a1, naux, Xt, Xt_lo, ldx, G, tile_list, n_valid_tiles);
+    case 5: return build_cfg<6, 2, 1, 4>(s, prec, v, a0, a1, naux, Xt, Xt_lo, ldx, G, tile_list, n_valid_tiles);
+    case 8: return build_cfg<4, 2, 1, 4>(s, prec, v, a0, a1, naux, Xt, Xt_lo, ldx, G, tile_list, n_valid_tiles);
+    case 9: return build_cfg<7, 2, 2, 4>(s, prec, v, a0, a1, naux, Xt, Xt_lo, ldx, G, tile_list, n_valid_tiles);
+    case 10: return build_cfg<7, 1, 2, 4>(s, prec, v, a0, a1, naux, Xt, Xt_lo, ldx, G, tile_list, n_valid_tiles);
     default: return fail(PPL_E_ARG, "tile %d is not a build tile", tile);
   }
 }
 
-int gemm_store_f64(hipStream_t s, int64_t M, int64_t N, int64_t Kpad, const double* A, int64_t lda,
+int gemm_store_f64(hipStream_t s, int64_t M, int64_t N, int64_t naux, const double* A, int64_t lda,
                    const double* B, int64_t ldb, double* C, int64_t ldc) {
   constexpr int WM = 4, WN = 4, WAVES_M = 2, WAVES_N = 2;
   constexpr int BM = 16 * WM * WAVES_M, BN = 16 * WN * WAVES_N;
-  MapGrid map{(M + BM - 1) / BM, (N + BN - 1) / BN, BM, BN, 1, Kpad / kKcF64, Kpad / kKcF64};
+  const int64_t K = build_k(naux, PPL_FP64, BM, BN);
+  MapGrid map{(M + BM - 1) / BM, (N + BN - 1) / BN, BM, BN, 1, K / kKcF64, K / kKcF64};
   EpiStore<double> epi{C, ldc, 0, M, N, 1.0, 0.0, 0};
-  return launch<double, WM, WN, WAVES_M, WAVES_N, kKcF64>(s, map.n_mt * map.n_nt, M, N, Kpad, A, lda, B,
+  return launch<double, WM, WN, WAVES_M, WAVES_N, kKcF64>(s, map.n_mt * map.n_nt, M, N, K, A, lda, B,
                                                       ldb, epi, map);
 }
 

@@ -113,7 +113,7 @@ struct ppl_plan_s {
   std::vector<ppl::Batch> batches;
   int a_per_batch = 0;
   int64_t g_pairs_cap = 0;             // pairs (a<=b) one build step may hold in G
-  int64_t ld_part = 0;                 // row length of split-K partial slices (streaming: one batch wide)
+  int64_t ld_part = 0;                 // row length of split-K partial slices (streaming full rows: one batch wide)
   // tiles
   int tile_build = 0, tile_contract = 0;
   int tile_build64 = 0;                // build tile of the FP64 copy of a mixed plan (ops[1])
@@ -146,12 +146,9 @@ struct ppl_plan_s {
   ppl::Region tiles;                   // per-batch (row tile, column tile) lists of the build GEMM (int32 pairs)
   bool sym_build = false;              // build the upper triangle of V+- (resident: rows of it, see kTriBlock;
                                        // streaming: contract U and U^T of each step, V = U + U^T)
-  int64_t ldq = 0, ldqm = 0;           // row lengths of the transposed streaming results (pad N+, N-)
-  int64_t ldk = 0;                     // row length of a transposed row block (its K range)
-  ppl::Region r2p, r2m;                // streaming U^T term, transposed: [P+][ldq], [P-][ldqm] (FP64)
-  ppl::Region ut;                      // one transposed row block of U+ or U-: [P+][ldk] (FP64)
+  int step_slices = 1;                 // streaming upper-triangle steps: K slices `part` holds of R+ and R- (1: none)
   ppl::Region cols;                    // operand rows of the upper-triangle build's columns (int32, v(v+1)/2)
-  ppl::Region cube_off;                // resident upper-triangle builds: cubes below each virtual (int64, v + 1)
+  ppl::Region cube_off;                // upper-triangle builds: cubes below each virtual (int64, v + 1)
   std::vector<int> cols_host;
   std::vector<int> tiles_host;         // host copy of the tile tables (kept alive for the async copy)
   std::vector<int64_t> tiles_off;      // element offset of each batch's list in `tiles`, [set][batch]
@@ -183,8 +180,8 @@ inline T* at(ppl_plan_t p, const Region& r) {
 // All launchers enqueue on the given stream and return PPL_OK or PPL_E_HIP.
 
 // Dense NT GEMM, C[M][N] = alpha * sum_k A[m][k] B[n][k] + beta * C (FP64 only; used
-// for the occupied-virtual integrals). K must be padded to ld with zeros.
-int gemm_store_f64(hipStream_t s, int64_t M, int64_t N, int64_t Kpad, const double* A, int64_t lda,
+// for integrals over naux Cholesky vectors). Rows are zero from naux to lda = ldb (a multiple of 64).
+int gemm_store_f64(hipStream_t s, int64_t M, int64_t N, int64_t naux, const double* A, int64_t lda,
                    const double* B, int64_t ldb, double* C, int64_t ldc);
 
 // Contraction C[N][P] = sum_k S[n][k] V[p][k] for one operand set (R+ or R-).
@@ -211,6 +208,22 @@ struct ContractSide {
 };
 bool contract_pair_ok(int prec, int tile, const ContractSide (&c)[2]);
 int gemm_contract_pair(hipStream_t s, int prec, int tile, const ContractSide (&c)[2]);
+// R+ or R- (FP64) += S' V_step for one step [p0, p1) of a streaming plan (EpiStep): U holds the
+// step's rows from row p0 rounded down to kStepRows on, and zero rows at its end. Slice s of K
+// goes to C + s * stride; first: C is written, not read.
+constexpr int kStepRows = 16;
+struct StepSide {
+  int64_t rows, cols, ld;   // occupied pairs, virtual pairs, row length of every operand and of C
+  const double *S, *U;
+  double* C;
+  int64_t stride, p0, p1;
+  int splits;
+  bool first;
+};
+int gemm_step(hipStream_t s, int tile, const StepSide& c);
+// C = the sum of n slices, in slice order
+int sum_slices(hipStream_t s, const double* part, int n, int64_t stride, int64_t rows, int64_t cols, int64_t ld,
+               double* C);
 // bytes of partial slots a stream-K contraction (splits == 0) with this tile needs at most
 uint64_t streamk_part_bytes(int tile, int prec, int64_t Nrows, int64_t Prows, int64_t Kpad);
 int64_t contract_jobs(int tile, int prec, int64_t Nrows, int64_t Prows, int64_t Kpad, int splits);
@@ -253,8 +266,8 @@ int gemm_grouped(hipStream_t s, int prec, char* base, const GroupDesc* groups, c
                  const int* q_begin, int* counters, int grid);
 
 // Integral build G[pair(a,b) - pair(a0,a0)][c][d] = sum_P Xt[(a,c)][P] Xt[(b,d)][P]
-// for a in [a0, a1), b in [a, v).
-int gemm_build(hipStream_t s, int prec, int tile, int v, int a0, int a1, int64_t Kpad,
+// for a in [a0, a1), b in [a, v). Rows are zero from naux to ldx.
+int gemm_build(hipStream_t s, int prec, int tile, int v, int a0, int a1, int64_t naux,
                const void* Xt, const void* Xt_lo, int64_t ldx, void* G, const int* tile_list,
                int64_t n_valid_tiles);
 // host helper: the valid (row tile, column tile) pairs of a build step in launch order
@@ -262,18 +275,12 @@ int gemm_build(hipStream_t s, int prec, int tile, int v, int a0, int a1, int64_t
 void build_tile_table(int tile, int v, int a0, int a1, std::vector<int>& tiles, int& n_mtiles,
                       int& n_ntiles);
 int build_tile_dims(int tile, int* bm, int* bn);
-// Upper-triangle build of a resident plan: G[pair(a,b) - pair(a0,a0)][c - a0][d - a0] =
-// (ac|bd) for a in [a0, a1), b >= a, c >= a, d >= a (W = v - a0); rows are the packed
-// pairs (a, c >= a) decoded through tab_vp, columns the operand rows in `cols`
-// (build_column_order).
-int gemm_build_sym(hipStream_t s, int prec, int tile, int v, int a0, int a1, int64_t Kpad, const void* Xt,
-                   const void* Xt_lo, int64_t ldx, void* G, const int* tile_list, int64_t n_valid_tiles,
+// Upper-triangle build of a step: T[pair(a,c) - pr0][pair(b,d) - pr0] = (ac|bd), row length
+// (v - a0)(v - a0 + 1) / 2, pr0 = pair(a0, a0), for a in [a0, a1), c >= a, b <= d and b >= a;
+// rows are decoded through tab_vp, columns are the operand rows in `cols` (build_column_order).
+int gemm_build_sym(hipStream_t s, int prec, int tile, int v, int a0, int a1, int64_t naux, const void* Xt,
+                   const void* Xt_lo, int64_t ldx, void* T, const int* tile_list, int64_t n_valid_tiles,
                    const int* tab_vp, const int* cols);
-// The same build in the GEMM's natural layout (resident plans): T[pair(a,c) - pr0][pair(b,d) - pr0]
-// = (ac|bd), row length (v - a0)(v - a0 + 1) / 2, pr0 = pair(a0, a0), for b <= d and b >= a.
-int gemm_build_natural(hipStream_t s, int prec, int tile, int v, int a0, int a1, int64_t Kpad, const void* Xt,
-                       const void* Xt_lo, int64_t ldx, void* T, const int* tile_list, int64_t n_valid_tiles,
-                       const int* tab_vp, const int* cols);
 void build_tile_table_sym(int tile, int v, int a0, int a1, std::vector<int>& tiles, int& n_mtiles,
                           int& n_ntiles);
 void build_column_order(int v, std::vector<int>& cols);
@@ -290,18 +297,15 @@ int stage_ov(hipStream_t s, const double* L, int o, int v, int naux, int64_t ldx
 int pack_vpm(hipStream_t s, int prec, int v, int a0, int a1, const void* G, void* vp, void* vp_lo,
              int64_t ldp, int64_t vp_row0, void* vm, void* vm_lo, int64_t ldm, int64_t vm_row0,
              const int* tab_vp, const int* tab_vm);
-// upper triangle of V+- rows from an upper-triangle build step (gemm_build_sym); resident rows
-// (resident: vp_row0 = vm_row0 = 0, half_diag = 0; streaming: rows relative to the
-// step's first pair, diagonal halved so that V = U + U^T, columns from zp / zm up to
-// the row's own pair zeroed)
-int pack_vpm_sym(hipStream_t s, int prec, int v, int a0, int a1, const void* G, void* vp, void* vp_lo,
-                 int64_t ldp, void* vm, void* vm_lo, int64_t ldm, const int* tab_vp, int64_t vp_row0 = 0,
-                 int64_t vm_row0 = 0, int half_diag = 0, int64_t zp = 0, int64_t zm = 0);
-// V+- rows of a resident build step from gemm_build_natural's T (row length ldt) as upper
-// triangles, FP64 and FP32 with whole diagonal blocks (kTriBlock); off[a] = cubes of the virtuals
-// below a (pack_cubes.h), v + 1 entries
+// V+- rows of a build step from gemm_build_sym's T (row length ldt) as upper triangles, FP64 and
+// FP32 with whole diagonal blocks (kTriBlock); off[a] = cubes of the virtuals below a
+// (pack_cubes.h), v + 1 entries
 int pack_vpm_tri(hipStream_t s, int prec, int v, int a0, int a1, const void* T, int64_t ldt, const int64_t* off,
                  void* vp, void* vp_lo, int64_t ldp, void* vm, void* vm_lo, int64_t ldm);
+// the same rows as a step of a streaming plan reads them (FP64; EpiStep): stored from the first pair
+// rounded down to kStepRows on, halved diagonal, zeros around them
+int pack_vpm_step(hipStream_t s, int v, const Batch& b, const double* T, int64_t ldt, const int64_t* off, double* vp,
+                  int64_t ldp, double* vm, int64_t ldm);
 // entries below the diagonal of rows [q0, q1) of a symmetric n x n bf16 matrix (every plane)
 int mirror_rows(hipStream_t s, int prec, void* hi, void* lo, int64_t n, int64_t ld, int64_t q0, int64_t q1);
 // a symmetric FP64 matrix stored that way to the whole matrix in an operand precision
@@ -313,9 +317,6 @@ int add_transposed(hipStream_t s, int c_prec, void* C, int64_t ldc, const double
 // w = (2 - d_kl) / (2 - d_ab) with (k, l) = tab_q[q], (a, b) = tab_p[p]
 int transpose_pm(hipStream_t s, const double* X, int64_t ldx, double* Y, int64_t ldy, int64_t nq, int64_t np,
                  const int* tab_q, const int* tab_p, int scaled, int pad = 1);
-// Ut[r][k] = U[k0 + k - u0][c0 + r] for u0 <= k0 + k < u1, else 0 (r < nr, k < nk)
-int transpose_block(hipStream_t s, int elem_bytes, const void* U, int64_t ldu, int64_t u0, int64_t u1, int64_t c0,
-                    int64_t k0, void* Ut, int64_t ldt, int64_t nr, int64_t nk);
 // pair tables
 int fill_tables(hipStream_t s, int o, int v, int* tab_vp, int* tab_vm, int* tab_op, int* tab_om);
 // generic pack of an (i,j,a,b)-indexed FP64 tensor into + / - packed rows of precision prec
