@@ -2349,8 +2349,13 @@ void contract_choose(int prec, int64_t Nrows, int64_t Prows, int64_t Kpad, int m
   *splits_out = bs;
 }
 
-// K of a product over naux Cholesky vectors: rows are zero from naux to their padded length.
-static int64_t build_k(int64_t naux, int, int, int) { return pad_ld(naux); }
+// K of a product over naux Cholesky vectors, in whole chunks. Rows are zero from naux to their padded
+// length (a multiple of 64, so of every chunk length); chunks that hold only zeros are left out: at
+// naux = 600, 38 chunks of 16 instead of 40.
+static int64_t build_k(int64_t naux, int prec, int bm, int bn) {
+  const int kc = kc_of(prec, bm, bn);
+  return (naux + kc - 1) / kc * kc;
+}
 
 template <int WM, int WN, int WAVES_M, int WAVES_N>
 static int build_cfg(hipStream_t s, int prec, int v, int a0, int a1, int64_t naux, const void* Xt,
