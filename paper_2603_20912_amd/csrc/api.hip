@@ -555,12 +555,12 @@ static int contract_packed(ppl_plan_t p, OperandSet& s, Slices (*out)[2] = nullp
     char* part_m = part + (keep_p ? part_p : 0);
     const uint64_t bytes_m = p->part.bytes - (keep_p ? part_p : 0);
     int np = 1, nm = 1;
-    if (keep_p && tile == tile_m && !p->prof_on) {
+    if (keep_p && !p->prof_on) {
       const ContractSide c[2] = {
-          {p->Np, p->Pp, p->ldp, sp, at<void>(p, s.vp), at<void>(p, p->rp), part, split_p, s.tri, &np},
-          {p->Nm, p->Pm, p->ldm, am, at<void>(p, s.vm), at<void>(p, p->rm), part_m, split_m, s.tri, &nm}};
-      if (contract_pair_ok(s.prec, tile, c)) {
-        PPL_TRY(gemm_contract_pair(st, s.prec, tile, c));
+          {tile, p->Np, p->Pp, p->ldp, sp, at<void>(p, s.vp), at<void>(p, p->rp), part, split_p, s.tri, &np},
+          {tile_m, p->Nm, p->Pm, p->ldm, am, at<void>(p, s.vm), at<void>(p, p->rm), part_m, split_m, s.tri, &nm}};
+      if (contract_pair_ok(s.prec, c)) {
+        PPL_TRY(gemm_contract_pair(st, s.prec, c));
         if (np > 1) (*out)[0] = Slices{part, np, p->Np * p->ldp};
         if (nm > 1) (*out)[1] = Slices{part_m, nm, p->Nm * p->ldm};
         return PPL_OK;

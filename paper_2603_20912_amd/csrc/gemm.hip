@@ -927,8 +927,9 @@ gemm_nt_kernel(int64_t M, int64_t N, int64_t Kpad, const T* __restrict__ A, int6
   }
 }
 
-// Two contractions (R+ and R-) on one tile in one launch: workgroups below grid0 (a multiple of 8,
-// so that both keep the XCD order of their maps) take the first, the others the second.
+// Two contractions (R+ and R-) in one launch, on tiles of 16 WM0 and 16 WM1 rows: workgroups below
+// grid0 (a multiple of 8, so that both keep the XCD order of their maps) take the first, the
+// others the second.
 template <class T>
 struct PairSide {
   int64_t M, N;
@@ -938,21 +939,22 @@ struct PairSide {
   MapGrid map;
 };
 
-template <class T, int WM, int WN, int WAVES_M, int WAVES_N, int KC>
-__global__ void __launch_bounds__(64 * WAVES_M * WAVES_N)
-__attribute__((amdgpu_waves_per_eu(GemmOccupancy<T, WM, WN, WAVES_M, WAVES_N, KC, EpiStore<T>>::waves)))
+template <class T, int WM0, int WM1, int KC>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 gemm_nt_pair_kernel(PairSide<T> p0, PairSide<T> p1, int64_t grid0) {
-  using G = TileGeom<T, WM, WN, WAVES_M, WAVES_N, KC>;
+  using G = TileGeom<T, (WM0 > WM1 ? WM0 : WM1), 2, 1, 4, KC>;
   __shared__ __attribute__((aligned(16))) T st0[G::BUF_A + G::BUF_B];
   __shared__ __attribute__((aligned(16))) T st1[G::BUF_A + G::BUF_B];
   __shared__ __attribute__((aligned(16))) T st2[G::BUF_A + G::BUF_B];
-  const bool second = blockIdx.x >= grid0;
-  const PairSide<T> p = second ? p1 : p0;
-  const int64_t bid = second ? blockIdx.x - grid0 : blockIdx.x;
   TileJob job;
-  if (bid >= p.map.n_mt * p.map.n_nt * p.map.splits) return;
-  p.map(bid, job);
-  tile_body_direct3<T, WM, WN, WAVES_M, WAVES_N, KC>(job, p.M, p.N, p.A, p.lda, p.B, p.ldb, p.epi, st0, st1, st2);
+  if (blockIdx.x < grid0) {
+    if (blockIdx.x >= p0.map.n_mt * p0.map.n_nt * p0.map.splits) return;
+    p0.map(blockIdx.x, job);
+    tile_body_direct3<T, WM0, 2, 1, 4, KC>(job, p0.M, p0.N, p0.A, p0.lda, p0.B, p0.ldb, p0.epi, st0, st1, st2);
+  } else {
+    p1.map(blockIdx.x - grid0, job);
+    tile_body_direct3<T, WM1, 2, 1, 4, KC>(job, p1.M, p1.N, p1.A, p1.lda, p1.B, p1.ldb, p1.epi, st0, st1, st2);
+  }
 }
 
 // ------------------------------------------------------------------ the kernel (BF16 x 3)
@@ -2228,14 +2230,15 @@ int sum_slices(hipStream_t s, const double* part, int n, int64_t stride, int64_t
   return PPL_OK;
 }
 
-template <class T, int WM, int WN, int WAVES_M, int WAVES_N>
+template <class T, int WM0, int WM1>
 static int pair_cfg(hipStream_t s, const ContractSide (&c)[2]) {
-  constexpr int BM = 16 * WM * WAVES_M, BN = 16 * WN * WAVES_N, KC = sizeof(T) == 8 ? kKcF64 : kKcF32;
+  constexpr int BN = 128, KC = sizeof(T) == 8 ? kKcF64 : kKcF32;
   static_assert(kTriBlock % BN == 0, "a column tile lies in one diagonal block of a triangular operand");
   PairSide<T> p[2];
   int64_t grid[2];
   for (int k = 0; k < 2; ++k) {
     const ContractSide& q = c[k];
+    const int BM = 16 * (k == 0 ? WM0 : WM1);
     const int64_t nk = q.ld / KC;
     int splits = q.splits > nk ? (int)nk : q.splits;
     const int64_t kps = (nk + splits - 1) / splits;
@@ -2248,35 +2251,52 @@ static int pair_cfg(hipStream_t s, const ContractSide (&c)[2]) {
     grid[k] = p[k].map.n_mt * p[k].map.n_nt * splits;
   }
   const int64_t grid0 = (grid[0] + 7) / 8 * 8;
-  hipLaunchKernelGGL((gemm_nt_pair_kernel<T, WM, WN, WAVES_M, WAVES_N, KC>), dim3((unsigned)(grid0 + grid[1])),
-                     dim3(64 * WAVES_M * WAVES_N), 0, s, p[0], p[1], grid0);
+  hipLaunchKernelGGL((gemm_nt_pair_kernel<T, WM0, WM1, KC>), dim3((unsigned)(grid0 + grid[1])), dim3(256), 0, s, p[0],
+                     p[1], grid0);
   PPL_HIP_TRY(hipGetLastError());
   return PPL_OK;
 }
 
 // One launch pays where two short ones leave the device idle between and after them: both
-// contractions together at most kPairJobs workgroups (two per CU; the launch and the tail of
-// one are then a good part of its time). A contraction at (5, 20), FP64: 14.9 us in three
-// launches (packing, this one, unpacking), 24.0 us in six with two GEMMs and two slice sums.
-bool contract_pair_ok(int prec, int tile, const ContractSide (&c)[2]) {
-  if ((prec != PPL_FP64 && prec != PPL_FP32) || tile < 6 || tile > 8) return false;
+// contractions together at most kPairJobs workgroups (two per CU; one contraction alone, sized
+// for the CUs, puts one on each and does not hide its latencies, and the launch and the tail
+// are then a good part of its time). A contraction at (5, 20), FP64: 14.9 us in three launches
+// (packing, this one, unpacking), 24.0 us in six with two GEMMs and two slice sums; R+ on 64
+// rows and R- on 48 at (10, 100) 107 us, 119 in two launches (474 workgroups).
+bool contract_pair_ok(int prec, const ContractSide (&c)[2]) {
+  if (prec != PPL_FP64 && prec != PPL_FP32) return false;
   constexpr int64_t kPairJobs = 512;
   int64_t jobs = 0;
   for (const ContractSide& q : c) {
-    if (q.rows <= 0 || q.cols <= 0 || q.splits < 1) return false;
-    jobs += contract_jobs(tile, prec, q.rows, q.cols, q.ld, q.splits);
+    if (q.tile < 6 || q.tile > 8 || q.rows <= 0 || q.cols <= 0 || q.splits < 1) return false;
+    jobs += contract_jobs(q.tile, prec, q.rows, q.cols, q.ld, q.splits);
   }
   return jobs <= kPairJobs;
 }
 
-int gemm_contract_pair(hipStream_t s, int prec, int tile, const ContractSide (&c)[2]) {
-  const bool d = prec == PPL_FP64;
-  switch (tile) {
-    case 6: return d ? pair_cfg<double, 2, 2, 1, 4>(s, c) : pair_cfg<float, 2, 2, 1, 4>(s, c);
-    case 7: return d ? pair_cfg<double, 3, 2, 1, 4>(s, c) : pair_cfg<float, 3, 2, 1, 4>(s, c);
-    case 8: return d ? pair_cfg<double, 4, 2, 1, 4>(s, c) : pair_cfg<float, 4, 2, 1, 4>(s, c);
-    default: return fail(PPL_E_ARG, "tile %d has no paired contraction", tile);
+// (tiles 6, 7 and 8: 16 x 2, 3 and 4 rows, 128 columns)
+template <class T, int WM0>
+static int pair_second(hipStream_t s, const ContractSide (&c)[2]) {
+  switch (c[1].tile) {
+    case 6: return pair_cfg<T, WM0, 2>(s, c);
+    case 7: return pair_cfg<T, WM0, 3>(s, c);
+    case 8: return pair_cfg<T, WM0, 4>(s, c);
+    default: return fail(PPL_E_ARG, "tile %d has no paired contraction", c[1].tile);
   }
+}
+
+template <class T>
+static int pair_first(hipStream_t s, const ContractSide (&c)[2]) {
+  switch (c[0].tile) {
+    case 6: return pair_second<T, 2>(s, c);
+    case 7: return pair_second<T, 3>(s, c);
+    case 8: return pair_second<T, 4>(s, c);
+    default: return fail(PPL_E_ARG, "tile %d has no paired contraction", c[0].tile);
+  }
+}
+
+int gemm_contract_pair(hipStream_t s, int prec, const ContractSide (&c)[2]) {
+  return prec == PPL_FP64 ? pair_first<double>(s, c) : pair_first<float>(s, c);
 }
 
 // Workgroups of one contraction launch for a (tile, splits) choice.

@@ -198,16 +198,17 @@ int gemm_contract(hipStream_t s, int prec, int tile, int64_t Nrows, int64_t Prow
                   int64_t ldv, void* C, int64_t ldc, int64_t c_col0, int splits, void* partial,
                   int64_t partial_ld, uint64_t partial_bytes, bool accumulate = false, bool tri = false,
                   int* slices = nullptr);
-// R+ and R- of one operand set in one launch (tile and K decompositions as gemm_contract)
+// R+ and R- of one operand set in one launch (tiles and K decompositions as gemm_contract)
 struct ContractSide {
+  int tile;
   int64_t rows, cols, ld;   // occupied pairs, virtual pairs, row length of every operand
   const void *S, *V;
   void *C, *partial;        // partial: [splits][rows][ld]
   int splits, tri;
   int* slices;              // out: K slices written (1: in C, more: in partial)
 };
-bool contract_pair_ok(int prec, int tile, const ContractSide (&c)[2]);
-int gemm_contract_pair(hipStream_t s, int prec, int tile, const ContractSide (&c)[2]);
+bool contract_pair_ok(int prec, const ContractSide (&c)[2]);
+int gemm_contract_pair(hipStream_t s, int prec, const ContractSide (&c)[2]);
 // R+ or R- (FP64) += S' V_step for one step [p0, p1) of a streaming plan (EpiStep): U holds the
 // step's rows from row p0 rounded down to kStepRows on, and zero rows at its end. Slice s of K
 // goes to C + s * stride; first: C is written, not read.
