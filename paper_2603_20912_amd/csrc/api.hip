@@ -623,7 +623,7 @@ static int setup_ov_integrals(ppl_plan_t p, const double* L) {
   const int64_t ov = (int64_t)p->o * p->v;
   double* vfull = at<double>(p, p->g);
   PPL_TRY(gemm_store_f64(st, ov, ov, p->naux, at<double>(p, p->xov), p->ldx, at<double>(p, p->xov), p->ldx,
-                         vfull, ov));
+                         vfull, ov, p->v));   // (packed below from the blocks i <= j)
   PPL_TRY(pack_pm(st, PPL_FP64, p->o, p->v, vfull, (int64_t)p->v * ov, p->v, ov, 1, 0.5, 0.5, 0.5,
                   at<double>(p, p->vs), nullptr, p->ldp, at<double>(p, p->va), nullptr, p->ldm, at<int>(p, p->tab_op)));
   return PPL_OK;

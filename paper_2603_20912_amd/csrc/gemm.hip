@@ -95,8 +95,10 @@ struct MapGrid {
   int bm, bn;
   int splits;
   int64_t nk, kps;       // K chunks in total and per split
+  int64_t blk = 0;       // > 0: tiles wholly left of their first row's diagonal blk x blk block are left out
+                         // (and the order of all tiles dealt over the XCDs, for equal shares)
   __device__ bool operator()(int64_t bid, TileJob& j) const {
-    const int64_t t = xcd_remap(bid, n_mt * n_nt * splits);
+    const int64_t t = blk > 0 ? bid : xcd_remap(bid, n_mt * n_nt * splits);
 #if PPL_SPLIT_OUTER
     const int64_t per = n_mt * n_nt, r = t % per;
     j.split = (int)(t / per);
@@ -110,7 +112,7 @@ struct MapGrid {
 #endif
     j.kc0 = j.split * kps;
     j.kc1 = j.kc0 + kps < nk ? j.kc0 + kps : nk;
-    return true;
+    return blk == 0 || j.n0 + bn > j.m0 / blk * blk;
   }
 };
 
@@ -2479,15 +2481,41 @@ int gemm_build(hipStream_t s, int prec, int tile, int v, int a0, int a1, int64_t
   }
 }
 
-int gemm_store_f64(hipStream_t s, int64_t M, int64_t N, int64_t naux, const double* A, int64_t lda,
-                   const double* B, int64_t ldb, double* C, int64_t ldc) {
-  constexpr int WM = 4, WN = 4, WAVES_M = 2, WAVES_N = 2;
+// Tile of an integral product, by the contractions' model (one K slice); with blk about half of the
+// columns are computed. (ia|jb) at (20, 200, 600): 372 us whole on 128 x 128 tiles, 249 the blocks
+// i <= j on 64 x 128; (kc|jb) at (18, 190, 570) 345 -> 240 us, (ki|lj) 75 -> 24.
+template <int WM, int WN, int WAVES_M, int WAVES_N>
+static int store_cfg(hipStream_t s, int64_t M, int64_t N, int64_t naux, const double* A, int64_t lda, const double* B,
+                     int64_t ldb, double* C, int64_t ldc, int64_t blk) {
   constexpr int BM = 16 * WM * WAVES_M, BN = 16 * WN * WAVES_N;
   const int64_t K = build_k(naux, PPL_FP64, BM, BN);
-  MapGrid map{(M + BM - 1) / BM, (N + BN - 1) / BN, BM, BN, 1, K / kKcF64, K / kKcF64};
+  MapGrid map{(M + BM - 1) / BM, (N + BN - 1) / BN, BM, BN, 1, K / kKcF64, K / kKcF64, blk};
   EpiStore<double> epi{C, ldc, 0, M, N, 1.0, 0.0, 0};
   return launch<double, WM, WN, WAVES_M, WAVES_N, kKcF64>(s, map.n_mt * map.n_nt, M, N, K, A, lda, B,
                                                       ldb, epi, map);
+}
+
+int gemm_store_f64(hipStream_t s, int64_t M, int64_t N, int64_t naux, const double* A, int64_t lda,
+                   const double* B, int64_t ldb, double* C, int64_t ldc, int64_t blk) {
+  int tile = -1, splits = 1;
+  contract_choose(PPL_FP64, M, blk > 0 ? (N + 1) / 2 : N, lda, 1, &tile, &splits);
+#define PPL_STORE(id, a, b, c, d) \
+  case id: return store_cfg<a, b, c, d>(s, M, N, naux, A, lda, B, ldb, C, ldc, blk);
+  switch (tile) {
+    PPL_STORE(0, 7, 2, 1, 4)
+    PPL_STORE(1, 4, 4, 2, 2)
+    PPL_STORE(2, 13, 1, 1, 4)
+    PPL_STORE(3, 2, 4, 1, 4)
+    PPL_STORE(4, 3, 4, 1, 4)
+    PPL_STORE(5, 6, 2, 1, 4)
+    PPL_STORE(6, 2, 2, 1, 4)
+    PPL_STORE(7, 3, 2, 1, 4)
+    PPL_STORE(8, 4, 2, 1, 4)
+    PPL_STORE(9, 7, 2, 2, 4)
+    PPL_STORE(10, 7, 1, 2, 4)
+    default: return fail(PPL_E_ARG, "no tile for a product of %lld x %lld", (long long)M, (long long)N);
+  }
+#undef PPL_STORE
 }
 
 // ------------------------------------------------------------------ grouped persistent contraction

@@ -181,8 +181,9 @@ inline T* at(ppl_plan_t p, const Region& r) {
 
 // Dense NT GEMM, C[M][N] = alpha * sum_k A[m][k] B[n][k] + beta * C (FP64 only; used
 // for integrals over naux Cholesky vectors). Rows are zero from naux to lda = ldb (a multiple of 64).
+// blk > 0: only the blk x blk blocks on and right of the diagonal are asked for.
 int gemm_store_f64(hipStream_t s, int64_t M, int64_t N, int64_t naux, const double* A, int64_t lda,
-                   const double* B, int64_t ldb, double* C, int64_t ldc);
+                   const double* B, int64_t ldb, double* C, int64_t ldc, int64_t blk = 0);
 
 // Contraction C[N][P] = sum_k S[n][k] V[p][k] for one operand set (R+ or R-).
 // Output in the accumulator precision (double for FP64, float otherwise).
