@@ -1131,8 +1131,6 @@ int ppl_hhl(ppl_plan_t p, const double* L, const double* t2, double* R, double a
 static int ring_integrals(hipStream_t st, int o, int v, int naux, const double* L, char* w, const RingLayout& r) {
   auto d = [&](uint64_t off) { return (double*)(w + off); };
   const int64_t ov = (int64_t)o * v;
-  // the K-dimension padding of J and K must read as zero (their GEMMs write n < o v only)
-  PPL_TRY(zero_bytes(st, w + r.j, 2 * (uint64_t)ov * r.ldk * 8));
   PPL_TRY(stage_ov(st, L, o, v, naux, r.ldx, d(r.xov)));
   PPL_TRY(stage_oo(st, L, o, v, naux, r.ldx, d(r.xoo)));
   PPL_TRY(stage_vv(st, PPL_FP64, L, o, v, naux, r.ldx, d(r.xvv), nullptr));
@@ -1140,7 +1138,7 @@ static int ring_integrals(hipStream_t st, int o, int v, int naux, const double* 
   PPL_TRY(gemm_store_f64(st, ov, ov, naux, d(r.xov), r.ldx, d(r.xov), r.ldx, d(r.j), r.ldk));
   PPL_TRY(gemm_store_f64(st, (int64_t)o * o, (int64_t)v * v, naux, d(r.xoo), r.ldx, d(r.xvv), r.ldx, d(r.g),
                          r.ldg));
-  return ring_exchange(st, o, v, d(r.g), r.ldg, d(r.k), r.ldk);
+  return ring_exchange(st, o, v, d(r.g), r.ldg, d(r.k), d(r.j), r.ldk);   // and zero padding of both rows
 }
 
 // R = beta R + alpha RING(t2) with J and K already in the scratch

@@ -394,7 +394,7 @@ int ring_pack(hipStream_t s, int o, int v, const double* t, int64_t ld, double* 
 // the same operands in precision prec (FP32, or bf16 planes: each *_lo is the lo / mid plane)
 int ring_pack_lp(hipStream_t s, int prec, int o, int v, const double* t, int64_t ld, void* Xa, void* Xa_lo,
                  void* An, void* An_lo, void* B, void* B_lo);
-int ring_exchange(hipStream_t s, int o, int v, const double* G, int64_t ldg, double* K, int64_t ld);
+int ring_exchange(hipStream_t s, int o, int v, const double* G, int64_t ldg, double* K, double* J, int64_t ld);
 int ring_unpack(hipStream_t s, int o, int v, const double* C1, const double* C2, int64_t ld, double* R, double alpha,
                 double beta);
 int ring_unpack_f32(hipStream_t s, int o, int v, const float* C1, const float* C2, int64_t ld, double* R, double alpha,
