@@ -405,14 +405,16 @@ static double build_flops(ppl_plan_t p, int a0, int a1) {
   return 2.0 * p->naux * f;
 }
 
+static int stage_vectors(ppl_plan_t p, OperandSet& s, const double* L) {
+  ProfScope ps(p, PPL_PROF_OTHER, 0.0);
+  return stage_vv(p->stream, s.prec, L, p->o, p->v, p->naux, p->ldx, at<void>(p, s.xt),
+                  s.xt_lo.bytes ? at<void>(p, s.xt_lo) : nullptr);
+}
+
 static int build_one(ppl_plan_t p, OperandSet& s, const double* L, int bi, bool staged) {
   const Batch& b = p->batches[bi];
   hipStream_t st = p->stream;
-  if (!staged) {
-    ProfScope ps(p, PPL_PROF_OTHER, 0.0);
-    PPL_TRY(stage_vv(st, s.prec, L, p->o, p->v, p->naux, p->ldx, at<void>(p, s.xt),
-                     s.xt_lo.bytes ? at<void>(p, s.xt_lo) : nullptr));
-  }
+  if (!staged) PPL_TRY(stage_vectors(p, s, L));
   // the FP64 copy of a mixed plan builds on the FP64 build tile, with its own lists
   const int set = (&s == &p->ops[1] && p->tile_sets == 2) ? 1 : 0;
   const int tile = (&s == &p->ops[1]) ? p->tile_build64 : p->tile_build;
@@ -469,8 +471,8 @@ static int build_one(ppl_plan_t p, OperandSet& s, const double* L, int bi, bool 
   return PPL_OK;
 }
 
-static int build_all(ppl_plan_t p, OperandSet& s, const double* L) {
-  for (int bi = 0; bi < (int)p->batches.size(); ++bi) PPL_TRY(build_one(p, s, L, bi, bi > 0));
+static int build_all(ppl_plan_t p, OperandSet& s, const double* L, bool staged) {
+  for (int bi = 0; bi < (int)p->batches.size(); ++bi) PPL_TRY(build_one(p, s, L, bi, staged || bi > 0));
   s.built = true;
   return PPL_OK;
 }
@@ -629,11 +631,15 @@ static int setup_ov_integrals(ppl_plan_t p, const double* L) {
   return PPL_OK;
 }
 
-// Sums that the host reads back go to mapped host memory where the plan has some (a plan that
-// iterates reads several per run: a copy and its wait took 24 us, the wait alone 11), else to
-// the workspace.
+// Sums that the host reads go to mapped host memory where the plan has some (from its first build
+// or iteration on; a copy and its wait took 24 us, the wait alone 11), else to the workspace.
 static double* red_target(ppl_plan_t p) {
   return p->host_red ? p->host_red : at<double>(p, p->red) + kReduceBlocks * 4;
+}
+
+static int need_host_red(ppl_plan_t p) {
+  if (!p->host_red) PPL_HIP_TRY(hipHostMalloc((void**)&p->host_red, kHostRed * sizeof(double), hipHostMallocMapped));
+  return PPL_OK;
 }
 
 static int read_red(ppl_plan_t p, double out[4]) {
@@ -644,15 +650,24 @@ static int read_red(ppl_plan_t p, double out[4]) {
   return PPL_OK;
 }
 
-// the upper-triangle build relies on symmetric Cholesky vectors (V+- symmetric): PPL_E_ARG
-// when the virtual block of L is not symmetric to a relative Frobenius asymmetry of 1e-10
-// (synchronous: reads one reduction back)
-static int check_symmetric(ppl_plan_t p, const double* L) {
+// The upper-triangle build relies on symmetric Cholesky vectors (V+- symmetric): PPL_E_ARG
+// when the virtual block of L is not symmetric to a relative Frobenius asymmetry of 1e-10. The host
+// waits for the sums only, so that work launched between the two calls hides the wait (a build's
+// staging: 44 us of idle device per build before).
+static int symmetry_sums(ppl_plan_t p, const double* L) {
   if (!p->sym_build) return PPL_OK;
-  double* partials = at<double>(p, p->red);
-  double h[4];
-  PPL_TRY(asymmetry_vv(p->stream, L, p->o, p->v, p->naux, partials, red_target(p)));
-  PPL_TRY(read_red(p, h));
+  PPL_TRY(need_host_red(p));
+  if (!p->ev_check) PPL_HIP_TRY(hipEventCreateWithFlags(&p->ev_check, hipEventDisableTiming | hipEventReleaseToSystem));
+  PPL_TRY(asymmetry_vv(p->stream, L, p->o, p->v, p->naux, at<double>(p, p->red), p->host_red + kHostRed - 4));
+  PPL_HIP_TRY(hipEventRecord(p->ev_check, p->stream));
+  return PPL_OK;
+}
+
+static int symmetry_verdict(ppl_plan_t p) {
+  if (!p->sym_build) return PPL_OK;
+  PPL_HIP_TRY(hipEventSynchronize(p->ev_check));
+  double h[2];
+  memcpy(h, p->host_red + kHostRed - 4, sizeof(h));
   if (!(h[0] <= 1e-20 * h[1]))
     return fail(PPL_E_ARG, "Cholesky vectors are not symmetric in their virtual block (relative asymmetry %.3g)",
                 h[1] > 0.0 ? sqrt(h[0] / h[1]) : 0.0);
@@ -683,18 +698,18 @@ static int derive_lowprec(ppl_plan_t p) {
   return PPL_OK;
 }
 
-// ppl_build_batch after its argument and symmetry checks
-static int build_checked(ppl_plan_t p, const double* L, int32_t batch) {
+// ppl_build_batch after its argument and symmetry checks (staged: the vectors are in Xt already)
+static int build_checked(ppl_plan_t p, const double* L, int32_t batch, bool staged = false) {
   const int nb = (int)p->batches.size();
   p->L_last = L;
   if (!p->resident) return PPL_OK;       // streaming plans build inside ppl_contract
   if (p->ops[1].present) {               // mixed: build in FP64, round to the low precision
     OperandSet& f = p->ops[1];
     if (batch < 0) {
-      PPL_TRY(build_all(p, f, L));
+      PPL_TRY(build_all(p, f, L, staged));
       return derive_lowprec(p);
     }
-    PPL_TRY(build_one(p, f, L, batch, false));
+    PPL_TRY(build_one(p, f, L, batch, staged));
     if (batch == nb - 1) {
       f.built = true;
       PPL_TRY(derive_lowprec(p));
@@ -705,13 +720,11 @@ static int build_checked(ppl_plan_t p, const double* L, int32_t batch) {
     OperandSet& s = p->ops[k];
     if (!s.present) continue;
     if (batch < 0) {
-      PPL_TRY(build_all(p, s, L));
+      PPL_TRY(build_all(p, s, L, staged));
     } else {
-      PPL_TRY(build_one(p, s, L, batch, false));
+      PPL_TRY(build_one(p, s, L, batch, staged));
       // a resident plan counts as built once its last batch is built in order
-      if (batch == nb - 1) {
-              s.built = true;
-      }
+      if (batch == nb - 1) s.built = true;
     }
   }
   return PPL_OK;
@@ -1004,8 +1017,12 @@ int ppl_build_batch(ppl_plan_t p, const double* L, int32_t batch) {
   if (!L) return fail(PPL_E_ARG, "null L");
   const int nb = (int)p->batches.size();
   if (batch < -1 || batch >= nb) return fail(PPL_E_ARG, "batch %d out of range [-1, %d)", batch, nb);
-  if (batch <= 0) PPL_TRY(check_symmetric(p, L));
-  return build_checked(p, L, batch);
+  // (a refused L leaves V+- as they were: Xt is filled anew by every build)
+  const bool check = batch <= 0 && p->sym_build, staged = check && p->resident;
+  if (check) PPL_TRY(symmetry_sums(p, L));
+  if (staged) PPL_TRY(stage_vectors(p, p->ops[1].present ? p->ops[1] : p->ops[0], L));
+  if (check) PPL_TRY(symmetry_verdict(p));
+  return build_checked(p, L, batch, staged);
 }
 
 }  // extern "C"
@@ -1294,7 +1311,7 @@ int ppl_iterate(ppl_plan_t p, const double* L, const double* e_occ, const double
   memset(&r, 0, sizeof(r));
   hipStream_t st = p->stream;
   double* partials = at<double>(p, p->red);
-  if (!p->host_red) PPL_HIP_TRY(hipHostMalloc((void**)&p->host_red, kHostRed * sizeof(double), hipHostMallocMapped));
+  PPL_TRY(need_host_red(p));
   double* const red_out = p->host_red;
   double h[4];
 
@@ -1316,8 +1333,9 @@ int ppl_iterate(ppl_plan_t p, const double* L, const double* e_occ, const double
   // the hole-hole W+- (the build scratch holds them for the sweeps of a resident plan)
   PPL_TRY(setup_ov_integrals(p, L));
   PPL_TRY(o.start == PPL_START_MP2 ? load_mp2() : load_given());
-  PPL_TRY(read_red(p, h));
   PPL_TRY(ppl_build_batch(p, L, -1));
+  if (p->sym_build) memcpy(h, p->host_red, sizeof(h));   // (its symmetry check has waited for the start too)
+  else PPL_TRY(read_red(p, h));
   if (o.hhl) PPL_TRY(hhl_integrals(p, L));
   RingLayout rl;
   if (o.ring) {
@@ -1726,6 +1744,7 @@ int ppl_destroy(ppl_plan_t p) {
   if (!p) return PPL_OK;
   for (hipEvent_t e : p->prof_pool) (void)hipEventDestroy(e);
   if (p->host_red) (void)hipHostFree(p->host_red);
+  if (p->ev_check) (void)hipEventDestroy(p->ev_check);
   delete p;
   return PPL_OK;
 }
@@ -2186,8 +2205,9 @@ int ppl_batch_build(ppl_batch_t b, const double* const* L) {
   if (!L) return fail(PPL_E_ARG, "null L array");
   for (int k = 0; k < b->n; ++k) {
     if (!L[k]) return fail(PPL_E_ARG, "null L for instance %d", k);
-    PPL_TRY(check_symmetric(b->plans[k], L[k]));
+    PPL_TRY(symmetry_sums(b->plans[k], L[k]));
   }
+  for (int k = 0; k < b->n; ++k) PPL_TRY(symmetry_verdict(b->plans[k]));
   PPL_TRY(batch_build_branches(b, L, true));
   b->built = true;
   return batch_prepare(b);

@@ -1188,19 +1188,26 @@ asym_kernel(const double* __restrict__ L, int n, int o, int v, int naux, double*
     while (k >= nb - A) k -= nb - A++;           // block pair (A, C = A + k)
     const int C = A + k;
     const double* Lp = L + P * n * n;
+    // blocks (C, A) and (A, C) by rows, all loads in flight; the first is stored transposed
+    double ca[4], ac[4];
 #pragma unroll
-    for (int e4 = 0; e4 < 4; ++e4) {             // block (C, A) by rows, stored transposed
+    for (int e4 = 0; e4 < 4; ++e4) {
       const int e = tid + 256 * e4, r = e >> 5, q = e & 31;
-      const int c = C * 32 + r, a = A * 32 + q;
-      tr[q][r] = (c < v && a < v) ? Lp[(int64_t)(o + c) * n + o + a] : 0.0;
+      ca[e4] = (C * 32 + r < v && A * 32 + q < v) ? Lp[(int64_t)(o + C * 32 + r) * n + o + A * 32 + q] : 0.0;
+      ac[e4] = (A * 32 + r < v && C * 32 + q < v) ? Lp[(int64_t)(o + A * 32 + r) * n + o + C * 32 + q] : 0.0;
+    }
+#pragma unroll
+    for (int e4 = 0; e4 < 4; ++e4) {
+      const int e = tid + 256 * e4, r = e >> 5, q = e & 31;
+      tr[q][r] = ca[e4];
     }
     __syncthreads();
 #pragma unroll
-    for (int e4 = 0; e4 < 4; ++e4) {             // block (A, C) by rows, against it
+    for (int e4 = 0; e4 < 4; ++e4) {
       const int e = tid + 256 * e4, r = e >> 5, q = e & 31;
       const int a = A * 32 + r, c = C * 32 + q;
       if (a < c && c < v) {
-        const double lac = Lp[(int64_t)(o + a) * n + o + c], lca = tr[r][q];
+        const double lac = ac[e4], lca = tr[r][q];
         d2 += (lac - lca) * (lac - lca);
         l2 += lac * lac + lca * lca;
       }

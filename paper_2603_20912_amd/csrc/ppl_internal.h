@@ -155,7 +155,8 @@ struct ppl_plan_s {
   std::vector<int64_t> tiles_n;        // tiles in each batch's list, [set][batch]
   int tile_sets = 1;                   // 2 when the FP64 copy builds on a tile of its own
   const double* L_last = nullptr;
-  double* host_red = nullptr;          // mapped host memory for the iteration's sums (kHostRed doubles)
+  double* host_red = nullptr;          // mapped host memory for sums that the host reads (kHostRed doubles)
+  hipEvent_t ev_check = nullptr;       // after the symmetry check's sums
   bool setup_done = false;
   // kernel timing
   struct ProfRec {
@@ -424,7 +425,7 @@ int mlp_infer_launch(hipStream_t s, const float* prm, int o, int v, const double
 int sumsq_launch(hipStream_t s, const double* x, int64_t n, double* partials, double* red_out);
 
 constexpr int kReduceBlocks = 1024;
-constexpr int kHostRed = 4 + kDiisMax;
+constexpr int kHostRed = 4 + kDiisMax + 4;   // sums, DIIS products, symmetry check
 constexpr int kReduceThreads = 256;
 
 }  // namespace ppl

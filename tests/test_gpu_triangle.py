@@ -128,3 +128,22 @@ def test_bf16_rows_completed_from_triangles(P, monkeypatch, prec, bound, o, v, n
         eng.close()
     assert rel(out[0], O.ppl(s["L"], o, t)) < bound
     assert np.array_equal(out[0], out[1]) and np.array_equal(out[0], out[2])
+
+
+@pytest.mark.parametrize("kw", [dict(prec="fp64"), dict(prec="bf16x6"), dict(prec="fp32", keep_fp64=True)])
+def test_refused_vectors_leave_the_operands(P, kw):
+    """The staging of a build runs while the host waits for the symmetry check: a refused L must
+    leave V+- as they were."""
+    o, v, naux = SIZES[0]
+    say(f"refused vectors {kw}")
+    s = S.make_system(o, v, naux, 86)
+    t = dev(S.make_amplitudes(o, v, 87))
+    eng = P.PPL(o, v, naux, **kw)
+    eng.build(dev(s["L"]))
+    before = eng.contract(t).cpu().numpy()
+    bad = s["L"].copy()
+    bad[0, o, o + 1] += 1.0
+    with pytest.raises(P.PPLError):
+        eng.build(dev(bad))
+    assert np.array_equal(eng.contract(t).cpu().numpy(), before)
+    eng.close()
