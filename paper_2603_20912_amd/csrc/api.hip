@@ -435,7 +435,7 @@ static int build_one(ppl_plan_t p, OperandSet& s, const double* L, int bi, bool 
       return fail(PPL_E_STATE, "build step %d exceeds the V+- rows of the plan", bi);
   }
   if (p->sym_build) {
-    // natural GEMM layout, then upper triangles (FP64, FP32), completed to whole rows in BF16
+    // natural GEMM layout, then upper triangles
     {
       ProfScope ps(p, PPL_PROF_BUILD_GEMM, build_flops(p, b.a0, b.a1));
       PPL_TRY(gemm_build_sym(st, s.prec, tile, p->v, b.a0, b.a1, p->naux, at<void>(p, s.xt),
@@ -449,11 +449,8 @@ static int build_one(ppl_plan_t p, OperandSet& s, const double* L, int bi, bool 
                            at<double>(p, s.vp), p->ldp, at<double>(p, s.vm), p->ldm);
     void* vp_lo = s.vp_lo.bytes ? at<void>(p, s.vp_lo) : nullptr;
     void* vm_lo = s.vm_lo.bytes ? at<void>(p, s.vm_lo) : nullptr;
-    PPL_TRY(pack_vpm_tri(st, s.prec, p->v, b.a0, b.a1, at<void>(p, p->g), W * (W + 1) / 2, at<int64_t>(p, p->cube_off),
-                         at<void>(p, s.vp), vp_lo, p->ldp, at<void>(p, s.vm), vm_lo, p->ldm));
-    if (s.tri) return PPL_OK;
-    PPL_TRY(mirror_rows(st, s.prec, at<void>(p, s.vp), vp_lo, p->Pp, p->ldp, b.p0, b.p1));
-    return mirror_rows(st, s.prec, at<void>(p, s.vm), vm_lo, p->Pm, p->ldm, b.q0, b.q1);
+    return pack_vpm_tri(st, s.prec, p->v, b.a0, b.a1, at<void>(p, p->g), W * (W + 1) / 2, at<int64_t>(p, p->cube_off),
+                        at<void>(p, s.vp), vp_lo, p->ldp, at<void>(p, s.vm), vm_lo, p->ldm);
   }
   {
     ProfScope ps(p, PPL_PROF_BUILD_GEMM, build_flops(p, b.a0, b.a1));
@@ -891,9 +888,7 @@ static int plan_create(const ppl_desc_t* d, ppl_plan_t* out, bool external_g) {
   if (need <= budget) {
     p->resident = true;
     if (p->sym_build) build_column_order(p->v, p->cols_host);
-    // the set that the build fills: a mixed plan's low-precision one is rounded from the FP64 one
-    for (OperandSet& s : p->ops)
-      s.tri = s.present && p->sym_build && (s.prec == PPL_FP64 || (s.prec == PPL_FP32 && !p->keep_fp64));
+    for (OperandSet& s : p->ops) s.tri = s.present && p->sym_build;
   } else {
     // streaming: upper-triangle steps contracted as U and U^T (FP64 plans with one operand set)
     p->sym_build = p->sym_build && p->prec == PPL_FP64 && !p->keep_fp64;

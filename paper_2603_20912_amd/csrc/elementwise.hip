@@ -246,9 +246,9 @@ static_assert(kCube == 16, "the cube packing splits an element index into 4-bit 
 // a <= x <= y (pr0 = pair(a0, a0)); T is symmetric in (x, y) since the Cholesky vectors are. For
 // row (ab) and column (cd) >= (ab) in packed order
 //   V+[ab][cd] = ((ac|bd) + (ad|bc)) / 2,   V-[ab][cd] = ((ac|bd) - (ad|bc)) / 2  (a < b, c < d).
-// Entries below the diagonal: FP64 and FP32 get those inside a diagonal block (kTriBlock) here and
-// need no others; BF16 gets them all from mirror_rows; a streaming step (STEP, EpiStep) has none,
-// halves its diagonal and stores its rows from global rows row0p / row0m on. One workgroup per cube of 16 x 16 x 16
+// Of the entries below the diagonal those inside a diagonal block (kTriBlock) are written; a
+// streaming step (STEP, EpiStep) has none, halves its diagonal and stores its rows from global rows
+// row0p / row0m on. One workgroup per cube of 16 x 16 x 16
 // indices (b, c, d), thread (c, d), b unrolled, so that the rows are written along d. (ac|bd) is
 // read in that shape where b <= d (contiguous along d); (ad|bc) is contiguous along c (b <= c) or
 // b and goes through one LDS array s[b][d][c], and where b > d so does (ac|bd), contiguous along
@@ -258,7 +258,7 @@ static_assert(kCube == 16, "the cube packing splits an element index into 4-bit 
 // (FP64; four in FP32, three in BF16): 1.73 ms against 1.96 with all that fit and 2.01 with two, at
 // v = 200 in one step (3.2 GB written, 1.6 read); FP32 at v = 151 0.36 ms against 0.40; BF16x6 at
 // v = 137 0.353 against 0.435 with all and 0.391 with four. Writing every mirror entry here, along
-// b, took 3.35 ms (FP64), 0.58 ms (FP32) and 0.845 ms (BF16x6; 0.62 with mirror_rows).
+// b, took 3.35 ms (FP64), 0.58 ms (FP32) and 0.845 ms (BF16x6).
 template <class Tg, int PREC, bool STEP>
 __global__ void __launch_bounds__(kPackThreads)
 pack_vpm_tri_kernel(int v, int a0, int a1, const Tg* __restrict__ T, int64_t ldt, const int64_t* __restrict__ off,
@@ -319,7 +319,7 @@ pack_vpm_tri_kernel(int v, int a0, int a1, const Tg* __restrict__ T, int64_t ldt
     const int64_t rm = pair_minus(a, b0, v), cm = pair_minus(c, d, v);
     // some mirror entry of the cube lies in a diagonal block (the same for every thread)
     const int e0 = d0 > c0 ? d0 : c0, bl = b0 + C < v ? b0 + C - 1 : v - 1;
-    const bool near = (PREC == PPL_FP64 || PREC == PPL_FP32) && !STEP &&
+    const bool near = !STEP &&
                       (pair_plus(c0, e0, v) / kTriBlock <= pair_plus(a, bl, v) / kTriBlock ||
                        pair_minus(c0, e0 > c0 ? e0 : c0 + 1, v) / kTriBlock <= pair_minus(a, bl, v) / kTriBlock);
 #pragma unroll
@@ -401,68 +401,6 @@ int pack_vpm_step(hipStream_t s, int v, const Batch& b, const double* T, int64_t
   if (b.q1 > b.q0)
     hipLaunchKernelGGL(step_zero_kernel, dim3((unsigned)(b.q1 - km + kStepRows)), dim3(256), 0, s, vm, ldm, km, b.q0,
                        b.q1);
-  PPL_LAUNCH_CHECK();
-  return PPL_OK;
-}
-
-// V[r][q] = V[q][r] for q in [q0, q1), q < r < n: the entries below the diagonal of a build step's
-// rows, for each bf16 plane (planes lie equally far apart: hi, lo and, in BF16x6, 2 lo - hi).
-// One 64 x 64 block pair (I >= J) and plane per workgroup, through LDS: rows J, columns I are read
-// and rows I, columns J written along contiguous rows, as 16-byte vectors where the block is whole
-// (rows of V are 128-byte multiples, so blocks start aligned). Bound by memory: 0.27 ms at
-// v = 137 for three planes (0.53 GB each way), 3.9 TB/s.
-__global__ void __launch_bounds__(256)
-mirror_rows_kernel(uint16_t* hi, uint16_t* lo, int64_t n, int64_t ld, int64_t q0, int64_t q1, int64_t t0) {
-  __shared__ uint16_t sh[64][65];
-  // blocks counted from the last: t = j (j + 1) / 2 + i, j = T - 1 - J, i = T - 1 - I
-  const int64_t T = (n + 63) / 64, t = t0 + blockIdx.x;
-  int64_t j = (int64_t)((sqrt(8.0 * (double)t + 1.0) - 1.0) * 0.5);
-  while (j * (j + 1) / 2 > t) --j;
-  while ((j + 1) * (j + 2) / 2 <= t) ++j;
-  const int64_t r0 = (T - 1 - (t - j * (j + 1) / 2)) * 64, c0 = (T - 1 - j) * 64;
-  uint16_t* V = hi + (int64_t)blockIdx.y * (lo - hi);
-  const int tid = threadIdx.x;
-  if (r0 > c0 && r0 + 64 <= n && c0 >= q0 && c0 + 64 <= q1) {
-    union Vec { uint4 u; uint16_t e[8]; };
-    for (int x = tid; x < 64 * 8; x += 256) {
-      const int ql = x / 8, w = x % 8;
-      Vec y;
-      y.u = *reinterpret_cast<const uint4*>(&V[(c0 + ql) * ld + r0 + w * 8]);
-#pragma unroll
-      for (int k = 0; k < 8; ++k) sh[ql][w * 8 + k] = y.e[k];
-    }
-    __syncthreads();
-    for (int x = tid; x < 64 * 8; x += 256) {
-      const int rl = x / 8, w = x % 8;
-      Vec y;
-#pragma unroll
-      for (int k = 0; k < 8; ++k) y.e[k] = sh[w * 8 + k][rl];
-      *reinterpret_cast<uint4*>(&V[(r0 + rl) * ld + c0 + w * 8]) = y.u;
-    }
-    return;
-  }
-  for (int e = tid; e < 64 * 64; e += 256) {
-    const int ql = e >> 6, rl = e & 63;
-    const int64_t q = c0 + ql, r = r0 + rl;
-    if (q >= q0 && q < q1 && r < n && q < r) sh[ql][rl] = V[q * ld + r];
-  }
-  __syncthreads();
-  for (int e = tid; e < 64 * 64; e += 256) {
-    const int rl = e >> 6, ql = e & 63;
-    const int64_t r = r0 + rl, q = c0 + ql;
-    if (q >= q0 && q < q1 && r < n && q < r) V[r * ld + q] = sh[ql][rl];
-  }
-}
-
-int mirror_rows(hipStream_t s, int prec, void* hi, void* lo, int64_t n, int64_t ld, int64_t q0, int64_t q1) {
-  if (q1 <= q0 || n <= 1) return PPL_OK;
-  const int64_t T = (n + 63) / 64, ja = T - 1 - (q1 - 1) / 64, jb = T - q0 / 64;
-  const int64_t t0 = ja * (ja + 1) / 2, blocks = jb * (jb + 1) / 2 - t0;
-  if (blocks > 0x7fffffffLL) return fail(PPL_E_ARG, "mirror of %lld rows too large", (long long)n);
-  if ((prec != PPL_BF16X3 && prec != PPL_BF16X6) || ld % 8 != 0 || (uintptr_t)hi % 16 != 0 || (uintptr_t)lo % 16 != 0)
-    return fail(PPL_E_ARG, "mirror_rows: not bf16 planes of 16-byte aligned rows");
-  hipLaunchKernelGGL(mirror_rows_kernel, dim3((unsigned)blocks, prec == PPL_BF16X6 ? 3 : 2), dim3(256), 0, s,
-                     (uint16_t*)hi, (uint16_t*)lo, n, ld, q0, q1, t0);
   PPL_LAUNCH_CHECK();
   return PPL_OK;
 }
@@ -699,57 +637,34 @@ __device__ inline void put4(void* hi, void* lo, int64_t i, const double (&x)[4])
   }
 }
 
-// A symmetric n x n FP64 matrix stored as its upper triangle (kTriBlock; rows of ld, a multiple
-// of 64) to the whole matrix in an operand precision, zero padding included: one workgroup per
-// 64 x 64 block on or above the diagonal, read once, rounded and written both ways round.
+// An n x n FP64 matrix stored as its upper triangle (kTriBlock; rows of ld, a multiple of 64) to the
+// same in an operand precision: one workgroup per row and eighth of the columns, four entries per
+// thread and step. Bound by memory: (20, 200) to BF16x3 516 us per sign for 2.4 GB (643 with the mirror half).
 template <int PREC>
 __global__ void __launch_bounds__(256)
-convert_tri_kernel(const double* __restrict__ src, int64_t n, int64_t ld, void* dh, void* dl) {
-  __shared__ double sh[64][65];
-  const int64_t t = blockIdx.x;               // block (I <= J) of the packed upper triangle, J slowest
-  int64_t J = (int64_t)((sqrt(8.0 * (double)t + 1.0) - 1.0) * 0.5);
-  while (J * (J + 1) / 2 > t) --J;
-  while ((J + 1) * (J + 2) / 2 <= t) ++J;
-  const int64_t I = t - J * (J + 1) / 2, r0 = I * 64, q0 = J * 64;
-  const int c4 = (threadIdx.x & 15) * 4;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const int rl = (threadIdx.x >> 4) + 16 * e;
-    double x[4] = {0, 0, 0, 0};
-    if (r0 + rl < n) {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) x[k] = src[(r0 + rl) * ld + q0 + c4 + k];
-      put4<PREC>(dh, dl, (r0 + rl) * ld + q0 + c4, x);
-    }
-    if (I < J)
-#pragma unroll
-      for (int k = 0; k < 4; ++k) sh[rl][c4 + k] = x[k];
-  }
-  if (I == J) return;                         // a diagonal block is whole
-  __syncthreads();
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const int ql = (threadIdx.x >> 4) + 16 * e;
-    if (q0 + ql >= n) continue;
+convert_tri_kernel(const double* __restrict__ src, int64_t ld, void* dh, void* dl) {
+  const int64_t r = blockIdx.x, b = r / kTriBlock * kTriBlock;
+  const int64_t seg = ((ld - b) / 4 + gridDim.y - 1) / gridDim.y * 4;
+  const int64_t q0 = b + blockIdx.y * seg, q1 = q0 + seg < ld ? q0 + seg : ld;
+  for (int64_t q = q0 + threadIdx.x * 4; q < q1; q += 1024) {
     double x[4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) x[k] = sh[c4 + k][ql];
-    put4<PREC>(dh, dl, (q0 + ql) * ld + r0 + c4, x);
+    for (int k = 0; k < 4; ++k) x[k] = src[r * ld + q + k];
+    put4<PREC>(dh, dl, r * ld + q, x);
   }
 }
 
 int convert_tri(hipStream_t s, int prec, const double* src, int64_t n, int64_t ld, void* dst, void* dst_lo) {
   if (n <= 0) return PPL_OK;
-  const int64_t nb = (n + 63) / 64, blocks = nb * (nb + 1) / 2;
-  if (ld != nb * 64 || blocks > 0x7fffffffLL)
+  if (ld % 64 != 0 || ld < n || n > 0x7fffffffLL)
     return fail(PPL_E_ARG, "convert_tri: %lld rows of %lld elements", (long long)n, (long long)ld);
-  const dim3 grid((unsigned)blocks);
+  const dim3 grid((unsigned)n, (unsigned)std::max<int64_t>(1, ld / 4096));
   if (prec == PPL_FP32)
-    hipLaunchKernelGGL(convert_tri_kernel<PPL_FP32>, grid, dim3(256), 0, s, src, n, ld, dst, dst_lo);
+    hipLaunchKernelGGL(convert_tri_kernel<PPL_FP32>, grid, dim3(256), 0, s, src, ld, dst, dst_lo);
   else if (prec == PPL_BF16X3)
-    hipLaunchKernelGGL(convert_tri_kernel<PPL_BF16X3>, grid, dim3(256), 0, s, src, n, ld, dst, dst_lo);
+    hipLaunchKernelGGL(convert_tri_kernel<PPL_BF16X3>, grid, dim3(256), 0, s, src, ld, dst, dst_lo);
   else if (prec == PPL_BF16X6)
-    hipLaunchKernelGGL(convert_tri_kernel<PPL_BF16X6>, grid, dim3(256), 0, s, src, n, ld, dst, dst_lo);
+    hipLaunchKernelGGL(convert_tri_kernel<PPL_BF16X6>, grid, dim3(256), 0, s, src, ld, dst, dst_lo);
   else
     return fail(PPL_E_ARG, "convert_tri: unknown precision %d", prec);
   PPL_LAUNCH_CHECK();

@@ -320,12 +320,6 @@ struct EpiBuildT {
 #ifndef PPL_PREFETCH
 #define PPL_PREFETCH 0
 #endif
-#ifndef PPL_BF3_DIRECT
-#define PPL_BF3_DIRECT 1
-#endif
-#ifndef PPL_BF6_DIRECT
-#define PPL_BF6_DIRECT 1
-#endif
 #ifndef PPL_BUILD_DIRECT3
 #define PPL_BUILD_DIRECT3 1
 #endif
@@ -334,8 +328,6 @@ constexpr int kFragVec = PPL_FRAG_VEC;
 constexpr int kSchedFence = PPL_SCHED_FENCE;
 constexpr int kDirectLds = PPL_DIRECT_LDS;   // 1: chunks go global -> LDS without registers (layout 1 only)
 constexpr int kPrefetch = PPL_PREFETCH;      // chunks in flight in registers: 1, 2, or 0 = per tile (below)
-constexpr int kBf3Direct = PPL_BF3_DIRECT;   // 1: BF16x3 chunks go global -> LDS, three stages, two in flight
-constexpr int kBf6Direct = PPL_BF6_DIRECT;   // 1: BF16x6 chunks go global -> LDS, two stages
 static_assert(!kDirectLds || kLdsLayout == 1, "direct LDS loads need the unpadded swizzled layout");
 
 template <class T, int WM, int WN, int WAVES_M, int WAVES_N, int KC>
@@ -963,6 +955,45 @@ gemm_nt_pair_kernel(PairSide<T> p0, PairSide<T> p1, int64_t grid0) {
 // x = hi + lo with hi = bf16(x), lo = bf16(x - hi); x*y ~ hi*hi + hi*lo + lo*hi,
 // the two small cross products accumulated in their own FP32 register set and
 // added to the hi*hi set once at the end.
+// First chunk of a job that reads B along its rows: a triangular operand (kTriBlock) gives the chunks
+// k < n0 from its rows k.
+template <int KC, class Epi>
+__device__ __forceinline__ int64_t below_diagonal(const TileJob& job, const Epi& epi) {
+  int64_t cd = job.kc0;
+  if constexpr (Epi::kTri)
+    if (epi.tri) {
+      cd = job.n0 / KC;
+      cd = cd < job.kc0 ? job.kc0 : (cd > job.kc1 ? job.kc1 : cd);
+    }
+  return cd;
+}
+
+// A staged K-major plane of a bf16 B chunk (rows k of BN elements, in blocks of 16 columns). A
+// fragment of block j, eight k of one column per lane, is read by two transposing reads of
+// 4 x 16 elements per 16 lanes; row k holds block b at b ^ swz(k), so that the sixteen rows of one
+// read lie on different banks.
+// Against whole rows of V+-: R+- at (13, 137) in BF16x6 134 us each (164), BF16x3 on 32 x 128 at that
+// size 98 (135), R+ at (40, 400) in BF16x3 on 224 x 128 29.4 ms (29.5); half the bytes, and no pass
+// that writes the mirror half (222 us of an evaluation at (13, 137)).
+template <int BN>
+struct KMajor {
+  __host__ __device__ static constexpr int swz(int k) {
+    return BN >= 128 ? (k & 3) | ((k >> 3) & 1) << 2 : ((k >> 1) & 1) | ((k >> 3) & 1) << 1;
+  }
+  __device__ static int at(int lane, int block) {
+    const int k = 8 * (lane >> 4) + ((lane & 15) >> 2);
+    return k * BN + (block ^ swz(k)) * 16 + 4 * (lane & 3);
+  }
+  __device__ __forceinline__ static bf8 frag(const __bf16* p) {
+    typedef short s4 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) s4 lds_s4;
+    union { s4 h[2]; bf8 v; } u;
+    u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)p);
+    u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)(p + 4 * BN));
+    return u.v;
+  }
+};
+
 template <int WM, int WN, int WAVES_M, int WAVES_N, int KC>
 struct Bf3Geom {
   static constexpr int NT = 64 * WAVES_M * WAVES_N;
@@ -974,18 +1005,17 @@ struct Bf3Geom {
   static constexpr int LDSR = KC;
   static constexpr int VPR = KC / 8;
   __host__ __device__ static constexpr int key(int r) { return VPR >= 8 ? (r & 7) : ((r >> 1) & 3); }
-  static constexpr int LDS_A = 2 * BM * LDSR, LDS_B = 2 * BN * LDSR;   // per plane, two buffers
-  // direct loads: one stage holds the hi and lo planes of A, then those of B
+  // one stage holds the hi and lo planes of A, then those of B
   static constexpr int STAGE = 2 * (BM + BN) * LDSR;
-  static_assert(!kBf3Direct || 3 * STAGE * 2 <= 160 * 1024, "three BF16x3 stages exceed the LDS");
+  static_assert(3 * STAGE * 2 <= 160 * 1024, "three BF16x3 stages exceed the LDS");
 };
 
 // The tile with chunks moved straight from global memory into LDS (global_load_lds, 16
 // bytes a lane), in three stages: step k multiplies chunk k while chunk k+1 is still
 // arriving and issues chunk k+2, so that the wait at the end of a step is never for
 // loads issued in that step, and no registers or LDS store instructions stage them
-// (measured at (40, 400, 1200), R+ on tile 9: 28.7 ms against 38.5 ms for the
-// register-staged two-buffer loop, which stays as the PPL_BF3_DIRECT=0 build). One
+// (measured at (40, 400, 1200), R+ on tile 9: 28.7 ms against 38.5 ms for a
+// register-staged two-buffer loop). One
 // wave instruction fills 64 / VPR whole staged rows of one plane (1 KB); lane l loads the
 // global vector that the swizzled layout keeps at slot l. The 2 (BM + BN) / (64 / VPR)
 // instructions of a chunk are dealt round-robin over the waves; where they do not divide
@@ -1005,6 +1035,7 @@ __device__ __forceinline__ void bf3_tile_body_direct(const TileJob& job, int64_t
   constexpr int GA = BM / RPI, GB = BN / RPI;      // instructions per plane and chunk
   constexpr int GT = 2 * (GA + GB);                // instructions per chunk
   constexpr int NI = (GT + NW - 1) / NW;           // per wave
+  using Km = KMajor<BN>;
   static_assert(64 % VPR == 0 && BM % RPI == 0 && BN % RPI == 0 && GT >= NW, "direct LDS geometry");
   static_assert(KC == 32 || KC % 64 == 0, "the swizzle permutes aligned groups of 4 (or 8) 16-byte vectors");
   const int lane = threadIdx.x & 63;
@@ -1013,33 +1044,48 @@ __device__ __forceinline__ void bf3_tile_body_direct(const TileJob& job, int64_t
   const int lr = lane / VPR, slot = lane % VPR;
 
   // instruction q = wave + i NW of a chunk (q - GT past the end): plane Ah (q < GA), Al,
-  // Bh, then Bl; src is this lane's global vector, dst the instruction's 1 KB in a stage
+  // Bh, then Bl; src is this lane's global vector, dst the instruction's 1 KB in a stage; for B rows n (NN false) or B rows k (NN true), from chunk c0 on
   const __bf16* src[NI];
   int dst[NI];
+  auto aim = [&](auto nn, int64_t c0) __attribute__((always_inline)) {
+    constexpr bool NN = decltype(nn)::value;
 #pragma unroll
-  for (int i = 0; i < NI; ++i) {
-    int q = wave + i * NW;
-    if (q >= GT) q -= GT;
-    src[i] = Ah;
-    dst[i] = 0;
-    if (q < 2 * GA) {
-      const int plane = q / GA, g = q % GA, r = g * RPI + lr;
-      int64_t gr = job.m0 + r;
-      if (gr > M - 1) gr = M - 1;
-      src[i] = (plane ? Al : Ah) + epi.arow(gr) * lda + (slot ^ G::key(r)) * 8 + job.kc0 * KC;
-      dst[i] = (plane * BM + g * RPI) * LDSR;
-    } else if (q < GT) {
-      const int plane = (q - 2 * GA) / GB, g = (q - 2 * GA) % GB, r = g * RPI + lr;
-      int64_t gr = job.n0 + r;
-      if (gr > N - 1) gr = N - 1;
-      src[i] = (plane ? Bl : Bh) + epi.brow(gr) * ldb + (slot ^ G::key(r)) * 8 + job.kc0 * KC;
-      dst[i] = (2 * BM + plane * BN + g * RPI) * LDSR;
+    for (int i = 0; i < NI; ++i) {
+      int q = wave + i * NW;
+      if (q >= GT) q -= GT;
+      src[i] = Ah;
+      dst[i] = 0;
+      if (q < 2 * GA) {
+        const int plane = q / GA, g = q % GA, r = g * RPI + lr;
+        int64_t gr = job.m0 + r;
+        if (gr > M - 1) gr = M - 1;
+        src[i] = (plane ? Al : Ah) + epi.arow(gr) * lda + (slot ^ G::key(r)) * 8 + c0 * KC;
+        dst[i] = (plane * BM + g * RPI) * LDSR;
+      } else if (q < GT) {
+        const int plane = (q - 2 * GA) / GB, g = (q - 2 * GA) % GB;
+        dst[i] = (2 * BM + plane * BN + g * RPI) * LDSR;
+        if constexpr (NN) {
+          const int id = g * 64 + lane, kr = id / (BN / 8), cv = id % (BN / 8);
+          src[i] = (plane ? Bl : Bh) + (c0 * KC + kr) * ldb + job.n0 + (cv ^ (Km::swz(kr) * 2)) * 8;
+        } else {
+          const int r = g * RPI + lr;
+          int64_t gr = job.n0 + r;
+          if (gr > N - 1) gr = N - 1;
+          src[i] = (plane ? Bl : Bh) + epi.brow(gr) * ldb + (slot ^ G::key(r)) * 8 + c0 * KC;
+        }
+      }
     }
-  }
-  auto issue = [&](int64_t c, __bf16* st) __attribute__((always_inline)) {
+  };
+  // chunk c (relative to aim's) into stage st
+  auto issue = [&](auto nn, int64_t c, __bf16* st) __attribute__((always_inline)) {
+    constexpr bool NN = decltype(nn)::value;
 #pragma unroll
-    for (int i = 0; i < NI; ++i)
-      __builtin_amdgcn_global_load_lds((global_cvoid_t*)(src[i] + c * KC), (lds_void_t*)(st + dst[i]), 16, 0, 0);
+    for (int i = 0; i < NI; ++i) {
+      int q = wave + i * NW;
+      if (q >= GT) q -= GT;
+      const int64_t off = NN && q >= 2 * GA ? c * (KC * ldb) : c * KC;
+      __builtin_amdgcn_global_load_lds((global_cvoid_t*)(src[i] + off), (lds_void_t*)(st + dst[i]), 16, 0, 0);
+    }
   };
   // Wait until at most one chunk of this wave's loads is outstanding (vmcnt counts loads
   // in issue order), or none. The waits are s_waitcnt builtins (vmcnt only: expcnt and
@@ -1073,12 +1119,15 @@ __device__ __forceinline__ void bf3_tile_body_direct(const TileJob& job, int64_t
   const int arow = (wm * WM * 16 + (lane & 15)) * LDSR;
   const int brow = (2 * BM + wn * WN * 16 + (lane & 15)) * LDSR;
   const int fsw = G::key(lane & 15);
-  const int64_t nk = job.kc1 - job.kc0;
+  int kcol[WN];                                    // K-major: this lane's first row and column of block j
+#pragma unroll
+  for (int j = 0; j < WN; ++j) kcol[j] = 2 * BM * LDSR + Km::at(lane, wn * WN + j);
 
   // Multiply the chunk staged in st; when go, start chunk c into stage nx between the
   // LDS reads of the first 32-wide K group and its MFMAs (the empty asm keeps the reads
-  // first, so that a wait the compiler may place before them never covers chunk c).
-  auto compute = [&](const __bf16* __restrict__ st, bool go, int64_t c, __bf16* nx) __attribute__((always_inline)) {
+  // first, so that a wait the compiler may place before them never covers that chunk).
+  auto compute = [&](auto nn, const __bf16* __restrict__ st, bool go, int64_t c, __bf16* nx) __attribute__((always_inline)) {
+    constexpr bool NN = decltype(nn)::value;
 #pragma unroll
     for (int kk = 0; kk < KC; kk += 32) {
       const int col = ((((kk) >> 3) + (lane >> 4)) ^ fsw) * 8;
@@ -1090,12 +1139,17 @@ __device__ __forceinline__ void bf3_tile_body_direct(const TileJob& job, int64_t
       }
 #pragma unroll
       for (int j = 0; j < WN; ++j) {
-        bh[j] = *reinterpret_cast<const bf8*>(&st[brow + j * 16 * LDSR + col]);
-        bl[j] = *reinterpret_cast<const bf8*>(&st[BN * LDSR + brow + j * 16 * LDSR + col]);
+        if constexpr (NN) {
+          bh[j] = Km::frag(st + kcol[j] + kk * BN);
+          bl[j] = Km::frag(st + BN * LDSR + kcol[j] + kk * BN);
+        } else {
+          bh[j] = *reinterpret_cast<const bf8*>(&st[brow + j * 16 * LDSR + col]);
+          bl[j] = *reinterpret_cast<const bf8*>(&st[BN * LDSR + brow + j * 16 * LDSR + col]);
+        }
       }
       if (kk == 0) {
         asm volatile("" ::: "memory");
-        if (go) issue(c, nx);
+        if (go) issue(nn, c, nx);
       }
 #pragma unroll
       for (int i = 0; i < WM; ++i)
@@ -1115,41 +1169,51 @@ __device__ __forceinline__ void bf3_tile_body_direct(const TileJob& job, int64_t
   // across the back edge); placed before that step's own loads it covers only chunk
   // kt+1, and a loop trip of 3 U steps pays it once.
   constexpr int U = 2;
-  issue(0, st0);
-  if (nk > 1) {
-    issue(1, st1);
-    wait_one();
-  } else {
-    wait_all();
-  }
-  meet();
-  int64_t kt = 0;
-  for (; kt + 3 * U + 1 < nk; kt += 3 * U) {   // 3 U steps whose k+2 exists
+  auto run = [&](auto nn, int64_t c0, int64_t c1) __attribute__((always_inline)) {   // chunks [c0, c1)
+    const int64_t n = c1 - c0;
+    aim(nn, c0);
+    issue(nn, 0, st0);
+    if (n > 1) {
+      issue(nn, 1, st1);
+      wait_one();
+    } else {
+      wait_all();
+    }
+    meet();
+    int64_t kt = 0;
+    for (; kt + 3 * U + 1 < n; kt += 3 * U) {   // 3 U steps whose k+2 exists
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      compute(st0, true, kt + 3 * u + 2, st2);
-      wait_one();
-      meet();
-      compute(st1, true, kt + 3 * u + 3, st0);
-      wait_one();
-      meet();
-      compute(st2, true, kt + 3 * u + 4, st1);
-      wait_one();
-      meet();
+      for (int u = 0; u < U; ++u) {
+        compute(nn, st0, true, kt + 3 * u + 2, st2);
+        wait_one();
+        meet();
+        compute(nn, st1, true, kt + 3 * u + 3, st0);
+        wait_one();
+        meet();
+        compute(nn, st2, true, kt + 3 * u + 4, st1);
+        wait_one();
+        meet();
+      }
     }
-  }
-  // the last steps (at most 3 U + 1): chunk kt in st0, kt+1 (if any) in flight to st1
-  for (int64_t j = kt; j < nk; ++j) {
-    const int sj = (int)((j - kt) % 3);
-    const __bf16* cur = sj == 0 ? st0 : (sj == 1 ? st1 : st2);
-    __bf16* nx = sj == 0 ? st2 : (sj == 1 ? st0 : st1);   // the stage of chunk j+2
-    compute(cur, j + 2 < nk, j + 2, nx);
-    if (j + 1 < nk) {
-      if (j + 2 < nk) wait_one();
-      else wait_all();
-      meet();
+    // the last steps (at most 3 U + 1): chunk kt in st0, kt+1 (if any) in flight to st1
+    for (int64_t j = kt; j < n; ++j) {
+      const int sj = (int)((j - kt) % 3);
+      const __bf16* cur = sj == 0 ? st0 : (sj == 1 ? st1 : st2);
+      __bf16* nx = sj == 0 ? st2 : (sj == 1 ? st0 : st1);   // the stage of chunk j+2
+      compute(nn, cur, j + 2 < n, j + 2, nx);
+      if (j + 1 < n) {
+        if (j + 2 < n) wait_one();
+        else wait_all();
+        meet();
+      }
     }
+  };
+  const int64_t cd = below_diagonal<KC>(job, epi);
+  if constexpr (Epi::kTri) {
+    if (job.kc0 < cd) run(std::true_type{}, job.kc0, cd);
+    if (job.kc0 < cd && cd < job.kc1) meet();      // every wave has read the last stages
   }
+  if (cd < job.kc1) run(std::false_type{}, cd, job.kc1);
 
 #pragma unroll
   for (int i = 0; i < WM; ++i) {
@@ -1168,144 +1232,6 @@ __device__ __forceinline__ void bf3_tile_body_direct(const TileJob& job, int64_t
   }
 }
 
-// One BM x BN tile over the K chunks [job.kc0, job.kc1); the s* arrays hold two LDS
-// buffers each of the hi and lo planes.
-template <int WM, int WN, int WAVES_M, int WAVES_N, int KC, class Epi>
-__device__ __forceinline__ void bf3_tile_body(const TileJob& job, int64_t M, int64_t N, const __bf16* __restrict__ Ah,
-                                              const __bf16* __restrict__ Al, int64_t lda,
-                                              const __bf16* __restrict__ Bh, const __bf16* __restrict__ Bl,
-                                              int64_t ldb, const Epi& epi, __bf16* __restrict__ sAh,
-                                              __bf16* __restrict__ sAl, __bf16* __restrict__ sBh,
-                                              __bf16* __restrict__ sBl) {
-  constexpr int NT = 64 * WAVES_M * WAVES_N;
-  constexpr int BM = 16 * WM * WAVES_M, BN = 16 * WN * WAVES_N;
-  constexpr int VEC = 8;                           // bf16 per 16-byte load
-  constexpr int LDSR = Bf3Geom<WM, WN, WAVES_M, WAVES_N, KC>::LDSR;
-  constexpr int VPR = KC / VEC;
-  constexpr int NLA = (BM * VPR + NT - 1) / NT;
-  constexpr int NLB = (BN * VPR + NT - 1) / NT;
-  static_assert(KC % 32 == 0, "bad KC");
-  const int64_t m0 = job.m0, n0 = job.n0;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave % WAVES_M, wn = wave / WAVES_M;
-
-  int64_t ga[NLA], gb[NLB];
-  int oa[NLA], ob[NLB];
-#pragma unroll
-  for (int i = 0; i < NLA; ++i) {
-    int idx = tid + i * NT;
-    if (idx >= BM * VPR) idx = BM * VPR - 1;
-    const int r = idx / VPR, kv = idx % VPR;
-    int64_t gr = m0 + r;
-    if (gr > M - 1) gr = M - 1;
-    ga[i] = epi.arow(gr) * lda + kv * VEC + job.kc0 * KC;
-    oa[i] = r * LDSR + (kv ^ Bf3Geom<WM, WN, WAVES_M, WAVES_N, KC>::key(r)) * VEC;
-  }
-#pragma unroll
-  for (int i = 0; i < NLB; ++i) {
-    int idx = tid + i * NT;
-    if (idx >= BN * VPR) idx = BN * VPR - 1;
-    const int r = idx / VPR, kv = idx % VPR;
-    int64_t gr = n0 + r;
-    if (gr > N - 1) gr = N - 1;
-    gb[i] = epi.brow(gr) * ldb + kv * VEC + job.kc0 * KC;
-    ob[i] = r * LDSR + (kv ^ Bf3Geom<WM, WN, WAVES_M, WAVES_N, KC>::key(r)) * VEC;
-  }
-  f4 acc[WM][WN], accx[WM][WN];
-#pragma unroll
-  for (int i = 0; i < WM; ++i)
-#pragma unroll
-    for (int j = 0; j < WN; ++j) {
-      acc[i][j] = f4{0, 0, 0, 0};
-      accx[i][j] = f4{0, 0, 0, 0};
-    }
-
-  // fragment rows start at multiples of 16, so a row's swizzle key is that of lane & 15
-  const int arow = (wm * WM * 16 + (lane & 15)) * LDSR;
-  const int brow = (wn * WN * 16 + (lane & 15)) * LDSR;
-  const int fsw = Bf3Geom<WM, WN, WAVES_M, WAVES_N, KC>::key(lane & 15);
-  static_assert(KC == 32 || KC % 64 == 0, "the swizzle permutes aligned groups of 4 (or 8) 16-byte vectors");
-  const int64_t nk = job.kc1 - job.kc0;
-
-// element offset of this lane's 8-element fragment vector at K offset kk of a staged row
-#define PPL_BF3_COL(kk) (((((kk) >> 3) + (lane >> 4)) ^ fsw) * 8)
-#define PPL_BF3_LOAD(k0)                                                     \
-  _Pragma("unroll") for (int i = 0; i < NLA; ++i) {                          \
-    rah[i] = *reinterpret_cast<const uint4*>(Ah + ga[i] + (k0));             \
-    ral[i] = *reinterpret_cast<const uint4*>(Al + ga[i] + (k0));             \
-  }                                                                          \
-  _Pragma("unroll") for (int i = 0; i < NLB; ++i) {                          \
-    rbh[i] = *reinterpret_cast<const uint4*>(Bh + gb[i] + (k0));             \
-    rbl[i] = *reinterpret_cast<const uint4*>(Bl + gb[i] + (k0));             \
-  }
-#define PPL_BF3_STORE(buf)                                                   \
-  _Pragma("unroll") for (int i = 0; i < NLA; ++i) {                          \
-    *reinterpret_cast<uint4*>(&sAh[(buf) * (BM * LDSR) + oa[i]]) = rah[i];                    \
-    *reinterpret_cast<uint4*>(&sAl[(buf) * (BM * LDSR) + oa[i]]) = ral[i];                    \
-  }                                                                          \
-  _Pragma("unroll") for (int i = 0; i < NLB; ++i) {                          \
-    *reinterpret_cast<uint4*>(&sBh[(buf) * (BN * LDSR) + ob[i]]) = rbh[i];                    \
-    *reinterpret_cast<uint4*>(&sBl[(buf) * (BN * LDSR) + ob[i]]) = rbl[i];                    \
-  }
-#define PPL_BF3_COMPUTE(buf)                                                                   \
-  _Pragma("unroll") for (int kk = 0; kk < KC; kk += 32) {                                      \
-    bf8 ah[WM], al[WM], bh[WN], bl[WN];                                                        \
-    _Pragma("unroll") for (int i = 0; i < WM; ++i) {                                           \
-      ah[i] = *reinterpret_cast<const bf8*>(&sAh[(buf) * (BM * LDSR) + arow + i * 16 * LDSR + PPL_BF3_COL(kk)]); \
-      al[i] = *reinterpret_cast<const bf8*>(&sAl[(buf) * (BM * LDSR) + arow + i * 16 * LDSR + PPL_BF3_COL(kk)]); \
-    }                                                                                          \
-    _Pragma("unroll") for (int j = 0; j < WN; ++j) {                                           \
-      bh[j] = *reinterpret_cast<const bf8*>(&sBh[(buf) * (BN * LDSR) + brow + j * 16 * LDSR + PPL_BF3_COL(kk)]); \
-      bl[j] = *reinterpret_cast<const bf8*>(&sBl[(buf) * (BN * LDSR) + brow + j * 16 * LDSR + PPL_BF3_COL(kk)]); \
-    }                                                                                          \
-    _Pragma("unroll") for (int i = 0; i < WM; ++i)                                             \
-    _Pragma("unroll") for (int j = 0; j < WN; ++j) {                                           \
-      accx[i][j] = mfma16(al[i], bh[j], accx[i][j]);                                           \
-      accx[i][j] = mfma16(ah[i], bl[j], accx[i][j]);                                           \
-      acc[i][j] = mfma16(ah[i], bh[j], acc[i][j]);                                             \
-    }                                                                                          \
-  }
-
-  {
-    uint4 rah[NLA], ral[NLA], rbh[NLB], rbl[NLB];
-    PPL_BF3_LOAD(0)
-    PPL_BF3_STORE(0)
-  }
-  __syncthreads();
-  for (int64_t kt = 0; kt + 1 < nk; ++kt) {
-    const int buf = (int)(kt & 1);
-    uint4 rah[NLA], ral[NLA], rbh[NLB], rbl[NLB];
-    PPL_BF3_LOAD((kt + 1) * KC)
-    PPL_BF3_COMPUTE(buf)
-    PPL_BF3_STORE(buf ^ 1)
-    __syncthreads();
-  }
-  {
-    const int buf = (int)((nk - 1) & 1);
-    PPL_BF3_COMPUTE(buf)
-  }
-#undef PPL_BF3_LOAD
-#undef PPL_BF3_STORE
-#undef PPL_BF3_COMPUTE
-#undef PPL_BF3_COL
-
-#pragma unroll
-  for (int i = 0; i < WM; ++i) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int64_t m = m0 + wm * WM * 16 + i * 16 + AccOf<__bf16>::row(lane, r);
-      int64_t base;
-      bool ok;
-      epi.row(job.split, m, base, ok);
-#pragma unroll
-      for (int j = 0; j < WN; ++j) {
-        const int64_t n = n0 + wn * WN * 16 + j * 16 + (lane & 15);
-        epi.put(base, ok, n, acc[i][j][r] + accx[i][j][r]);
-      }
-    }
-  }
-}
-
 template <int WM, int WN, int WAVES_M, int WAVES_N, int KC, class Epi, class Map>
 __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N)
 gemm_nt_bf16x3_kernel(int64_t M, int64_t N, int64_t Kpad, const __bf16* __restrict__ Ah,
@@ -1314,22 +1240,13 @@ gemm_nt_bf16x3_kernel(int64_t M, int64_t N, int64_t Kpad, const __bf16* __restri
   using G = Bf3Geom<WM, WN, WAVES_M, WAVES_N, KC>;
   (void)Kpad;
   TileJob job;
-  if constexpr (kBf3Direct) {
-    // three distinct arrays, so that the compiler can tell the loads into one stage
-    // from the reads of another
-    __shared__ __attribute__((aligned(16))) __bf16 st0[G::STAGE];
-    __shared__ __attribute__((aligned(16))) __bf16 st1[G::STAGE];
-    __shared__ __attribute__((aligned(16))) __bf16 st2[G::STAGE];
-    if (!map(blockIdx.x, job)) return;
-    bf3_tile_body_direct<WM, WN, WAVES_M, WAVES_N, KC>(job, M, N, Ah, Al, lda, Bh, Bl, ldb, epi, st0, st1, st2);
-  } else {
-    __shared__ __attribute__((aligned(16))) __bf16 sAh[G::LDS_A];
-    __shared__ __attribute__((aligned(16))) __bf16 sAl[G::LDS_A];
-    __shared__ __attribute__((aligned(16))) __bf16 sBh[G::LDS_B];
-    __shared__ __attribute__((aligned(16))) __bf16 sBl[G::LDS_B];
-    if (!map(blockIdx.x, job)) return;
-    bf3_tile_body<WM, WN, WAVES_M, WAVES_N, KC>(job, M, N, Ah, Al, lda, Bh, Bl, ldb, epi, sAh, sAl, sBh, sBl);
-  }
+  // three distinct arrays, so that the compiler can tell the loads into one stage
+  // from the reads of another
+  __shared__ __attribute__((aligned(16))) __bf16 st0[G::STAGE];
+  __shared__ __attribute__((aligned(16))) __bf16 st1[G::STAGE];
+  __shared__ __attribute__((aligned(16))) __bf16 st2[G::STAGE];
+  if (!map(blockIdx.x, job)) return;
+  bf3_tile_body_direct<WM, WN, WAVES_M, WAVES_N, KC>(job, M, N, Ah, Al, lda, Bh, Bl, ldb, epi, st0, st1, st2);
 }
 
 // ------------------------------------------------------------------ the kernel (BF16 x 6)
@@ -1346,140 +1263,9 @@ template <int WM, int WN, int WAVES_M, int WAVES_N>
 struct Bf6Geom {
   static constexpr int BM = 16 * WM * WAVES_M, BN = 16 * WN * WAVES_N;
   static constexpr int LDSR = kKcBf6;
-  static constexpr int BUF_A = BM * LDSR, BUF_B = BN * LDSR;     // one buffer of one plane
-  static constexpr int LDS_A = 6 * BUF_A, LDS_B = 6 * BUF_B;     // [plane][buffer]
-  static_assert((LDS_A + LDS_B) * 2 <= 160 * 1024, "BF16x6 tile exceeds the LDS");
-  static constexpr int STAGE = 3 * (BM + BN) * LDSR;              // direct loads: all planes
+  static constexpr int STAGE = 3 * (BM + BN) * LDSR;              // one chunk, all planes
+  static_assert(2 * STAGE * 2 <= 160 * 1024, "two BF16x6 stages exceed the LDS");
 };
-
-template <int WM, int WN, int WAVES_M, int WAVES_N, class Epi>
-__device__ __forceinline__ void bf6_tile_body(const TileJob& job, int64_t M, int64_t N, const __bf16* Ah,
-                                              const __bf16* Am, int64_t lda, const __bf16* Bh,
-                                              const __bf16* Bm, int64_t ldb, const Epi& epi,
-                                              __bf16* __restrict__ sA, __bf16* __restrict__ sB) {
-  constexpr int KC = kKcBf6;
-  constexpr int NT = 64 * WAVES_M * WAVES_N;
-  using G = Bf6Geom<WM, WN, WAVES_M, WAVES_N>;
-  constexpr int BM = G::BM, BN = G::BN, LDSR = G::LDSR;
-  constexpr int VEC = 8;                           // bf16 per 16-byte load
-  constexpr int VPR = KC / VEC;                    // 4 vectors per staged row
-  constexpr int NLA = (BM * VPR + NT - 1) / NT;
-  constexpr int NLB = (BN * VPR + NT - 1) / NT;
-  const int64_t m0 = job.m0, n0 = job.n0;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave % WAVES_M, wn = wave / WAVES_M;
-  const __bf16* Ap[3] = {Ah, Am, Am + (Am - Ah)};
-  const __bf16* Bp[3] = {Bh, Bm, Bm + (Bm - Bh)};
-
-  // swizzled slot of vector kv of staged row r (64-byte rows: key (r / 2) mod 4)
-  auto key = [](int r) { return (r >> 1) & 3; };
-  int64_t ga[NLA], gb[NLB];
-  int oa[NLA], ob[NLB];
-#pragma unroll
-  for (int i = 0; i < NLA; ++i) {
-    int idx = tid + i * NT;
-    if (idx >= BM * VPR) idx = BM * VPR - 1;
-    const int r = idx / VPR, kv = idx % VPR;
-    int64_t gr = m0 + r;
-    if (gr > M - 1) gr = M - 1;
-    ga[i] = epi.arow(gr) * lda + kv * VEC + job.kc0 * KC;
-    oa[i] = r * LDSR + (kv ^ key(r)) * VEC;
-  }
-#pragma unroll
-  for (int i = 0; i < NLB; ++i) {
-    int idx = tid + i * NT;
-    if (idx >= BN * VPR) idx = BN * VPR - 1;
-    const int r = idx / VPR, kv = idx % VPR;
-    int64_t gr = n0 + r;
-    if (gr > N - 1) gr = N - 1;
-    gb[i] = epi.brow(gr) * ldb + kv * VEC + job.kc0 * KC;
-    ob[i] = r * LDSR + (kv ^ key(r)) * VEC;
-  }
-  f4 acc[WM][WN], accx[WM][WN];
-#pragma unroll
-  for (int i = 0; i < WM; ++i)
-#pragma unroll
-    for (int j = 0; j < WN; ++j) {
-      acc[i][j] = f4{0, 0, 0, 0};
-      accx[i][j] = f4{0, 0, 0, 0};
-    }
-  const int arow = (wm * WM * 16 + (lane & 15)) * LDSR;
-  const int brow = (wn * WN * 16 + (lane & 15)) * LDSR;
-  const int col = (((lane >> 4)) ^ key(lane & 15)) * 8;   // this lane's 8-element fragment vector
-  const int64_t nk = job.kc1 - job.kc0;
-
-#define PPL_BF6_LOAD(k0)                                                                  \
-  _Pragma("unroll") for (int q = 0; q < 3; ++q) {                                         \
-    _Pragma("unroll") for (int i = 0; i < NLA; ++i)                                       \
-      ra[q][i] = *reinterpret_cast<const uint4*>(Ap[q] + ga[i] + (k0));                   \
-    _Pragma("unroll") for (int i = 0; i < NLB; ++i)                                       \
-      rb[q][i] = *reinterpret_cast<const uint4*>(Bp[q] + gb[i] + (k0));                   \
-  }
-#define PPL_BF6_STORE(buf)                                                                \
-  _Pragma("unroll") for (int q = 0; q < 3; ++q) {                                         \
-    _Pragma("unroll") for (int i = 0; i < NLA; ++i)                                       \
-      *reinterpret_cast<uint4*>(&sA[(2 * q + (buf)) * G::BUF_A + oa[i]]) = ra[q][i];      \
-    _Pragma("unroll") for (int i = 0; i < NLB; ++i)                                       \
-      *reinterpret_cast<uint4*>(&sB[(2 * q + (buf)) * G::BUF_B + ob[i]]) = rb[q][i];      \
-  }
-#define PPL_BF6_COMPUTE(buf)                                                                               \
-  {                                                                                                        \
-    bf8 a[3][WM], b[3][WN];                                                                                \
-    _Pragma("unroll") for (int q = 0; q < 3; ++q) {                                                        \
-      _Pragma("unroll") for (int i = 0; i < WM; ++i)                                                       \
-        a[q][i] = *reinterpret_cast<const bf8*>(&sA[(2 * q + (buf)) * G::BUF_A + arow + i * 16 * LDSR + col]); \
-      _Pragma("unroll") for (int j = 0; j < WN; ++j)                                                       \
-        b[q][j] = *reinterpret_cast<const bf8*>(&sB[(2 * q + (buf)) * G::BUF_B + brow + j * 16 * LDSR + col]); \
-    }                                                                                                      \
-    _Pragma("unroll") for (int i = 0; i < WM; ++i)                                                         \
-    _Pragma("unroll") for (int j = 0; j < WN; ++j) {                                                       \
-      accx[i][j] = mfma16(a[2][i], b[0][j], accx[i][j]);                                                   \
-      accx[i][j] = mfma16(a[0][i], b[2][j], accx[i][j]);                                                   \
-      accx[i][j] = mfma16(a[1][i], b[1][j], accx[i][j]);                                                   \
-      accx[i][j] = mfma16(a[1][i], b[0][j], accx[i][j]);                                                   \
-      accx[i][j] = mfma16(a[0][i], b[1][j], accx[i][j]);                                                   \
-      acc[i][j] = mfma16(a[0][i], b[0][j], acc[i][j]);                                                     \
-    }                                                                                                      \
-  }
-
-  {
-    uint4 ra[3][NLA], rb[3][NLB];
-    PPL_BF6_LOAD(0)
-    PPL_BF6_STORE(0)
-  }
-  __syncthreads();
-  for (int64_t kt = 0; kt + 1 < nk; ++kt) {
-    const int buf = (int)(kt & 1);
-    uint4 ra[3][NLA], rb[3][NLB];
-    PPL_BF6_LOAD((kt + 1) * KC)
-    PPL_BF6_COMPUTE(buf)
-    PPL_BF6_STORE(buf ^ 1)
-    __syncthreads();
-  }
-  {
-    const int buf = (int)((nk - 1) & 1);
-    PPL_BF6_COMPUTE(buf)
-  }
-#undef PPL_BF6_LOAD
-#undef PPL_BF6_STORE
-#undef PPL_BF6_COMPUTE
-
-#pragma unroll
-  for (int i = 0; i < WM; ++i) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int64_t m = m0 + wm * WM * 16 + i * 16 + AccOf<__bf16>::row(lane, r);
-      int64_t base;
-      bool ok;
-      epi.row(job.split, m, base, ok);
-#pragma unroll
-      for (int j = 0; j < WN; ++j) {
-        const int64_t n = n0 + wn * WN * 16 + j * 16 + (lane & 15);
-        epi.put(base, ok, n, acc[i][j][r] + accx[i][j][r]);
-      }
-    }
-  }
-}
 
 // The BF16x6 tile with chunks moved straight from global memory into LDS, in two stages
 // (three planes of 224 + 128 rows leave no room for a third): step k issues chunk k+1
@@ -1500,6 +1286,7 @@ __device__ __forceinline__ void bf6_tile_body_direct(const TileJob& job, int64_t
   constexpr int GA = BM / RPI, GB = BN / RPI;      // instructions per plane and chunk
   constexpr int GT = 3 * (GA + GB);                // instructions per chunk
   constexpr int NI = (GT + NW - 1) / NW;           // per wave (the short waves repeat one)
+  using Km = KMajor<BN>;
   static_assert(BM % RPI == 0 && BN % RPI == 0 && GT >= NW && NI < 16, "direct LDS geometry");
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1508,30 +1295,45 @@ __device__ __forceinline__ void bf6_tile_body_direct(const TileJob& job, int64_t
   auto key = [](int r) { return (r >> 1) & 3; };
   auto plane_of = [](const __bf16* h, const __bf16* m, int q) { return q == 0 ? h : (q == 1 ? m : m + (m - h)); };
 
+  // as in the BF16x3 tile: B rows n (NN false) or B rows k (NN true), from chunk c0 on
   const __bf16* src[NI];
   int dst[NI];
+  auto aim = [&](auto nn, int64_t c0) __attribute__((always_inline)) {
+    constexpr bool NN = decltype(nn)::value;
 #pragma unroll
-  for (int i = 0; i < NI; ++i) {
-    int q = wave + i * NW;
-    if (q >= GT) q -= GT;
-    if (q < 3 * GA) {
-      const int plane = q / GA, g = q % GA, r = g * RPI + lr;
-      int64_t gr = job.m0 + r;
-      if (gr > M - 1) gr = M - 1;
-      src[i] = plane_of(Ah, Am, plane) + epi.arow(gr) * lda + (slot ^ key(r)) * 8 + job.kc0 * KC;
-      dst[i] = (plane * BM + g * RPI) * LDSR;
-    } else {
-      const int plane = (q - 3 * GA) / GB, g = (q - 3 * GA) % GB, r = g * RPI + lr;
-      int64_t gr = job.n0 + r;
-      if (gr > N - 1) gr = N - 1;
-      src[i] = plane_of(Bh, Bm, plane) + epi.brow(gr) * ldb + (slot ^ key(r)) * 8 + job.kc0 * KC;
-      dst[i] = (3 * BM + plane * BN + g * RPI) * LDSR;
+    for (int i = 0; i < NI; ++i) {
+      int q = wave + i * NW;
+      if (q >= GT) q -= GT;
+      if (q < 3 * GA) {
+        const int plane = q / GA, g = q % GA, r = g * RPI + lr;
+        int64_t gr = job.m0 + r;
+        if (gr > M - 1) gr = M - 1;
+        src[i] = plane_of(Ah, Am, plane) + epi.arow(gr) * lda + (slot ^ key(r)) * 8 + c0 * KC;
+        dst[i] = (plane * BM + g * RPI) * LDSR;
+      } else {
+        const int plane = (q - 3 * GA) / GB, g = (q - 3 * GA) % GB;
+        dst[i] = (3 * BM + plane * BN + g * RPI) * LDSR;
+        if constexpr (NN) {
+          const int id = g * 64 + lane, kr = id / (BN / 8), cv = id % (BN / 8);
+          src[i] = plane_of(Bh, Bm, plane) + (c0 * KC + kr) * ldb + job.n0 + (cv ^ (Km::swz(kr) * 2)) * 8;
+        } else {
+          const int r = g * RPI + lr;
+          int64_t gr = job.n0 + r;
+          if (gr > N - 1) gr = N - 1;
+          src[i] = plane_of(Bh, Bm, plane) + epi.brow(gr) * ldb + (slot ^ key(r)) * 8 + c0 * KC;
+        }
+      }
     }
-  }
-  auto issue = [&](int64_t c, __bf16* st) __attribute__((always_inline)) {
+  };
+  auto issue = [&](auto nn, int64_t c, __bf16* st) __attribute__((always_inline)) {
+    constexpr bool NN = decltype(nn)::value;
 #pragma unroll
-    for (int i = 0; i < NI; ++i)
-      __builtin_amdgcn_global_load_lds((global_cvoid_t*)(src[i] + c * KC), (lds_void_t*)(st + dst[i]), 16, 0, 0);
+    for (int i = 0; i < NI; ++i) {
+      int q = wave + i * NW;
+      if (q >= GT) q -= GT;
+      const int64_t off = NN && q >= 3 * GA ? c * (KC * ldb) : c * KC;
+      __builtin_amdgcn_global_load_lds((global_cvoid_t*)(src[i] + off), (lds_void_t*)(st + dst[i]), 16, 0, 0);
+    }
   };
   // vmcnt(0) as a builtin (expcnt and lgkmcnt fields at their maxima), so that the
   // compiler knows no load is pending; then the barrier without the fence of
@@ -1554,14 +1356,17 @@ __device__ __forceinline__ void bf6_tile_body_direct(const TileJob& job, int64_t
   const int arow = (wm * WM * 16 + (lane & 15)) * LDSR;
   const int brow = (3 * BM + wn * WN * 16 + (lane & 15)) * LDSR;
   const int col = ((lane >> 4) ^ key(lane & 15)) * 8;   // this lane's 8-element fragment vector
-  const int64_t nk = job.kc1 - job.kc0;
+  int kcol[WN];                                    // K-major: this lane's first row and column of block j
+#pragma unroll
+  for (int j = 0; j < WN; ++j) kcol[j] = 3 * BM * LDSR + Km::at(lane, wn * WN + j);
 
   // Multiply the chunk in st; when go, first issue chunk c into nx. The empty asm keeps
   // the LDS reads, and with them the MFMAs, below the loads: left to itself the compiler
   // sinks the loads below the MFMAs, and the wait that ends the step would then find
   // them just issued.
-  auto compute = [&](const __bf16* __restrict__ st, bool go, int64_t c, __bf16* nx) __attribute__((always_inline)) {
-    if (go) issue(c, nx);
+  auto compute = [&](auto nn, const __bf16* __restrict__ st, bool go, int64_t c, __bf16* nx) __attribute__((always_inline)) {
+    constexpr bool NN = decltype(nn)::value;
+    if (go) issue(nn, c, nx);
     asm volatile("" ::: "memory");
     bf8 a[3][WM], b[3][WN];
 #pragma unroll
@@ -1569,7 +1374,10 @@ __device__ __forceinline__ void bf6_tile_body_direct(const TileJob& job, int64_t
 #pragma unroll
       for (int i = 0; i < WM; ++i) a[q][i] = *reinterpret_cast<const bf8*>(&st[q * BM * LDSR + arow + i * 16 * LDSR + col]);
 #pragma unroll
-      for (int j = 0; j < WN; ++j) b[q][j] = *reinterpret_cast<const bf8*>(&st[q * BN * LDSR + brow + j * 16 * LDSR + col]);
+      for (int j = 0; j < WN; ++j) {
+        if constexpr (NN) b[q][j] = Km::frag(st + q * BN * LDSR + kcol[j]);
+        else b[q][j] = *reinterpret_cast<const bf8*>(&st[q * BN * LDSR + brow + j * 16 * LDSR + col]);
+      }
     }
 #pragma unroll
     for (int i = 0; i < WM; ++i)
@@ -1584,22 +1392,32 @@ __device__ __forceinline__ void bf6_tile_body_direct(const TileJob& job, int64_t
       }
   };
 
-  // chunk j lives in stage j mod 2
-  issue(0, st0);
-  wait_meet();
-  int64_t kt = 0;
-  for (; kt + 2 < nk; kt += 2) {
-    compute(st0, true, kt + 1, st1);
+  // chunks [c0, c1), alternating between the stages
+  auto run = [&](auto nn, int64_t c0, int64_t c1) __attribute__((always_inline)) {
+    const int64_t n = c1 - c0;
+    aim(nn, c0);
+    issue(nn, 0, st0);
     wait_meet();
-    compute(st1, true, kt + 2, st0);
-    wait_meet();
+    int64_t kt = 0;
+    for (; kt + 2 < n; kt += 2) {
+      compute(nn, st0, true, kt + 1, st1);
+      wait_meet();
+      compute(nn, st1, true, kt + 2, st0);
+      wait_meet();
+    }
+    // one or two chunks remain, chunk kt in st0
+    compute(nn, st0, kt + 1 < n, kt + 1, st1);
+    if (kt + 1 < n) {
+      wait_meet();
+      compute(nn, st1, false, 0, st0);
+    }
+  };
+  const int64_t cd = below_diagonal<KC>(job, epi);
+  if constexpr (Epi::kTri) {
+    if (job.kc0 < cd) run(std::true_type{}, job.kc0, cd);
+    if (job.kc0 < cd && cd < job.kc1) wait_meet();   // every wave has read the last stages
   }
-  // one or two chunks remain, chunk kt in st0
-  compute(st0, kt + 1 < nk, kt + 1, st1);
-  if (kt + 1 < nk) {
-    wait_meet();
-    compute(st1, false, 0, st0);
-  }
+  if (cd < job.kc1) run(std::false_type{}, cd, job.kc1);
 
 #pragma unroll
   for (int i = 0; i < WM; ++i) {
@@ -1624,17 +1442,10 @@ gemm_nt_bf16x6_kernel(int64_t M, int64_t N, const __bf16* Ah, const __bf16* Am, 
                       const __bf16* Bm, int64_t ldb, Epi epi, Map map) {
   using G = Bf6Geom<WM, WN, WAVES_M, WAVES_N>;
   TileJob job;
-  if constexpr (kBf6Direct) {
-    __shared__ __attribute__((aligned(16))) __bf16 st0[G::STAGE];
-    __shared__ __attribute__((aligned(16))) __bf16 st1[G::STAGE];
-    if (!map(blockIdx.x, job)) return;
-    bf6_tile_body_direct<WM, WN, WAVES_M, WAVES_N>(job, M, N, Ah, Am, lda, Bh, Bm, ldb, epi, st0, st1);
-  } else {
-    __shared__ __attribute__((aligned(16))) __bf16 sA[G::LDS_A];
-    __shared__ __attribute__((aligned(16))) __bf16 sB[G::LDS_B];
-    if (!map(blockIdx.x, job)) return;
-    bf6_tile_body<WM, WN, WAVES_M, WAVES_N>(job, M, N, Ah, Am, lda, Bh, Bm, ldb, epi, sA, sB);
-  }
+  __shared__ __attribute__((aligned(16))) __bf16 st0[G::STAGE];
+  __shared__ __attribute__((aligned(16))) __bf16 st1[G::STAGE];
+  if (!map(blockIdx.x, job)) return;
+  bf6_tile_body_direct<WM, WN, WAVES_M, WAVES_N>(job, M, N, Ah, Am, lda, Bh, Bm, ldb, epi, st0, st1);
 }
 
 // ------------------------------------------------------------------ tile configurations
@@ -1869,13 +1680,11 @@ template <int WM, int WN, int WAVES_M, int WAVES_N, int KC>
 __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N)
 gemm_streamk_bf16x3_kernel(int64_t M, int64_t N, const __bf16* __restrict__ Ah, const __bf16* __restrict__ Al,
                            int64_t lda, const __bf16* __restrict__ Bh, const __bf16* __restrict__ Bl, int64_t ldb,
-                           float* C, int64_t ldc, int64_t c_col0, float* part, StreamK sk) {
+                           float* C, int64_t ldc, int64_t c_col0, float* part, StreamK sk, int tri) {
   using G = Bf3Geom<WM, WN, WAVES_M, WAVES_N, KC>;
-  constexpr int SA = kBf3Direct ? G::STAGE : G::LDS_A, SB = kBf3Direct ? G::STAGE : G::LDS_B;
-  __shared__ __attribute__((aligned(16))) __bf16 sAh[SA];
-  __shared__ __attribute__((aligned(16))) __bf16 sAl[SA];
-  __shared__ __attribute__((aligned(16))) __bf16 sBh[SB];
-  __shared__ __attribute__((aligned(16))) __bf16 sBl[kBf3Direct ? 8 : G::LDS_B];
+  __shared__ __attribute__((aligned(16))) __bf16 st0[G::STAGE];
+  __shared__ __attribute__((aligned(16))) __bf16 st1[G::STAGE];
+  __shared__ __attribute__((aligned(16))) __bf16 st2[G::STAGE];
   const int64_t w = xcd_remap(blockIdx.x, gridDim.x);
   const int64_t begin = sk.start(w), end = sk.start(w + 1);
   const int64_t first_tile = begin / sk.nk;
@@ -1886,11 +1695,8 @@ gemm_streamk_bf16x3_kernel(int64_t M, int64_t N, const __bf16* __restrict__ Ah, 
     const bool whole = k0 == 0 && k1 == sk.nk;
     EpiSK<float> epi{C, ldc, c_col0, M, N,
                      part + (w * 2 + (tile == first_tile ? 0 : 1)) * (int64_t)(G::BM * G::BN),
-                     job.m0, job.n0, G::BN, !whole};
-    if constexpr (kBf3Direct)   // the first three arrays serve as the three stages
-      bf3_tile_body_direct<WM, WN, WAVES_M, WAVES_N, KC>(job, M, N, Ah, Al, lda, Bh, Bl, ldb, epi, sAh, sAl, sBh);
-    else
-      bf3_tile_body<WM, WN, WAVES_M, WAVES_N, KC>(job, M, N, Ah, Al, lda, Bh, Bl, ldb, epi, sAh, sAl, sBh, sBl);
+                     job.m0, job.n0, G::BN, !whole, tri};
+    bf3_tile_body_direct<WM, WN, WAVES_M, WAVES_N, KC>(job, M, N, Ah, Al, lda, Bh, Bl, ldb, epi, st0, st1, st2);
     it = t0 + k1;
     __syncthreads();   // the next tile refills the LDS buffers
   }
@@ -1900,11 +1706,10 @@ template <int WM, int WN, int WAVES_M, int WAVES_N>
 __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N)
 gemm_streamk_bf16x6_kernel(int64_t M, int64_t N, const __bf16* Ah, const __bf16* Am, int64_t lda, const __bf16* Bh,
                            const __bf16* Bm, int64_t ldb, float* C, int64_t ldc, int64_t c_col0, float* part,
-                           StreamK sk) {
+                           StreamK sk, int tri) {
   using G = Bf6Geom<WM, WN, WAVES_M, WAVES_N>;
-  // (the direct body takes the two arrays as its two stages: 2 STAGE = LDS_A + LDS_B)
-  __shared__ __attribute__((aligned(16))) __bf16 sA[kBf6Direct ? G::STAGE : G::LDS_A];
-  __shared__ __attribute__((aligned(16))) __bf16 sB[kBf6Direct ? G::STAGE : G::LDS_B];
+  __shared__ __attribute__((aligned(16))) __bf16 st0[G::STAGE];
+  __shared__ __attribute__((aligned(16))) __bf16 st1[G::STAGE];
   const int64_t w = xcd_remap(blockIdx.x, gridDim.x);
   const int64_t begin = sk.start(w), end = sk.start(w + 1);
   const int64_t first_tile = begin / sk.nk;
@@ -1915,11 +1720,8 @@ gemm_streamk_bf16x6_kernel(int64_t M, int64_t N, const __bf16* Ah, const __bf16*
     const bool whole = k0 == 0 && k1 == sk.nk;
     EpiSK<float> epi{C, ldc, c_col0, M, N,
                      part + (w * 2 + (tile == first_tile ? 0 : 1)) * (int64_t)(G::BM * G::BN),
-                     job.m0, job.n0, G::BN, !whole};
-    if constexpr (kBf6Direct)
-      bf6_tile_body_direct<WM, WN, WAVES_M, WAVES_N>(job, M, N, Ah, Am, lda, Bh, Bm, ldb, epi, sA, sB);
-    else
-      bf6_tile_body<WM, WN, WAVES_M, WAVES_N>(job, M, N, Ah, Am, lda, Bh, Bm, ldb, epi, sA, sB);
+                     job.m0, job.n0, G::BN, !whole, tri};
+    bf6_tile_body_direct<WM, WN, WAVES_M, WAVES_N>(job, M, N, Ah, Am, lda, Bh, Bm, ldb, epi, st0, st1);
     it = t0 + k1;
     __syncthreads();   // the next tile refills the LDS buffers
   }
@@ -2012,7 +1814,7 @@ static int streamk_setup(int64_t resident, int64_t M, int64_t N, int64_t nk, int
 template <int WM, int WN, int WAVES_M, int WAVES_N, int KC>
 static int launch_streamk_bf3(hipStream_t s, int64_t M, int64_t N, int64_t Kpad, const __bf16* Ah,
                               const __bf16* Al, int64_t lda, const __bf16* Bh, const __bf16* Bl, int64_t ldb,
-                              float* C, int64_t ldc, int64_t c_col0, void* part, uint64_t part_bytes) {
+                              float* C, int64_t ldc, int64_t c_col0, void* part, uint64_t part_bytes, int tri) {
   using G = Bf3Geom<WM, WN, WAVES_M, WAVES_N, KC>;
   if (Kpad % KC != 0) return fail(PPL_E_ARG, "K padding %lld not a multiple of %d", (long long)Kpad, KC);
   auto kern = gemm_streamk_bf16x3_kernel<WM, WN, WAVES_M, WAVES_N, KC>;
@@ -2022,7 +1824,7 @@ static int launch_streamk_bf3(hipStream_t s, int64_t M, int64_t N, int64_t Kpad,
                         part_bytes, sk, n_tiles));
   if (sk.iters <= 0) return PPL_OK;
   hipLaunchKernelGGL(kern, dim3((unsigned)sk.G), dim3(G::NT), 0, s, M, N, Ah, Al, lda, Bh, Bl, ldb, C, ldc,
-                     c_col0, (float*)part, sk);
+                     c_col0, (float*)part, sk, tri);
   PPL_HIP_TRY(hipGetLastError());
   hipLaunchKernelGGL(streamk_fixup_kernel<float>, dim3((unsigned)n_tiles), dim3(256), 0, s, (const float*)part,
                      C, ldc, c_col0, M, N, G::BM, G::BN, sk);
@@ -2033,7 +1835,7 @@ static int launch_streamk_bf3(hipStream_t s, int64_t M, int64_t N, int64_t Kpad,
 template <int WM, int WN, int WAVES_M, int WAVES_N>
 static int launch_streamk_bf6(hipStream_t s, int64_t M, int64_t N, int64_t Kpad, const __bf16* Ah,
                               const __bf16* Am, int64_t lda, const __bf16* Bh, const __bf16* Bm, int64_t ldb,
-                              float* C, int64_t ldc, int64_t c_col0, void* part, uint64_t part_bytes) {
+                              float* C, int64_t ldc, int64_t c_col0, void* part, uint64_t part_bytes, int tri) {
   using G = Bf6Geom<WM, WN, WAVES_M, WAVES_N>;
   constexpr int NT = 64 * WAVES_M * WAVES_N;
   if (Kpad % kKcBf6 != 0) return fail(PPL_E_ARG, "K padding %lld not a multiple of %d", (long long)Kpad, kKcBf6);
@@ -2045,7 +1847,7 @@ static int launch_streamk_bf6(hipStream_t s, int64_t M, int64_t N, int64_t Kpad,
                         part_bytes, sk, n_tiles));
   if (sk.iters <= 0) return PPL_OK;
   hipLaunchKernelGGL(kern, dim3((unsigned)sk.G), dim3(NT), 0, s, M, N, Ah, Am, lda, Bh, Bm, ldb, C, ldc, c_col0,
-                     (float*)part, sk);
+                     (float*)part, sk, tri);
   PPL_HIP_TRY(hipGetLastError());
   hipLaunchKernelGGL(streamk_fixup_kernel<float>, dim3((unsigned)n_tiles), dim3(256), 0, s, (const float*)part,
                      C, ldc, c_col0, M, N, G::BM, G::BN, sk);
@@ -2084,8 +1886,7 @@ static int contract_cfg(hipStream_t s, int prec, int64_t Nrows, int64_t Prows, i
   constexpr int BM = 16 * WM * WAVES_M, BN = 16 * WN * WAVES_N;
   static_assert(kTriBlock % BN == 0, "a column tile lies in one diagonal block of a triangular operand");
   if (accumulate && splits != 1) return fail(PPL_E_ARG, "an accumulating contraction runs one K slice");
-  if (tri && (c_col0 != 0 || (prec != PPL_FP64 && prec != PPL_FP32)))
-    return fail(PPL_E_ARG, "triangular operands are whole FP64 or FP32 matrices");
+  if (tri && c_col0 != 0) return fail(PPL_E_ARG, "triangular operands are whole matrices");
   const double cbeta = accumulate ? 1.0 : 0.0;
   if (splits == 0) {   // stream-K
     if (prec == PPL_FP64)
@@ -2099,12 +1900,12 @@ static int contract_cfg(hipStream_t s, int prec, int64_t Nrows, int64_t Prows, i
     if (prec == PPL_BF16X3)
       return launch_streamk_bf3<WM, WN, WAVES_M, WAVES_N, bf3_kc(BM, BN)>(
           s, Nrows, Prows, Kpad, (const __bf16*)S, (const __bf16*)S_lo, lds_, (const __bf16*)V,
-          (const __bf16*)V_lo, ldv, (float*)C, ldc, c_col0, partial, partial_bytes);
+          (const __bf16*)V_lo, ldv, (float*)C, ldc, c_col0, partial, partial_bytes, tri);
     if (prec == PPL_BF16X6)
       return launch_streamk_bf6<WM, WN, WAVES_M, WAVES_N>(s, Nrows, Prows, Kpad, (const __bf16*)S,
                                                           (const __bf16*)S_lo, lds_, (const __bf16*)V,
                                                           (const __bf16*)V_lo, ldv, (float*)C, ldc, c_col0, partial,
-                                                          partial_bytes);
+                                                          partial_bytes, tri);
     return fail(PPL_E_ARG, "unknown precision %d", prec);
   }
   const int KC = kc_of(prec, BM, BN);
@@ -2131,14 +1932,14 @@ static int contract_cfg(hipStream_t s, int prec, int64_t Nrows, int64_t Prows, i
     rc = launch<float, WM, WN, WAVES_M, WAVES_N, kKcF32>(s, grid, Nrows, Prows, Kpad, (const float*)S, lds_,
                                                      (const float*)V, ldv, epi, map);
   } else if (prec == PPL_BF16X3) {
-    EpiStore<float> epi = direct ? EpiStore<float>{(float*)C, ldc, c_col0, Nrows, Prows, 1.0, cbeta, 0}
-                                 : EpiStore<float>{(float*)partial, partial_ld, 0, Nrows, Prows, 1.0, 0.0, pstride};
+    EpiStore<float> epi = direct ? EpiStore<float>{(float*)C, ldc, c_col0, Nrows, Prows, 1.0, cbeta, 0, tri}
+                                 : EpiStore<float>{(float*)partial, partial_ld, 0, Nrows, Prows, 1.0, 0.0, pstride, tri};
     rc = launch_bf3<WM, WN, WAVES_M, WAVES_N, bf3_kc(BM, BN)>(s, grid, Nrows, Prows, Kpad, (const __bf16*)S,
                                                   (const __bf16*)S_lo, lds_, (const __bf16*)V,
                                                   (const __bf16*)V_lo, ldv, epi, map);
   } else if (prec == PPL_BF16X6) {
-    EpiStore<float> epi = direct ? EpiStore<float>{(float*)C, ldc, c_col0, Nrows, Prows, 1.0, cbeta, 0}
-                                 : EpiStore<float>{(float*)partial, partial_ld, 0, Nrows, Prows, 1.0, 0.0, pstride};
+    EpiStore<float> epi = direct ? EpiStore<float>{(float*)C, ldc, c_col0, Nrows, Prows, 1.0, cbeta, 0, tri}
+                                 : EpiStore<float>{(float*)partial, partial_ld, 0, Nrows, Prows, 1.0, 0.0, pstride, tri};
     rc = launch_bf6<WM, WN, WAVES_M, WAVES_N>(s, grid, Nrows, Prows, Kpad, (const __bf16*)S, (const __bf16*)S_lo,
                                               lds_, (const __bf16*)V, (const __bf16*)V_lo, ldv, epi, map);
   } else {

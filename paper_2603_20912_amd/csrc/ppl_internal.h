@@ -48,7 +48,7 @@ static_assert(64 % kKcF64 == 0 && 64 % kKcF32 == 0 && 64 % bf3_kc(0, 0) == 0,
 
 __host__ __device__ inline int64_t pad_ld(int64_t k) { return (k + 63) / 64 * 64; }
 
-// Resident FP64 and FP32 V+- are stored as upper triangles: entry [r][q] is valid where
+// Resident V+- are stored as upper triangles: entry [r][q] is valid where
 // q >= r or r / kTriBlock == q / kTriBlock (whole diagonal blocks), and the rest is never
 // read. Every column tile of a contraction (64, 128 or 256 wide, from a multiple of its
 // width) then lies in one diagonal block.
@@ -192,7 +192,7 @@ int gemm_store_f64(hipStream_t s, int64_t M, int64_t N, int64_t naux, const doub
 // mid for BF16x6, whose lo plane lies one plane further on (mid + (mid - hi)).
 // splits > 1 splits K into that many slices written to `partial` ([splits][Nrows][partial_ld],
 // accumulator type) and summed in slice order into C. accumulate: C += the product (one
-// K slice only; PPL_E_ARG with split-K or stream-K). tri (FP64, FP32): V is a symmetric
+// K slice only; PPL_E_ARG with split-K or stream-K). tri: V is a symmetric
 // matrix stored as kTriBlock describes; the result is that of the full matrix, bit for bit.
 // slices: the K slices stay unsummed in `partial`, *slices of them (1: the result is in C).
 int gemm_contract(hipStream_t s, int prec, int tile, int64_t Nrows, int64_t Prows, int64_t Kpad,
@@ -300,8 +300,8 @@ int stage_ov(hipStream_t s, const double* L, int o, int v, int naux, int64_t ldx
 int pack_vpm(hipStream_t s, int prec, int v, int a0, int a1, const void* G, void* vp, void* vp_lo,
              int64_t ldp, int64_t vp_row0, void* vm, void* vm_lo, int64_t ldm, int64_t vm_row0,
              const int* tab_vp, const int* tab_vm);
-// V+- rows of a build step from gemm_build_sym's T (row length ldt) as upper triangles, FP64 and
-// FP32 with whole diagonal blocks (kTriBlock); off[a] = cubes of the virtuals below a
+// V+- rows of a build step from gemm_build_sym's T (row length ldt) as upper triangles with whole
+// diagonal blocks (kTriBlock); off[a] = cubes of the virtuals below a
 // (pack_cubes.h), v + 1 entries
 int pack_vpm_tri(hipStream_t s, int prec, int v, int a0, int a1, const void* T, int64_t ldt, const int64_t* off,
                  void* vp, void* vp_lo, int64_t ldp, void* vm, void* vm_lo, int64_t ldm);
@@ -309,9 +309,7 @@ int pack_vpm_tri(hipStream_t s, int prec, int v, int a0, int a1, const void* T, 
 // rounded down to kStepRows on, halved diagonal, zeros around them
 int pack_vpm_step(hipStream_t s, int v, const Batch& b, const double* T, int64_t ldt, const int64_t* off, double* vp,
                   int64_t ldp, double* vm, int64_t ldm);
-// entries below the diagonal of rows [q0, q1) of a symmetric n x n bf16 matrix (every plane)
-int mirror_rows(hipStream_t s, int prec, void* hi, void* lo, int64_t n, int64_t ld, int64_t q0, int64_t q1);
-// a symmetric FP64 matrix stored that way to the whole matrix in an operand precision
+// an FP64 matrix stored that way to the same in an operand precision
 int convert_tri(hipStream_t s, int prec, const double* src, int64_t n, int64_t ld, void* dst, void* dst_lo);
 // C[q][p] += T[p][q] for q < nq, p < np (T FP64; C FP64 or FP32 by c_prec)
 int add_transposed(hipStream_t s, int c_prec, void* C, int64_t ldc, const double* T, int64_t ldt, int64_t nq,

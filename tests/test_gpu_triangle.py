@@ -1,4 +1,4 @@
-"""Resident FP64 and FP32 plans hold V+- as upper triangles with whole 256 x 256 diagonal
+"""Resident plans hold V+- as upper triangles with whole 256 x 256 diagonal
 blocks. Every workspace byte is set to 0xff (NaN in every type) before the build, so a read
 of an entry that is not stored shows in the result; the results must equal, bit for bit,
 those of a plan that builds and stores every row in full (the same products summed in the
@@ -76,7 +76,7 @@ def test_triangle_equals_full_rows_in_every_configuration(P, monkeypatch, prec, 
 @pytest.mark.parametrize("prec", ["fp32", "bf16x3", "bf16x6"])
 @pytest.mark.parametrize("o,v,naux", SIZES)
 def test_low_precision_copy_of_a_triangle(P, monkeypatch, prec, o, v, naux):
-    """The low-precision V+- of a mixed plan, rounded from the FP64 triangle and completed."""
+    """The low-precision V+- of a mixed plan, rounded from the FP64 triangle."""
     say(f"mixed operands from a triangle {prec} ({o},{v},{naux})")
     s = S.make_system(o, v, naux, 82)
     t = dev(S.make_amplitudes(o, v, 83))
@@ -108,10 +108,11 @@ def test_grouped_launch_reads_triangles(P, prec, bound):
 
 @pytest.mark.parametrize("prec,bound", [("bf16x3", 4e-5), ("bf16x6", 2e-6)])
 @pytest.mark.parametrize("o,v,naux", SIZES)
-def test_bf16_rows_completed_from_triangles(P, monkeypatch, prec, bound, o, v, naux):
-    """BF16 rows are packed as upper triangles and completed step by step: every entry is
-    written (poisoned workspace) and steps give the same rows in any order."""
-    say(f"bf16 rows {prec} ({o},{v},{naux})")
+def test_bf16_triangles(P, monkeypatch, prec, bound, o, v, naux):
+    """BF16 triangles: every entry that is read is written (poisoned workspace), steps give the
+    same rows in any order, and every tile (64, 128 and 256 columns, K chunks of 32 and 64) the
+    same sums for a number of slices."""
+    say(f"bf16 triangles {prec} ({o},{v},{naux})")
     s = S.make_system(o, v, naux, 84)
     t = S.make_amplitudes(o, v, 85)
     L = dev(s["L"])
@@ -125,9 +126,21 @@ def test_bf16_rows_completed_from_triangles(P, monkeypatch, prec, bound, o, v, n
             for k in list(range(nb))[::order] + [nb - 1]:
                 eng.build(L, k)
         out.append(eng.contract(dev(t)).cpu().numpy())
-        eng.close()
-    assert rel(out[0], O.ppl(s["L"], o, t)) < bound
+        if order != -1:
+            eng.close()
+    ref = O.ppl(s["L"], o, t)
+    assert rel(out[0], ref) < bound
     assert np.array_equal(out[0], out[1]) and np.array_equal(out[0], out[2])
+    for splits in (1, 3, 8, 0):
+        res = []
+        for tile in range(P.ppl_tile_count()):
+            say(f"  tile {tile} splits {splits}")
+            eng.set_contract_config(tile, splits, tile, splits)
+            res.append(eng.contract(dev(t)).cpu().numpy())
+            assert rel(res[-1], ref) < bound
+            if splits == 1:
+                assert np.array_equal(res[-1], res[0])
+    eng.close()
 
 
 @pytest.mark.parametrize("kw", [dict(prec="fp64"), dict(prec="bf16x6"), dict(prec="fp32", keep_fp64=True)])
