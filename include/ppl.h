@@ -146,7 +146,7 @@ int ppl_bind_workspace(ppl_plan_t plan, void* dptr, uint64_t bytes);
  * Every L^P must be symmetric (real orbitals, as the paper assumes), which makes
  * V+ and V- symmetric matrices: a resident plan builds their upper triangle
  * (rows (a, c >= a) of the integrals against the packed column pairs (b <= d), since
- * (ac|bd) = (ac|db)) and stores upper triangles (FP64, FP32) or whole rows (BF16);
+ * (ac|bd) = (ac|db)) and stores upper triangles;
  * an FP64 streaming plan builds upper-triangle steps as well (contracted as U and
  * U^T), other streaming plans build full rows. Plans that build upper triangles
  * first check (batch 0 or -1) that the virtual block of L is symmetric to a relative

@@ -24,9 +24,10 @@ PPL_HD inline int64_t cubes_of(int v, int a) {
   return nt * nt * (nt + 1) / 2;
 }
 
-// The r-th cube of a virtual with nt blocks. Cubes (x, ci, y) and (y, ci, x) stage the same
-// integrals (ac|bd) (rows c of block ci, pairs {b, d} with one index in block x and one in
-// block y), so they are taken one after the other: ci slowest; for each ci first the cubes
+// The r-th cube of a virtual with nt blocks, in an order of equal integrals (the host-side replay
+// walks the cubes in it; the packing kernel in that of cube_decode_rows). Cubes (x, ci, y) and
+// (y, ci, x) stage the same integrals (ac|bd) (rows c of block ci, pairs {b, d} with one index in
+// block x and one in block y), so they are taken one after the other: ci slowest; for each ci first the cubes
 // with bi < ci (no such partner), then the square bi, di >= ci by unordered pairs {x <= y},
 // (x, x) alone and (x, y), (y, x) together. nt (nt - ci) cubes per ci.
 PPL_HD inline void cube_decode(int64_t r, int nt, int& bi, int& ci, int& di) {
