@@ -821,8 +821,6 @@ static int plan_create(const ppl_desc_t* d, ppl_plan_t* out, bool external_g) {
   p->ops[0].present = true;
   p->ops[1].prec = PPL_FP64;
   p->ops[1].present = p->keep_fp64 != 0;
-  p->tile_build = build_tile_for_prec(p->prec);
-  p->tile_build64 = p->ops[1].present ? build_tile_for_prec(PPL_FP64) : p->tile_build;
   {
     int t = d->tile_contract, sp = 1;
     contract_choose(p->prec, p->Np, p->Pp, p->ldp, kMaxSplits, &t, &sp);
@@ -882,6 +880,11 @@ static int plan_create(const ppl_desc_t* d, ppl_plan_t* out, bool external_g) {
     const char* e = getenv("PPL_SYM_BUILD");
     p->sym_build = !(e && e[0] == '0');
   }
+  auto choose_build_tiles = [&]() {
+    p->tile_build = build_tile_for(p->prec, p->v, p->sym_build);
+    p->tile_build64 = p->ops[1].present ? build_tile_for(PPL_FP64, p->v, p->sym_build) : p->tile_build;
+  };
+  choose_build_tiles();
   make_batches(p->v, gcap, p->batches);
   make_tile_tables(p);
   uint64_t need = assign_layout(p, gcap, true, 0);
@@ -892,6 +895,7 @@ static int plan_create(const ppl_desc_t* d, ppl_plan_t* out, bool external_g) {
   } else {
     // streaming: upper-triangle steps contracted as U and U^T (FP64 plans with one operand set)
     p->sym_build = p->sym_build && p->prec == PPL_FP64 && !p->keep_fp64;
+    choose_build_tiles();
     // streaming: V+- rows of one build step at a time; the largest step that fits
     // (the need grows with the step's pair count, so a bisection over it suffices)
     p->resident = false;

@@ -236,17 +236,22 @@ int contract_min_splits(int prec, int64_t Kpad);
 // *tile_out >= 0 on entry fixes the tile and only chooses the split count
 void contract_choose(int prec, int64_t Nrows, int64_t Prows, int64_t Kpad, int max_splits, int* tile_out,
                      int* splits_out);
-// contraction tile the integral build GEMM of a plan runs on (measured at (20, 200, 600),
-// (30, 300, 900) and (40, 400, 1200): 64 x 128 with direct loads for FP64 operands,
-// 128 x 128 for FP32, 96 x 128 for BF16x3 and BF16x6)
-#ifndef PPL_BUILD_TILE
-#define PPL_BUILD_TILE 1     // FP32 integral-build tile (contraction tile id)
-#endif
-#ifndef PPL_BUILD_TILE_F64
-#define PPL_BUILD_TILE_F64 8 // FP64 integral-build tile
-#endif
-inline int build_tile_for_prec(int prec) {
-  return prec == PPL_BF16X3 || prec == PPL_BF16X6 ? 5 : (prec == PPL_FP64 ? PPL_BUILD_TILE_F64 : PPL_BUILD_TILE);
+// Contraction tile the integral build GEMM runs on: 64 x 128 for FP64 (direct loads; 128 x 128 13.7
+// against 13.1 ms at (20, 200, 600) over full rows) and, in upper-triangle builds, where a tile has
+// few chunks and the smaller one puts more workgroups on a CU, for BF16 and small FP32 problems:
+//   v, naux = 3 v        60          100         137         200          300         400
+//   BF16x3, 96 x 128     10.3 us     55          198         1.12 ms      7.85        30.9
+//           64 x 128      9.2        46          156         0.99         7.38        30.0
+//   BF16x6, 96 x 128     13.5        85          307         1.80         12.9        52.3
+//           64 x 128     11.5        67          264         1.67         12.1        49.4
+//   FP32,  128 x 128     18.9        97          337         1.93         13.98       56.9
+//           64 x 128     12.1        89          334         1.96         14.28       58.3
+// (FP32 even from v = 120 to 150). Full rows: 128 x 128 for FP32, 96 x 128 for BF16, measured at
+// (20, 200, 600), (30, 300, 900) and (40, 400, 1200).
+inline int build_tile_for(int prec, int v, bool triangle) {
+  const bool bf16 = prec == PPL_BF16X3 || prec == PPL_BF16X6;
+  if (prec == PPL_FP64 || (triangle && (bf16 || v <= 110))) return 8;
+  return bf16 ? 5 : 1;
 }
 constexpr int kMaxSplits = 8;          // split-K slices 1 .. kMaxSplits; 0 selects stream-K
 constexpr int64_t kStreamKMaxGrid = 1024;   // stream-K workgroups at most (partial slots: 2 each)

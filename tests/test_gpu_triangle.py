@@ -160,3 +160,18 @@ def test_refused_vectors_leave_the_operands(P, kw):
         eng.build(dev(bad))
     assert np.array_equal(eng.contract(t).cpu().numpy(), before)
     eng.close()
+
+
+@pytest.mark.parametrize("prec,bound", [("fp32", 2e-6), ("bf16x3", 4e-5), ("bf16x6", 2e-6)])
+@pytest.mark.parametrize("v,naux", [(110, 33), (111, 31)])
+def test_builds_on_both_sides_of_the_tile_rule(P, prec, bound, v, naux):
+    """FP32 builds change their tile at v = 110; one chunk of vectors, and one more vector."""
+    say(f"builds {prec} (2,{v},{naux})")
+    s = S.make_system(2, v, naux, 88)
+    t = S.make_amplitudes(2, v, 89)
+    eng = P.PPL(2, v, naux, prec=prec)
+    eng.workspace.fill_(255)
+    P.ppl_bind_workspace(eng.plan, eng.workspace)
+    eng.build(dev(s["L"]))
+    assert rel(eng.contract(dev(t)).cpu().numpy(), O.ppl(s["L"], 2, t)) < bound
+    eng.close()
