@@ -628,8 +628,8 @@ static int setup_ov_integrals(ppl_plan_t p, const double* L) {
   return PPL_OK;
 }
 
-// Sums that the host reads go to mapped host memory where the plan has some (from its first build
-// or iteration on; a copy and its wait took 24 us, the wait alone 11), else to the workspace.
+// Sums that the host reads go to mapped host memory where the plan has some (from its binding or
+// first iteration on; a copy and its wait took 24 us, the wait alone 11), else to the workspace.
 static double* red_target(ppl_plan_t p) {
   return p->host_red ? p->host_red : at<double>(p, p->red) + kReduceBlocks * 4;
 }
@@ -647,14 +647,22 @@ static int read_red(ppl_plan_t p, double out[4]) {
   return PPL_OK;
 }
 
+// What the symmetry check of a build needs: taken when the workspace is bound (18 us once), so that
+// a first build is not slower than the next.
+static int need_check(ppl_plan_t p) {
+  PPL_TRY(need_host_red(p));
+  if (!p->ev_check)
+    PPL_HIP_TRY(hipEventCreateWithFlags(&p->ev_check, hipEventDisableTiming | hipEventReleaseToSystem));
+  return PPL_OK;
+}
+
 // The upper-triangle build relies on symmetric Cholesky vectors (V+- symmetric): PPL_E_ARG
 // when the virtual block of L is not symmetric to a relative Frobenius asymmetry of 1e-10. The host
 // waits for the sums only, so that work launched between the two calls hides the wait (a build's
 // staging: 44 us of idle device per build before).
 static int symmetry_sums(ppl_plan_t p, const double* L) {
   if (!p->sym_build) return PPL_OK;
-  PPL_TRY(need_host_red(p));
-  if (!p->ev_check) PPL_HIP_TRY(hipEventCreateWithFlags(&p->ev_check, hipEventDisableTiming | hipEventReleaseToSystem));
+  PPL_TRY(need_check(p));
   PPL_TRY(asymmetry_vv(p->stream, L, p->o, p->v, p->naux, at<double>(p, p->red), p->host_red + kHostRed - 4));
   PPL_HIP_TRY(hipEventRecord(p->ev_check, p->stream));
   return PPL_OK;
@@ -1006,6 +1014,7 @@ int ppl_bind_workspace(ppl_plan_t p, void* dptr, uint64_t bytes) {
                                hipMemcpyHostToDevice, st));
   }
   PPL_HIP_TRY(hipStreamSynchronize(st));   // the host tile table must not be reused before the copy ends
+  if (p->sym_build) PPL_TRY(need_check(p));
   p->setup_done = true;
   return PPL_OK;
 }
