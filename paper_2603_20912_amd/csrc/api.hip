@@ -1707,7 +1707,9 @@ int ppl_mp2(ppl_plan_t p, const double* L, const double* e_occ, const double* e_
   if (!L || !e_occ || !e_vir || !t2_out) return fail(PPL_E_ARG, "null device pointer");
   hipStream_t st = p->stream;
   double* partials = at<double>(p, p->red);
-  double* red_out = red_target(p);
+  // without an energy the call only enqueues: a graph that recorded it may be replayed when the plan
+  // is gone, so its sums then go to the caller's workspace
+  double* red_out = e_mp2 ? red_target(p) : partials + kReduceBlocks * 4;
   PPL_TRY(setup_ov_integrals(p, L));
   double* s64 = at<double>(p, p->s64);
   double* a64 = at<double>(p, p->a64);
