@@ -21,6 +21,8 @@
  *   - Every pointer argument that names device memory is owned by the caller.
  *     The library never allocates or frees device memory: all its device
  *     storage lives in one caller-provided workspace (ppl_bind_workspace).
+ *     Sums that calls return to the host pass through one block of pinned host
+ *     memory (48 KB) that the process takes when a first plan is bound and keeps.
  *   - Work is enqueued asynchronously on the plan's stream unless stated.
  *   - Functions return PPL_OK (0) or a negative PPL_E_* code; nothing throws
  *     or aborts across the ABI, and there is no CPU fallback. ppl_last_error()
@@ -442,7 +444,8 @@ int ppl_profile_enable(ppl_plan_t plan, int on);
 /* ppl_profile_read: synchronize the plan's stream and sum the recorded event pairs by kind. */
 int ppl_profile_read(ppl_plan_t plan, ppl_profile_t* out);
 
-/* ppl_destroy: free the plan's host metadata (never the workspace). NULL is a no-op. */
+/* ppl_destroy: free the plan's host metadata (never the workspace), without waiting for the
+ * device. NULL is a no-op. */
 int ppl_destroy(ppl_plan_t plan);
 
 /* Thread-local text of the last error ("" if none). Valid until the next call on this thread. */

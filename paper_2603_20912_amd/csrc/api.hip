@@ -318,7 +318,7 @@ static uint64_t assign_layout(ppl_plan_t p, int64_t gcap, bool resident, int64_t
   p->tab_vm = L.take((uint64_t)std::max<int64_t>(p->Pm, 1) * 4);
   p->tab_op = L.take((uint64_t)p->Np * 4);
   p->tab_om = L.take((uint64_t)std::max<int64_t>(p->Nm, 1) * 4);
-  p->red = L.take((uint64_t)(kReduceBlocks * 4 + 8) * 8);
+  p->red = L.take((uint64_t)(kReduceBlocks * 4 + kHostRed) * 8);
   p->diis_slot_n = p->Np * p->ldp + std::max<int64_t>(p->Nm, 1) * p->ldm;
   if (p->diis_max > 0) {
     p->diis_t = L.take((uint64_t)p->diis_max * p->diis_slot_n * 8);
@@ -628,31 +628,56 @@ static int setup_ov_integrals(ppl_plan_t p, const double* L) {
   return PPL_OK;
 }
 
-// Sums that the host reads go to mapped host memory where the plan has some (from its binding or
-// first iteration on; a copy and its wait took 24 us, the wait alone 11), else to the workspace.
+// Sums that the host reads go to mapped host memory (a copy and its wait took 24 us, the wait alone
+// 11): a slot of one pinned block of the process (48 KB, kept: freeing pinned memory waits for the
+// whole device, and a plan goes without a wait). A plan holds a slot from its binding to its end;
+// where none is free the sums go to its workspace and are copied.
+constexpr int kHostSlots = 256;
+static std::mutex g_slots_mutex;
+static double* g_slots = nullptr;
+static bool g_slot_taken[kHostSlots];
+
+static double* host_slot_take() {
+  std::lock_guard<std::mutex> lock(g_slots_mutex);
+  if (!g_slots) {
+    // (pinned memory may be taken while another stream records a graph)
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    if (hipHostMalloc((void**)&g_slots, (size_t)kHostSlots * kHostRed * sizeof(double),
+                      hipHostMallocMapped | hipHostMallocPortable) != hipSuccess) {
+      g_slots = nullptr;
+      (void)hipGetLastError();
+    }
+    if (swapped) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (!g_slots) return nullptr;
+  }
+  for (int k = 0; k < kHostSlots; ++k)
+    if (!g_slot_taken[k]) {
+      g_slot_taken[k] = true;
+      return g_slots + (size_t)k * kHostRed;
+    }
+  return nullptr;
+}
+
+static void host_slot_return(double* slot) {
+  std::lock_guard<std::mutex> lock(g_slots_mutex);
+  g_slot_taken[(slot - g_slots) / kHostRed] = false;
+}
+
+// Where launches leave sums for the host: entries 0 .. 2 + kDiisMax, and the symmetry check's behind.
 static double* red_target(ppl_plan_t p) {
+  if (p->host_red) p->host_pending = true;
   return p->host_red ? p->host_red : at<double>(p, p->red) + kReduceBlocks * 4;
 }
+constexpr int kRedCheck = kHostRed - 4;
 
-static int need_host_red(ppl_plan_t p) {
-  if (!p->host_red) PPL_HIP_TRY(hipHostMalloc((void**)&p->host_red, kHostRed * sizeof(double), hipHostMallocMapped));
-  return PPL_OK;
-}
-
-static int read_red(ppl_plan_t p, double out[4]) {
+// the first n of them, when everything enqueued before is done
+static int read_red(ppl_plan_t p, double* out, int n = 3) {
   if (!p->host_red)
-    PPL_HIP_TRY(hipMemcpyAsync(out, red_target(p), 4 * sizeof(double), hipMemcpyDeviceToHost, p->stream));
+    PPL_HIP_TRY(hipMemcpyAsync(out, red_target(p), n * sizeof(double), hipMemcpyDeviceToHost, p->stream));
   PPL_HIP_TRY(hipStreamSynchronize(p->stream));
-  if (p->host_red) memcpy(out, p->host_red, 4 * sizeof(double));
-  return PPL_OK;
-}
-
-// What the symmetry check of a build needs: taken when the workspace is bound (18 us once), so that
-// a first build is not slower than the next.
-static int need_check(ppl_plan_t p) {
-  PPL_TRY(need_host_red(p));
-  if (!p->ev_check)
-    PPL_HIP_TRY(hipEventCreateWithFlags(&p->ev_check, hipEventDisableTiming | hipEventReleaseToSystem));
+  p->host_pending = false;
+  if (p->host_red) memcpy(out, p->host_red, n * sizeof(double));
   return PPL_OK;
 }
 
@@ -662,17 +687,29 @@ static int need_check(ppl_plan_t p) {
 // staging: 44 us of idle device per build before).
 static int symmetry_sums(ppl_plan_t p, const double* L) {
   if (!p->sym_build) return PPL_OK;
-  PPL_TRY(need_check(p));
-  PPL_TRY(asymmetry_vv(p->stream, L, p->o, p->v, p->naux, at<double>(p, p->red), p->host_red + kHostRed - 4));
+  PPL_TRY(asymmetry_vv(p->stream, L, p->o, p->v, p->naux, at<double>(p, p->red), red_target(p) + kRedCheck));
   PPL_HIP_TRY(hipEventRecord(p->ev_check, p->stream));
+  return PPL_OK;
+}
+
+// (the event's wait covers everything enqueued before the sums, too)
+static int symmetry_wait(ppl_plan_t p) {
+  if (!p->sym_build) return PPL_OK;
+  PPL_HIP_TRY(hipEventSynchronize(p->ev_check));
+  p->host_pending = false;
   return PPL_OK;
 }
 
 static int symmetry_verdict(ppl_plan_t p) {
   if (!p->sym_build) return PPL_OK;
-  PPL_HIP_TRY(hipEventSynchronize(p->ev_check));
+  PPL_TRY(symmetry_wait(p));
   double h[2];
-  memcpy(h, p->host_red + kHostRed - 4, sizeof(h));
+  if (p->host_red) {
+    memcpy(h, p->host_red + kRedCheck, sizeof(h));
+  } else {
+    PPL_HIP_TRY(hipMemcpyAsync(h, red_target(p) + kRedCheck, sizeof(h), hipMemcpyDeviceToHost, p->stream));
+    PPL_HIP_TRY(hipStreamSynchronize(p->stream));
+  }
   if (!(h[0] <= 1e-20 * h[1]))
     return fail(PPL_E_ARG, "Cholesky vectors are not symmetric in their virtual block (relative asymmetry %.3g)",
                 h[1] > 0.0 ? sqrt(h[0] / h[1]) : 0.0);
@@ -1014,7 +1051,9 @@ int ppl_bind_workspace(ppl_plan_t p, void* dptr, uint64_t bytes) {
                                hipMemcpyHostToDevice, st));
   }
   PPL_HIP_TRY(hipStreamSynchronize(st));   // the host tile table must not be reused before the copy ends
-  if (p->sym_build) PPL_TRY(need_check(p));
+  if (!p->host_red) p->host_red = host_slot_take();
+  if (p->sym_build && !p->ev_check)
+    PPL_HIP_TRY(hipEventCreateWithFlags(&p->ev_check, hipEventDisableTiming | hipEventReleaseToSystem));
   p->setup_done = true;
   return PPL_OK;
 }
@@ -1319,9 +1358,7 @@ int ppl_iterate(ppl_plan_t p, const double* L, const double* e_occ, const double
   memset(&r, 0, sizeof(r));
   hipStream_t st = p->stream;
   double* partials = at<double>(p, p->red);
-  PPL_TRY(need_host_red(p));
-  double* const red_out = p->host_red;
-  double h[4];
+  double h[3 + kDiisMax];
 
   const int* tabs[4] = {at<int>(p, p->tab_op), at<int>(p, p->tab_om), at<int>(p, p->tab_vp),
                         at<int>(p, p->tab_vm)};
@@ -1330,19 +1367,19 @@ int ppl_iterate(ppl_plan_t p, const double* L, const double* e_occ, const double
   // each leaves the start's energy and non-finite count in the sums that the host reads
   auto load_mp2 = [&]() -> int {
     return mp2_start(st, p->o, p->v, e_occ, e_vir, at<double>(p, p->vs), at<double>(p, p->va), p->ldp,
-                     p->ldm, s64, a64, tabs[0], tabs[1], tabs[2], tabs[3], partials, red_out);
+                     p->ldm, s64, a64, tabs[0], tabs[1], tabs[2], tabs[3], partials, red_target(p));
   };
   auto load_given = [&]() -> int {
     PPL_TRY(pack_amplitudes(p, nullptr, t2));
     return energy_only(st, p->o, p->v, at<double>(p, p->vs), at<double>(p, p->va), s64, a64, p->ldp, p->ldm,
-                       tabs[0], tabs[1], tabs[2], tabs[3], partials, red_out);
+                       tabs[0], tabs[1], tabs[2], tabs[3], partials, red_target(p));
   };
   // integrals V = (ia|jb) packed into VS / VA and the start, then V+- of every operand set, then
   // the hole-hole W+- (the build scratch holds them for the sweeps of a resident plan)
   PPL_TRY(setup_ov_integrals(p, L));
   PPL_TRY(o.start == PPL_START_MP2 ? load_mp2() : load_given());
   PPL_TRY(ppl_build_batch(p, L, -1));
-  if (p->sym_build) memcpy(h, p->host_red, sizeof(h));   // (its symmetry check has waited for the start too)
+  if (p->sym_build && p->host_red) memcpy(h, p->host_red, 3 * sizeof(double));   // (its check has waited for them)
   else PPL_TRY(read_red(p, h));
   if (o.hhl) PPL_TRY(hhl_integrals(p, L));
   RingLayout rl;
@@ -1434,9 +1471,9 @@ int ppl_iterate(ppl_plan_t p, const double* L, const double* e_occ, const double
     const OperandRows op = slot < 0 ? rows_of(s) : OperandRows{};
     PPL_TRY(update_sweep(st, s.prec == PPL_FP64 ? PPL_FP64 : PPL_FP32, p->o, p->v, e_occ, e_vir,
                          at<double>(p, p->vs), at<double>(p, p->va), res[0], res[1], p->ldp, p->ldm, s64, a64,
-                         tabs[0], tabs[1], tabs[2], tabs[3], partials, red_out, op, d));
+                         tabs[0], tabs[1], tabs[2], tabs[3], partials, red_target(p), op, d));
     fresh = op.prec != PPL_FP64 ? &s : nullptr;
-    return read_red(p, h);
+    return read_red(p, h, 3 + d.others.n);
   };
   // before a DIIS sweep: the slot it writes (the oldest vector's once the subspace is full)
   auto diis_pick_slot = [&]() {
@@ -1454,7 +1491,7 @@ int ppl_iterate(ppl_plan_t p, const double* L, const double* e_occ, const double
     DiisSet set{};
     set.n = (int)sub.size();
     // the sweep left <e, e_i> of the earlier errors behind its own sums; <e, e> is the residual^2
-    for (int i = 0; i + 1 < set.n; ++i) B[slot][sub[i]] = B[sub[i]][slot] = red_out[3 + i];
+    for (int i = 0; i + 1 < set.n; ++i) B[slot][sub[i]] = B[sub[i]][slot] = h[3 + i];
     B[slot][slot] = h[0];
     double c[kDiisMax];
     while (!diis_solve(B, sub, c)) {
@@ -1718,7 +1755,7 @@ int ppl_mp2(ppl_plan_t p, const double* L, const double* e_occ, const double* e_
                     at<int>(p, p->tab_vm), partials, red_out));
   PPL_TRY(unpack_t(st, p->o, p->v, s64, p->ldp, a64, p->ldm, t2_out));
   if (e_mp2) {
-    double h[4];
+    double h[3];
     PPL_TRY(read_red(p, h));
     *e_mp2 = h[1];
   }
@@ -1733,7 +1770,7 @@ int ppl_mlp_sigma(ppl_plan_t p, const double* t_mp2, double* sigma) {
   double* red_out = red_target(p);
   const int64_t n = (int64_t)p->o * p->o * p->v * p->v;
   PPL_TRY(sumsq_launch(p->stream, t_mp2, n, partials, red_out));
-  double h[4];
+  double h[3];
   PPL_TRY(read_red(p, h));
   *sigma = sqrt(h[0] / (double)n);
   return PPL_OK;
@@ -1753,7 +1790,8 @@ int ppl_mlp_samples(ppl_plan_t p, const double* t_mp2, const double* t_star, con
 int ppl_destroy(ppl_plan_t p) {
   if (!p) return PPL_OK;
   for (hipEvent_t e : p->prof_pool) (void)hipEventDestroy(e);
-  if (p->host_red) (void)hipHostFree(p->host_red);
+  // (a launch that a failed call left behind may still write to its slot, which is then not reused)
+  if (p->host_red && !p->host_pending) host_slot_return(p->host_red);
   if (p->ev_check) (void)hipEventDestroy(p->ev_check);
   delete p;
   return PPL_OK;
@@ -2217,6 +2255,7 @@ int ppl_batch_build(ppl_batch_t b, const double* const* L) {
     if (!L[k]) return fail(PPL_E_ARG, "null L for instance %d", k);
     PPL_TRY(symmetry_sums(b->plans[k], L[k]));
   }
+  for (int k = 0; k < b->n; ++k) PPL_TRY(symmetry_wait(b->plans[k]));
   for (int k = 0; k < b->n; ++k) PPL_TRY(symmetry_verdict(b->plans[k]));
   PPL_TRY(batch_build_branches(b, L, true));
   b->built = true;

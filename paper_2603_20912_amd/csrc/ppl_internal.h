@@ -155,7 +155,8 @@ struct ppl_plan_s {
   std::vector<int64_t> tiles_n;        // tiles in each batch's list, [set][batch]
   int tile_sets = 1;                   // 2 when the FP64 copy builds on a tile of its own
   const double* L_last = nullptr;
-  double* host_red = nullptr;          // mapped host memory for sums that the host reads (kHostRed doubles)
+  double* host_red = nullptr;          // mapped host memory for sums that the host reads (kHostRed doubles), if any
+  bool host_pending = false;           // launches that write there were enqueued and not waited for
   hipEvent_t ev_check = nullptr;       // after the symmetry check's sums
   bool setup_done = false;
   // kernel timing

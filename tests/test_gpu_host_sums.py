@@ -5,6 +5,7 @@ import sys
 import numpy as np
 import pytest
 
+import oracle as O
 import ppl_synth as S
 
 pytestmark = pytest.mark.gpu
@@ -58,4 +59,93 @@ def test_captured_mp2_outlives_its_plan(P):
         torch.cuda.synchronize()
         assert np.array_equal(t.cpu().numpy(), ref[k])
     del graph
+    eng.close()
+
+
+def solve(P, s, o, v, naux, **kw):
+    eng = P.PPL(o, v, naux, hbm_budget=1 << 30, diis_max=4, **kw)
+    t = torch.zeros((o, o, v, v), dtype=torch.float64, device="cuda")
+    rep = eng.iterate(dev(s["L"]), dev(s["e_occ"]), dev(s["e_vir"]), t, max_sweeps=8, tol=0.0,
+                      fail_on_noconv=False, diis=4)
+    return eng, t.cpu().numpy(), rep
+
+
+def test_plans_beyond_the_pinned_slots(P):
+    """A plan that finds no free slot copies its sums from the workspace: the same numbers (start
+    energy, symmetry check, residuals, DIIS products); a slot given back serves a later plan."""
+    o, v, naux = 3, 12, 36
+    s = S.make_system(o, v, naux, 7, "contractive")
+    bad = s["L"].copy()
+    bad[0, o, o + 1] += 1.0
+    first = solve(P, s, o, v, naux)
+    say(f"plans beyond the slots ({o},{v},{naux}), {first[0].info['workspace_bytes']} B each")
+    _, hist, _ = O.jacobi_diis(s["L"], o, s["e_occ"], s["e_vir"], m=4, max_sweeps=8, tol=0.0)
+    h, hr = np.array(first[2]["history"]), np.array(hist)
+    big = hr > 1e-8                      # residuals agree to rounding until they approach it
+    assert big.sum() >= 4 and np.all(np.abs(h[big] - hr[big]) <= 1e-6 * hr[big])
+    held = [first[0]] + [P.PPL(o, v, naux, hbm_budget=1 << 30) for _ in range(300)]
+    for k in range(2):
+        eng, t, rep = solve(P, s, o, v, naux)
+        assert np.array_equal(t, first[1]) and rep == first[2]
+        e2, em = eng.mp2(dev(s["L"]), dev(s["e_occ"]), dev(s["e_vir"]))
+        assert em == rep["energy_start"] and np.isfinite(e2.cpu().numpy()).all()
+        with pytest.raises(P.PPLError):
+            eng.build(dev(bad))
+        eng.close()
+        for h in held:
+            h.close()
+        held = []
+
+
+def test_destroy_waits_for_no_other_work(P):
+    """ppl_destroy frees host metadata: work of other streams is still running when it returns."""
+    o, v, naux = 2, 8, 6
+    say("destroy beside a busy stream")
+    eng = P.PPL(o, v, naux)
+    eng.build(dev(S.make_system(o, v, naux, 131)["L"]))
+    a = torch.randn(6144, 6144, dtype=torch.float64, device="cuda")
+    c = torch.empty_like(a)
+    torch.mm(a, a, out=c)
+    torch.cuda.synchronize()
+    busy = torch.cuda.Stream()
+    with torch.cuda.stream(busy):
+        for _ in range(60):              # about 6.5 ms each
+            torch.mm(a, a, out=c)
+    plan, eng.plan = eng.plan, None
+    P.ppl_destroy(plan)
+    running = not busy.query()
+    torch.cuda.synchronize()
+    assert running
+    eng.close()
+
+
+def test_bind_and_destroy_beside_a_capture(P):
+    """Plans come and go while another stream records a graph."""
+    o, v, naux = 3, 9, 7
+    say("destroy inside a capture")
+    s = S.make_system(o, v, naux, 132)
+    t = dev(S.make_amplitudes(o, v, 133))
+    st = torch.cuda.Stream()
+    eng = P.PPL(o, v, naux, stream=st)
+    other = P.PPL(o, v, naux)
+    eng.build(dev(s["L"]))
+    other.build(dev(s["L"]))
+    torch.cuda.synchronize()
+    R = torch.empty_like(t)
+    eng.contract(t, R)
+    torch.cuda.synchronize()
+    ref = R.cpu().numpy()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=st):
+        plan, other.plan = other.plan, None
+        P.ppl_destroy(plan)
+        eng.contract(t, R)
+    for _ in range(3):
+        R.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(R.cpu().numpy(), ref)
+    del graph
+    other.close()
     eng.close()
