@@ -106,7 +106,9 @@ typedef struct {
   int32_t  n_minus;           /* N- = o(o-1)/2 occupied pairs i<j */
   int32_t  p_plus;            /* P+ = v(v+1)/2 virtual pairs a<=b */
   int32_t  p_minus;           /* P- = v(v-1)/2 virtual pairs a<b */
-  int32_t  splits_contract;   /* split-K slices of the R+ contraction GEMM (1 = none, 0 = stream-K) */
+  int32_t  splits_contract;   /* split-K slices of the R+ contraction GEMM (1 = none, 0 = stream-K). An FP64 streaming plan
+                               made with stream-K, or with more slices than its workspace holds sums
+                               for, takes as many as it holds and reports them here */
   int32_t  tile_contract_minus;   /* tile id of the R- contraction GEMM */
   int32_t  splits_contract_minus; /* split-K slices of the R- contraction GEMM (0 = stream-K) */
   uint64_t build_scratch_bytes;   /* bytes of the integral-build scratch */
@@ -350,6 +352,10 @@ int ppl_mlp_destroy(ppl_mlp_t mlp);
  * per workgroup the device holds at once; tiles shared by several workgroups are
  * summed afterwards in workgroup order). Split-K slices are summed in slice order,
  * so a fixed configuration on a given device gives bitwise reproducible results.
+ * FP64 streaming plans contract upper-triangle steps, each cut into the slices asked for; where
+ * the workspace holds fewer sums, slices share them in slice order, in several launches. These
+ * steps have no stream-K form: 0 selects as many slices as the workspace holds sums, and
+ * ppl_plan_query reports that number.
  * The planner (and ppl_autotune) give PPL_BF16X6 plans K slices of at most 12288
  * elements, because its error grows with the length of each FP32 accumulation; a
  * configuration set here with fewer slices, or stream-K, runs but is less accurate.

@@ -271,8 +271,8 @@ static uint64_t assign_layout(ppl_plan_t p, int64_t gcap, bool resident, int64_t
   }
   p->rp = L.take((uint64_t)p->Np * p->ldp * 8);
   p->rm = L.take((uint64_t)std::max<int64_t>(p->Nm, 1) * p->ldm * 8);
-  // upper-triangle steps accumulate each K slice over all columns, in as many slices as the plan was
-  // given, where they take no more than the step's own V+ rows
+  // upper-triangle steps accumulate each K slice over all columns, in as many sums as the plan was
+  // given slices, where they take no more than the step's own V+ rows
   p->step_slices = 1;
   if (!resident && p->sym_build) {
     const uint64_t slice = (uint64_t)p->Np * p->ldp * 8 + (uint64_t)p->Nm * p->ldm * 8;
@@ -332,6 +332,10 @@ static uint64_t assign_layout(ppl_plan_t p, int64_t gcap, bool resident, int64_t
   p->cube_off = p->sym_build ? L.take((uint64_t)(v + 1) * 8) : Region{};
   return L.cur;
 }
+
+// K slices of a plan of upper-triangle steps: at most as many as it holds sums, and as many for
+// stream-K, which those steps have no form of
+static int step_splits(ppl_plan_t p, int sp) { return sp > 0 ? std::min(sp, p->step_slices) : p->step_slices; }
 
 // Build tile lists per step: set 0 for the plan's operands, set 1 for the FP64 copy of
 // a mixed plan when that builds on another tile.
@@ -480,18 +484,27 @@ static int build_all(ppl_plan_t p, OperandSet& s, const double* L, bool staged) 
 // (30, 300, 900) with a third of V+- in memory 58.6 ms (62 TF/s, 6 steps), 81 as two products per
 // sign, the second through a transposed copy of the step's rows into transposed sums (8 steps:
 // that copy took as much memory as a step's V+ rows, and half of the step's own columns was
-// computed on zeros). K slices accumulate apart and are summed by the consumer (out) or at the end.
+// computed on zeros). K slices accumulate apart and are summed by the consumer (out) or at the end;
+// a plan given more of them than it holds sums (step_slices) takes them in several launches, slice s
+// accumulating in sum s mod step_slices.
 static int contract_stream_sym(ppl_plan_t p, OperandSet& s, int tile, int tile_m, int split_p, int split_m,
                                Slices (*out)[2]) {
   hipStream_t st = p->stream;
   if (s.prec != PPL_FP64) return fail(PPL_E_STATE, "streaming upper-triangle plan in precision %d", s.prec);
-  auto slices = [&](int sp) { return sp > 0 ? std::min(sp, p->step_slices) : p->step_slices; };
-  const int np = slices(split_p), nm = slices(split_m);
+  const int np = std::min(split_p, p->step_slices), nm = std::min(split_m, p->step_slices);
   double* part = at<double>(p, p->part);
   StepSide plus{p->Np, p->Pp, p->ldp, at<double>(p, s.sp), at<double>(p, s.vp), np > 1 ? part : at<double>(p, p->rp),
-                p->Np * p->ldp, 0, 0, np, false};
+                p->Np * p->ldp, 0, 0, split_p, 0, 0, false};
   StepSide minus{p->Nm, p->Pm, p->ldm, at<double>(p, s.am), at<double>(p, s.vm),
-                 nm > 1 ? part + p->step_slices * plus.stride : at<double>(p, p->rm), p->Nm * p->ldm, 0, 0, nm, false};
+                 nm > 1 ? part + p->step_slices * plus.stride : at<double>(p, p->rm), p->Nm * p->ldm, 0, 0, split_m, 0, 0, false};
+  auto product = [&](int t, StepSide& c, bool first) {
+    for (c.s0 = 0; c.s0 < c.splits; c.s0 += p->step_slices) {
+      c.ns = std::min(p->step_slices, c.splits - c.s0);
+      c.first = first && c.s0 == 0;
+      PPL_TRY(gemm_step(st, t, c));
+    }
+    return PPL_OK;
+  };
   // one half (U or U^T) of a step's rows [r0, r1) of an n-row block: useful flops
   auto half_flops = [](int64_t rows, int64_t n, int64_t r0, int64_t r1) {
     const double w = (double)(r1 - r0);
@@ -501,13 +514,12 @@ static int contract_stream_sym(ppl_plan_t p, OperandSet& s, int tile, int tile_m
     const Batch& b = p->batches[bi];
     PPL_TRY(build_one(p, s, p->L_last, bi, bi > 0));
     plus.p0 = b.p0, plus.p1 = b.p1, minus.p0 = b.q0, minus.p1 = b.q1;
-    plus.first = minus.first = bi == 0;
     {
       ProfScope ps(p, PPL_PROF_CONTRACT_PLUS, 2.0 * half_flops(p->Np, p->Pp, b.p0, b.p1));
-      PPL_TRY(gemm_step(st, tile, plus));
+      PPL_TRY(product(tile, plus, bi == 0));
     }
     ProfScope ps(p, PPL_PROF_CONTRACT_MINUS, 2.0 * half_flops(p->Nm, p->Pm, b.q0, b.q1));
-    PPL_TRY(gemm_step(st, tile_m, minus));
+    PPL_TRY(product(tile_m, minus, bi == 0));
   }
   ProfScope ps(p, PPL_PROF_OTHER, 0.0);
   if (np > 1) {
@@ -970,7 +982,11 @@ static int plan_create(const ppl_desc_t* d, ppl_plan_t* out, bool external_g) {
     }
     need = need_for(lo);
     gcap = lo;
-    if (p->sym_build) build_column_order(p->v, p->cols_host);
+    if (p->sym_build) {
+      build_column_order(p->v, p->cols_host);
+      p->split_p = step_splits(p, p->split_p);
+      p->split_m = step_splits(p, p->split_m);
+    }
   }
   p->g_pairs_cap = gcap;
   p->a_per_batch = p->batches.empty() ? 0 : p->batches[0].a1 - p->batches[0].a0;
@@ -1601,10 +1617,11 @@ int ppl_set_contract_config(ppl_plan_t p, int32_t tp, int32_t sp, int32_t tm, in
   if (tp < 0 || tp >= nt || tm < 0 || tm >= nt) return fail(PPL_E_ARG, "tile id out of range [0, %d)", nt);
   if (sp < 0 || sp > kMaxSplits || sm < 0 || sm > kMaxSplits)
     return fail(PPL_E_ARG, "split count out of range [0, %d] (0 = stream-K)", kMaxSplits);
+  const bool steps = !p->resident && p->sym_build;
   p->tile_contract = tp;
-  p->split_p = sp;
+  p->split_p = steps && sp == 0 ? p->step_slices : sp;
   p->tile_m = tm;
-  p->split_m = sm;
+  p->split_m = steps && sm == 0 ? p->step_slices : sm;
   return PPL_OK;
 }
 

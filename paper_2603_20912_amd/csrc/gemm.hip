@@ -206,15 +206,15 @@ struct EpiSK {           // stream-K: whole tiles go to C, shared tiles to a den
 // row k0 on, zero in the rows [k0, p0) and p1 .. p1 + 15, and in the columns of a row's
 // kTriBlock block before its own pair. Column tile n0 takes the chunks of the step's rows
 // k < n0 + bn, K-major (U^T), and, where it meets the step's own columns, then the chunks from
-// its first column on along the rows n (U). Both runs are cut into `splits` equal slices,
-// slice s accumulating in C + s * stride (first: written).
+// its first column on along the rows n (U). Both runs are cut into `splits` equal slices, of which
+// this launch takes those from s0 on; its slice j accumulates in C + j * stride (first: written).
 struct EpiStep {
   static constexpr bool kTri = false, kStep = true;
   static constexpr int KC = kKcF64;
   double* C;
   int64_t ldc, M, N, stride;
   int64_t k0, p0, p1, nk;   // nk: chunks of a whole row
-  int splits;
+  int splits, s0;
   bool first;
   __device__ int64_t arow(int64_t r) const { return r; }
   // columns outside the step take a zero row
@@ -224,11 +224,12 @@ struct EpiStep {
     const int64_t ka = k0 / KC, ke = (p1 + KC - 1) / KC, ne = (j.n0 + bn) / KC;
     const int64_t nn = (ke < ne ? ke : ne) - ka;
     const int64_t ta = j.n0 / KC > ka ? j.n0 / KC : ka, total = nn + (j.n0 < p1 ? nk - ta : 0);
-    const int64_t s0 = total * j.split / splits, s1 = total * (j.split + 1) / splits;
-    c0 = ka + (s0 < nn ? s0 : nn);
-    cd = ka + (s1 < nn ? s1 : nn);
-    t0 = ta + (s0 > nn ? s0 - nn : 0);
-    c1 = ta + (s1 > nn ? s1 - nn : 0);
+    const int s = s0 + j.split;
+    const int64_t lo = total * s / splits, hi = total * (s + 1) / splits;
+    c0 = ka + (lo < nn ? lo : nn);
+    cd = ka + (hi < nn ? hi : nn);
+    t0 = ta + (lo > nn ? lo - nn : 0);
+    c1 = ta + (hi > nn ? hi - nn : 0);
   }
   __device__ void row(int split, int64_t m, int64_t& base, bool& ok) const {
     ok = m < M;
@@ -1997,16 +1998,17 @@ static int step_cfg(hipStream_t s, const StepSide& c) {
   constexpr int BM = 16 * WM * WAVES_M, BN = 16 * WN * WAVES_N;
   static_assert(kTriBlock % BN == 0, "a column tile lies in one diagonal block");
   const EpiStep epi{(double*)c.C, c.ld, c.rows, c.cols, c.stride, c.p0 / kStepRows * kStepRows,
-                    c.p0, c.p1, c.ld / kKcF64, c.splits, c.first};
-  const MapStep map{(c.rows + BM - 1) / BM, c.p0 / BN, (c.p1 + BN - 1) / BN, (c.cols + BN - 1) / BN, BM, BN, c.splits};
-  return launch<double, WM, WN, WAVES_M, WAVES_N, kKcF64>(s, map.n_mt * (map.n_nt - map.nt0) * c.splits, c.rows, c.cols,
+                    c.p0, c.p1, c.ld / kKcF64, c.splits, c.s0, c.first};
+  const MapStep map{(c.rows + BM - 1) / BM, c.p0 / BN, (c.p1 + BN - 1) / BN, (c.cols + BN - 1) / BN, BM, BN, c.ns};
+  return launch<double, WM, WN, WAVES_M, WAVES_N, kKcF64>(s, map.n_mt * (map.n_nt - map.nt0) * c.ns, c.rows, c.cols,
                                                       c.ld, c.S, c.ld, c.U, c.ld, epi, map);
 }
 
 int gemm_step(hipStream_t s, int tile, const StepSide& c) {
   static_assert(kStepRows == kKcF64, "a step starts on a chunk");
   if (c.rows <= 0 || c.p1 <= c.p0) return PPL_OK;
-  if (c.p1 > c.cols || c.ld % 64 != 0 || c.ld < c.cols || c.splits < 1 || c.splits > kMaxSplits)
+  if (c.p1 > c.cols || c.ld % 64 != 0 || c.ld < c.cols || c.splits < 1 || c.splits > kMaxSplits || c.s0 < 0 ||
+      c.ns < 1 || c.s0 + c.ns > c.splits)
     return fail(PPL_E_ARG, "streaming step out of range");
   switch (tile) {
     case 0: return step_cfg<7, 2, 1, 4>(s, c);

@@ -146,7 +146,7 @@ struct ppl_plan_s {
   ppl::Region tiles;                   // per-batch (row tile, column tile) lists of the build GEMM (int32 pairs)
   bool sym_build = false;              // build the upper triangle of V+- (resident: rows of it, see kTriBlock;
                                        // streaming: contract U and U^T of each step, V = U + U^T)
-  int step_slices = 1;                 // streaming upper-triangle steps: K slices `part` holds of R+ and R- (1: none)
+  int step_slices = 1;                 // streaming upper-triangle steps: sums `part` holds of R+ and R- (1: none)
   ppl::Region cols;                    // operand rows of the upper-triangle build's columns (int32, v(v+1)/2)
   ppl::Region cube_off;                // upper-triangle builds: cubes below each virtual (int64, v + 1)
   std::vector<int> cols_host;
@@ -213,15 +213,16 @@ struct ContractSide {
 bool contract_pair_ok(int prec, const ContractSide (&c)[2]);
 int gemm_contract_pair(hipStream_t s, int prec, const ContractSide (&c)[2]);
 // R+ or R- (FP64) += S' V_step for one step [p0, p1) of a streaming plan (EpiStep): U holds the
-// step's rows from row p0 rounded down to kStepRows on, and zero rows at its end. Slice s of K
-// goes to C + s * stride; first: C is written, not read.
+// step's rows from row p0 rounded down to kStepRows on, and zero rows at its end. Of `splits` slices
+// of K those in [s0, s0 + ns) are computed, slice s into C + (s - s0) * stride; first: C is written, not
+// read.
 constexpr int kStepRows = 16;
 struct StepSide {
   int64_t rows, cols, ld;   // occupied pairs, virtual pairs, row length of every operand and of C
   const double *S, *U;
   double* C;
   int64_t stride, p0, p1;
-  int splits;
+  int splits, s0, ns;
   bool first;
 };
 int gemm_step(hipStream_t s, int tile, const StepSide& c);
