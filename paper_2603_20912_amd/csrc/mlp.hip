@@ -35,16 +35,18 @@ int64_t mlp_train_partials(int64_t max_batch) {
   return std::min<int64_t>((max_batch + kTrainRows - 1) / kTrainRows, kTrainGroups);
 }
 
-// z / (1 + exp(-z)) with one reciprocal and one residual step for the quotient: compared over
-// every float on gfx950, the bits of the correctly rounded quotient for 1e-30 <= |z| <= 80. The
-// exponent is held at 2^125.5 so that 1 + exp(-z) and its reciprocal stay normal numbers; below
-// z = -87 the result is still within 1e-35 of its value, zero in every later sum.
+// z / (1 + exp(-z)) with one reciprocal and one residual step for the quotient. Compared over every
+// float on gfx950 with that expression as written: the same bits, except for -89 < z < -87.3, where
+// it gives -0 for values of at most 1.1e-36, and z = +inf, where it gives NaN for +inf (silu_any has
+// +inf). The exponential is held below 2^128, so that 1 + exp(-z) is finite; its reciprocal is flushed
+// to zero above 2^126, which makes the result -0 for every finite z beyond.
 __device__ inline float silu_f(float z) {
-  const float d = 1.0f + __builtin_amdgcn_exp2f(fminf(-1.44269504088896340736f * z, 125.5f));
+  const float d = 1.0f + __builtin_amdgcn_exp2f(fminf(-1.44269504088896340736f * z, 127.99f));
   const float r = __builtin_amdgcn_rcpf(d);
   const float y = z * r;
   return fmaf(fmaf(-d, y, z), r, y);
 }
+__device__ inline float silu_any(float z) { return z == __builtin_huge_valf() ? z : silu_f(z); }
 
 // Sum over the 16 lanes of a row (l / 16 equal), the same in each: x + x(l^1), then l^2, then the
 // other half of eight and of sixteen, whose lanes already hold equal sums.
@@ -373,6 +375,29 @@ int mlp_samples_launch(hipStream_t s, int o, int v, const double* tm, const doub
 // Bound by the vector unit, 256 SiLUs per element: 1.10 ms at (20, 200), 8.0e6 evaluations; 3.51
 // with the weights staged in LDS for every 64 elements, scattered partners and the compiler's
 // quotient (1.56 with that quotient). Results are bit-identical to that form.
+// The network's output (without its bias) at x where some hidden unit is NaN or +inf, so that the
+// output is NaN or infinite in any order of its sums: element by element, the first layer anew
+// for each unit of the second.
+__device__ inline float far_output(const float* __restrict__ prm, f4 x) {
+  auto h1 = [&](int k) __attribute__((always_inline)) {
+    const float* w = &prm[kOffW1 + 4 * k];
+    const float z = fmaf(w[3], x[3], fmaf(w[2], x[2], fmaf(w[1], x[1], fmaf(w[0], x[0], prm[kOffB1 + k]))));
+    return (float)(__bf16)silu_any(z);
+  };
+#pragma unroll 1
+  for (int k = 0; k < kH; ++k)
+    if (const float h = h1(k); h != h) return h;
+  float y = 0.0f;
+#pragma unroll 1
+  for (int j = 0; j < kH; ++j) {
+    float z = 0.0f;
+#pragma unroll 1
+    for (int k = 0; k < kH; ++k) z = fmaf((float)(__bf16)prm[kOffW2 + j * kH + k], h1(k), z);
+    y = fmaf(prm[kOffW3 + j], silu_any(z + prm[kOffB2 + j]), y);
+  }
+  return y;
+}
+
 constexpr int kInferThreads = 256;
 
 __global__ void __launch_bounds__(kInferThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
@@ -424,6 +449,7 @@ mlp_infer_kernel(const float* __restrict__ prm, int o, int v, const double* __re
     const double eo = e_occ[i] + e_occ[j], evb = b < v ? e_vir[b] : 0.0;
     const int64_t row_ij = ((int64_t)i * o + j) * vv, row_ji = ((int64_t)j * o + i) * vv;
     const int na = v - 16 * A < 16 ? v - 16 * A : 16;
+    bool nan = false;
     double t = b < v ? tm[row_ij + (int64_t)(16 * A) * v + b] : 0.0;
     for (int al = 0; al < na; ++al) {
       const int a = 16 * A + al;
@@ -462,11 +488,22 @@ mlp_infer_kernel(const float* __restrict__ prm, int o, int v, const double* __re
         const int r = c16 & 3;
         const float y = r == 0 ? part[0] : (r == 1 ? part[1] : (r == 2 ? part[2] : part[3]));
         const double guess = fma(sigma, (double)(y + b3), t);
+        nan |= guess != guess;
         sT[wave][c16][al] = guess;
         if (b < v && (!diag || a <= b)) tout[row_ij + (int64_t)a * v + b] = guess;
       }
       t = tn;
     }
+    if (nan)                         // NaN where a hidden unit may be at +inf: which of the two it is
+      for (int al = 0; al < na; ++al) {
+        const int a = 16 * A + al;
+        const double tx = b < v ? tm[row_ij + (int64_t)a * v + b] : 0.0, eva = e_vir[a];
+        if (sT[wave][c16][al] == sT[wave][c16][al] || tx != tx) continue;
+        const float y = far_output(prm, f4{(float)(tx / sigma), (float)(eo - eva - evb), (float)eo, (float)(eva + evb)});
+        const double guess = fma(sigma, (double)(y + b3), tx);
+        sT[wave][c16][al] = guess;
+        if (b < v && (!diag || a <= b)) tout[row_ij + (int64_t)a * v + b] = guess;
+      }
     // partners (j,i,b,a), along a (the wave's own LDS writes: in order, no barrier needed)
     __builtin_amdgcn_wave_barrier();
     const int a = 16 * A + c16;
