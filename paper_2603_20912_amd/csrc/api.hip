@@ -1956,10 +1956,10 @@ int ppl_mlp_train_step(ppl_mlp_t q, const float* X, const float* Y, int64_t n, f
   PPL_TRY(mlp_check(q));
   if (!X || !Y || n < 1 || n > q->max_batch) return fail(PPL_E_ARG, "bad batch (n = %lld)", (long long)n);
   if (!(lr > 0.0f)) return fail(PPL_E_ARG, "lr must be > 0");
-  q->step += 1;
   PPL_TRY(mlp_step_launch(q->stream, mat<float>(q, q->prm), X, Y, n, mat<float>(q, q->gpart),
                           mat<float>(q, q->lpart), mat<float>(q, q->grad), mat<float>(q, q->loss),
-                          mat<float>(q, q->m), mat<float>(q, q->v), lr, q->step, 0.9f, 0.999f, 1e-8f));
+                          mat<float>(q, q->m), mat<float>(q, q->v), lr, q->step + 1, 0.9f, 0.999f, 1e-8f));
+  q->step += 1;                  // (counted once its update is on the stream)
   if (host_loss) {
     PPL_HIP_TRY(hipMemcpyAsync(host_loss, mat<float>(q, q->loss), 4, hipMemcpyDeviceToHost, q->stream));
     PPL_HIP_TRY(hipStreamSynchronize(q->stream));
