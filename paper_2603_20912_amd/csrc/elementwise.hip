@@ -313,15 +313,10 @@ pack_vpm_tri_kernel(int v, int a0, int a1, const Tg* __restrict__ T, int64_t ldt
   for (int k = 0; k < C; ++k) gdc[k] = s[k * LB + f * LD + m];
   const int c = c0 + m, d = d0 + f;
   if (d < v && c <= d) {
-    // b = b0 + k < v, and d >= b where c == a
-    const int kmax = min(min(C, v - b0), c == a ? d - b0 + 1 : C);
+    const int kmax = cube_rows(v, a, b0, c, d);
     const int64_t rp = pair_plus(a, b0, v), cp = pair_plus(c, d, v);
     const int64_t rm = pair_minus(a, b0, v), cm = pair_minus(c, d, v);
-    // some mirror entry of the cube lies in a diagonal block (the same for every thread)
-    const int e0 = d0 > c0 ? d0 : c0, bl = b0 + C < v ? b0 + C - 1 : v - 1;
-    const bool near = !STEP &&
-                      (pair_plus(c0, e0, v) / kTriBlock <= pair_plus(a, bl, v) / kTriBlock ||
-                       pair_minus(c0, e0 > c0 ? e0 : c0 + 1, v) / kTriBlock <= pair_minus(a, bl, v) / kTriBlock);
+    const bool near = !STEP && cube_near(v, a, b0, c0, d0);   // (the same for every thread)
 #pragma unroll
     for (int k = 0; k < C; ++k) {
       if (k < kmax) {
@@ -382,25 +377,21 @@ int pack_vpm_tri(hipStream_t s, int prec, int v, int a0, int a1, const void* T, 
   return fail(PPL_E_ARG, "pack_vpm_tri: unknown precision %d", prec);
 }
 
-// The zeros that EpiStep reads: of rows k in [p0, p1) the columns of their kTriBlock block before
-// the own pair, of the rows [k0, p0) and from p1 on everything right of k0's block.
+// The zeros of a step's rows (triangle.h)
 __global__ void __launch_bounds__(256)
-step_zero_kernel(double* U, int64_t ld, int64_t k0, int64_t p0, int64_t p1) {
-  const int64_t k = k0 + blockIdx.x;
-  const bool own = k >= p0 && k < p1;
-  const int64_t c1 = own ? k : ld;
-  for (int64_t c = (own ? k : k0) / kTriBlock * kTriBlock + threadIdx.x; c < c1; c += 256) U[(k - k0) * ld + c] = 0.0;
+step_zero_kernel(double* U, int64_t ld, int64_t p0, int64_t p1) {
+  const int64_t k = step_row0(p0) + blockIdx.x, c1 = step_zero_to(k, p0, p1, ld);
+  for (int64_t c = step_zero_from(k, p0, p1) + threadIdx.x; c < c1; c += 256) U[(int64_t)blockIdx.x * ld + c] = 0.0;
 }
 
 int pack_vpm_step(hipStream_t s, int v, const Batch& b, const double* T, int64_t ldt, const int64_t* off, double* vp,
                   int64_t ldp, double* vm, int64_t ldm) {
-  const int64_t kp = b.p0 / kStepRows * kStepRows, km = b.q0 / kStepRows * kStepRows;
+  const int64_t kp = step_row0(b.p0), km = step_row0(b.q0);
   PPL_TRY((launch_vpm_tri<double, PPL_FP64, true>(s, v, b.a0, b.a1, T, ldt, off, vp, nullptr, ldp, vm, nullptr, ldm, kp,
                                                   km)));
-  hipLaunchKernelGGL(step_zero_kernel, dim3((unsigned)(b.p1 - kp + kStepRows)), dim3(256), 0, s, vp, ldp, kp, b.p0, b.p1);
+  hipLaunchKernelGGL(step_zero_kernel, dim3((unsigned)(b.p1 - kp + kStepRows)), dim3(256), 0, s, vp, ldp, b.p0, b.p1);
   if (b.q1 > b.q0)
-    hipLaunchKernelGGL(step_zero_kernel, dim3((unsigned)(b.q1 - km + kStepRows)), dim3(256), 0, s, vm, ldm, km, b.q0,
-                       b.q1);
+    hipLaunchKernelGGL(step_zero_kernel, dim3((unsigned)(b.q1 - km + kStepRows)), dim3(256), 0, s, vm, ldm, b.q0, b.q1);
   PPL_LAUNCH_CHECK();
   return PPL_OK;
 }

@@ -130,7 +130,7 @@ struct MapStep {
     j.split = (int)(t / n);
     j.m0 = (r % n_mt) * bm;
     j.n0 = ((second ? nt_own : nt0) + r / n_mt) * bn;
-    j.kc0 = j.kc1 = 0;   // EpiStep::phases
+    j.kc0 = j.kc1 = 0;   // EpiStep::chunks
     return true;
   }
 };
@@ -201,35 +201,21 @@ struct EpiSK {           // stream-K: whole tiles go to C, shared tiles to a den
   }
 };
 
-// One step of a streaming plan, R += S' V_step: V = U + U^T, and the step holds the rows
-// k in [p0, p1) of U (entries at and right of the row's own pair, its diagonal halved) from global
-// row k0 on, zero in the rows [k0, p0) and p1 .. p1 + 15, and in the columns of a row's
-// kTriBlock block before its own pair. Column tile n0 takes the chunks of the step's rows
-// k < n0 + bn, K-major (U^T), and, where it meets the step's own columns, then the chunks from
-// its first column on along the rows n (U). Both runs are cut into `splits` equal slices, of which
-// this launch takes those from s0 on; its slice j accumulates in C + j * stride (first: written).
+// One step of a streaming plan, R += S' V_step, from the rows that triangle.h describes. Each column
+// tile takes the two runs of step_chunks; of their `splits` slices this launch takes those from s0 on,
+// and its slice j accumulates in C + j * stride (first: written).
 struct EpiStep {
   static constexpr bool kTri = false, kStep = true;
   static constexpr int KC = kKcF64;
   double* C;
   int64_t ldc, M, N, stride;
-  int64_t k0, p0, p1, nk;   // nk: chunks of a whole row
+  int64_t p0, p1, nk;       // nk: chunks of a whole row
   int splits, s0;
   bool first;
   __device__ int64_t arow(int64_t r) const { return r; }
-  // columns outside the step take a zero row
-  __device__ int64_t brow(int64_t n) const { return n < k0 || n >= p1 ? p1 - k0 : n - k0; }
-  // chunks [c0, cd) K-major and [t0, c1) along the rows of V
-  __device__ void phases(const TileJob& j, int bn, int64_t& c0, int64_t& cd, int64_t& t0, int64_t& c1) const {
-    const int64_t ka = k0 / KC, ke = (p1 + KC - 1) / KC, ne = (j.n0 + bn) / KC;
-    const int64_t nn = (ke < ne ? ke : ne) - ka;
-    const int64_t ta = j.n0 / KC > ka ? j.n0 / KC : ka, total = nn + (j.n0 < p1 ? nk - ta : 0);
-    const int s = s0 + j.split;
-    const int64_t lo = total * s / splits, hi = total * (s + 1) / splits;
-    c0 = ka + (lo < nn ? lo : nn);
-    cd = ka + (hi < nn ? hi : nn);
-    t0 = ta + (lo > nn ? lo - nn : 0);
-    c1 = ta + (hi > nn ? hi - nn : 0);
+  __device__ int64_t brow(int64_t n) const { return step_row(n, p0, p1); }
+  __device__ StepChunks chunks(const TileJob& j, int bn) const {
+    return step_chunks(j.n0, bn, p0, p1, nk, KC, s0 + j.split, splits);
   }
   __device__ void row(int split, int64_t m, int64_t& base, bool& ok) const {
     ok = m < M;
@@ -569,7 +555,7 @@ __device__ __forceinline__ void tile_body_direct3(const TileJob& job, int64_t M,
       } else if constexpr (NN) {
         const int id = (q - GA) * 64 + lane, kr = id / BV, cv = id % BV;
         int64_t k = c0 * KC + kr;
-        if constexpr (Epi::kStep) k -= epi.k0;
+        if constexpr (Epi::kStep) k -= step_row0(epi.p0);
         src[i] = B + k * ldb + job.n0 + (cv ^ (((kr / VEC) & XK) * VB)) * VEC;
         step[i] = (int)(KC * ldb);
         dst[i] = (BM + (q - GA) * RPI) * LDSR;
@@ -689,13 +675,10 @@ __device__ __forceinline__ void tile_body_direct3(const TileJob& job, int64_t M,
 
   int64_t c0 = job.kc0, cd = c0, t0 = c0, c1 = job.kc1;   // chunks [c0, cd) from B rows k, [t0, c1) from rows n
   if constexpr (Epi::kTri) {
-    if (epi.tri) {
-      cd = job.n0 / KC;
-      cd = cd < c0 ? c0 : (cd > c1 ? c1 : cd);
-      t0 = cd;
-    }
+    if (epi.tri) cd = t0 = tri_split(job.n0, c0, c1, KC);
   } else if constexpr (Epi::kStep) {
-    epi.phases(job, BN, c0, cd, t0, c1);
+    const StepChunks c = epi.chunks(job, BN);
+    c0 = c.c0, cd = c.cd, t0 = c.t0, c1 = c.c1;
   }
   if constexpr (Epi::kTri || Epi::kStep) {
     if (c0 < cd) run(std::true_type{}, c0, cd);
@@ -960,13 +943,9 @@ gemm_nt_pair_kernel(PairSide<T> p0, PairSide<T> p1, int64_t grid0) {
 // k < n0 from its rows k.
 template <int KC, class Epi>
 __device__ __forceinline__ int64_t below_diagonal(const TileJob& job, const Epi& epi) {
-  int64_t cd = job.kc0;
   if constexpr (Epi::kTri)
-    if (epi.tri) {
-      cd = job.n0 / KC;
-      cd = cd < job.kc0 ? job.kc0 : (cd > job.kc1 ? job.kc1 : cd);
-    }
-  return cd;
+    if (epi.tri) return tri_split(job.n0, job.kc0, job.kc1, KC);
+  return job.kc0;
 }
 
 // A staged K-major plane of a bf16 B chunk (rows k of BN elements, in blocks of 16 columns). A
@@ -1997,8 +1976,8 @@ template <int WM, int WN, int WAVES_M, int WAVES_N>
 static int step_cfg(hipStream_t s, const StepSide& c) {
   constexpr int BM = 16 * WM * WAVES_M, BN = 16 * WN * WAVES_N;
   static_assert(kTriBlock % BN == 0, "a column tile lies in one diagonal block");
-  const EpiStep epi{(double*)c.C, c.ld, c.rows, c.cols, c.stride, c.p0 / kStepRows * kStepRows,
-                    c.p0, c.p1, c.ld / kKcF64, c.splits, c.s0, c.first};
+  const EpiStep epi{(double*)c.C, c.ld, c.rows, c.cols, c.stride, c.p0, c.p1, c.ld / kKcF64,
+                    c.splits, c.s0, c.first};
   const MapStep map{(c.rows + BM - 1) / BM, c.p0 / BN, (c.p1 + BN - 1) / BN, (c.cols + BN - 1) / BN, BM, BN, c.ns};
   return launch<double, WM, WN, WAVES_M, WAVES_N, kKcF64>(s, map.n_mt * (map.n_nt - map.nt0) * c.ns, c.rows, c.cols,
                                                       c.ld, c.S, c.ld, c.U, c.ld, epi, map);

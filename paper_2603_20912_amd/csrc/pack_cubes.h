@@ -1,15 +1,11 @@
 // Index arithmetic of the cube-blocked packing of V+- from the natural output of the
 // upper-triangle build (T[(a, c)][(x, y)] = (ac|xy) over packed pairs c >= a, x <= y).
-// Shared by the packing kernel and the host-side replay that checks its coverage.
+// Shared by the packing kernel and the host-side replays that check its coverage.
 #pragma once
 
 #include <stdint.h>
 
-#if defined(__HIPCC__)
-#define PPL_HD __host__ __device__
-#else
-#define PPL_HD
-#endif
+#include "triangle.h"
 
 namespace ppl {
 
@@ -24,8 +20,8 @@ PPL_HD inline int64_t cubes_of(int v, int a) {
   return nt * nt * (nt + 1) / 2;
 }
 
-// The r-th cube of a virtual with nt blocks, in an order of equal integrals (the host-side replay
-// walks the cubes in it; the packing kernel in that of cube_decode_rows). Cubes (x, ci, y) and
+// The r-th cube of a virtual with nt blocks, in an order of equal integrals. No kernel takes it any
+// more: a replay of the packing with every mirror entry (host_check.cpp) walks the cubes in it. Cubes (x, ci, y) and
 // (y, ci, x) stage the same integrals (ac|bd) (rows c of block ci, pairs {b, d} with one index in
 // block x and one in block y), so they are taken one after the other: ci slowest; for each ci first the cubes
 // with bi < ci (no such partner), then the square bi, di >= ci by unordered pairs {x <= y},
@@ -70,6 +66,22 @@ PPL_HD inline void cube_decode_rows(int64_t r, int nt, int& bi, int& ci, int& di
     ++ci;
   }
   di = ci + q;
+}
+
+// Rows b0 + k < v, k < cube_rows, of the cube have an entry at column (c, d): column (cd) >= row (ab),
+// that is d >= b where c == a.
+PPL_HD inline int cube_rows(int v, int a, int b0, int c, int d) {
+  int n = v - b0 < kCube ? v - b0 : kCube;
+  if (c == a && d - b0 + 1 < n) n = d - b0 + 1;
+  return n;
+}
+
+// Whether a mirror entry of the cube from (b0, c0, d0) can lie in a diagonal block (kTriBlock): the first
+// column of the cube against its last row.
+PPL_HD inline bool cube_near(int v, int a, int b0, int c0, int d0) {
+  const int e0 = d0 > c0 ? d0 : c0, bl = b0 + kCube < v ? b0 + kCube - 1 : v - 1;
+  return pair_plus(c0, e0, v) / kTriBlock <= pair_plus(a, bl, v) / kTriBlock ||
+         pair_minus(c0, e0 > c0 ? e0 : c0 + 1, v) / kTriBlock <= pair_minus(a, bl, v) / kTriBlock;
 }
 
 // Virtual a of cube g given the prefix table off (off[a] = cubes of all virtuals below a),

@@ -8,19 +8,10 @@
 #include <vector>
 
 #include "../../include/ppl.h"
+#include "triangle.h"
 
 namespace ppl {
 
-// ------------------------------------------------------------------ pair indices
-// Row-major packed upper triangles of an n x n index space:
-//   plus : pairs (a, b) with a <= b, index a*n - a(a+1)/2 + b
-//   minus: pairs (a, b) with a <  b, index a*(n-1) - a(a+1)/2 + b - 1
-__host__ __device__ inline int64_t pair_plus(int64_t a, int64_t b, int64_t n) {
-  return a * n - a * (a + 1) / 2 + b;
-}
-__host__ __device__ inline int64_t pair_minus(int64_t a, int64_t b, int64_t n) {
-  return a * (n - 1) - a * (a + 1) / 2 + b - 1;
-}
 __host__ __device__ inline int64_t npairs_plus(int64_t n) { return n * (n + 1) / 2; }
 __host__ __device__ inline int64_t npairs_minus(int64_t n) { return n * (n - 1) / 2; }
 
@@ -47,12 +38,6 @@ static_assert(64 % kKcF64 == 0 && 64 % kKcF32 == 0 && 64 % bf3_kc(0, 0) == 0,
               "K chunk must divide the leading-dimension padding");
 
 __host__ __device__ inline int64_t pad_ld(int64_t k) { return (k + 63) / 64 * 64; }
-
-// Resident V+- are stored as upper triangles: entry [r][q] is valid where
-// q >= r or r / kTriBlock == q / kTriBlock (whole diagonal blocks), and the rest is never
-// read. Every column tile of a contraction (64, 128 or 256 wide, from a multiple of its
-// width) then lies in one diagonal block.
-constexpr int kTriBlock = 256;
 
 // ------------------------------------------------------------------ errors
 void set_error(const char* fmt, ...);
@@ -216,7 +201,6 @@ int gemm_contract_pair(hipStream_t s, int prec, const ContractSide (&c)[2]);
 // step's rows from row p0 rounded down to kStepRows on, and zero rows at its end. Of `splits` slices
 // of K those in [s0, s0 + ns) are computed, slice s into C + (s - s0) * stride; first: C is written, not
 // read.
-constexpr int kStepRows = 16;
 struct StepSide {
   int64_t rows, cols, ld;   // occupied pairs, virtual pairs, row length of every operand and of C
   const double *S, *U;
