@@ -254,17 +254,31 @@ static_assert(kCube == 16, "the cube packing splits an element index into 4-bit 
 // b and goes through one LDS array s[b][d][c], and where b > d so does (ac|bd), contiguous along
 // b, in a round of its own. The cubes with ci == di == 0 also zero the rows' padding.
 // Bound by the writes of its 16 x 16 row segments: the lines that segments share are merged in
-// L2 only while few are open, so spare LDS (kTriSpareLds) holds it to three workgroups per CU
-// (FP64; four in FP32, three in BF16): 1.73 ms against 1.96 with all that fit and 2.01 with two, at
-// v = 200 in one step (3.2 GB written, 1.6 read); FP32 at v = 151 0.36 ms against 0.40; BF16x6 at
-// v = 137 0.353 against 0.435 with all and 0.391 with four. Writing every mirror entry here, along
-// b, took 3.35 ms (FP64), 0.58 ms (FP32) and 0.845 ms (BF16x6).
+// L2 only while few are open, so spare LDS holds it to a few workgroups per CU (TriLds). By workgroups
+// per CU, the most being what fits (ms per build):
+//   FP64, v = 200 in one step (3.2 GB written, 1.6 read)   two 1.74   three 1.94   four 2.01
+//   FP64, v = 300 in eight steps                           two 9.3    three 10.2   four 10.5
+//   FP32, v = 151                                          two 0.374  four 0.356   eight 0.420
+//   BF16x6, v = 137                                        two 0.388  three 0.379 four 0.411   eight 0.471
+//   BF16x3, v = 137                                        two 0.319  three 0.285 four 0.299   eight 0.361
+// Writing every mirror entry here, along b, took 3.35 ms (FP64), 0.58 ms (FP32) and 0.845 ms (BF16x6).
+template <class Tg, int PREC>
+struct TriLds {
+  static constexpr int LD = kCube + 1, LB = kCube * LD + 1;   // both strides odd: no bank conflicts
+  static constexpr unsigned bytes = kCube * LB * sizeof(Tg);
+  // workgroups per CU (160 KB of LDS, dealt in units of 1280 bytes) and the least that holds it to them
+  static constexpr unsigned groups = PREC == PPL_FP64 ? 2 : PREC == PPL_FP32 ? 4 : 3;
+  static constexpr unsigned cu = 160 * 1024, unit = 1280, all = (cu / (groups + 1) / unit + 1) * unit;
+  static constexpr unsigned spare = all - bytes;
+  static_assert(all >= bytes && groups * all <= cu && (groups + 1) * all > cu, "workgroups per CU");
+};
+
 template <class Tg, int PREC, bool STEP>
 __global__ void __launch_bounds__(kPackThreads)
 pack_vpm_tri_kernel(int v, int a0, int a1, const Tg* __restrict__ T, int64_t ldt, const int64_t* __restrict__ off,
                     int64_t g0, int64_t ncubes, void* vp, void* vp_lo, int64_t ldp, void* vm, void* vm_lo,
                     int64_t ldm, int64_t Pp, int64_t Pm, int64_t row0p, int64_t row0m) {
-  constexpr int C = kCube, LD = kCube + 1, LB = kCube * LD + 1;   // both strides odd: no bank conflicts
+  constexpr int C = kCube, LD = TriLds<Tg, PREC>::LD, LB = TriLds<Tg, PREC>::LB;
   __shared__ Tg s[C * LB];
   const int64_t g = g0 + cube_of_slot(blockIdx.x, ncubes);
   const int a = cube_virtual(off, a0, a1, g);
@@ -354,10 +368,9 @@ static int launch_vpm_tri(hipStream_t s, int v, int a0, int a1, const void* T, i
   for (int a = 0; a < a1; ++a) (a < a0 ? g0 : n) += cubes_of(v, a);
   if (n <= 0) return PPL_OK;
   if (n > 0x7fffffffLL) return fail(PPL_E_ARG, "pack_vpm_tri: %lld cubes", (long long)n);
-  constexpr unsigned kTriSpareLds = PREC == PPL_FP64 || PREC == PPL_FP32 ? 20000 : 36000;
-  hipLaunchKernelGGL((pack_vpm_tri_kernel<Tg, PREC, STEP>), dim3((unsigned)n), dim3(kPackThreads), kTriSpareLds, s, v,
-                     a0, a1, (const Tg*)T, ldt, off, g0, n, vp, vp_lo, ldp, vm, vm_lo, ldm, npairs_plus(v),
-                     npairs_minus(v), row0p, row0m);
+  hipLaunchKernelGGL((pack_vpm_tri_kernel<Tg, PREC, STEP>), dim3((unsigned)n), dim3(kPackThreads),
+                     (TriLds<Tg, PREC>::spare), s, v, a0, a1, (const Tg*)T, ldt, off, g0, n, vp, vp_lo, ldp, vm, vm_lo,
+                     ldm, npairs_plus(v), npairs_minus(v), row0p, row0m);
   PPL_LAUNCH_CHECK();
   return PPL_OK;
 }
