@@ -428,7 +428,8 @@ int ppl_batch_destroy(ppl_batch_t batch);
 /* ------------------------------------------------ kernel timing (HIP events) */
 #define PPL_PROF_BUILD_GEMM     0  /* integral-build GEMM launches */
 #define PPL_PROF_BUILD_PACK     1  /* G -> V+- packing launches */
-#define PPL_PROF_CONTRACT_PLUS  2  /* R+ = S' V+ GEMM launches */
+#define PPL_PROF_CONTRACT_PLUS  2  /* R+ = S' V+ GEMM launches (K slices that the unpacking or the update sums
+                                      as it reads count there, not here) */
 #define PPL_PROF_CONTRACT_MINUS 3  /* R- = A' V- GEMM launches */
 #define PPL_PROF_UPDATE         4  /* packed Jacobi update + reductions */
 #define PPL_PROF_OTHER          5  /* staging, packing of t2, unpacking, (ia|jb) */
@@ -443,7 +444,8 @@ typedef struct {
 /*
  * ppl_profile_enable: on != 0 starts (and clears) per-launch timing: every
  * library launch on the plan's stream is bracketed by a pair of HIP events.
- * on == 0 stops recording. Events are created lazily and kept by the plan.
+ * on == 0 stops recording. Events are created lazily and kept by the plan. While it records, R+ and
+ * R- of a small problem, otherwise one launch, are launched one after the other (same results).
  */
 int ppl_profile_enable(ppl_plan_t plan, int on);
 

@@ -272,7 +272,11 @@ static uint64_t assign_layout(ppl_plan_t p, int64_t gcap, bool resident, int64_t
   p->rp = L.take((uint64_t)p->Np * p->ldp * 8);
   p->rm = L.take((uint64_t)std::max<int64_t>(p->Nm, 1) * p->ldm * 8);
   // upper-triangle steps accumulate each K slice over all columns, in as many sums as the plan was
-  // given slices, where they take no more than the step's own V+ rows
+  // given slices, where they take no more than the step's own V+ rows. That costs some pairs per step
+  // and pays where a step's tiles leave CUs idle: one sum against the plan's own slices, with a
+  // fraction of V+- in memory, (20, 200, 600) 1/4 18.3 -> 11.8 ms (7 -> 8 steps), (10, 300, 900) 1/6
+  // 70.6 -> 45.8 (12), (30, 300, 900) 1/8 101.3 -> 98.6 (13 -> 14); at (40, 400, 1200) 1/4 one to eight
+  // slices take 449 to 456 ms (7 to 9 steps).
   p->step_slices = 1;
   if (!resident && p->sym_build) {
     const uint64_t slice = (uint64_t)p->Np * p->ldp * 8 + (uint64_t)p->Nm * p->ldm * 8;

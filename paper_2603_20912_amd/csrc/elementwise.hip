@@ -642,8 +642,8 @@ __device__ inline void put4(void* hi, void* lo, int64_t i, const double (&x)[4])
 }
 
 // An n x n FP64 matrix stored as its upper triangle (kTriBlock; rows of ld, a multiple of 64) to the
-// same in an operand precision: one workgroup per row and eighth of the columns, four entries per
-// thread and step. Bound by memory: (20, 200) to BF16x3 516 us per sign for 2.4 GB (643 with the mirror half).
+// same in an operand precision: one workgroup per row and share of its stored columns (a share
+// per 4096 columns of a whole row), four entries per thread and step. Bound by memory: (20, 200) to BF16x3 516 us per sign for 2.4 GB (643 with the mirror half).
 template <int PREC>
 __global__ void __launch_bounds__(256)
 convert_tri_kernel(const double* __restrict__ src, int64_t ld, void* dh, void* dl) {

@@ -883,12 +883,11 @@ gemm_nt_kernel(int64_t M, int64_t N, int64_t Kpad, const T* __restrict__ A, int6
   using G = TileGeom<T, WM, WN, WAVES_M, WAVES_N, KC>;
   (void)Kpad;
   TileJob job;
-  // The contractions take the three-stage direct loads, and so do the FP64 integral
-  // builds on their 64 x 128 tile (13.1 against 13.7 ms per build at (20, 200, 600), 307
-  // against 321 ms at (40, 400, 1200), for the register-staged loop on the 128 x 128
-  // tile); the other builds keep the register-staged loop (FP32 on 128 x 128: 171
-  // against 195 ms with direct loads at (40, 400, 1200); the FP64 copy of a mixed plan,
-  // built on the 96 x 128 tile of its low-precision operands).
+  // The contractions take the three-stage direct loads, and so do the FP64 integral builds, all on
+  // their 64 x 128 tile (13.1 against 13.7 ms per full-row build at (20, 200, 600), 307 against 321 ms
+  // at (40, 400, 1200), for the register-staged loop on the 128 x 128 tile); FP32 builds keep the
+  // register-staged loop (128 x 128, full rows: 171 against 195 ms with direct loads at
+  // (40, 400, 1200)).
   if constexpr (GemmOccupancy<T, WM, WN, WAVES_M, WAVES_N, KC, Epi>::direct) {
     __shared__ __attribute__((aligned(16))) T st0[G::BUF_A + G::BUF_B];
     __shared__ __attribute__((aligned(16))) T st1[G::BUF_A + G::BUF_B];
@@ -1024,7 +1023,8 @@ __device__ __forceinline__ void bf3_tile_body_direct(const TileJob& job, int64_t
   const int lr = lane / VPR, slot = lane % VPR;
 
   // instruction q = wave + i NW of a chunk (q - GT past the end): plane Ah (q < GA), Al,
-  // Bh, then Bl; src is this lane's global vector, dst the instruction's 1 KB in a stage; for B rows n (NN false) or B rows k (NN true), from chunk c0 on
+  // Bh, then Bl; src is this lane's global vector, dst the instruction's 1 KB in a stage; for B
+  // rows n (NN false) or B rows k (NN true), from chunk c0 on
   const __bf16* src[NI];
   int dst[NI];
   auto aim = [&](auto nn, int64_t c0) __attribute__((always_inline)) {
@@ -2101,7 +2101,16 @@ int64_t contract_jobs(int tile, int prec, int64_t Nrows, int64_t Prows, int64_t 
 // FP32 ranks tiles 9, 8 and 0 the same way). BF16x3
 // (three-stage direct loads): R+ and R- at (40, 400, 1200), best of 1 and 2 slices, per
 // padded flop. BF16x6 (two-stage direct loads): R+ and R- at (40, 400, 1200) in the 7
-// slices its error bound asks for there, per padded flop.
+// slices its error bound asks for there, per padded flop. All on whole rows of V+-; on triangles,
+// half of them read K-major, the same measurement gives
+//   FP64    0.93 0.92 0.89 0.84 0.91 0.94 0.92 0.97 0.98 1.00 0.97   (30, 300, 900)
+//   FP32    0.91 0.94 0.84 0.81 0.87 0.89 0.91 0.94 0.97 1.00 0.95   (30, 300, 900)
+//   BF16x3  0.76 0.77 0.65 0.41 0.54 0.70 0.48 0.42 0.50 1.00 0.68
+//   BF16x6  0.78 0.85 0.67 0.43 0.60 0.76 0.46 0.54 0.68 1.00 0.73
+// within 0.06 of the table. At these sizes, (20, 200) and (10, 100) in FP64, (20, 200) in BF16x3,
+// (17, 151) in FP32 and (13, 137) in BF16x6 the tile the model takes is the fastest one, but for two
+// products 4 to 5% behind it: R- in FP64 at (30, 300, 900) (26.2 ms, tile 9 25.0) and R+ at (10, 100)
+// (64.7 us, tile 6 62.0).
 static const double kTileEff[4][11] = {
     /* FP64   */ {0.90, 0.91, 0.85, 0.83, 0.85, 0.91, 0.90, 0.95, 0.97, 0.98, 1.00},
     /* FP32   */ {0.94, 0.96, 0.87, 0.82, 0.90, 0.92, 0.92, 0.95, 0.97, 1.00, 0.93},
@@ -2122,8 +2131,8 @@ int contract_min_splits(int prec, int64_t Kpad) {
 }
 
 // Model choice of (tile, splits): useful work over the work of the padded tiles,
-// times the fill of the last round of workgroups over 256 CUs, times the
-// measured relative throughput of the tile.
+// times the fill of the last round of workgroups over 256 CUs (one each, also where
+// two would fit), times the measured relative throughput of the tile.
 void contract_choose(int prec, int64_t Nrows, int64_t Prows, int64_t Kpad, int max_splits, int* tile_out,
                      int* splits_out) {
   double best = -1.0;

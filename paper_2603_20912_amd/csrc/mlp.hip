@@ -68,7 +68,7 @@ __device__ inline float row_sum16(float x) {
 // holds A[l%16][l/16], B[l/16][l%16], D[4 (l/16) + r][l%16]). Wave w owns the columns
 // [16 w, 16 w + 16) of H1, Z2 and dH1 and the same rows of dW2; 16-element groups of the summed
 // index are read as k = 16 g + 4 (l/16) + e in step e, the same for both operands.
-// Bound by the latencies of its phases (loads, three dependent products, five barriers):
+// Bound by the latencies of its phases (loads, three dependent products, six barriers):
 // the products are 0.8 GFLOP at 8192 rows, 5 us of the matrix cores; 22 us (98 on the vector
 // unit, with the weights and the gradient partials of every 32 rows moved per workgroup).
 constexpr int kTrainThreads = 512;
