@@ -73,7 +73,10 @@ template <> struct Store<PPL_FP32> {
   __device__ static void put(void* hi, void*, int64_t i, double x) { ((float*)hi)[i] = (float)x; }
 };
 template <> struct Store<PPL_BF16X3> {
-  // x -> FP32 (round to nearest), hi = bf16(x32), lo = bf16(x32 - hi); both round to nearest even
+  // x -> FP32 (round to nearest), hi = bf16(x32), lo = bf16(x32 - hi); both round to nearest even.
+  // (The compiler may round x to hi in one step: where x32 lies halfway between two bf16 numbers and x
+  // does not, hi is then the one nearer to x. x32 = hi + lo to the same 17 bits either way. A kernel
+  // that must go through x32 passes via_f32(x).)
   __device__ static void put(void* hi, void* lo, int64_t i, double x) {
     const float xf = (float)x;
     const __bf16 h = (__bf16)xf;
@@ -99,6 +102,17 @@ template <> struct Store<PPL_BF16X6> {
     (pm + (pm - ph))[i] = l;
   }
 };
+
+// x, rounded to FP32 first for a bf16 operand
+template <int PREC>
+__device__ inline double via_f32(double x) {
+  if constexpr (PREC == PPL_BF16X3 || PREC == PPL_BF16X6) {
+    float y = (float)x;
+    asm("" : "+v"(y));
+    return y;
+  }
+  return x;
+}
 
 // ------------------------------------------------------------------ staging (transposing copy)
 // X[r1*R2 + r2][P] = L[P][r1_off + r1][r2_off + r2] for P < naux, 0 for naux <= P < ldx.
@@ -264,7 +278,7 @@ static_assert(kCube == 16, "the cube packing splits an element index into 4-bit 
 // Writing every mirror entry here, along b, took 3.35 ms (FP64), 0.58 ms (FP32) and 0.845 ms (BF16x6).
 template <class Tg, int PREC>
 struct TriLds {
-  static constexpr int LD = kCube + 1, LB = kCube * LD + 1;   // both strides odd: no bank conflicts
+  static constexpr int LD = kCube + 1, LB = kCube * LD + 1;   // odd strides: at most a few lanes meet on a bank
   static constexpr unsigned bytes = kCube * LB * sizeof(Tg);
   // workgroups per CU (160 KB of LDS, dealt in units of 1280 bytes) and the least that holds it to them
   static constexpr unsigned groups = PREC == PPL_FP64 ? 2 : PREC == PPL_FP32 ? 4 : 3;
@@ -643,7 +657,8 @@ __device__ inline void put4(void* hi, void* lo, int64_t i, const double (&x)[4])
 
 // An n x n FP64 matrix stored as its upper triangle (kTriBlock; rows of ld, a multiple of 64) to the
 // same in an operand precision: one workgroup per row and share of its stored columns (a share
-// per 4096 columns of a whole row), four entries per thread and step. Bound by memory: (20, 200) to BF16x3 516 us per sign for 2.4 GB (643 with the mirror half).
+// per 4096 columns of a whole row), four entries per thread and step. Bound by memory: (20, 200) to
+// BF16x3 516 us per sign for 2.4 GB (643 with the mirror half).
 template <int PREC>
 __global__ void __launch_bounds__(256)
 convert_tri_kernel(const double* __restrict__ src, int64_t ld, void* dh, void* dl) {
@@ -1198,9 +1213,9 @@ ring_pack_kernel(int o, int v, const double* __restrict__ t, int64_t ld, void* X
     auto put = [&](int row, int col, double u, double w) __attribute__((always_inline)) {
       if (row >= v || col >= v) return;
       const int64_t y = (i * v + row) * ld + k * v + col;
-      Store<PREC>::put(Xa, Xa_lo, y, 2.0 * u - w);
-      Store<PREC>::put(An, An_lo, y, -u);
-      Store<PREC>::put(B, B_lo, y, w);
+      Store<PREC>::put(Xa, Xa_lo, y, via_f32<PREC>(2.0 * u - w));
+      Store<PREC>::put(An, An_lo, y, via_f32<PREC>(-u));
+      Store<PREC>::put(B, B_lo, y, via_f32<PREC>(w));
     };
 #pragma unroll
     for (int e = 0; e < 4; ++e) put(a0 + m + 8 * e, c0 + f, ac[e], sq[f][m + 8 * e]);
