@@ -365,16 +365,6 @@ int mlp_samples_launch(hipStream_t s, int o, int v, const double* tm, const doub
 }
 
 // ------------------------------------------------------------------ inference (BF16 MFMA hidden layer)
-// A work item is one 16 x 16 tile (a, b) of an occupied pair: (i < j) all tiles, (i = j) the
-// tiles A <= B and in them a <= b. Each element gives the guess at (i,j,a,b) and at its pair
-// partner (j,i,b,a), so no entry is written twice; the partners are written along their rows
-// from an LDS transpose. A wave takes items in turn and 16 elements (fixed a) at a time: lane
-// l holds element b = l % 16 and computes the hidden units k = 32 kk + 8 (l / 16) + 0..7 of it,
-// which is the A operand of the 16x16x32 MFMA, so the first layer never leaves the registers;
-// so does not the second layer's weight matrix, 128 registers of bf16 per lane, loaded once.
-// Bound by the vector unit, 256 SiLUs per element: 1.10 ms at (20, 200), 8.0e6 evaluations; 3.51
-// with the weights staged in LDS for every 64 elements, scattered partners and the compiler's
-// quotient (1.56 with that quotient). Results are bit-identical to that form.
 // The network's output (without its bias) at x where some hidden unit is NaN or +inf, so that the
 // output is NaN or infinite in any order of its sums: element by element, the first layer anew
 // for each unit of the second.
@@ -398,12 +388,23 @@ __device__ inline float far_output(const float* __restrict__ prm, f4 x) {
   return y;
 }
 
+// A work item is one 16 x 16 tile (a, b) of an occupied pair: (i < j) all tiles, (i = j) the
+// tiles A <= B and in them a <= b. Each element gives the guess at (i,j,a,b) and at its pair
+// partner (j,i,b,a), so no entry is written twice; the partners are written along their rows
+// from an LDS transpose. A wave takes items in turn and 16 elements (fixed a) at a time: lane
+// l holds element b = l % 16 and computes the hidden units k = 32 kk + 8 (l / 16) + 0..7 of it,
+// which is the A operand of the 16x16x32 MFMA, so the first layer never leaves the registers;
+// so does not the second layer's weight matrix, 128 registers of bf16 per lane, loaded once.
+// Bound by the vector unit, 256 SiLUs per element: 1.0 ms at (20, 200), 8.0e6 evaluations; 3.4
+// with the weights staged in LDS for every 64 elements, scattered partners and the compiler's
+// quotient (1.56 with that quotient). Results are bit-identical to that form.
 constexpr int kInferThreads = 256;
 
 __global__ void __launch_bounds__(kInferThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 mlp_infer_kernel(const float* __restrict__ prm, int o, int v, const double* __restrict__ tm,
                  const double* __restrict__ e_occ, const double* __restrict__ e_vir, double sigma,
-                 const int* __restrict__ tab_om, int64_t n_first, int64_t n_items, double* __restrict__ tout) {
+                 const int* __restrict__ tab_om, int64_t n_first, int64_t n_items, int shift,
+                 double* __restrict__ tout) {
   __shared__ __attribute__((aligned(16))) float sW1[kH][4], sb1[kH];
   __shared__ float sb2[kH], sW3[kH];
   __shared__ double sT[kInferThreads / 64][16][17];
@@ -416,20 +417,26 @@ mlp_infer_kernel(const float* __restrict__ prm, int o, int v, const double* __re
     sW3[tid] = prm[kOffW3 + tid];
   }
   const float b3 = prm[kOffB3];
-  // B[k][n] = W2[n][k]: lane l holds n = 16 jb + l % 16, k = 32 kk + 8 (l / 16) + 0..7
+  // B[k][n] = W2[n][k]: lane l holds n = 16 jb + l % 16, k = 32 kk + 8 (l / 16) + 0..7 (through LDS: read
+  // by every wave from L2, 2048 waves took 10 us)
+  constexpr int LD2 = kH + 8;
+  __shared__ __attribute__((aligned(16))) __bf16 sW2[kH * LD2];
+  for (int e = tid; e < kH * kH / 4; e += kInferThreads) {
+    const f4 x = *reinterpret_cast<const f4*>(&prm[kOffW2 + 4 * e]);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) sW2[e / (kH / 4) * LD2 + e % (kH / 4) * 4 + k] = (__bf16)x[k];
+  }
+  __syncthreads();
   bf8 w2[kH / 16][kH / 32];
 #pragma unroll
   for (int jb = 0; jb < kH / 16; ++jb)
 #pragma unroll
-    for (int kk = 0; kk < kH / 32; ++kk) {
-      const float* src = &prm[kOffW2 + (16 * jb + c16) * kH + 32 * kk + 8 * q];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) w2[jb][kk][e] = (__bf16)src[e];
-    }
-  __syncthreads();
+    for (int kk = 0; kk < kH / 32; ++kk)
+      w2[jb][kk] = *reinterpret_cast<const bf8*>(&sW2[(16 * jb + c16) * LD2 + 32 * kk + 8 * q]);
   const int nb = (v + 15) / 16, per = nb * (nb + 1) / 2;
   const int64_t vv = (int64_t)v * v, nbb = (int64_t)nb * nb, nw = (int64_t)gridDim.x * (kInferThreads / 64);
-  for (int64_t it = (int64_t)blockIdx.x * (kInferThreads / 64) + wave; it < n_items; it += nw) {
+  for (int64_t part = (int64_t)blockIdx.x * (kInferThreads / 64) + wave; part < n_items << shift; part += nw) {
+    const int64_t it = part >> shift;
     int i, j, A, B;
     if (it < n_first) {
       const int ij = tab_om[it / nbb], rem = (int)(it % nbb);
@@ -448,10 +455,12 @@ mlp_infer_kernel(const float* __restrict__ prm, int o, int v, const double* __re
     const int b = 16 * B + c16;
     const double eo = e_occ[i] + e_occ[j], evb = b < v ? e_vir[b] : 0.0;
     const int64_t row_ij = ((int64_t)i * o + j) * vv, row_ji = ((int64_t)j * o + i) * vv;
-    const int na = v - 16 * A < 16 ? v - 16 * A : 16;
+    const int a0 = (int)(part & ((1 << shift) - 1)) * (16 >> shift), a1 = a0 + (16 >> shift);
+    const int na = v - 16 * A < a1 ? v - 16 * A : a1;        // this part's rows a0 .. na - 1 of the tile
+    if (a0 >= na) continue;
     bool nan = false;
-    double t = b < v ? tm[row_ij + (int64_t)(16 * A) * v + b] : 0.0;
-    for (int al = 0; al < na; ++al) {
+    double t = b < v ? tm[row_ij + (int64_t)(16 * A + a0) * v + b] : 0.0;
+    for (int al = a0; al < na; ++al) {
       const int a = 16 * A + al;
       const double tn = (al + 1 < na && b < v) ? tm[row_ij + (int64_t)(a + 1) * v + b] : 0.0;
       const double eva = e_vir[a];
@@ -495,7 +504,7 @@ mlp_infer_kernel(const float* __restrict__ prm, int o, int v, const double* __re
       t = tn;
     }
     if (nan)                         // NaN where a hidden unit may be at +inf: which of the two it is
-      for (int al = 0; al < na; ++al) {
+      for (int al = a0; al < na; ++al) {
         const int a = 16 * A + al;
         const double tx = b < v ? tm[row_ij + (int64_t)a * v + b] : 0.0, eva = e_vir[a];
         if (sT[wave][c16][al] == sT[wave][c16][al] || tx != tx) continue;
@@ -510,7 +519,7 @@ mlp_infer_kernel(const float* __restrict__ prm, int o, int v, const double* __re
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const int bl = 4 * k + q, bb = 16 * B + bl;
-      if (a < v && bb < v && (!diag || a < bb)) tout[row_ji + (int64_t)bb * v + a] = sT[wave][bl][c16];
+      if (c16 >= a0 && c16 < na && bb < v && (!diag || a < bb)) tout[row_ji + (int64_t)bb * v + a] = sT[wave][bl][c16];
     }
     __builtin_amdgcn_wave_barrier();
   }
@@ -520,10 +529,16 @@ int mlp_infer_launch(hipStream_t s, const float* prm, int o, int v, const double
                      const double* e_vir, double sigma, const int* tab_om, double* tout) {
   const int64_t nb = (v + 15) / 16;
   const int64_t n_first = npairs_minus(o) * nb * nb, n_items = n_first + (int64_t)o * (nb * (nb + 1) / 2);
-  // two waves per SIMD (the weights take half of the registers), items dealt to them in turn
-  const int64_t groups = (n_items + kInferThreads / 64 - 1) / (kInferThreads / 64);
+  // Two waves per SIMD (the weights take half of the registers), items dealt to them in turn, in parts of
+  // fewer rows where there are less than kInferItems per wave: whole tiles of 16 rows leave most waves
+  // without work at (3, 17) (46 us; 8.5 so, 15.1 by 64 elements per workgroup) and their last round
+  // uneven at (10, 100) (91 us; 74 with two items per wave, 84 and 81 with one and four).
+  constexpr int64_t kWaves = 512 * (kInferThreads / 64), kInferItems = 2;
+  int shift = 0;
+  while (shift < 4 && n_items << shift < kInferItems * kWaves) ++shift;
+  const int64_t groups = ((n_items << shift) + kInferThreads / 64 - 1) / (kInferThreads / 64);
   hipLaunchKernelGGL(mlp_infer_kernel, dim3((unsigned)std::min<int64_t>(groups, 512)), dim3(kInferThreads), 0, s, prm,
-                     o, v, tm, e_occ, e_vir, sigma, tab_om, n_first, n_items, tout);
+                     o, v, tm, e_occ, e_vir, sigma, tab_om, n_first, n_items, shift, tout);
   PPL_HIP_TRY(hipGetLastError());
   return PPL_OK;
 }
