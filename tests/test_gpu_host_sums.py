@@ -149,3 +149,34 @@ def test_bind_and_destroy_beside_a_capture(P):
     del graph
     other.close()
     eng.close()
+
+
+def test_plans_of_several_threads(P):
+    """Slots are taken and given back by several host threads at once: every solve reads its own."""
+    import threading
+
+    o, v, naux = 3, 12, 36
+    say(f"solves in six threads ({o},{v},{naux})")
+    systems = [S.make_system(o, v, naux, 140 + k, "contractive") for k in range(6)]
+    ref = []
+    for s in systems:
+        eng, t, rep = solve(P, s, o, v, naux)
+        eng.close()
+        ref.append((t, rep))
+    wrong = []
+
+    def work(k):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for _ in range(8):
+                eng, t, rep = solve(P, systems[k], o, v, naux)
+                torch.cuda.current_stream().synchronize()
+                eng.close()
+                if not np.array_equal(t, ref[k][0]) or rep != ref[k][1]:
+                    wrong.append(k)
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(6)]
+    for th in threads:
+        th.start()
+    for th in threads:
+        th.join()
+    assert not wrong
